@@ -94,3 +94,22 @@ def test_empty_volume_has_no_triangles():
     g = T.Volume(configs.C1_VOLUME, 160, 120)
     V, Kk = g.mesh()
     assert len(V) == 0 and len(Kk) == 0
+
+
+@pytest.mark.parametrize("n_buckets,n_excess", [(16, 40), (1 << 12, 1 << 10), (1 << 18, 1 << 12)])
+def test_rough_blocks_and_table_sizes_match_oracle(n_buckets, n_excess):
+    """One chunk of 64 entries, one scan group and two (the counts' offsets
+    take another path in each), on blocks whose signs change from voxel to
+    voxel: more triangles in a block than the 256 that emission lists at a time."""
+    from synth.scenes import Intrinsics
+    rng = np.random.default_rng(n_buckets)
+    K = Intrinsics(200.0, 200.0, 23.5, 19.5, 48, 40)
+    vp = configs.VolumeParams(0.01, 0.08, 100, n_buckets, n_excess, 4096)
+    P = np.eye(4, dtype=np.float32)
+    frames = (0.52 + 0.035 * rng.choice([-1.0, 1.0], size=(1, 40, 48))).astype(np.float32)
+    g = _fused(vp, frames, [P], K)
+    gV, gK, err = _compare(g, vp.voxel_size, f"rough {n_buckets}")
+    cell = np.floor(gV.reshape(-1, 3, 3).mean(axis=1) / (8 * vp.voxel_size)).astype(int)
+    most = np.unique(cell, axis=0, return_counts=True)[1].max()
+    print(f"rough mesh, {n_buckets} buckets: {len(gV)} triangles, at most {most} in a block, error {err:.2e}", flush=True)
+    assert most > 256
