@@ -70,6 +70,20 @@ __device__ __forceinline__ T gload(const T *p)
     return *(const __attribute__((address_space(1))) T *)p;
 }
 
+// two adjacent 16-bit values / four of them, at any 2-byte alignment
+typedef uint32_t u32_any2 __attribute__((aligned(2)));
+typedef unsigned long long u64_any2 __attribute__((aligned(2)));
+
+__device__ __forceinline__ uint32_t gload_pair(const uint8_t *p)
+{
+    return *(const __attribute__((address_space(1))) u32_any2 *)p;
+}
+
+__device__ __forceinline__ unsigned long long gload_quad(const uint8_t *p)
+{
+    return *(const __attribute__((address_space(1))) u64_any2 *)p;
+}
+
 typedef int v4i __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ int4 load_entry(const DEntry *e, uint32_t i)
@@ -789,13 +803,9 @@ __device__ __forceinline__ void cell_index(int ix, int iy, int iz, bool sx, bool
     j[7] = j[3] + dz;
 }
 
-// absent voxels read 1.0 (bit c of `present` clear: corner c has no block);
-// lerp a + (b - a) t along x, then y, then z
-__device__ __forceinline__ float cell_lerp(uint32_t present, const int16_t (&s)[8], float tx, float ty, float tz)
+// lerp a + (b - a) t of a cell's corners along x, then y, then z
+__device__ __forceinline__ float lerp8(const float (&f)[8], float tx, float ty, float tz)
 {
-    float f[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) f[c] = ((present >> c) & 1u) ? (float)s[c] * (1.0f / 32767.0f) : 1.0f;
     const float c00 = f[0] + (f[1] - f[0]) * tx;
     const float c10 = f[2] + (f[3] - f[2]) * tx;
     const float c01 = f[4] + (f[5] - f[4]) * tx;
@@ -803,6 +813,15 @@ __device__ __forceinline__ float cell_lerp(uint32_t present, const int16_t (&s)[
     const float c0 = c00 + (c10 - c00) * ty;
     const float c1 = c01 + (c11 - c01) * ty;
     return c0 + (c1 - c0) * tz;
+}
+
+// absent voxels read 1.0 (bit c of `present` clear: corner c has no block)
+__device__ __forceinline__ float cell_lerp(uint32_t present, const int16_t (&s)[8], float tx, float ty, float tz)
+{
+    float f[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) f[c] = ((present >> c) & 1u) ? (float)s[c] * (1.0f / 32767.0f) : 1.0f;
+    return lerp8(f, tx, ty, tz);
 }
 
 __device__ __forceinline__ float cell_interp(const Cell &C, const int16_t (&s)[8])

@@ -200,14 +200,21 @@ __global__ __launch_bounds__(256) void k_range_bin(Vol v, Cam c, int all)
     }
 }
 
-// LDS of a raycast tile: the (block key -> device pointer) table of the bin's
-// blocks and the bin's pixel boxes and z ranges (the first 16 bytes of each
-// record) for the per-pixel range
+// LDS of a raycast tile: the (block key -> record of the tile's bin) table,
+// and, first, the records' pixel boxes and z ranges (their first 16 bytes)
+// with each wave's list of those that matter to it, for the per-pixel range;
+// then, in the same bytes, the device pointers of every record's block and of
+// its neighbours, n = 1..7 at (n & 1, n >> 1 & 1, n >> 2), -1 where absent.
 struct TileTable {
     unsigned long long key[kTileTable];   // 0 = empty slot
-    int ptr[kTileTable];
-    uint4 box[kBinCap];                   // x0, y0, x1, y1 (int16), zlo, zhi (float)
-    uint16_t wlist[4][kBinCap];           // per wave: the staged records whose box meets its pixels
+    union {
+        struct {
+            uint4 box[kBinCap];           // x0, y0, x1, y1 (int16), zlo, zhi (float)
+            uint16_t wlist[4][kBinCap];   // per wave: the staged records whose box meets its pixels
+        } r;
+        int nb[kBinCap][8];
+    };
+    uint16_t rec[kTileTable];             // record of the slot's block
     int wcnt[4];
     int complete;                         // the table holds the whole bin
 };
@@ -220,6 +227,38 @@ __device__ __forceinline__ uint32_t table_slot(int bx, int by, int bz)
     const int x = (int16_t)bx, y = (int16_t)by, z = (int16_t)bz;
     const uint32_t h = (uint32_t)(x * 0x1f1f1f) ^ (uint32_t)(y * 0x3c6ef3) ^ (uint32_t)(z * 0x5a8279);
     return (h ^ (h >> 10)) & (uint32_t)(kTileTable - 1);
+}
+
+// the record of a block (coordinates in the 16-bit range) in the tile's table, or -1
+__device__ __forceinline__ int table_find(const TileTable *tt, int bx, int by, int bz)
+{
+    const unsigned long long key = pack_key(bx, by, bz);
+    uint32_t sl = table_slot(bx, by, bz);
+    for (int k = 0; k < kTileTable; ++k) {
+        const unsigned long long kk = tt->key[sl];
+        if (kk == key) return (int)tt->rec[sl];
+        if (kk == 0ull) break;
+        sl = (sl + 1u) & (uint32_t)(kTileTable - 1);
+    }
+    return -1;
+}
+
+// device pointer of a block (coordinates in the 16-bit range; -1 = absent or
+// not on the device) from its occupancy brick and its bucket entry, loaded
+// together; the chain beyond the bucket only when the entry is another block's
+__device__ __forceinline__ int map_find(const Vol &v, int bx, int by, int bz)
+{
+    const uint32_t h = hash_index(bx, by, bz, v.n_buckets - 1u);
+    const uint32_t bw = gload(v.brick + brick_word(bx, by, bz));
+    const int4 w = load_entry(v.entries, h);
+    if (!(bw & brick_bit(bx, by, bz))) return -1;
+    const uint32_t kxy = (uint32_t)(uint16_t)bx | ((uint32_t)(uint16_t)by << 16);
+    if ((uint32_t)w.x == kxy && (int16_t)(w.y & 0xffff) == (int16_t)bz && w.w >= 0) return w.w;
+    if (w.z < 1 || (uint32_t)(w.z - 1) >= v.n_excess) return -1;
+    int ptr = -1;
+    const int e = find_entry_from(v.entries, v.n_buckets, v.n_excess, v.n_buckets + (uint32_t)(w.z - 1), bx, by, bz, 0,
+                                  &ptr);
+    return e >= 0 ? ptr : -1;
 }
 
 // The tile's block table and the search range of pixel (px, py) from the
@@ -242,10 +281,14 @@ __device__ __forceinline__ void tile_range(const Vol &v, int tile, int tx0, int 
     const int n = fallback ? (int)v.ctrl->n_rec : cnt;
     if (threadIdx.x == 0) tt->complete = table && !fallback;
     float lo = __builtin_inff(), hi = -__builtin_inff();
+    int4 own[2];           // {bx | by << 16, bz, ptr} of this thread's records of a table's bin
     for (int base = 0; base < n; base += kBinCap) {
         const int m = n - base < kBinCap ? n - base : kBinCap;
         __syncthreads();   // the cleared table, or the previous chunk consumed
-        for (int j = (int)threadIdx.x; j < m; j += 256) {
+#pragma unroll
+        for (int h = 0; h < kBinCap / 256; ++h) {
+            const int j = (int)threadIdx.x + 256 * h;
+            if (j >= m) break;
             const Rec r = fallback ? v.recs[base + j] : v.bins[(size_t)tile * kBinCap + j];
             if (table && !fallback) {
                 // keys in one bin are distinct; the table is at most half full
@@ -253,13 +296,14 @@ __device__ __forceinline__ void tile_range(const Vol &v, int tile, int tx0, int 
                 uint32_t sl = table_slot(r.bx, r.by, r.bz);
                 for (int k = 0; k < kTileTable; ++k) {
                     if (atomicCAS(&tt->key[sl], 0ull, key) == 0ull) {
-                        tt->ptr[sl] = r.ptr;
+                        tt->rec[sl] = (uint16_t)j;
                         break;
                     }
                     sl = (sl + 1u) & (uint32_t)(kTileTable - 1);
                 }
+                own[h] = make_int4((int)((uint32_t)(uint16_t)r.bx | ((uint32_t)(uint16_t)r.by << 16)), r.bz, r.ptr, 0);
             }
-            tt->box[j] = make_uint4((uint32_t)(uint16_t)r.x0 | ((uint32_t)(uint16_t)r.y0 << 16),
+            tt->r.box[j] = make_uint4((uint32_t)(uint16_t)r.x0 | ((uint32_t)(uint16_t)r.y0 << 16),
                                     (uint32_t)(uint16_t)r.x1 | ((uint32_t)(uint16_t)r.y1 << 16),
                                     __float_as_uint(r.zlo), __float_as_uint(r.zhi));
 #pragma unroll
@@ -267,14 +311,14 @@ __device__ __forceinline__ void tile_range(const Vol &v, int tile, int tx0, int 
                 const int wx0 = tx0 + (quads ? (w & 1) * 8 : 0), wy0 = ty0 + (quads ? (w >> 1) * 8 : 4 * w);
                 const int wx1 = wx0 + (quads ? 7 : 15), wy1 = wy0 + (quads ? 7 : 3);
                 if (r.x0 <= wx1 && r.x1 >= wx0 && r.y0 <= wy1 && r.y1 >= wy0)
-                    tt->wlist[w][atomicAdd(&tt->wcnt[w], 1)] = (uint16_t)j;
+                    tt->r.wlist[w][atomicAdd(&tt->wcnt[w], 1)] = (uint16_t)j;
             }
         }
         __syncthreads();
         // the order of a wave's list varies with the atomics; min and max do not
         const int nw = __builtin_amdgcn_readfirstlane(tt->wcnt[wave]);
         for (int i = 0; i < nw; ++i) {
-            const uint4 b = tt->box[tt->wlist[wave][i]];
+            const uint4 b = tt->r.box[tt->r.wlist[wave][i]];
             const int x0 = (int16_t)(b.x & 0xffffu), y0 = (int16_t)(b.x >> 16);
             const int x1 = (int16_t)(b.y & 0xffffu), y1 = (int16_t)(b.y >> 16);
             if (px >= x0 && px <= x1 && py >= y0 && py <= y1) {
@@ -286,9 +330,38 @@ __device__ __forceinline__ void tile_range(const Vol &v, int tile, int tx0, int 
         // this wave's list is consumed; the next chunk's staging starts after the barrier above
         if ((threadIdx.x & 63) == 0) tt->wcnt[wave] = 0;
     }
-    __syncthreads();   // the table is complete before any lookup
+    __syncthreads();   // the table is complete before any lookup, the boxes are read
     zmin = lo;
     zmax = hi;
+    if (!table || fallback) return;
+    // The neighbours of every block of the bin, eight lanes to a record: a ray
+    // that crosses a block face then reads them with its own block instead of
+    // looking up to seven blocks up one after another (the march's longest
+    // chain: 25 to 32% of the kernel).
+#pragma unroll
+    for (int h = 0; h < kBinCap / 256; ++h) {
+        const int j = (int)threadIdx.x + 256 * h;
+        if (j >= n) break;
+        tt->nb[j][0] = own[h].z;
+        tt->nb[j][1] = own[h].x;
+        tt->nb[j][2] = own[h].y;
+    }
+    __syncthreads();
+    const int nn = (int)threadIdx.x & 7;
+    for (int i = (int)threadIdx.x; i < 8 * n; i += 256) {
+        const int j = i >> 3;
+        const int kxy = tt->nb[j][1], bz = tt->nb[j][2] + (nn >> 2);
+        const int bx = (int16_t)(kxy & 0xffff) + (nn & 1), by = (int16_t)((uint32_t)kxy >> 16) + ((nn >> 1) & 1);
+        __builtin_amdgcn_wave_barrier();   // the record's eight lanes have read its key
+        if (nn == 0) continue;
+        int p = -1;
+        if (in_short_range(bx) && in_short_range(by) && in_short_range(bz)) {
+            const int k = table_find(tt, bx, by, bz);
+            p = k >= 0 ? tt->nb[k][0] : map_find(v, bx, by, bz);
+        }
+        tt->nb[j][nn] = p;
+    }
+    __syncthreads();   // before any lookup
 }
 
 // End of a raycast-kind workgroup (every thread calls it, after its last
@@ -318,10 +391,11 @@ namespace {
 
 
 // one-entry block cache (the paper's IndexCache, Sec. 3.3): the last block
-// key looked up and its device pointer (-1 = absent or not on the device);
-// `local`: lookups of this ray may trust a miss in the tile's table
+// key looked up, its device pointer (-1 = absent or not on the device) and
+// its record in the tile's table (-1 = not there); `local`: lookups of this
+// ray may trust a miss in the tile's table
 struct BlockCache {
-    int bx, by, bz, ptr;
+    int bx, by, bz, ptr, rec;
     bool local;
 };
 
@@ -333,28 +407,9 @@ struct BlockCache {
 __device__ __forceinline__ int lookup_block(const Vol &v, const TileTable *tt, int bx, int by, int bz, bool local)
 {
     if (!in_short_range(bx) || !in_short_range(by) || !in_short_range(bz)) return -1;
-    const unsigned long long key = pack_key(bx, by, bz);
-    uint32_t sl = table_slot(bx, by, bz);
-    for (int k = 0; k < kTileTable; ++k) {
-        const unsigned long long kk = tt->key[sl];
-        if (kk == key) return tt->ptr[sl];
-        if (kk == 0ull) break;
-        sl = (sl + 1u) & (uint32_t)(kTileTable - 1);
-    }
-    if (local) return -1;
-    // the block's occupancy brick and its bucket entry, loaded together; the
-    // chain beyond the bucket only when the entry is another block's
-    const uint32_t h = hash_index(bx, by, bz, v.n_buckets - 1u);
-    const uint32_t bw = gload(v.brick + brick_word(bx, by, bz));
-    const int4 w = load_entry(v.entries, h);
-    if (!(bw & brick_bit(bx, by, bz))) return -1;
-    const uint32_t kxy = (uint32_t)(uint16_t)bx | ((uint32_t)(uint16_t)by << 16);
-    if ((uint32_t)w.x == kxy && (int16_t)(w.y & 0xffff) == (int16_t)bz && w.w >= 0) return w.w;
-    if (w.z < 1 || (uint32_t)(w.z - 1) >= v.n_excess) return -1;
-    int ptr = -1;
-    const int e = find_entry_from(v.entries, v.n_buckets, v.n_excess, v.n_buckets + (uint32_t)(w.z - 1), bx, by, bz, 0,
-                                  &ptr);
-    return e >= 0 ? ptr : -1;
+    const int k = table_find(tt, bx, by, bz);
+    if (k >= 0) return tt->nb[k][0];
+    return local ? -1 : map_find(v, bx, by, bz);
 }
 
 __device__ __forceinline__ int cached_block(const Vol &v, const TileTable *tt, int bx, int by, int bz,
@@ -364,24 +419,46 @@ __device__ __forceinline__ int cached_block(const Vol &v, const TileTable *tt, i
     cc.bx = bx;
     cc.by = by;
     cc.bz = bz;
-    cc.ptr = lookup_block(v, tt, bx, by, bz, cc.local);
+    cc.rec = -1;
+    cc.ptr = -1;
+    if (in_short_range(bx) && in_short_range(by) && in_short_range(bz)) {
+        cc.rec = table_find(tt, bx, by, bz);
+        if (cc.rec >= 0)
+            cc.ptr = tt->nb[cc.rec][0];
+        else if (!cc.local)
+            cc.ptr = map_find(v, bx, by, bz);
+    }
     return cc.ptr;
 }
 
-// A trilinear cell ready to load: the corners' SDF addresses as byte offsets
-// into the voxel array (32-bit when the array spans at most 4 GiB), which
-// corners have a block, and the interpolation fractions.  An absent corner
-// addresses block 0; its value is not used.
+// A trilinear cell ready to load.  Corners c and c + 4 are one voxel apart
+// along z, next to each other in memory unless the cell crosses its block's
+// upper z face: o[c] are the byte offsets of the four lower corners into the
+// voxel array (32-bit when the array spans at most 4 GiB), each read as one
+// 4-byte pair; oz[c] those of the upper corners, read only when `sz`.
+// `present`: which corners have a block (an absent corner addresses block 0;
+// its value is not used).
 template <bool kOff32>
 struct RayCell {
-    typename std::conditional<kOff32, uint32_t, size_t>::type o[8];
+    using Off = typename std::conditional<kOff32, uint32_t, size_t>::type;
+    Off o[4], oz[4];
     uint32_t present;
+    bool sz;
     float tx, ty, tz;
 };
 
-// corner blocks: the cell's own block through the ray's cache; where the
-// cell crosses a block face (local index 7), the neighbouring blocks by
-// direct lookups
+// byte offset of voxel j of block p into the voxel array
+template <bool kOff32>
+__device__ __forceinline__ typename RayCell<kOff32>::Off voxel_offset(int p, int j)
+{
+    const uint32_t pc = p >= 0 ? (uint32_t)p : 0u;
+    if (kOff32) return __umul24(pc, (uint32_t)kBlockBytes) + 2u * (uint32_t)j;
+    return (typename RayCell<kOff32>::Off)((size_t)pc * kBlockBytes + 2u * (uint32_t)j);
+}
+
+// corner blocks: the cell's own block through the ray's cache; where the cell
+// crosses a block face (local index 7), the neighbouring blocks from the
+// record of the own block, or, for a block outside the tile's table, looked up
 template <bool kOff32>
 __device__ __forceinline__ void cell_setup(const Vol &v, const TileTable *tt, float X, float Y, float Z,
                                            BlockCache &cc, RayCell<kOff32> &C)
@@ -393,40 +470,83 @@ __device__ __forceinline__ void cell_setup(const Vol &v, const TileTable *tt, fl
     const int ix = (int)bx, iy = (int)by, iz = (int)bz;
     const int Bx = ix >> 3, By = iy >> 3, Bz = iz >> 3;
     const bool sx = (ix & 7) == 7, sy = (iy & 7) == 7, sz = (iz & 7) == 7;
-    int p[8];
-    p[0] = cached_block(v, tt, Bx, By, Bz, cc);
-#pragma unroll
-    for (int c = 1; c < 8; ++c) p[c] = p[0];
+    const int p0 = cached_block(v, tt, Bx, By, Bz, cc);
+    int n1 = p0, n2 = p0, n3 = p0, n4 = p0, n5 = p0, n6 = p0, n7 = p0;
     if (sx | sy | sz) {
-        const bool lc = cc.local;
-        if (sx) p[1] = lookup_block(v, tt, Bx + 1, By, Bz, lc);
-        if (sy) p[2] = lookup_block(v, tt, Bx, By + 1, Bz, lc);
-        if (sz) p[4] = lookup_block(v, tt, Bx, By, Bz + 1, lc);
-        p[3] = (sx & sy) ? lookup_block(v, tt, Bx + 1, By + 1, Bz, lc) : (sx ? p[1] : p[2]);
-        p[5] = (sx & sz) ? lookup_block(v, tt, Bx + 1, By, Bz + 1, lc) : (sx ? p[1] : p[4]);
-        p[6] = (sy & sz) ? lookup_block(v, tt, Bx, By + 1, Bz + 1, lc) : (sy ? p[2] : p[4]);
-        p[7] = (sx & sy & sz) ? lookup_block(v, tt, Bx + 1, By + 1, Bz + 1, lc)
-                              : (sx & sy) ? p[3] : (sx & sz) ? p[5] : (sy & sz) ? p[6] : sx ? p[1] : sy ? p[2] : p[4];
+        if (cc.rec >= 0) {
+            const int4 a = *reinterpret_cast<const int4 *>(&tt->nb[cc.rec][0]);
+            const int4 b = *reinterpret_cast<const int4 *>(&tt->nb[cc.rec][4]);
+            n1 = a.y;
+            n2 = a.z;
+            n3 = a.w;
+            n4 = b.x;
+            n5 = b.y;
+            n6 = b.z;
+            n7 = b.w;
+        } else {
+            const int need = (sx ? 1 : 0) | (sy ? 2 : 0) | (sz ? 4 : 0);
+#pragma unroll 1
+            for (int n = 1; n < 8; ++n) {
+                if ((n & need) != n) continue;
+                const int p = lookup_block(v, tt, Bx + (n & 1), By + ((n >> 1) & 1), Bz + (n >> 2), cc.local);
+                n1 = n == 1 ? p : n1;
+                n2 = n == 2 ? p : n2;
+                n3 = n == 3 ? p : n3;
+                n4 = n == 4 ? p : n4;
+                n5 = n == 5 ? p : n5;
+                n6 = n == 6 ? p : n6;
+                n7 = n == 7 ? p : n7;
+            }
+        }
     }
-    int j[8];
-    cell_index(ix, iy, iz, sx, sy, sz, j);
-    C.present = 0u;
+    const int p[4] = {p0, sx ? n1 : p0, sy ? n2 : p0, sx ? (sy ? n3 : n1) : (sy ? n2 : p0)};
+    // in-block indices of the lower corners; a step across a face wraps to index 0
+    int j[4];
+    j[0] = (iz & 7) + 8 * (iy & 7) + 64 * (ix & 7);
+    const int dx = sx ? -448 : 64, dy = sy ? -56 : 8;
+    j[1] = j[0] + dx;
+    j[2] = j[0] + dy;
+    j[3] = j[1] + dy;
+    uint32_t present = 0u;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        C.present |= (p[c] >= 0 ? 1u : 0u) << c;
-        const uint32_t pc = p[c] >= 0 ? (uint32_t)p[c] : 0u;
-        if (kOff32)
-            C.o[c] = __umul24(pc, (uint32_t)kBlockBytes) + 2u * (uint32_t)j[c];
-        else
-            C.o[c] = (size_t)pc * kBlockBytes + 2u * (uint32_t)j[c];
+    for (int c = 0; c < 4; ++c) {
+        present |= (p[c] >= 0 ? 0x11u : 0u) << c;
+        C.o[c] = voxel_offset<kOff32>(p[c], j[c]);
     }
+    C.sz = sz;
+    if (sz) {
+        const int u[4] = {n4, sx ? n5 : n4, sy ? n6 : n4, sx ? (sy ? n7 : n5) : (sy ? n6 : n4)};
+        present &= 0xfu;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            present |= (u[c] >= 0 ? 0x10u : 0u) << c;
+            C.oz[c] = voxel_offset<kOff32>(u[c], j[c] - 7);
+        }
+    }
+    C.present = present;
 }
 
+// The reads are bound by the vector memory unit's rate over the lanes' lines:
+// four 4-byte pairs (any 2-byte alignment; voxel 7's pair reads two bytes past
+// its column, still within its block) instead of eight 2-byte reads.
 template <bool kOff32>
 __device__ __forceinline__ void cell_load(const Vol &v, const RayCell<kOff32> &C, int16_t (&s)[8])
 {
+    uint32_t d[4];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) s[c] = gload(reinterpret_cast<const int16_t *>(v.voxels + C.o[c]));
+    for (int c = 0; c < 4; ++c) d[c] = gload_pair(v.voxels + C.o[c]);
+    uint32_t u[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) u[c] = d[c] >> 16;
+    if (C.sz) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) u[c] = gload(reinterpret_cast<const uint16_t *>(v.voxels + C.oz[c]));
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        s[c] = (int16_t)(d[c] & 0xffffu);
+        s[c + 4] = (int16_t)u[c];
+    }
 }
 
 // trilinear interpolation of F at voxel-unit P (Sec. 4.4)
@@ -459,10 +579,14 @@ __device__ __forceinline__ float trilinear_diff(const Vol &v, const TileTable *t
 // F(P - e_a)) / 2 for the three axes.  The six trilinear cells are those of
 // floor(P) -+ e_a; together they read 32 distinct voxels of the 4 x 4 x 4
 // around floor(P), which spans at most two blocks per axis, so the block
-// pointers are looked up once and the 32 loads issued together.  Each cell
-// keeps the fractions of its own point P -+ e_a, as separate trilinear reads
-// would.  Returns false (nothing computed) when rounding of P -+ 1 moves a
-// cell off floor(P) -+ e_a.
+// pointers are looked up once.  The voxels lie in 12 z columns: four of
+// z - 1 .. z + 2 (dx, dy 0..1), read as 8 bytes each, and eight of z .. z + 1
+// (dx or dy -1 or 2), read as 4 bytes; where the columns cross the block's z
+// face, the rest comes from the block across it.  All loads are issued
+// together; 32 single reads cost the vector memory unit twice the lookups.
+// Each cell keeps the fractions of its own point P -+ e_a, as separate
+// trilinear reads would.  Returns false (nothing computed) when rounding of
+// P -+ 1 moves a cell off floor(P) -+ e_a.
 template <bool kOff32>
 __device__ __forceinline__ bool normal_gradient(const Vol &v, const TileTable *tt, float X, float Y, float Z,
                                                 BlockCache &cc, float &gx, float &gy, float &gz)
@@ -490,62 +614,83 @@ __device__ __forceinline__ bool normal_gradient(const Vol &v, const TileTable *t
                     ? -1
                     : lookup_block(v, tt, Bx + (sx ? ax : 0), By + (sy ? ay : 0), Bz + (sz ? az : 0), lc);
     }
-    // voxel (ix + dx, iy + dy, iz + dz): x-cells dx -1..2, dy 0..1, dz 0..1;
-    // then the y-cells' dy = -1, 2 and the z-cells' dz = -1, 2 (dx, dy 0..1)
-    constexpr int kN = 32;
-    int16_t sv[kN];
-    uint32_t present = 0u;
+    // columns 0..3: (dx, dy) = (c & 1, c >> 1), z - 1 .. z + 2; 4..7: dx -1 / 2
+    // (c & 1), dy 0 / 1 (c >> 1 & 1), and 8..11: dx 0 / 1, dy -1 / 2, z .. z + 1
+    constexpr int kCols = 12;
+    const int lz = iz & 7;
+    const int q0 = lz < 1 ? 0 : (lz > 5 ? 4 : lz - 1);     // first voxel of the own block's 8 bytes
+    unsigned long long quad[4];
+    uint32_t pair[8], over[4], up[8];
+    uint32_t lo = 0u, hi = 0u;                             // columns whose own / other z block is present
+    typename RayCell<kOff32>::Off oo[kCols];               // the other z block's reads
 #pragma unroll
-    for (int i = 0; i < kN; ++i) {
-        int dx, dy, dz;
-        if (i < 16) {
-            dx = (i & 3) - 1;
-            dy = (i >> 2) & 1;
-            dz = i >> 3;
-        } else if (i < 24) {
-            dx = i & 1;
-            dy = ((i >> 1) & 1) ? 2 : -1;
-            dz = (i >> 2) & 1;
-        } else {
-            dx = i & 1;
-            dy = (i >> 1) & 1;
-            dz = ((i >> 2) & 1) ? 2 : -1;
-        }
-        const int x = ix + dx, y = iy + dy, z = iz + dz;
+    for (int c = 0; c < kCols; ++c) {
+        const int k = c & 3;
+        const int dx = c < 4 || c >= 8 ? k & 1 : ((k & 1) ? 2 : -1);
+        const int dy = c < 8 ? k >> 1 : ((k >> 1) ? 2 : -1);
+        const int x = ix + dx, y = iy + dy;
         // selects, not an indexed private array (which would live in scratch)
-        const bool bx = (x >> 3) != Bx, by = (y >> 3) != By, bz = (z >> 3) != Bz;
-        const int pc = bz ? (by ? (bx ? pb[7] : pb[6]) : (bx ? pb[5] : pb[4]))
-                          : (by ? (bx ? pb[3] : pb[2]) : (bx ? pb[1] : pb[0]));
-        present |= (pc >= 0 ? 1u : 0u) << i;
-        const uint32_t pu = pc >= 0 ? (uint32_t)pc : 0u;
-        const uint32_t j = (uint32_t)((z & 7) + 8 * (y & 7) + 64 * (x & 7));
-        if (kOff32)
-            sv[i] = gload(reinterpret_cast<const int16_t *>(v.voxels + (__umul24(pu, (uint32_t)kBlockBytes) + 2u * j)));
+        const bool bx = (x >> 3) != Bx, by = (y >> 3) != By;
+        const int pl = by ? (bx ? pb[3] : pb[2]) : (bx ? pb[1] : pb[0]);
+        const int ph = by ? (bx ? pb[7] : pb[6]) : (bx ? pb[5] : pb[4]);
+        lo |= (pl >= 0 ? 1u : 0u) << c;
+        hi |= (ph >= 0 ? 1u : 0u) << c;
+        const int j = 8 * (y & 7) + 64 * (x & 7);
+        if (c < 4)
+            quad[c] = gload_quad(v.voxels + voxel_offset<kOff32>(pl, j + q0));
         else
-            sv[i] = gload(reinterpret_cast<const int16_t *>(v.voxels + ((size_t)pu * kBlockBytes + 2u * j)));
+            pair[c - 4] = gload_pair(v.voxels + voxel_offset<kOff32>(pl, j + lz));
+        oo[c] = voxel_offset<kOff32>(ph, j + (c < 4 && lz == 0 ? 6 : 0));
     }
-    // a cell from 8 of the loaded voxels, corner c at (c & 1, c >> 1 & 1, c >> 2)
-    auto cell = [&](const int (&idx)[8], float tx, float ty, float tz) {
-        int16_t s8[8];
-        uint32_t pr = 0u;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            s8[c] = sv[idx[c]];
-            pr |= ((present >> idx[c]) & 1u) << c;
+    for (int c = 0; c < 4; ++c) over[c] = 0u;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) up[c] = pair[c] >> 16;
+    if (az != 0) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) over[c] = gload_pair(v.voxels + oo[c]);
+        if (lz == 7) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) up[c] = gload(reinterpret_cast<const uint16_t *>(v.voxels + oo[c + 4]));
         }
-        return cell_lerp(pr, s8, tx, ty, tz);
+    }
+    // F of the columns' voxels (an absent voxel reads 1.0): fq[c][k] at z - 1 + k, fp[c][k] at z + k
+    const auto value = [](uint32_t s, bool there) {
+        return there ? (float)(int16_t)(s & 0xffffu) * (1.0f / 32767.0f) : 1.0f;
     };
+    float fq[4][4], fp[8][2];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const bool pl = (lo >> c) & 1u, ph = (hi >> c) & 1u;
+        // 16-bit positions 0..3 hold z - 1 .. z + 2: the own block's voxels
+        // shifted into place, the other block's in the freed ones
+        const unsigned long long own = quad[c], oth = over[c];
+        const unsigned long long w = lz == 0   ? (own << 16) | (oth >> 16)
+                                     : lz == 7 ? (own >> 32) | (oth << 32)
+                                     : lz == 6 ? (own >> 16) | (oth << 48)
+                                               : own;
+        fq[c][0] = value((uint32_t)w, lz == 0 ? ph : pl);
+        fq[c][1] = value((uint32_t)(w >> 16), pl);
+        fq[c][2] = value((uint32_t)(w >> 32), lz == 7 ? ph : pl);
+        fq[c][3] = value((uint32_t)(w >> 48), lz >= 6 ? ph : pl);
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const bool pl = (lo >> (c + 4)) & 1u, ph = (hi >> (c + 4)) & 1u;
+        fp[c][0] = value(pair[c], pl);
+        fp[c][1] = value(up[c], lz == 7 ? ph : pl);
+    }
     const float tx = X - fX, ty = Y - fY, tz = Z - fZ;
-    // x-cells: index (dx + 1) + 4 dy + 8 dz
-    const int xp[8] = {2, 3, 6, 7, 10, 11, 14, 15}, xm[8] = {0, 1, 4, 5, 8, 9, 12, 13};
-    gx = (cell(xp, Xp - fXp, ty, tz) - cell(xm, Xm - fXm, ty, tz)) * 0.5f;
-    // y-cells: dy 0 / 1 from the x-cells (dx 0 / 1: indices 1, 2 + 4 dy + 8 dz),
-    // dy -1 / 2 at 16 + dx + 2 (dy == 2) + 4 dz
-    const int yp[8] = {5, 6, 18, 19, 13, 14, 22, 23}, ym[8] = {16, 17, 1, 2, 20, 21, 9, 10};
-    gy = (cell(yp, tx, Yp - fYp, tz) - cell(ym, tx, Ym - fYm, tz)) * 0.5f;
-    // z-cells: dz 0 / 1 from the x-cells, dz -1 / 2 at 24 + dx + 2 dy + 4 (dz == 2)
-    const int zp[8] = {9, 10, 13, 14, 28, 29, 30, 31}, zm[8] = {24, 25, 26, 27, 1, 2, 5, 6};
-    gz = (cell(zp, tx, ty, Zp - fZp) - cell(zm, tx, ty, Zm - fZm)) * 0.5f;
+    // cells by their four columns (x, y), (x + 1, y), (x, y + 1), (x + 1, y + 1)
+    const float xp[8] = {fq[1][1], fp[1][0], fq[3][1], fp[3][0], fq[1][2], fp[1][1], fq[3][2], fp[3][1]};
+    const float xm[8] = {fp[0][0], fq[0][1], fp[2][0], fq[2][1], fp[0][1], fq[0][2], fp[2][1], fq[2][2]};
+    gx = (lerp8(xp, Xp - fXp, ty, tz) - lerp8(xm, Xm - fXm, ty, tz)) * 0.5f;
+    const float yp[8] = {fq[2][1], fq[3][1], fp[6][0], fp[7][0], fq[2][2], fq[3][2], fp[6][1], fp[7][1]};
+    const float ym[8] = {fp[4][0], fp[5][0], fq[0][1], fq[1][1], fp[4][1], fp[5][1], fq[0][2], fq[1][2]};
+    gy = (lerp8(yp, tx, Yp - fYp, tz) - lerp8(ym, tx, Ym - fYm, tz)) * 0.5f;
+    const float zp[8] = {fq[0][2], fq[1][2], fq[2][2], fq[3][2], fq[0][3], fq[1][3], fq[2][3], fq[3][3]};
+    const float zm[8] = {fq[0][0], fq[1][0], fq[2][0], fq[3][0], fq[0][1], fq[1][1], fq[2][1], fq[3][1]};
+    gz = (lerp8(zp, tx, ty, Zp - fZp) - lerp8(zm, tx, ty, Zm - fZm)) * 0.5f;
     return true;
 }
 
@@ -624,7 +769,7 @@ __global__ __launch_bounds__(256) void k_raycast(Vol v, Cam c, int all_blocks, f
         // blocks outside it.
         const float zscale = vs * rcz;
         const bool local = all_blocks && tbl.complete && (t - 8.0f - 2.0f * mu_v) * zscale >= kZNear;
-        BlockCache cc = {0x7fffffff, 0, 0, -1, local};
+        BlockCache cc = {0x7fffffff, 0, 0, -1, -1, local};
         int steps = 0;
         while (t < t_end && steps < kMaxRaySteps) {
             if (state == SEARCH_BLOCK_COARSE || state == SEARCH_BLOCK_FINE) {
