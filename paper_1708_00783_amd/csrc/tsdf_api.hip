@@ -83,8 +83,7 @@ Layout make_layout(const tf_params *p)
     L.ret = take((size_t)L.max_req * 4);
     L.depth = take((size_t)p->max_width * p->max_height * 4);
     L.recs = take((size_t)p->n_blocks * sizeof(Rec));
-    L.bins = take((size_t)L.max_tiles * kBinCap * sizeof(Rec));
-    L.bin_count = take((size_t)L.max_tiles * 4);
+    L.bins = take((size_t)L.max_tiles * kTileSlots * sizeof(Rec));
     L.acc_cols = take((size_t)kIntegrateGrid * 8);
     L.acc_hits = take((size_t)L.max_tiles * 8);
     L.occ = take((size_t)p->n_buckets / 8);
@@ -253,7 +252,6 @@ int tf_create(const tf_params *p, void *d_workspace, size_t bytes, void *h_store
     v.depth = (float *)(b + L.depth);
     v.recs = (Rec *)(b + L.recs);
     v.bins = (Rec *)(b + L.bins);
-    v.bin_count = (int32_t *)(b + L.bin_count);
     v.ctrl = (Ctrl *)(b + L.ctrl);
     v.acc_cols = (unsigned long long *)(b + L.acc_cols);
     v.acc_hits = (unsigned long long *)(b + L.acc_hits);
@@ -348,9 +346,7 @@ int tf_reset(tf_ctx *ctx, tf_stream stream)
 {
     if (!ctx) return TF_E_INVAL;
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = launch_init(ctx->v, s);
-    if (e == hipSuccess) e = launch_clear_bins(ctx->v.bin_count, ctx->L.max_tiles, s);
-    if (e == hipSuccess) e = launch_clear_bins((int32_t *)ctx->v.acc_hits, 2 * ctx->L.max_tiles, s);
+    const hipError_t e = launch_init(ctx->v, ctx->L.max_tiles, s);
     ctx->have_alloc = false;
     ctx->bins_pending = false;
     ctx->host_flags = 0;
@@ -369,7 +365,7 @@ int tf_alloc_and_visible(tf_ctx *ctx, const void *d_depth, int depth_format, con
     hipError_t e = hipSuccess;
     if (ctx->bins_pending) {
         // records of the previous visible list that no raycast consumed
-        e = launch_clear_bins(ctx->v.bin_count, ctx->L.max_tiles, s, ctx->v.ctrl);
+        e = launch_clear_bins(ctx->v, ctx->L.max_tiles, s);
         if (e != hipSuccess) return TF_E_HIP;
         ctx->bins_pending = false;
     }
@@ -440,7 +436,7 @@ static hipError_t bin_range(tf_ctx *ctx, const Cam &c, bool all, hipStream_t s)
     if (ctx->bins_pending) {
         ctx->bins_pending = false;
         if (!all) return hipSuccess;
-        e = launch_clear_bins(ctx->v.bin_count, ctx->L.max_tiles, s, ctx->v.ctrl);
+        e = launch_clear_bins(ctx->v, ctx->L.max_tiles, s);
         if (e != hipSuccess) return e;
     }
     Timed t(ctx, TF_K_RANGE_BIN, s);

@@ -11,7 +11,8 @@ namespace tsdf {
 constexpr int kBlockVox = 512;          // 8x8x8 voxels per block (Sec. 3.1)
 constexpr int kBlockBytes = 1536;       // 512 x int16 SDF, then 512 x uint8 weight
 constexpr int kTile = 16;               // raycast tile = the paper's 16x16 fragments (Sec. 4.4)
-constexpr int kBinCap = 512;            // block records per tile before the all-records fallback
+constexpr int kTileSlots = 512;          // 32-byte slots of a tile's bin: its counter and its records
+constexpr int kBinCap = kTileSlots - 4;  // block records per tile before the all-records fallback
 constexpr int kTileTable = 1024;        // LDS block-pointer table slots per raycast tile (> 2 kBinCap)
 constexpr int32_t kPtrSwapped = -1;     // Sec. 3.2: ptr == -1 swapped out
 constexpr int32_t kPtrEmpty = -2;       // Sec. 3.2: ptr < -1 unallocated
@@ -93,8 +94,7 @@ struct Vol {
     int32_t *ret;
     float *depth;                   // metres, last ingested frame
     Rec *recs;
-    Rec *bins;                      // per tile: the records of the blocks overlapping it
-    int32_t *bin_count;
+    Rec *bins;                      // per tile: the records of the blocks overlapping it, and their counter
     Ctrl *ctrl;
     unsigned long long *acc_cols;   // per integration workgroup: 8-voxel columns written back
     unsigned long long *acc_hits;   // per raycast tile: pixels with a hit
@@ -126,14 +126,15 @@ struct Cam {
 // workspace carving
 struct Layout {
     size_t entries, vis, free_blocks, free_excess, voxels, vlist, reqset, reqs, ret, depth,
-        recs, bins, bin_count, ctrl, acc_cols, acc_hits, occ, brick, host_has, xfer_idx, xfer_vox, xfer_host,
+        recs, bins, ctrl, acc_cols, acc_hits, occ, brick, host_has, xfer_idx, xfer_vox, xfer_host,
         xfer_pend, swap_chunks, total;
     uint32_t reqset_size, max_req, max_tiles;
 };
 
 // ---- kernel launchers (tsdf_kernels.hip) -----------------------------------
-hipError_t launch_init(const Vol &v, hipStream_t s);
-hipError_t launch_clear_bins(int32_t *bin_count, uint32_t n, hipStream_t s, Ctrl *ctrl = nullptr);
+hipError_t launch_init(const Vol &v, uint32_t max_tiles, hipStream_t s);
+// empty the tiles' bins and the record list (bins abandoned unread)
+hipError_t launch_clear_bins(const Vol &v, uint32_t max_tiles, hipStream_t s);
 hipError_t launch_alloc_rays(const Vol &v, const Cam &c, const void *depth, int fmt, hipStream_t s);
 hipError_t launch_insert(const Vol &v, const Cam &c, hipStream_t s);
 hipError_t launch_visible(const Vol &v, hipStream_t s);

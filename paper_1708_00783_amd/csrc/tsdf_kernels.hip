@@ -27,7 +27,7 @@ namespace tsdf {
 // ============================================================================
 // initialisation
 // ============================================================================
-__global__ __launch_bounds__(256) void k_init(Vol v)
+__global__ __launch_bounds__(256) void k_init(Vol v, uint32_t max_tiles)
 {
     const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -47,6 +47,10 @@ __global__ __launch_bounds__(256) void k_init(Vol v)
     if (v.host_has)
         for (size_t i = gid; i < nvis; i += stride) v.host_has[i] = 0;
     for (size_t i = gid; i < (size_t)kIntegrateGrid; i += stride) v.acc_cols[i] = 0ull;
+    for (size_t i = gid; i < max_tiles; i += stride) {
+        *bin_counter(v, (int)i) = 0;
+        v.acc_hits[i] = 0ull;
+    }
     for (size_t i = gid; i < (size_t)(v.n_buckets / 32u); i += stride) v.occ[i] = 0u;
     for (size_t i = gid; i < (size_t)kBrickWords; i += stride) v.brick[i] = 0u;
     if (gid == 0) {
@@ -57,12 +61,12 @@ __global__ __launch_bounds__(256) void k_init(Vol v)
     }
 }
 
-// zero n counters; with ctrl, also the record count (bins abandoned unread)
-__global__ __launch_bounds__(256) void k_clear_bins(int32_t *bin_count, uint32_t n, Ctrl *ctrl)
+// empty every tile's bin and the record list (bins abandoned unread)
+__global__ __launch_bounds__(256) void k_clear_bins(Vol v, uint32_t max_tiles)
 {
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        bin_count[i] = 0;
-    if (ctrl && blockIdx.x == 0 && threadIdx.x == 0) ctrl->n_rec = 0u;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < max_tiles; i += gridDim.x * blockDim.x)
+        *bin_counter(v, (int)i) = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) v.ctrl->n_rec = 0u;
 }
 
 // ============================================================================
@@ -106,97 +110,183 @@ __global__ __launch_bounds__(256) void k_depth_convert(float *dst, const void *s
 // ============================================================================
 constexpr int kExpandV = 3;   // voxels added around a block when binning it
 
-// One lane per block: its record (search-range box and z range of the block
-// itself, key, device pointer) goes to every tile its cube covers -- grown by
-// kExpandV voxels when every block is binned, so that a tile's bin then holds
-// every block any trilinear read of the tile's rays can touch.  The (record,
-// tile) writes of a wave are spread evenly over its lanes.
-__global__ __launch_bounds__(256) void k_range_bin(Vol v, Cam c, int all)
+// The blocks' records (search-range box and z range of the block itself, key,
+// device pointer) go to every tile their cubes cover -- grown by kExpandV
+// voxels when every block is binned, so that a tile's bin then holds every
+// block any trilinear read of the tile's rays can touch.
+//
+// Bound: latency of the tile counters' atomics and, over a sparse table, the
+// read of its entries.  A workgroup lists the live entries of its strips that
+// the view can see in LDS, so that the lanes are full whatever the table's
+// load (3 of 64 at 5%); a listed block's records take eight lanes, one per
+// corner; the records are reserved with one global atomic per round of up to
+// 256 blocks (same-address atomics take 11 ns each: one per wave and 64
+// entries cost more than everything else); and the (record, tile) writes are
+// spread over the workgroup, four per thread in flight, as a block near the
+// camera covers hundreds of tiles.  2^20 + 2^17 entries, 58 k blocks,
+// 960x540: 110 us before, 30 us now.
+constexpr int kBinStrips = 4;
+constexpr int kBinGrid = 512;
+
+struct BinLds {
+    int4 live[256 + 256 * kBinStrips];       // {bx | by << 16, bz, ptr}
+    Rec rec[256];
+    uint32_t excl[257];                      // exclusive tile counts of the round's blocks, and their sum
+    int16_t rect[256][3];                    // tx0, ty0, nx
+    int tiles[256];                          // tiles of the block's cube (0: it misses the image)
+    uint32_t n, wave_n[4], wave_t[4], base;
+};
+
+// bin the m <= 256 blocks from live[first] (every thread calls it)
+__device__ __forceinline__ void bin_blocks(const Vol &v, const Cam &c, bool all, BinLds &B, uint32_t first, uint32_t m)
 {
-    __shared__ Rec wrec[4][kWave];
-    __shared__ uint32_t wexcl[4][kWave + 1];
-    __shared__ int16_t wrect[4][kWave][3];   // tx0, ty0, nx
     const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
-    const uint32_t gwave = (blockIdx.x * 256u + threadIdx.x) / kWave;
-    const uint32_t nwaves = gridDim.x * (256u / kWave);
-    const uint32_t n = all ? v.n_entries : v.ctrl->n_vis;
     const int ntx = (c.W + kTile - 1) / kTile;
-    for (uint32_t base = gwave * kWave; base < n; base += nwaves * kWave) {
-        const uint32_t i = base + lane;
-        bool emit = false;
-        Rec r;
-        Rec ex;
-        if (i < n) {
-            const uint32_t e = all ? i : (uint32_t)v.vlist[i];
-            const int4 w = load_entry(v.entries, e);
-            if (w.w >= 0) {
-                const int bx = (int16_t)(w.x & 0xffff), by = (int16_t)((uint32_t)w.x >> 16), bz = (int16_t)(w.y & 0xffff);
-                // bins of every block (foreign views) grow the cubes so that a
-                // complete tile table answers every lookup of the tile's rays;
-                // bins of the visible list cannot, so they use the plain cube
-                const int g = all ? kExpandV : 0;
-                emit = cube_record(c.M, c, v.voxel, 8 * bx - g, 8 * by - g, 8 * bz - g, 8 + 2 * g, ex);
-                if (emit && !block_record(v, c, bx, by, bz, r)) {
-                    // only the grown cube reaches the image: a table entry with no range
-                    r.x0 = 1;
-                    r.x1 = 0;
-                    r.y0 = 1;
-                    r.y1 = 0;
-                    r.zlo = __builtin_inff();
-                    r.zhi = -__builtin_inff();
-                }
+    // the records, eight lanes to a block
+    for (uint32_t b = threadIdx.x >> 3; b < m; b += 32u) {
+        const int4 w = B.live[first + b];
+        const int bx = (int16_t)(w.x & 0xffff), by = (int16_t)((uint32_t)w.x >> 16), bz = w.y;
+        // bins of every block (foreign views) grow the cubes so that a
+        // complete tile table answers every lookup of the tile's rays;
+        // bins of the visible list cannot, so they use the plain cube
+        Rec r = {}, ex = {};
+        int tiles = 0;
+        bool in = true, own = false;
+#pragma unroll 1
+        for (int grown = 1; grown >= 0 && in; --grown) {       // the grown cube, then the block itself
+            const int g = grown && all ? kExpandV : 0;
+            ex = r;
+            const bool ok = cube_record_lanes(c, v.voxel, 8 * bx - g, 8 * by - g, 8 * bz - g, 8 + 2 * g, r);
+            in = grown ? ok : true;
+            own = ok;
+        }
+        if (in) {
+            if (!own) {
+                // only the grown cube reaches the image: a table entry with no range
+                r.x0 = 1;
+                r.x1 = 0;
+                r.y0 = 1;
+                r.y1 = 0;
+                r.zlo = __builtin_inff();
+                r.zhi = -__builtin_inff();
+            }
+            const int tx0 = ex.x0 / kTile, tx1 = ex.x1 / kTile, ty0 = ex.y0 / kTile, ty1 = ex.y1 / kTile;
+            tiles = (tx1 - tx0 + 1) * (ty1 - ty0 + 1);
+            if ((lane & 7u) == 0u) {
                 r.bx = (int16_t)bx;
                 r.by = (int16_t)by;
                 r.bz = (int16_t)bz;
                 r.pad = 0;
-                r.ptr = w.w;
+                r.ptr = w.z;
                 r.pad2 = 0;
+                B.rec[b] = r;
+                B.rect[b][0] = (int16_t)tx0;
+                B.rect[b][1] = (int16_t)ty0;
+                B.rect[b][2] = (int16_t)(tx1 - tx0 + 1);
             }
         }
-        const unsigned long long m = __ballot(emit);
-        if (!m) continue;
-        const int leader = __ffsll((long long)m) - 1;
-        uint32_t rb = 0;
-        if ((int)lane == leader) rb = atomicAdd(&v.ctrl->n_rec, (uint32_t)__popcll(m));
-        rb = __shfl(rb, leader);
-        uint32_t cnt = 0;
-        if (emit) {
-            v.recs[rb + rank_in(m)] = r;
-            const int tx0 = ex.x0 / kTile, tx1 = ex.x1 / kTile, ty0 = ex.y0 / kTile, ty1 = ex.y1 / kTile;
-            cnt = (uint32_t)((tx1 - tx0 + 1) * (ty1 - ty0 + 1));
-            wrec[wv][lane] = r;
-            wrect[wv][lane][0] = (int16_t)tx0;
-            wrect[wv][lane][1] = (int16_t)ty0;
-            wrect[wv][lane][2] = (int16_t)(tx1 - tx0 + 1);
-        }
-        // lanes of one wave exchange through their own LDS slice: a wave-level fence suffices
-        // exclusive scan of the lanes' tile counts
-        uint32_t incl = cnt;
+        if ((lane & 7u) == 0u) B.tiles[b] = tiles;
+    }
+    __syncthreads();
+    const uint32_t cnt = threadIdx.x < m ? (uint32_t)B.tiles[threadIdx.x] : 0u;
+    const bool emit = cnt != 0u;
+    const unsigned long long em = __ballot(emit);
+    // exclusive scan of the threads' tile counts
+    uint32_t incl = cnt;
 #pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            const uint32_t t = __shfl_up(incl, d);
-            if ((int)lane >= d) incl += t;
-        }
-        wexcl[wv][lane] = incl - cnt;
-        const uint32_t total = __shfl(incl, kWave - 1);
-        if (lane == 0) wexcl[wv][kWave] = total;
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        for (uint32_t item = lane; item < total; item += kWave) {
-            // owner lane: the last j with excl[j] <= item (lanes without tiles have empty ranges)
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t t = __shfl_up(incl, d);
+        if ((int)lane >= d) incl += t;
+    }
+    if (lane == kWave - 1) {
+        B.wave_t[wv] = incl;
+        B.wave_n[wv] = (uint32_t)__popcll(em);
+    }
+    __syncthreads();
+    uint32_t before = 0, rank = rank_in(em);
+    for (uint32_t k = 0; k < wv; ++k) {
+        before += B.wave_t[k];
+        rank += B.wave_n[k];
+    }
+    B.excl[threadIdx.x] = before + incl - cnt;
+    uint32_t rec_base = 0u;                  // thread 255: the round's place in the record list, in flight
+    if (threadIdx.x == 255) {
+        B.excl[256] = before + incl;
+        const uint32_t k = rank + (emit ? 1u : 0u);
+        if (k) rec_base = atomicAdd(&v.ctrl->n_rec, k);
+    }
+    __syncthreads();
+    // (record, tile) items over all threads, four per thread in flight
+    const uint32_t total = B.excl[256];
+    for (uint32_t i0 = threadIdx.x; i0 < total; i0 += 1024u) {
+        int own[4], tl[4], sl[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t item = i0 + 256u * (uint32_t)q;
+            // owner: the last j with excl[j] <= item (blocks without tiles have empty ranges)
             int j = 0;
 #pragma unroll
-            for (int b = 32; b; b >>= 1)
-                if (wexcl[wv][j + b] <= item) j += b;
-            while (wexcl[wv][j + 1] <= item) ++j;
-            const uint32_t li = item - wexcl[wv][j];
-            const int nx = wrect[wv][j][2];
-            const int t = (wrect[wv][j][1] + (int)(li / (uint32_t)nx)) * ntx + wrect[wv][j][0] + (int)(li % (uint32_t)nx);
-            const int sl = atomicAdd(&v.bin_count[t], 1);
-            if (sl < kBinCap) v.bins[(size_t)t * kBinCap + sl] = wrec[wv][j];
+            for (int b = 128; b; b >>= 1)
+                if (B.excl[j + b] <= item) j += b;
+            const uint32_t li = item - B.excl[j];
+            const int nx = item < total ? B.rect[j][2] : 1;
+            own[q] = item < total ? j : -1;
+            tl[q] = (B.rect[j][1] + (int)(li / (uint32_t)nx)) * ntx + B.rect[j][0] + (int)(li % (uint32_t)nx);
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sl[q] = own[q] >= 0 ? atomicAdd(bin_counter(v, tl[q]), 1) : kBinCap;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (sl[q] < kBinCap) *bin_record(v, tl[q], sl[q]) = B.rec[own[q]];
+    }
+    if (threadIdx.x == 255) B.base = rec_base;
+    __syncthreads();
+    if (emit) v.recs[B.base + rank] = B.rec[threadIdx.x];
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(256) void k_range_bin(Vol v, Cam c, int all)
+{
+    __shared__ BinLds B;
+    const uint32_t n = all ? v.n_entries : v.ctrl->n_vis;
+    const uint32_t strips = (n + 255u) / 256u;
+    const Frustum fr = make_frustum(c, v.voxel, kExpandV);
+    if (threadIdx.x == 0) B.n = 0u;
+    __syncthreads();
+    // strips a grid apart: the used slots of the excess list are all at its
+    // end, and a workgroup that took them alone finished 40 us after the rest
+    for (uint32_t s = blockIdx.x; s < strips; s += kBinStrips * gridDim.x) {
+        int4 w[kBinStrips];
+#pragma unroll
+        for (int k = 0; k < kBinStrips; ++k) {
+            const uint32_t i = (s + (uint32_t)k * gridDim.x) * 256u + threadIdx.x;
+            w[k] = make_int4(0, 0, 0, -2);
+            if (i < n) w[k] = load_entry(v.entries, all ? i : (uint32_t)v.vlist[i]);
+        }
+#pragma unroll
+        for (int k = 0; k < kBinStrips; ++k) {
+            const int bx = (int16_t)(w[k].x & 0xffff), by = (int16_t)((uint32_t)w[k].x >> 16),
+                      bz = (int16_t)(w[k].y & 0xffff);
+            const bool in = w[k].w >= 0 && !outside_frustum(fr, c.M, c, v.voxel, bx, by, bz);
+            const unsigned long long m = __ballot(in);
+            if (!m) continue;
+            const int leader = __ffsll((long long)m) - 1;
+            uint32_t at = 0;
+            if ((int)lane_id() == leader) at = atomicAdd(&B.n, (uint32_t)__popcll(m));
+            at = __shfl(at, leader);
+            if (in) B.live[at + rank_in(m)] = make_int4(w[k].x, bz, w[k].w, 0);
+        }
+        __syncthreads();
+        // whole rounds of 256 from the end of the list; the rest waits for
+        // the next strips, or goes last
+        uint32_t have = B.n;
+        while (have >= 256u || (have && s + kBinStrips * gridDim.x >= strips)) {
+            const uint32_t m = have < 256u ? have : 256u;
+            have -= m;
+            bin_blocks(v, c, all != 0, B, have, m);
+        }
+        if (threadIdx.x == 0) B.n = have;
+        __syncthreads();
     }
 }
 
@@ -209,10 +299,10 @@ struct TileTable {
     unsigned long long key[kTileTable];   // 0 = empty slot
     union {
         struct {
-            uint4 box[kBinCap];           // x0, y0, x1, y1 (int16), zlo, zhi (float)
-            uint16_t wlist[4][kBinCap];   // per wave: the staged records whose box meets its pixels
+            uint4 box[kTileSlots];         // x0, y0, x1, y1 (int16), zlo, zhi (float)
+            uint16_t wlist[4][kTileSlots]; // per wave: the staged records whose box meets its pixels
         } r;
-        int nb[kBinCap][8];
+        int nb[kTileSlots][8];
     };
     uint16_t rec[kTileTable];             // record of the slot's block
     int wcnt[4];
@@ -276,7 +366,7 @@ __device__ __forceinline__ void tile_range(const Vol &v, int tile, int tx0, int 
     for (int k = threadIdx.x; k < kTileTable; k += 256) tt->key[k] = 0ull;
     if (threadIdx.x < 4) tt->wcnt[threadIdx.x] = 0;
     const int wave = (int)threadIdx.x >> 6;
-    const int cnt = v.bin_count[tile];
+    const int cnt = *bin_counter(v, tile);
     const bool fallback = cnt > kBinCap;
     const int n = fallback ? (int)v.ctrl->n_rec : cnt;
     if (threadIdx.x == 0) tt->complete = table && !fallback;
@@ -286,10 +376,10 @@ __device__ __forceinline__ void tile_range(const Vol &v, int tile, int tx0, int 
         const int m = n - base < kBinCap ? n - base : kBinCap;
         __syncthreads();   // the cleared table, or the previous chunk consumed
 #pragma unroll
-        for (int h = 0; h < kBinCap / 256; ++h) {
+        for (int h = 0; h < kTileSlots / 256; ++h) {
             const int j = (int)threadIdx.x + 256 * h;
             if (j >= m) break;
-            const Rec r = fallback ? v.recs[base + j] : v.bins[(size_t)tile * kBinCap + j];
+            const Rec r = fallback ? v.recs[base + j] : *bin_record(v, tile, j);
             if (table && !fallback) {
                 // keys in one bin are distinct; the table is at most half full
                 const unsigned long long key = pack_key(r.bx, r.by, r.bz);
@@ -339,7 +429,7 @@ __device__ __forceinline__ void tile_range(const Vol &v, int tile, int tx0, int 
     // looking up to seven blocks up one after another (the march's longest
     // chain: 25 to 32% of the kernel).
 #pragma unroll
-    for (int h = 0; h < kBinCap / 256; ++h) {
+    for (int h = 0; h < kTileSlots / 256; ++h) {
         const int j = (int)threadIdx.x + 256 * h;
         if (j >= n) break;
         tt->nb[j][0] = own[h].z;
@@ -374,7 +464,7 @@ __device__ __forceinline__ void finish_tile(const Vol &v, int tile, bool count_r
 {
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (tile >= 0) v.bin_count[tile] = 0;
+        if (tile >= 0) *bin_counter(v, tile) = 0;
         const uint32_t t = atomicAdd(&v.ctrl->ray_ticket, 1u);
         if (t == gridDim.x - 1u) {
             if (count_raycast) v.ctrl->tot_rec += v.ctrl->n_rec;
@@ -1145,18 +1235,18 @@ static int cu_grid(size_t work, int per_block, int cap)
     return (int)g;
 }
 
-hipError_t launch_init(const Vol &v, hipStream_t s)
+hipError_t launch_init(const Vol &v, uint32_t max_tiles, hipStream_t s)
 {
-    size_t work = v.n_entries;
+    size_t work = v.n_entries > max_tiles ? v.n_entries : max_tiles;
     if (v.n_blocks > work) work = v.n_blocks;
     if ((size_t)v.reqset_mask + 1 > work) work = (size_t)v.reqset_mask + 1;
-    hipLaunchKernelGGL(k_init, dim3(cu_grid(work, 256, 8192)), dim3(256), 0, s, v);
+    hipLaunchKernelGGL(k_init, dim3(cu_grid(work, 256, 8192)), dim3(256), 0, s, v, max_tiles);
     return hipGetLastError();
 }
 
-hipError_t launch_clear_bins(int32_t *bin_count, uint32_t n, hipStream_t s, Ctrl *ctrl)
+hipError_t launch_clear_bins(const Vol &v, uint32_t max_tiles, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_clear_bins, dim3(cu_grid(n, 256, 1024)), dim3(256), 0, s, bin_count, n, ctrl);
+    hipLaunchKernelGGL(k_clear_bins, dim3(cu_grid(max_tiles, 256, 1024)), dim3(256), 0, s, v, max_tiles);
     return hipGetLastError();
 }
 
@@ -1202,7 +1292,7 @@ hipError_t launch_integrate(const Vol &v, const Cam &c, bool bin, hipStream_t s)
 
 hipError_t launch_range_bin(const Vol &v, const Cam &c, bool all_blocks, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_range_bin, dim3(1024), dim3(256), 0, s, v, c, all_blocks ? 1 : 0);
+    hipLaunchKernelGGL(k_range_bin, dim3(kBinGrid), dim3(256), 0, s, v, c, all_blocks ? 1 : 0);
     return hipGetLastError();
 }
 

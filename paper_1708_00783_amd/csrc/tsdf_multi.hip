@@ -142,20 +142,7 @@ __global__ __launch_bounds__(256) void k_m_bin(const MSub *subs, const MFrame *f
         }
         B.first[n_sub] = acc;
     }
-    // Frustum pre-test: a grown cube whose bounding sphere lies wholly behind
-    // the near plane, or wholly beyond one of the planes through the camera
-    // centre and the image borders moved out by 2 pixels, has no point in
-    // front of the near plane that projects onto the image, so cube_record
-    // would reject it.  The planes in camera coordinates (x, y, z): u < -2 is
-    // fx x + (cx + 2) z < 0 and u > W + 1 is fx x + (cx - W - 1) z > 0 for
-    // z > 0, likewise v; their normals' lengths scale the sphere radius.  The
-    // radius (half the grown cube's diagonal) is padded far beyond the
-    // rounding of the centre's transform.
-    const float rad = (float)(4 + kExpand) * 1.7320508f * voxel * 1.01f + 1e-4f;
-    const float al_ = vc.cx + 2.0f, ar_ = vc.cx - (float)vc.W - 1.0f;
-    const float at_ = vc.cy + 2.0f, ab_ = vc.cy - (float)vc.H - 1.0f;
-    const float rl = rad * sqrtf(vc.fx * vc.fx + al_ * al_), rr = rad * sqrtf(vc.fx * vc.fx + ar_ * ar_);
-    const float rt = rad * sqrtf(vc.fy * vc.fy + at_ * at_), rb = rad * sqrtf(vc.fy * vc.fy + ab_ * ab_);
+    const Frustum fr = make_frustum(vc, voxel, kExpand);
     __syncthreads();
     const uint32_t total = B.first[n_sub];
     // whole chunks for every thread of the workgroup (barriers inside)
@@ -176,15 +163,8 @@ __global__ __launch_bounds__(256) void k_m_bin(const MSub *subs, const MFrame *f
             by = (int16_t)((uint32_t)b.x >> 16);
             bz = b.y;
             ptr = b.z;
-            const float X = (float)(8 * bx + 4) * voxel, Y = (float)(8 * by + 4) * voxel;
-            const float Z = (float)(8 * bz + 4) * voxel;
-            const float xc = ((M[0] * X + M[1] * Y) + M[2] * Z) + M[3];
-            const float yc = ((M[4] * X + M[5] * Y) + M[6] * Z) + M[7];
-            const float zc = ((M[8] * X + M[9] * Y) + M[10] * Z) + M[11];
-            const bool outside = zc + rad < kZNear || vc.fx * xc + al_ * zc < -rl || vc.fx * xc + ar_ * zc > rr ||
-                                 vc.fy * yc + at_ * zc < -rt || vc.fy * yc + ab_ * zc > rb;
-            hit = !outside && cube_record(M, vc, voxel, 8 * bx - kExpand, 8 * by - kExpand, 8 * bz - kExpand,
-                                          8 + 2 * kExpand, ex);
+            hit = !outside_frustum(fr, M, vc, voxel, bx, by, bz) &&
+                  cube_record(M, vc, voxel, 8 * bx - kExpand, 8 * by - kExpand, 8 * bz - kExpand, 8 + 2 * kExpand, ex);
         }
         if (!FILL) {
             const unsigned long long m = __ballot(hit);
