@@ -73,10 +73,17 @@ __device__ __forceinline__ T gload(const T *p)
 // two adjacent 16-bit values / four of them, at any 2-byte alignment
 typedef uint32_t u32_any2 __attribute__((aligned(2)));
 typedef unsigned long long u64_any2 __attribute__((aligned(2)));
+typedef uint16_t u16_any1 __attribute__((aligned(1)));
 
 __device__ __forceinline__ uint32_t gload_pair(const uint8_t *p)
 {
     return *(const __attribute__((address_space(1))) u32_any2 *)p;
+}
+
+// two adjacent bytes at any address
+__device__ __forceinline__ uint32_t gload_byte_pair(const uint8_t *p)
+{
+    return *(const __attribute__((address_space(1))) u16_any1 *)p;
 }
 
 __device__ __forceinline__ unsigned long long gload_quad(const uint8_t *p)

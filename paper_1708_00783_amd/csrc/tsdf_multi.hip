@@ -406,70 +406,142 @@ __device__ __forceinline__ float zbucket_floor(uint32_t b)
 }
 
 // LDS of one tile: the (submap, block) -> pointer table, the tile's submaps
-// in ascending order with what the field reads, and the per-pixel range
+// in ascending order with what the field reads
 template <int NT>
 struct MTileLds {
-    static constexpr int TT = NT >= 128 ? 4096 : 2048;   // table slots (8 bytes each)
-    unsigned long long slot[TT];                // 0 = empty, else mkey(...) | device pointer
+    static constexpr int kBits = NT >= 128 ? 12 : 11;
+    static constexpr int TT = 1 << kBits;       // table slots (8 bytes each)
+    static constexpr int kStage = TT / 4;       // records staged at a time for the range
+    union {
+        unsigned long long slot[TT];            // 0 = empty, else key << 32 | device pointer
+        struct {
+            uint4 box[kStage];                  // x0, y0, x1, y1 (int16), zlo, zhi (float)
+            uint16_t wlist[NT / 64][kStage];    // per wave: the staged records whose box meets its pixels
+        } r;                                    // before the table is filled
+    };
     float Rs[kMaxSubmaps][12];                  // rotation rows, then translation (voxel units)
     const DEntry *ent[kMaxSubmaps];
     const uint32_t *occ[kMaxSubmaps];
     const uint8_t *vox[kMaxSubmaps];
     uint32_t nb[kMaxSubmaps], ne[kMaxSubmaps];
     int smid[kMaxSubmaps];
+    int org[kMaxSubmaps][3];                    // block at the low corner of the table's window
     unsigned long long mask;
-    uint32_t n_tab, hits, unfit;                // unfit: a record whose key or pointer does not pack
+    uint32_t n_tab, hits;
     uint32_t cut;                               // depth buckets 0 .. cut - 1 are in the table
-    float dlim;                                 // a lookup miss proves absence for reads of points shallower than this
-    uint32_t zlo[NT], zhi[NT];                  // per-pixel range as float bits (all values > 0)
-    uint32_t zlo_all, zhi_all;                  // from records covering the whole tile
+    uint32_t dlim;                              // a lookup miss proves absence for reads of points shallower
+                                                // than this depth (float bits)
+    int wcnt[NT / 64];
 };
 
+// Table key of a block of the tile's k-th submap: its position within a window
+// of 256 blocks per axis, 8 bits each, the submap and a valid bit.  Blocks in
+// the table lie at 1 .. 254 of the window, so that the seven neighbours of any
+// position 0 .. 254 have the keys key + 1, + 256, + 65536 and their sums, and
+// outside that no neighbour is in the table either.  The slot hash is a
+// multiplication, so the neighbours' hashes are sums as well: a cell that
+// crosses block faces finds its seven blocks with a few additions and seven
+// reads in flight, where one lookup after another cost ~70 instructions each.
+constexpr uint32_t kHashMul = 0x9e3779b1u;
+
+__device__ __forceinline__ uint32_t m_neighbour(int n)   // key offset of neighbour n at (n & 1, n >> 1 & 1, n >> 2)
+{
+    return (uint32_t)((n & 1) | ((n & 2) << 7) | ((n & 4) << 14));
+}
+
 template <int NT>
-__device__ __forceinline__ uint32_t mslot(int sm, int bx, int by, int bz)
+__device__ __forceinline__ bool m_key(const MTileLds<NT> &L, int k, int bx, int by, int bz, uint32_t &key)
 {
-    return (hash_index(bx, by, bz, 0xffffffffu) ^ ((uint32_t)sm * 0x9e3779b1u)) & (uint32_t)(MTileLds<NT>::TT - 1);
+    const uint32_t rx = (uint32_t)(bx - L.org[k][0]), ry = (uint32_t)(by - L.org[k][1]),
+                   rz = (uint32_t)(bz - L.org[k][2]);
+    key = 0x80000000u | ((uint32_t)k << 24) | (rz << 16) | (ry << 8) | rx;
+    const uint32_t m = rx > ry ? rx : ry;
+    return (m > rz ? m : rz) <= 254u;
 }
 
-// packed table slot: valid bit 63, submap (6 bits), bz, by, bx (11-bit
-// two's complement each) above the 24-bit device block pointer
-__device__ __forceinline__ bool mfits(int bx, int by, int bz)
+template <int NT>
+__device__ __forceinline__ uint32_t m_slot(uint32_t hash)
 {
-    return bx >= -1024 && bx < 1024 && by >= -1024 && by < 1024 && bz >= -1024 && bz < 1024;
+    return hash >> (32 - MTileLds<NT>::kBits);
 }
 
-__device__ __forceinline__ unsigned long long mkey(int sm, int bx, int by, int bz)
+// records of tile g's bin, from o0 on
+__device__ __forceinline__ int m_bin_range(const MTiles &t, uint32_t g, uint32_t &o0)
 {
-    return (1ull << 63) | ((unsigned long long)sm << 57) | ((unsigned long long)(bz & 0x7ff) << 46) |
-           ((unsigned long long)(by & 0x7ff) << 35) | ((unsigned long long)(bx & 0x7ff) << 24);
+    o0 = t.off[g];
+    uint32_t o1 = t.off[g + 1];
+    if (o1 > t.cap) o1 = t.cap;
+    return o1 > o0 ? (int)(o1 - o0) : 0;
 }
 
-// Search range of the pixel and the tile's LDS state from its bin.  The range
-// is a min/max over the records covering the pixel: each record updates the
-// pixels of its box inside the tile with LDS atomics (positive floats order
-// like their bit patterns); a record covering the whole tile updates one
-// tile-wide pair instead.  Every thread of the workgroup calls it; pixel
-// (px, py) is the calling thread's, the tile spans [tx0, tx0 + TW) x [ty0, ty0 + TH).
+// Search range of pixel (px, py) -- the calling thread's, in its wave's 8 x 8
+// square of the tile [tx0, tx0 + TW) x [ty0, ty0 + TH) -- and the tile's
+// submap set from its bin.  Every thread of the workgroup calls it.  The range is a min / max over the records covering the
+// pixel: the records' boxes are staged in LDS (in the bytes of the block table,
+// filled afterwards), each listed for the waves whose pixels it meets, and
+// every thread goes through its wave's list.  Scattering each record to the
+// pixels of its box instead took two LDS atomics per pixel and record, with a
+// few lanes at work on the largest boxes.
 template <int NT, int TW, int TH>
-__device__ __forceinline__ void m_tile_setup(const MSub *subs, const MTiles &t, uint32_t g, int tx0, int ty0,
-                                             MTileLds<NT> &L)
+__device__ __forceinline__ void m_pixel_range(const MTiles &t, uint32_t g, int tx0, int ty0, int px, int py,
+                                              MTileLds<NT> &L, float &zmin, float &zmax)
 {
-    constexpr int TT = MTileLds<NT>::TT;
-    for (int k = threadIdx.x; k < TT; k += NT) L.slot[k] = 0ull;
-    L.zlo[threadIdx.x] = 0x7f800000u;   // +inf
-    L.zhi[threadIdx.x] = 0u;            // below every positive float
+    constexpr int kStage = MTileLds<NT>::kStage, kWaves = NT / 64;
+    const int wave = (int)threadIdx.x >> 6;
+    if (threadIdx.x < kWaves) L.wcnt[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
         L.mask = 0ull;
         L.n_tab = 0u;
         L.hits = 0u;
-        L.unfit = 0u;
-        L.zlo_all = 0x7f800000u;
-        L.zhi_all = 0u;
     }
-    const uint32_t o0 = t.off[g];
-    uint32_t o1 = t.off[g + 1];
-    if (o1 > t.cap) o1 = t.cap;
-    const int n = o1 > o0 ? (int)(o1 - o0) : 0;
+    uint32_t o0;
+    const int n = m_bin_range(t, g, o0);
+    zmin = __builtin_inff();
+    zmax = -__builtin_inff();
+    for (int b0 = 0; b0 < n; b0 += kStage) {
+        const int m = n - b0 < kStage ? n - b0 : kStage;
+        __syncthreads();   // the lists are empty, the previous records consumed
+        for (int j = (int)threadIdx.x; j < m; j += NT) {
+            const uint4 b = *reinterpret_cast<const uint4 *>(t.bins + o0 + (uint32_t)(b0 + j));
+            L.r.box[j] = b;
+            atomicOr(&L.mask, 1ull << (uint32_t)t.bins[o0 + (uint32_t)(b0 + j)].pad);
+            const int x0 = (int16_t)(b.x & 0xffffu), y0 = (int16_t)(b.x >> 16);
+            const int x1 = (int16_t)(b.y & 0xffffu), y1 = (int16_t)(b.y >> 16);
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const int wx0 = tx0 + (w % (TW / 8)) * 8, wy0 = ty0 + (w / (TW / 8)) * 8;
+                if (x0 <= wx0 + 7 && x1 >= wx0 && y0 <= wy0 + 7 && y1 >= wy0)
+                    L.r.wlist[w][atomicAdd(&L.wcnt[w], 1)] = (uint16_t)j;
+            }
+        }
+        __syncthreads();
+        // the order of a wave's list varies with the atomics; min and max do not
+        const int nw = __builtin_amdgcn_readfirstlane(L.wcnt[wave]);
+        for (int i = 0; i < nw; ++i) {
+            const uint4 b = L.r.box[L.r.wlist[wave][i]];
+            const int x0 = (int16_t)(b.x & 0xffffu), y0 = (int16_t)(b.x >> 16);
+            const int x1 = (int16_t)(b.y & 0xffffu), y1 = (int16_t)(b.y >> 16);
+            if (px >= x0 && px <= x1 && py >= y0 && py <= y1) {
+                const float zl = __uint_as_float(b.z), zh = __uint_as_float(b.w);
+                zmin = zl < zmin ? zl : zmin;
+                zmax = zh > zmax ? zh : zmax;
+            }
+        }
+        if ((threadIdx.x & 63) == 0) L.wcnt[wave] = 0;
+    }
+    __syncthreads();   // the boxes are read: their bytes become the table
+}
+
+// The tile's block table and its submaps' data, after m_pixel_range (every
+// thread of the workgroup calls it).
+template <int NT, int TW, int TH>
+__device__ __forceinline__ void m_table(const MSub *subs, const MTiles &t, uint32_t g, int tx0, int ty0, const Cam &c,
+                                        float voxel, MTileLds<NT> &L)
+{
+    constexpr int TT = MTileLds<NT>::TT;
+    uint32_t o0;
+    const int n = m_bin_range(t, g, o0);
+    for (int k = threadIdx.x; k < TT; k += NT) L.slot[k] = 0ull;
     uint32_t cut = kZBuckets;
     if (n > TT / 2) {
         // More records than the table holds: those nearest the camera go in.
@@ -491,42 +563,10 @@ __device__ __forceinline__ void m_tile_setup(const MSub *subs, const MTiles &t, 
         cut = L.cut;
         for (int k = threadIdx.x; k < kZBuckets; k += NT) hist[k] = 0u;
     }
-    if (threadIdx.x == 0) L.dlim = cut >= kZBuckets ? __builtin_inff() : zbucket_floor(cut);
-    __syncthreads();
-    for (int j = (int)threadIdx.x; j < n; j += NT) {
-        const Rec r = t.bins[o0 + (uint32_t)j];
-        atomicOr(&L.mask, 1ull << (uint32_t)r.pad);
-        // keys in one bin are distinct; the table is at most half full
-        if (zbucket((uint32_t)r.pad2) >= cut) {
-            // left out: deeper than the table's depth limit
-        } else if (!mfits(r.bx, r.by, r.bz) || r.ptr >= (1 << 24)) {
-            L.unfit = 1u;
-        } else if (atomicAdd(&L.n_tab, 1u) < (uint32_t)(TT / 2)) {
-            const unsigned long long val = mkey(r.pad, r.bx, r.by, r.bz) | (unsigned long long)r.ptr;
-            uint32_t sl = mslot<NT>(r.pad, r.bx, r.by, r.bz);
-            for (int k = 0; k < TT; ++k) {
-                if (atomicCAS(&L.slot[sl], 0ull, val) == 0ull) break;
-                sl = (sl + 1u) & (uint32_t)(TT - 1);
-            }
-        }
-        const int x0 = r.x0 > tx0 ? r.x0 : tx0, x1 = r.x1 < tx0 + TW - 1 ? r.x1 : tx0 + TW - 1;
-        const int y0 = r.y0 > ty0 ? r.y0 : ty0, y1 = r.y1 < ty0 + TH - 1 ? r.y1 : ty0 + TH - 1;
-        if (x0 > x1 || y0 > y1) continue;
-        const uint32_t lo = __float_as_uint(r.zlo), hi = __float_as_uint(r.zhi);
-        if (x0 == tx0 && x1 == tx0 + TW - 1 && y0 == ty0 && y1 == ty0 + TH - 1) {
-            atomicMin(&L.zlo_all, lo);
-            atomicMax(&L.zhi_all, hi);
-            continue;
-        }
-        for (int y = y0; y <= y1; ++y)
-            for (int x = x0; x <= x1; ++x) {
-                const int pi = (y - ty0) * TW + (x - tx0);
-                atomicMin(&L.zlo[pi], lo);
-                atomicMax(&L.zhi[pi], hi);
-            }
-    }
-    __syncthreads();
-    // the tile's submaps, ascending
+    if (threadIdx.x == 0) L.dlim = __float_as_uint(cut >= kZBuckets ? __builtin_inff() : zbucket_floor(cut));
+    // the tile's submaps, ascending, each with its table window: centred 120
+    // blocks out on the tile's central ray, so that it holds everything from the
+    // camera to twice that whatever the submap's rotation
     if (threadIdx.x < (unsigned)kMaxSubmaps) {
         const unsigned long long m = L.mask;
         const int sm = (int)threadIdx.x;
@@ -541,100 +581,47 @@ __device__ __forceinline__ void m_tile_setup(const MSub *subs, const MTiles &t, 
             L.nb[k] = S.n_buckets;
             L.ne[k] = S.n_excess;
             L.smid[k] = sm;
+            const float a = ((float)(tx0 + TW / 2) - c.cx) / c.fx, b = ((float)(ty0 + TH / 2) - c.cy) / c.fy;
+            const float far = 960.0f / sqrtf((a * a + b * b) + 1.0f), inv_vs = 1.0f / voxel;
+            float P[3];
+            for (int q = 0; q < 3; ++q)
+                P[q] = c.ti[q] * inv_vs + far * ((c.Ri[3 * q] * a + c.Ri[3 * q + 1] * b) + c.Ri[3 * q + 2]);
+            for (int q = 0; q < 3; ++q)
+                L.org[k][q] =
+                    block_of(((S.R[3 * q] * P[0] + S.R[3 * q + 1] * P[1]) + S.R[3 * q + 2] * P[2]) + S.s[q]) - 127;
+        }
+    }
+    __syncthreads();
+    for (int j = (int)threadIdx.x; j < n; j += NT) {
+        const Rec r = t.bins[o0 + (uint32_t)j];
+        if (zbucket((uint32_t)r.pad2) >= cut) continue;    // left out: deeper than the table's depth limit
+        const int k = __popcll(L.mask & ((1ull << (uint32_t)r.pad) - 1ull));
+        uint32_t key;
+        const bool fits = m_key(L, k, r.bx, r.by, r.bz, key) && (key & 0xffu) && (key & 0xff00u) && (key & 0xff0000u);
+        if (fits && atomicAdd(&L.n_tab, 1u) < (uint32_t)(TT / 2)) {
+            // keys in one bin are distinct; the table is at most half full
+            const unsigned long long val = ((unsigned long long)key << 32) | (uint32_t)r.ptr;
+            uint32_t sl = m_slot<NT>(key * kHashMul);
+            for (int q = 0; q < TT; ++q) {
+                if (atomicCAS(&L.slot[sl], 0ull, val) == 0ull) break;
+                sl = (sl + 1u) & (uint32_t)(TT - 1);
+            }
+        } else {
+            // left out: reads at points shallower than its grown cube cannot touch it
+            atomicMin(&L.dlim, (uint32_t)r.pad2);
         }
     }
     __syncthreads();
 }
 
-// the calling thread's pixel range after m_tile_setup (pixel index pi in the tile)
-template <int NT>
-__device__ __forceinline__ void m_pixel_range(const MTileLds<NT> &L, int pi, float &zmin, float &zmax)
-{
-    const uint32_t lo = L.zlo[pi] < L.zlo_all ? L.zlo[pi] : L.zlo_all;
-    const uint32_t hi = L.zhi[pi] > L.zhi_all ? L.zhi[pi] : L.zhi_all;
-    zmin = __uint_as_float(lo);                               // +inf when nothing covers the pixel
-    zmax = hi ? __uint_as_float(hi) : -__builtin_inff();
-}
-
 // device pointer of block (bx, by, bz) of the k-th submap of the tile (-1 =
-// absent): the LDS table first; unless `local`, then the submap's bucket
-// bitmap and hash table.  `local` holds when the table has every record of
-// the tile's bin and the read belongs to a ray point at or beyond the near
-// plane: every block within 3 voxels of such a point is in the bin (blocks
-// are binned by their cube grown by 3 voxels), so a miss proves absence.
-// A lookup in two halves, so that two submaps' lookups can be in flight
-// together: begin probes the LDS table and, when the table cannot answer,
-// issues the bucket's occupancy word and entry loads; end resolves them
-// (walking the chain beyond the bucket when the entry is another block's).
-struct MLookup {
-    int ptr;        // the answer when `pending` is false
-    bool pending;
-    uint32_t h, ow;
-    int4 w;
-};
-
+// absent) from the submap's bucket bitmap and hash table: the bucket's
+// occupancy bit and its entry, loaded together; the chain beyond the bucket
+// only when the entry is another block's
 template <int NT>
-__device__ __forceinline__ void m_lookup_begin(const MTileLds<NT> &L, int k, int bx, int by, int bz, bool local,
-                                               MLookup &q)
+__device__ __forceinline__ int m_map_find(const MTileLds<NT> &L, int k, int bx, int by, int bz)
 {
-    constexpr int TT = MTileLds<NT>::TT;
-    q.pending = false;
-    q.ptr = -1;
-    if (!in_short_range(bx) || !in_short_range(by) || !in_short_range(bz)) return;
-    const int sm = L.smid[k];
-    if (mfits(bx, by, bz)) {
-        const unsigned long long key = mkey(sm, bx, by, bz) >> 24;
-        uint32_t sl = mslot<NT>(sm, bx, by, bz);
-        for (int it = 0; it < TT; ++it) {
-            const unsigned long long kk = L.slot[sl];
-            if ((kk >> 24) == key) {
-                q.ptr = (int)(kk & 0xffffffull);
-                return;
-            }
-            if (kk == 0ull) break;
-            sl = (sl + 1u) & (uint32_t)(TT - 1);
-        }
-    }
-    if (local) return;
-    q.pending = true;
-    q.h = hash_index(bx, by, bz, L.nb[k] - 1u);
-    q.ow = gload(L.occ[k] + (q.h >> 5));
-    q.w = load_entry(L.ent[k], q.h);
-}
-
-template <int NT>
-__device__ __forceinline__ int m_lookup_end(const MTileLds<NT> &L, int k, int bx, int by, int bz, const MLookup &q)
-{
-    if (!q.pending) return q.ptr;
-    if (!((q.ow >> (q.h & 31u)) & 1u)) return -1;
-    const uint32_t kxy = (uint32_t)(uint16_t)bx | ((uint32_t)(uint16_t)by << 16);
-    const int4 w = q.w;
-    if ((uint32_t)w.x == kxy && (int16_t)(w.y & 0xffff) == (int16_t)bz && w.w >= 0) return w.w;
-    if (w.z < 1 || (uint32_t)(w.z - 1) >= L.ne[k]) return -1;
-    int ptr = -1;
-    const int e = find_entry_from(L.ent[k], L.nb[k], L.ne[k], L.nb[k] + (uint32_t)(w.z - 1), bx, by, bz, 0, &ptr);
-    return e >= 0 ? ptr : -1;
-}
-
-template <int NT>
-__device__ __forceinline__ int m_lookup(const MTileLds<NT> &L, int k, int bx, int by, int bz, bool local)
-{
-    constexpr int TT = MTileLds<NT>::TT;
     if (!in_short_range(bx) || !in_short_range(by) || !in_short_range(bz)) return -1;
-    const int sm = L.smid[k];
-    if (mfits(bx, by, bz)) {
-        const unsigned long long key = mkey(sm, bx, by, bz) >> 24;
-        uint32_t sl = mslot<NT>(sm, bx, by, bz);
-        for (int it = 0; it < TT; ++it) {
-            const unsigned long long kk = L.slot[sl];
-            if ((kk >> 24) == key) return (int)(kk & 0xffffffull);
-            if (kk == 0ull) break;
-            sl = (sl + 1u) & (uint32_t)(TT - 1);
-        }
-    }
-    if (local) return -1;
-    // the bucket's occupancy bit and its entry, loaded together; the chain
-    // beyond the bucket only when the entry is another block's
     const uint32_t h = hash_index(bx, by, bz, L.nb[k] - 1u);
     const uint32_t ow = gload(L.occ[k] + (h >> 5));
     const int4 w = load_entry(L.ent[k], h);
@@ -647,6 +634,36 @@ __device__ __forceinline__ int m_lookup(const MTileLds<NT> &L, int k, int bx, in
     return e >= 0 ? ptr : -1;
 }
 
+// the LDS table's answer for a key with its hash: the pointer, or -1
+template <int NT>
+__device__ __forceinline__ int m_table_find(const MTileLds<NT> &L, uint32_t key, uint32_t hash)
+{
+    constexpr int TT = MTileLds<NT>::TT;
+    uint32_t sl = m_slot<NT>(hash);
+    for (int it = 0; it < TT; ++it) {
+        const unsigned long long kk = L.slot[sl];
+        if ((uint32_t)(kk >> 32) == key) return (int)(uint32_t)kk;
+        if (kk == 0ull) break;
+        sl = (sl + 1u) & (uint32_t)(TT - 1);
+    }
+    return -1;
+}
+
+// Device pointer of block (bx, by, bz) of the k-th submap: the LDS table
+// first; unless `local`, then the submap's own table.  `local` holds when the
+// read belongs to a ray point at or beyond the near plane and shallower than
+// every block left out of the LDS table: every block within 3 voxels of such
+// a point is in the bin (blocks are binned by their cube grown by 3 voxels),
+// so a miss proves absence.
+template <int NT>
+__device__ __forceinline__ int m_lookup(const MTileLds<NT> &L, int k, int bx, int by, int bz, bool local)
+{
+    uint32_t key;
+    int p = -1;
+    if (m_key(L, k, bx, by, bz, key)) p = m_table_find(L, key, key * kHashMul);
+    return p >= 0 || local ? p : m_map_find(L, k, bx, by, bz);
+}
+
 template <int NT>
 __device__ __forceinline__ void to_sub(const MTileLds<NT> &L, int k, float P0, float P1, float P2, float &Q0,
                                        float &Q1, float &Q2)
@@ -655,13 +672,6 @@ __device__ __forceinline__ void to_sub(const MTileLds<NT> &L, int k, float P0, f
     Q0 = ((R[0] * P0 + R[1] * P1) + R[2] * P2) + R[9];
     Q1 = ((R[3] * P0 + R[4] * P1) + R[5] * P2) + R[10];
     Q2 = ((R[6] * P0 + R[7] * P1) + R[8] * P2) + R[11];
-}
-
-// position in the tile's submap list of submap sm (a bit of L.mask)
-template <int NT>
-__device__ __forceinline__ int tile_slot(const MTileLds<NT> &L, int sm)
-{
-    return __popcll(L.mask & ((1ull << (uint32_t)sm) - 1ull));
 }
 
 // the tile's submaps that can be allocated at, or weigh in the field at,
@@ -674,110 +684,122 @@ __device__ __forceinline__ unsigned long long m_cell_mask(const MTiles &t, const
 }
 
 // "allocated" of the combined map: some submap has a device block at
-// floor(P_i X); only the submaps of P's cell mask cm can
+// floor(P_i X); only the submaps of P's cell mask cm can.  The submaps are
+// taken one by one by the whole wave (k and its data uniform); a lane takes
+// part in those of its mask.
 template <int NT>
-__device__ __forceinline__ bool m_allocated(const MTileLds<NT> &L, unsigned long long cm, float P0, float P1, float P2,
-                                            bool local)
+__device__ __forceinline__ bool m_allocated(const MTileLds<NT> &L, int nsub, unsigned long long cm, float P0, float P1,
+                                            float P2, bool local)
 {
-    for (; cm; cm &= cm - 1ull) {
-        const int k = tile_slot(L, __ffsll((long long)cm) - 1);
+    bool found = false;
+    for (int k = 0; k < nsub; ++k) {
+        const int sm = __builtin_amdgcn_readfirstlane(L.smid[k]);
+        if (found || !((cm >> (uint32_t)sm) & 1ull)) continue;
         float Q0, Q1, Q2;
         to_sub(L, k, P0, P1, P2, Q0, Q1, Q2);
-        if (m_lookup(L, k, block_of(Q0), block_of(Q1), block_of(Q2), local) >= 0) return true;
+        found = m_lookup(L, k, block_of(Q0), block_of(Q1), block_of(Q2), local) >= 0;
     }
-    return false;
+    return found;
 }
 
-// one submap's trilinear cell at P: the fractions, the base voxel and its
-// block, the crossed faces and (once set up) the corner pointers
-struct MCell {
-    float tx, ty, tz;
-    int ix, iy, iz;
-    int p[8];
-};
-
+// One submap's term of the combined field at P: its trilinear weight (absent
+// voxels weigh 0, the same lerp order as the SDF) and, when positive, its F.
+// Corners c and c + 4 are one voxel apart along z, next to each other in
+// memory unless the cell crosses its block's upper z face: SDF and weights are
+// read as pairs.
 template <int NT>
-__device__ __forceinline__ void m_cell_begin(const MTileLds<NT> &L, int k, float P0, float P1, float P2, bool local,
-                                             MCell &C, MLookup &q)
+__device__ __forceinline__ void m_term(const MTileLds<NT> &L, int k, float P0, float P1, float P2, bool local, int &cnt,
+                                       float &first, float &num, float &den)
 {
     float Q0, Q1, Q2;
     to_sub(L, k, P0, P1, P2, Q0, Q1, Q2);
     const float fbx = floorf(Q0), fby = floorf(Q1), fbz = floorf(Q2);
-    C.tx = Q0 - fbx;
-    C.ty = Q1 - fby;
-    C.tz = Q2 - fbz;
-    C.ix = (int)fbx;
-    C.iy = (int)fby;
-    C.iz = (int)fbz;
-    m_lookup_begin(L, k, C.ix >> 3, C.iy >> 3, C.iz >> 3, local, q);
-}
-
-// the corner pointers: the cell's own block from the pending lookup, the
-// blocks across crossed faces looked up directly
-template <int NT>
-__device__ __forceinline__ void m_cell_end(const MTileLds<NT> &L, int k, bool local, MCell &C, const MLookup &q)
-{
-    const int Bx = C.ix >> 3, By = C.iy >> 3, Bz = C.iz >> 3;
-    const bool sx = (C.ix & 7) == 7, sy = (C.iy & 7) == 7, sz = (C.iz & 7) == 7;
-    const int p000 = m_lookup_end(L, k, Bx, By, Bz, q);
-    int p100 = p000, p010 = p000, p001 = p000, p110 = p000, p101 = p000, p011 = p000, p111 = p000;
-    if (sx | sy | sz) {
-        if (sx) p100 = m_lookup(L, k, Bx + 1, By, Bz, local);
-        if (sy) p010 = m_lookup(L, k, Bx, By + 1, Bz, local);
-        if (sz) p001 = m_lookup(L, k, Bx, By, Bz + 1, local);
-        p110 = (sx & sy) ? m_lookup(L, k, Bx + 1, By + 1, Bz, local) : (sx ? p100 : p010);
-        p101 = (sx & sz) ? m_lookup(L, k, Bx + 1, By, Bz + 1, local) : (sx ? p100 : p001);
-        p011 = (sy & sz) ? m_lookup(L, k, Bx, By + 1, Bz + 1, local) : (sy ? p010 : p001);
-        p111 = (sx & sy & sz) ? m_lookup(L, k, Bx + 1, By + 1, Bz + 1, local)
-                              : (sx & sy) ? p110 : (sx & sz) ? p101 : (sy & sz) ? p011 : sx ? p100 : sy ? p010 : p001;
+    const float tx = Q0 - fbx, ty = Q1 - fby, tz = Q2 - fbz;
+    const int ix = (int)fbx, iy = (int)fby, iz = (int)fbz;
+    const int Bx = ix >> 3, By = iy >> 3, Bz = iz >> 3;
+    const bool sx = (ix & 7) == 7, sy = (iy & 7) == 7, sz = (iz & 7) == 7;
+    const int need = (sx ? 1 : 0) | (sy ? 2 : 0) | (sz ? 4 : 0);
+    uint32_t key;
+    const bool in = m_key(L, k, Bx, By, Bz, key);
+    const uint32_t hash = key * kHashMul;
+    // first probes of the block and, for a cell that crosses a face, its seven
+    // neighbours; `open`: those still to look up (slot of another block, or a
+    // miss that proves nothing)
+    int p[8];
+    uint32_t open = 0u;
+    {
+        const unsigned long long kk = in ? L.slot[m_slot<NT>(hash)] : 0ull;
+        const uint32_t hi = (uint32_t)(kk >> 32);
+        p[0] = hi == key ? (int)(uint32_t)kk : -1;
+        open |= (hi != key && (hi != 0u || !local)) ? 1u : 0u;
     }
-    C.p[0] = p000;
-    C.p[1] = p100;
-    C.p[2] = p010;
-    C.p[3] = p110;
-    C.p[4] = p001;
-    C.p[5] = p101;
-    C.p[6] = p011;
-    C.p[7] = p111;
-}
-
-// the cell's SDF and weight reads (an absent corner reads block 0; its
-// values are not used)
-template <int NT>
-__device__ __forceinline__ void m_cell_load(const MTileLds<NT> &L, int k, const MCell &C, int16_t (&s)[8],
-                                            uint8_t (&w8)[8])
-{
+#pragma unroll
+    for (int n = 1; n < 8; ++n) p[n] = -1;
+    if (need) {
+        unsigned long long kk[8];
+#pragma unroll
+        for (int n = 1; n < 8; ++n) kk[n] = in ? L.slot[m_slot<NT>(hash + m_neighbour(n) * kHashMul)] : 0ull;
+#pragma unroll
+        for (int n = 1; n < 8; ++n) {
+            const uint32_t hi = (uint32_t)(kk[n] >> 32), kn = key + m_neighbour(n);
+            p[n] = hi == kn ? (int)(uint32_t)kk[n] : -1;
+            if ((n & need) == n) open |= (hi != kn && (hi != 0u || !local)) ? 1u << n : 0u;
+        }
+    }
+    while (open) {
+        const int n = __ffs((int)open) - 1;
+        open &= open - 1u;
+        const int q = m_lookup(L, k, Bx + (n & 1), By + ((n >> 1) & 1), Bz + (n >> 2), local);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) p[m] = m == n ? q : p[m];
+    }
+    // corner blocks, lower then upper z
+    const int lo[4] = {p[0], sx ? p[1] : p[0], sy ? p[2] : p[0], sx ? (sy ? p[3] : p[1]) : (sy ? p[2] : p[0])};
+    const int up[4] = {sz ? p[4] : lo[0], sz ? (sx ? p[5] : p[4]) : lo[1], sz ? (sy ? p[6] : p[4]) : lo[2],
+                       sz ? (sx ? (sy ? p[7] : p[5]) : (sy ? p[6] : p[4])) : lo[3]};
+    int j[4];
+    j[0] = (iz & 7) + 8 * (iy & 7) + 64 * (ix & 7);
+    const int dx = sx ? -448 : 64, dy = sy ? -56 : 8;
+    j[1] = j[0] + dx;
+    j[2] = j[0] + dy;
+    j[3] = j[1] + dy;
     const uint8_t *vox = L.vox[k];
-    int j[8];
-    cell_index(C.ix, C.iy, C.iz, (C.ix & 7) == 7, (C.iy & 7) == 7, (C.iz & 7) == 7, j);
+    uint32_t sp[4], wp[4];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const uint8_t *blk = vox + (size_t)(C.p[c] >= 0 ? C.p[c] : 0) * kBlockBytes;
-        s[c] = gload(reinterpret_cast<const int16_t *>(blk) + j[c]);
-        w8[c] = gload(blk + 1024 + j[c]);
+    for (int c = 0; c < 4; ++c) {
+        const uint8_t *blk = vox + (size_t)(uint32_t)(lo[c] >= 0 ? lo[c] : 0) * kBlockBytes;
+        sp[c] = gload_pair(blk + 2 * j[c]);
+        // voxel 7's weight with the one below it (the pair above would end past the block)
+        wp[c] = gload_byte_pair(blk + 1024 + (sz ? j[c] - 1 : j[c]));
     }
-}
-
-// one submap's term of the combined field: its trilinear weight (absent
-// voxels weigh 0, same lerp order as the SDF) and, when positive, its F
-__device__ __forceinline__ void m_cell_accumulate(const MCell &C, const int16_t (&s)[8], const uint8_t (&w8)[8],
-                                                  int &cnt, float &first, float &num, float &den)
-{
-    float wf[8];
+    int16_t s[8];
+    uint32_t w8[8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) wf[c] = C.p[c] >= 0 ? (float)w8[c] : 0.0f;
-    const float c00 = wf[0] + (wf[1] - wf[0]) * C.tx;
-    const float c10 = wf[2] + (wf[3] - wf[2]) * C.tx;
-    const float c01 = wf[4] + (wf[5] - wf[4]) * C.tx;
-    const float c11 = wf[6] + (wf[7] - wf[6]) * C.tx;
-    const float c0 = c00 + (c10 - c00) * C.ty;
-    const float c1 = c01 + (c11 - c01) * C.ty;
-    const float w = c0 + (c1 - c0) * C.tz;
-    if (!(w > 0.0f)) return;
+    for (int c = 0; c < 4; ++c) {
+        s[c] = (int16_t)(sp[c] & 0xffffu);
+        s[c + 4] = (int16_t)(sp[c] >> 16);
+        w8[c] = sz ? wp[c] >> 8 : wp[c] & 0xffu;
+        w8[c + 4] = wp[c] >> 8;
+    }
+    if (sz) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint8_t *blk = vox + (size_t)(uint32_t)(up[c] >= 0 ? up[c] : 0) * kBlockBytes;
+            s[c + 4] = gload(reinterpret_cast<const int16_t *>(blk) + (j[c] - 7));
+            w8[c + 4] = gload(blk + 1024 + (j[c] - 7));
+        }
+    }
+    float wf[8];
     uint32_t present = 0u;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) present |= (C.p[c] >= 0 ? 1u : 0u) << c;
-    const float F = cell_lerp(present, s, C.tx, C.ty, C.tz);
+    for (int c = 0; c < 8; ++c) {
+        const bool there = (c < 4 ? lo[c & 3] : up[c & 3]) >= 0;
+        wf[c] = there ? (float)w8[c] : 0.0f;
+        present |= (there ? 1u : 0u) << c;
+    }
+    const float w = lerp8(wf, tx, ty, tz);
+    if (!(w > 0.0f)) return;
+    const float F = cell_lerp(present, s, tx, ty, tz);
     if (cnt == 0) first = F;
     num = num + w * F;
     den = den + w;
@@ -786,39 +808,25 @@ __device__ __forceinline__ void m_cell_accumulate(const MCell &C, const int16_t 
 
 // combined field at world voxel-unit P over the submaps of P's cell mask cm
 // (every submap with positive weight at P is one of them), in ascending
-// submap order.  Submaps are taken two at a time: both cells' lookups, then
-// both cells' reads are in flight together before either term is added.
+// submap order: the wave takes the submaps one by one, as in m_allocated
 template <int NT>
-__device__ __forceinline__ float m_field(const MTileLds<NT> &L, unsigned long long cm, float P0, float P1, float P2,
-                                         bool local)
+__device__ __forceinline__ float m_field(const MTileLds<NT> &L, int nsub, unsigned long long cm, float P0, float P1,
+                                         float P2, bool local)
 {
     int cnt = 0;
     float first = 1.0f, num = 0.0f, den = 0.0f;
-    while (cm) {
-        const int ka = tile_slot(L, __ffsll((long long)cm) - 1);
-        cm &= cm - 1ull;
-        const bool two = cm != 0ull;
-        const int kb = two ? tile_slot(L, __ffsll((long long)cm) - 1) : ka;
-        if (two) cm &= cm - 1ull;
-        MCell A, B;
-        MLookup qa, qb;
-        m_cell_begin(L, ka, P0, P1, P2, local, A, qa);
-        if (two) m_cell_begin(L, kb, P0, P1, P2, local, B, qb);
-        m_cell_end(L, ka, local, A, qa);
-        if (two) m_cell_end(L, kb, local, B, qb);
-        int16_t sa[8], sb[8];
-        uint8_t wa[8], wb[8];
-        m_cell_load(L, ka, A, sa, wa);
-        if (two) m_cell_load(L, kb, B, sb, wb);
-        m_cell_accumulate(A, sa, wa, cnt, first, num, den);
-        if (two) m_cell_accumulate(B, sb, wb, cnt, first, num, den);
+    for (int k = 0; k < nsub; ++k) {
+        const int sm = __builtin_amdgcn_readfirstlane(L.smid[k]);
+        if ((cm >> (uint32_t)sm) & 1ull) m_term(L, k, P0, P1, P2, local, cnt, first, num, den);
     }
     if (cnt == 0) return 1.0f;
     if (cnt == 1) return first;
     return num / den;
 }
 
-enum { M_COARSE, M_FINE, M_SURFACE, M_BEHIND, M_WRONG_SIDE };
+// M_REFINE: past the surface, the first refinement step taken; M_TAP: at the
+// hit, reading the normal's six taps
+enum { M_COARSE, M_FINE, M_SURFACE, M_WRONG_SIDE, M_REFINE, M_TAP };
 
 // the view of flat tile index g (views are few; their tile ranges ascend)
 __device__ __forceinline__ int view_of(const MFrame *f, int g)
@@ -847,13 +855,13 @@ __global__ __launch_bounds__(TW *TH) void k_m_raycast(const MSub *subs, const MF
     const int lx = (q % (TW / 8)) * 8 + (i & 7), ly = (q / (TW / 8)) * 8 + (i >> 3);
     const int px = tx0 + lx, py = ty0 + ly;
     float zmin, zmax;
-    m_tile_setup<NT, TW, TH>(subs, t, (uint32_t)g, tx0, ty0, L);
-    m_pixel_range<NT>(L, ly * TW + lx, zmin, zmax);
-    // the table holds every record of the bin shallower than its depth cut
-    const bool full = L.n_tab <= (uint32_t)(MTileLds<NT>::TT / 2) && !L.unfit;
-    // reads at points shallower than dcut (the cut less a voxel for the
-    // normal's taps and a millimetre for rounding) can trust a table miss
-    const float dcut = L.dlim - voxel - 1e-3f;
+    m_pixel_range<NT, TW, TH>(t, (uint32_t)g, tx0, ty0, px, py, L, zmin, zmax);
+    m_table<NT, TW, TH>(subs, t, (uint32_t)g, tx0, ty0, V.cam, voxel, L);
+    const int nsub = __builtin_amdgcn_readfirstlane(__popcll(L.mask));
+    // reads at points shallower than dcut (the table's depth limit less a
+    // voxel for the normal's taps and a millimetre for rounding) can trust a
+    // table miss
+    const float dcut = __uint_as_float(L.dlim) - voxel - 1e-3f;
     const bool inside = px < W && py < H;
     float4 out_p = make_float4(0.f, 0.f, 0.f, 0.f), out_n = make_float4(0.f, 0.f, 0.f, 0.f);
     if (inside && zmin <= zmax) {
@@ -872,9 +880,15 @@ __global__ __launch_bounds__(TW *TH) void k_m_raycast(const MSub *subs, const MF
         float tt = (zmin * nr) * inv_vs;
         const float t_end = (zmax * nr) * inv_vs;
         int state = M_COARSE;
-        float F = 1.0f;
-        int steps = 0;
-        while (tt < t_end && steps < kMaxRaySteps) {
+        int steps = 0, tap = 0;
+        float plus = 0.0f, gx = 0.0f, gy = 0.0f, gz = 0.0f;
+        // one loop for the march, the refinement and the normal's taps: the
+        // field's code stands once (three copies and their lookups were 100 KB,
+        // more than the instruction cache), and lanes at a hit read their taps
+        // beside lanes that still march
+        for (;;) {
+            const bool marching = state < M_REFINE;
+            if (marching && !(tt < t_end && steps < kMaxRaySteps)) break;
             if (state == M_COARSE || state == M_FINE) {
                 // Empty-space skip: while no block is found the march keeps
                 // its fixed step; the world cells of the next kSkip positions
@@ -906,85 +920,77 @@ __global__ __launch_bounds__(TW *TH) void k_m_raycast(const MSub *subs, const MF
                 if (!stop) tt = t2;
                 if (!(tt < t_end && steps < kMaxRaySteps)) break;
             }
-            ++steps;
-            const float P0 = ox + tt * dx, P1 = oy + tt * dy, P2 = oz + tt * dz;
-            const bool local = full && tt * zscale >= kZNear && tt * zscale < dcut;
+            if (marching) ++steps;
+            float P0 = ox + tt * dx, P1 = oy + tt * dy, P2 = oz + tt * dz;
+            // the taps P +- e_a lie within a voxel of the hit, which dcut covers
+            const bool local = tt * zscale >= kZNear && tt * zscale < dcut;
+            if (state == M_TAP) {
+                const float e = (tap & 1) ? -1.0f : 1.0f;
+                P0 = (tap >> 1) == 0 ? P0 + e : P0;
+                P1 = (tap >> 1) == 1 ? P1 + e : P1;
+                P2 = (tap >> 1) == 2 ? P2 + e : P2;
+            }
             // only the submaps of P's world cell can be allocated there
             const unsigned long long cm = m_cell_mask<NT>(t, L, P0, P1, P2);
-            const bool alloc = cm && m_allocated(L, cm, P0, P1, P2, local);
-            if (state == M_COARSE) {
+            if (marching) {
+                const bool alloc = cm && m_allocated(L, nsub, cm, P0, P1, P2, local);
                 if (!alloc) {
-                    tt += 8.0f;
-                } else {
+                    tt += state == M_COARSE ? 8.0f : mu_v;
+                    state = state == M_COARSE ? M_COARSE : M_FINE;
+                    continue;
+                }
+                if (state == M_COARSE) {
                     tt -= 8.0f;
                     state = M_FINE;
+                    continue;
                 }
-            } else if (!alloc) {
-                state = M_FINE;
-                tt += mu_v;
-            } else {
-                F = m_field(L, cm, P0, P1, P2, local);
-                if (state == M_SURFACE) {
-                    if (F < 0.0f) {
-                        state = M_BEHIND;
-                        break;
-                    }
+            }
+            const float F = m_field(L, nsub, cm, P0, P1, P2, local);
+            if (state == M_TAP) {
+                if (tap & 1) {
+                    const float d = (plus - F) * 0.5f;
+                    gx = tap == 1 ? d : gx;
+                    gy = tap == 3 ? d : gy;
+                    gz = tap == 5 ? d : gz;
+                    if (tap == 5) break;
+                } else {
+                    plus = F;
+                }
+                ++tap;
+            } else if (state == M_REFINE) {
+                tt += F * mu_v;
+                state = M_TAP;
+            } else if (state == M_SURFACE) {
+                if (F < 0.0f) {
+                    state = M_REFINE;
+                    tt += F * mu_v;
+                } else {
                     const float s = F * mu_v;
                     tt += (s > 1.0f) ? s : 1.0f;
-                } else if (F < 0.0f) {
-                    if (state == M_FINE) {
-                        state = M_WRONG_SIDE;
-                    } else {
-                        const float s = -F * mu_v;
-                        tt += (s > 1.0f) ? s : 1.0f;
-                    }
+                }
+            } else if (F < 0.0f) {
+                if (state == M_FINE) {
+                    state = M_WRONG_SIDE;
                 } else {
-                    // FINE or WRONG_SIDE meeting F >= 0 turns to SURFACE without
-                    // a step; the SURFACE iteration that follows (if the step
-                    // bound allows it) reads the same field at the same t, so
-                    // its step is taken here with this F
-                    state = M_SURFACE;
-                    if (steps < kMaxRaySteps) {
-                        ++steps;
-                        const float s = F * mu_v;
-                        tt += (s > 1.0f) ? s : 1.0f;
-                    }
+                    const float s = -F * mu_v;
+                    tt += (s > 1.0f) ? s : 1.0f;
+                }
+            } else {
+                // FINE or WRONG_SIDE meeting F >= 0 turns to SURFACE without
+                // a step; the SURFACE iteration that follows (if the step
+                // bound allows it) reads the same field at the same t, so
+                // its step is taken here with this F
+                state = M_SURFACE;
+                if (steps < kMaxRaySteps) {
+                    ++steps;
+                    const float s = F * mu_v;
+                    tt += (s > 1.0f) ? s : 1.0f;
                 }
             }
         }
-        if (state == M_BEHIND) {
-            tt += F * mu_v;
-            float P0 = ox + tt * dx, P1 = oy + tt * dy, P2 = oz + tt * dz;
-            F = m_field(L, m_cell_mask<NT>(t, L, P0, P1, P2), P0, P1, P2,
-                        full && tt * zscale >= kZNear && tt * zscale < dcut);
-            tt += F * mu_v;
-            P0 = ox + tt * dx;
-            P1 = oy + tt * dy;
-            P2 = oz + tt * dz;
+        if (state == M_TAP) {
+            const float P0 = ox + tt * dx, P1 = oy + tt * dy, P2 = oz + tt * dz;
             out_p = make_float4(P0 * voxel, P1 * voxel, P2 * voxel, 1.0f);
-            // the taps lie within a voxel of the hit, which the cut's margin covers
-            const bool lh = full && tt * zscale >= kZNear && tt * zscale < dcut;
-            // the six taps P +- e_a, one per step of a rolled loop (one copy
-            // of the field code, kept by selects)
-            float fp0 = 0.0f, fm0 = 0.0f, fp1 = 0.0f, fm1 = 0.0f, fp2 = 0.0f, fm2 = 0.0f;
-#pragma unroll 1
-            for (int tap = 0; tap < 6; ++tap) {
-                const int ax = tap >> 1;
-                const bool minus = (tap & 1) != 0;
-                const float X = ax == 0 ? (minus ? P0 - 1.0f : P0 + 1.0f) : P0;
-                const float Y = ax == 1 ? (minus ? P1 - 1.0f : P1 + 1.0f) : P1;
-                const float Z = ax == 2 ? (minus ? P2 - 1.0f : P2 + 1.0f) : P2;
-                const float f = m_field(L, m_cell_mask<NT>(t, L, X, Y, Z), X, Y, Z, lh);
-                fp0 = tap == 0 ? f : fp0;
-                fm0 = tap == 1 ? f : fm0;
-                fp1 = tap == 2 ? f : fp1;
-                fm1 = tap == 3 ? f : fm1;
-                fp2 = tap == 4 ? f : fp2;
-                fm2 = tap == 5 ? f : fm2;
-            }
-            const float gx = (fp0 - fm0) * 0.5f;
-            const float gy = (fp1 - fm1) * 0.5f;
-            const float gz = (fp2 - fm2) * 0.5f;
             const float gn = sqrtf((gx * gx + gy * gy) + gz * gz);
             if (gn > 0.0f) out_n = make_float4(gx / gn, gy / gn, gz / gn, 1.0f);
         }
@@ -1014,8 +1020,7 @@ __global__ __launch_bounds__(TW *TH) void k_m_range_write(const MSub *subs, cons
     const int lx = (q % (TW / 8)) * 8 + (i & 7), ly = (q / (TW / 8)) * 8 + (i >> 3);
     const int px = tx0 + lx, py = ty0 + ly;
     float zmin, zmax;
-    m_tile_setup<NT, TW, TH>(subs, t, (uint32_t)g, tx0, ty0, L);
-    m_pixel_range<NT>(L, ly * TW + lx, zmin, zmax);
+    m_pixel_range<NT, TW, TH>(t, (uint32_t)g, tx0, ty0, px, py, L, zmin, zmax);
     if (px >= V.cam.W || py >= V.cam.H) return;
     zmin_out[(size_t)py * V.cam.W + px] = zmin;
     zmax_out[(size_t)py * V.cam.W + px] = zmax;
