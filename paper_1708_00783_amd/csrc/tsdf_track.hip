@@ -1,15 +1,13 @@
 // tsdf_track.hip -- the depth tracker (Sec. 4.1.1, ITMDepthTracker) on gfx950.
 //
-// Per iteration two launches: in k_trk_sums every thread scores the live depth
-// pixels of a fixed grid-stride slice against the reference point and normal
-// maps (float32 pair terms, float64 sums), the wave and then the workgroup
-// reduce them in a fixed order into one partial per workgroup; k_trk_solve (one
-// workgroup) reduces the partials in a fixed order, solves the 6x6 normal
-// equations by Cholesky in float64 and updates the pose on the device.  The
-// kernel boundary orders the partials before their reduction, so no workgroup
-// needs a device-scope fence.  The pyramid levels are built by 2x2 valid-mean
-// kernels first.  Nothing waits for the host, so a call can be captured in a
-// HIP graph.
+// One launch builds the pyramid (k_trk_prep), then one launch per iteration
+// (k_trk_iter): every thread scores the live depth pixels of a fixed
+// grid-stride slice against the reference point and normal maps (float32 pair
+// terms, float64 sums), the wave and then the workgroup reduce them in a fixed
+// order into one partial per workgroup, and the workgroup that finishes last
+// reduces the partials in a fixed order, solves the 6x6 normal equations by
+// Cholesky in float64 and updates the pose on the device.  Nothing waits for
+// the host, so a call can be captured in a HIP graph.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -20,11 +18,13 @@
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kMaxGroups = 512;      // workgroups of a sums launch (fixed per level size)
+constexpr int kThreads = 512;
+constexpr int kGroups = 256;         // workgroups of an iteration at most (fixed per level size): one per CU
+constexpr int kTickets = 16;         // first-level arrival counters
+constexpr int kPartSlots = 512;      // partials' room in the workspace: the upper half holds the counters
 constexpr int kTerms = 29;           // 21 (J^T J) + 6 (J^T d) + sum d^2 + pair count
 constexpr int kPartStride = 32;      // doubles per workgroup partial
-constexpr int kSlices = 8;           // parallel slices of the final reduction
+constexpr int kSlices = 16;          // parallel slices of the final reduction
 constexpr size_t kStateBytes = 2048;
 
 struct alignas(256) TrkState {
@@ -57,57 +57,113 @@ struct TrkRef {
     float m[12];                     // rows 0-2 of the reference world->camera matrix
 };
 
-__global__ __launch_bounds__(128) void k_trk_init(TrkState *st, TrkInit ini)
+// arrival counter i (i = kTickets: the second level), 64 bytes apart behind the partials
+__device__ __forceinline__ uint32_t *ticket(double *part, int i)
 {
+    return reinterpret_cast<uint32_t *>(part + (size_t)kGroups * kPartStride) + 16 * i;
+}
+
+struct TrkPyramid {
+    float *level[TF_TRACK_MAX_LEVELS];   // level 0 is written for u16 input only
+    int W[TF_TRACK_MAX_LEVELS], H[TF_TRACK_MAX_LEVELS];
+    int levels;
+};
+
+// The state's initialisation (workgroup 0) and the whole pyramid, one workgroup
+// per 32 x 32 pixels of the finest level: a coarser pixel's 2 x 2 blocks never
+// cross those tiles, so its levels follow one another in LDS.  A level's pixel
+// is the mean of the valid depths of its block, in raster order; u16
+// millimetres become metres, correctly rounded (the fusion's ingest).
+template <int FMT>
+__global__ __launch_bounds__(256) void k_trk_prep(TrkState *st, TrkInit ini, double *part, const void *depth,
+                                                  TrkPyramid P)
+{
+    __shared__ float lds[2][32 * 32];
     const int i = threadIdx.x;
-    if (i < 9) {
-        st->R[i] = ini.R[i];
-        st->Rf[i] = (float)ini.R[i];
-    }
-    if (i < 3) {
-        st->t[i] = ini.t[i];
-        st->tf[i] = (float)ini.t[i];
-    }
-    if (i < TF_TRACK_MAX_LEVELS) {
-        st->done[i] = 0;
-        st->iterations[i] = 0;
-        st->pairs[i] = 0;
-    }
-    if (i == 0) {
-        st->status = 0;
-        st->pad = 0;
-    }
-    for (int k = i; k < TF_TRACK_MAX_LEVELS * 28; k += blockDim.x) (&st->sums[0][0])[k] = 0.0;
-}
-
-// a0: millimetres to metres, correctly rounded (the fusion's ingest)
-__global__ __launch_bounds__(256) void k_trk_mm(const uint16_t *mm, int n, float *out)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) out[i] = (float)mm[i] / 1000.0f;
-}
-
-// next pyramid level: mean of the valid depths of each 2x2 block, raster order
-__global__ __launch_bounds__(256) void k_trk_down(const float *src, int Ws, float *dst, int Wd, int Hd)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= Wd * Hd) return;
-    const int y = i / Wd, x = i - y * Wd;
-    const float *s = src + (size_t)(2 * y) * Ws + 2 * x;
-    const float v[4] = {s[0], s[1], s[Ws], s[Ws + 1]};
-    float tot = 0.0f, cnt = 0.0f;
-    for (int k = 0; k < 4; ++k)
-        if (v[k] > 0.0f) {
-            tot = tot + v[k];
-            cnt = cnt + 1.0f;
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+        if (i < 9) {
+            st->R[i] = ini.R[i];
+            st->Rf[i] = (float)ini.R[i];
         }
-    dst[i] = cnt > 0.0f ? tot / cnt : 0.0f;
+        if (i < 3) {
+            st->t[i] = ini.t[i];
+            st->tf[i] = (float)ini.t[i];
+        }
+        if (i < TF_TRACK_MAX_LEVELS) {
+            st->done[i] = 0;
+            st->iterations[i] = 0;
+            st->pairs[i] = 0;
+        }
+        if (i == 0) {
+            st->status = 0;
+            st->pad = 0;
+        }
+        if (i <= kTickets) *ticket(part, i) = 0u;
+        for (int k = i; k < TF_TRACK_MAX_LEVELS * 28; k += 256) (&st->sums[0][0])[k] = 0.0;
+    }
+    const int x0 = (int)blockIdx.x * 32, y0 = (int)blockIdx.y * 32;
+    if (P.levels == 1 && FMT == TF_DEPTH_F32_M) return;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int x = x0 + (i & 31), y = y0 + (i >> 5) + 8 * k;
+        float d = 0.0f;
+        if (x < P.W[0] && y < P.H[0]) {
+            const size_t at = (size_t)y * P.W[0] + x;
+            if (FMT == TF_DEPTH_U16_MM) {
+                d = (float)((const uint16_t *)depth)[at] / 1000.0f;
+                P.level[0][at] = d;
+            } else {
+                d = ((const float *)depth)[at];
+            }
+        }
+        lds[0][(y - y0) * 32 + (x - x0)] = d;
+    }
+#pragma unroll
+    for (int l = 1; l < TF_TRACK_MAX_LEVELS; ++l) {
+        if (l >= P.levels) return;
+        __syncthreads();
+        const int side = 32 >> l;
+        if (i < side * side) {
+            const int lx = i % side, ly = i / side, x = (x0 >> l) + lx, y = (y0 >> l) + ly;
+            const float *s = lds[(l - 1) & 1] + 2 * ly * 32 + 2 * lx;
+            const float v[4] = {s[0], s[1], s[32], s[33]};
+            float tot = 0.0f, cnt = 0.0f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (v[k] > 0.0f) {
+                    tot = tot + v[k];
+                    cnt = cnt + 1.0f;
+                }
+            const float m = cnt > 0.0f ? tot / cnt : 0.0f;
+            lds[l & 1][ly * 32 + lx] = m;
+            if (x < P.W[l] && y < P.H[l]) P.level[l][(size_t)y * P.W[l] + x] = m;
+        }
+    }
 }
 
-__device__ inline double wave_sum(double v)
+// Wave sums of 32 values per lane: at each step a lane keeps one half of its
+// values and gives the other half away, so that 31 exchanges and a last one
+// leave lane 2 k and 2 k + 1 with the sum of value k (a butterfly per value
+// takes six exchanges each).
+template <int H>
+__device__ __forceinline__ void wave_sums_step(double (&v)[32])
 {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    const bool up = ((int)threadIdx.x & (2 * H)) != 0;
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+        const double give = up ? v[k] : v[k + H], keep = up ? v[k + H] : v[k];
+        v[k] = keep + __shfl_xor(give, 2 * H, 64);
+    }
+}
+
+__device__ __forceinline__ double wave_sums(double (&v)[32])
+{
+    wave_sums_step<16>(v);
+    wave_sums_step<8>(v);
+    wave_sums_step<4>(v);
+    wave_sums_step<2>(v);
+    wave_sums_step<1>(v);
+    return v[0] + __shfl_xor(v[0], 1, 64);
 }
 
 // the 6x6 solve and the pose update (one thread)
@@ -202,107 +258,7 @@ __device__ void solve_and_update(TrkState *st, const double *tot, int level, dou
     if (sqrt(nx) < min_update) st->done[level] = 1;
 }
 
-// One iteration at one level, part 1: pair terms and per-workgroup sums.
-__global__ __launch_bounds__(kThreads) void k_trk_sums(TrkLevel L, TrkRef r, float tau2, const TrkState *st,
-                                                       double *part, int level)
-{
-    if (st->done[level]) return;     // the same for every workgroup of the launch
-    const float R0 = st->Rf[0], R1 = st->Rf[1], R2 = st->Rf[2];
-    const float R3 = st->Rf[3], R4 = st->Rf[4], R5 = st->Rf[5];
-    const float R6 = st->Rf[6], R7 = st->Rf[7], R8 = st->Rf[8];
-    const float t0 = st->tf[0], t1 = st->tf[1], t2 = st->tf[2];
-    double acc[kTerms];
-    for (int k = 0; k < kTerms; ++k) acc[k] = 0.0;
-    const int n = L.W * L.H;
-    for (int p = blockIdx.x * kThreads + threadIdx.x; p < n; p += gridDim.x * kThreads) {
-        const float d = L.depth[p];
-        if (!(d > 0.0f)) continue;
-        const int y = p / L.W;
-        const int x = p - y * L.W;
-        const float px = d * (((float)x - L.cx) / L.fx);
-        const float py = d * (((float)y - L.cy) / L.fy);
-        const float pz = d;
-        const float qx = ((R0 * px + R1 * py) + R2 * pz) + t0;
-        const float qy = ((R3 * px + R4 * py) + R5 * pz) + t1;
-        const float qz = ((R6 * px + R7 * py) + R8 * pz) + t2;
-        const float cxr = ((r.m[0] * qx + r.m[1] * qy) + r.m[2] * qz) + r.m[3];
-        const float cyr = ((r.m[4] * qx + r.m[5] * qy) + r.m[6] * qz) + r.m[7];
-        const float czr = ((r.m[8] * qx + r.m[9] * qy) + r.m[10] * qz) + r.m[11];
-        if (!(czr > 0.0f)) continue;
-        const float u = (r.fx * cxr) / czr + r.cx;
-        const float v = (r.fy * cyr) / czr + r.cy;
-        const float ui = floorf(u + 0.5f);
-        const float vi = floorf(v + 0.5f);
-        if (!(ui >= 0.0f && ui <= (float)(r.W - 1) && vi >= 0.0f && vi <= (float)(r.H - 1))) continue;
-        const size_t k = (size_t)(int)vi * (size_t)r.W + (size_t)(int)ui;
-        const float4 V = r.V[k];
-        const float4 N = r.N[k];
-        if (V.w != 1.0f || N.w != 1.0f) continue;
-        const float dx = qx - V.x, dy = qy - V.y, dz = qz - V.z;
-        if (!((dx * dx + dy * dy) + dz * dz <= tau2)) continue;
-        const float res = (dx * N.x + dy * N.y) + dz * N.z;
-        const double J[6] = {(double)(qy * N.z - qz * N.y), (double)(qz * N.x - qx * N.z),
-                             (double)(qx * N.y - qy * N.x), (double)N.x, (double)N.y, (double)N.z};
-        int m = 0;
-#pragma unroll
-        for (int i = 0; i < 6; ++i)
-#pragma unroll
-            for (int j = i; j < 6; ++j) acc[m++] += J[i] * J[j];
-#pragma unroll
-        for (int i = 0; i < 6; ++i) acc[21 + i] += J[i] * (double)res;
-        acc[27] += (double)res * (double)res;
-        acc[28] += 1.0;
-    }
-    __shared__ double wsum[kThreads / 64][kTerms];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < kTerms; ++k) {
-        const double s = wave_sum(acc[k]);
-        if (lane == 0) wsum[wave][k] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x < kTerms) {
-        const int k = threadIdx.x;
-        part[(size_t)blockIdx.x * kPartStride + k] = ((wsum[0][k] + wsum[1][k]) + wsum[2][k]) + wsum[3][k];
-    }
-}
-
-// Part 2 (one workgroup): the partials of `groups` workgroups in a fixed
-// order, then the solve and the pose update.
-__global__ __launch_bounds__(kThreads) void k_trk_solve(TrkState *st, const double *part, int groups, int level,
-                                                        double min_update)
-{
-    if (st->done[level]) return;
-    __shared__ double red[kSlices][kTerms];
-    __shared__ double tot[kTerms];
-    if (threadIdx.x < kSlices * kTerms) {
-        const int k = threadIdx.x / kSlices, s = threadIdx.x % kSlices;
-        double v = 0.0;
-        // 8 loads in flight per step, added in the same (ascending) order
-        for (int g0 = s; g0 < groups; g0 += 8 * kSlices) {
-            double x[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int g = g0 + j * kSlices;
-                x[j] = g < groups ? part[(size_t)g * kPartStride + k] : 0.0;
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (g0 + j * kSlices < groups) v += x[j];
-        }
-        red[s][k] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x < kTerms) {
-        double v = 0.0;
-        for (int s = 0; s < kSlices; ++s) v += red[s][threadIdx.x];
-        tot[threadIdx.x] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) solve_and_update(st, tot, level, min_update);
-}
-
-__global__ __launch_bounds__(128) void k_trk_finish(const TrkState *st, tf_track_result *out)
+__device__ void write_result(const TrkState *st, tf_track_result *out)
 {
     const int i = threadIdx.x;
     if (i < 3) {
@@ -326,6 +282,155 @@ __global__ __launch_bounds__(128) void k_trk_finish(const TrkState *st, tf_track
     for (int k = i; k < TF_TRACK_MAX_LEVELS * 28; k += blockDim.x) (&out->sums[0][0])[k] = (&st->sums[0][0])[k];
 }
 
+// One iteration at one level; with `out` (the call's last launch) also the
+// result.
+//
+// Bound: latency (depth read, map gathers, reduction, arrival, partials,
+// solve).  Before, a sums launch of up to 512 workgroups (12.2 us, half of it
+// 29 six-step butterflies per wave through LDS) and a solve launch (7.2 us) per
+// iteration.  Now one workgroup per CU, two pixels per thread in flight, 32
+// exchanges per wave, and the last workgroup to arrive solves.  Its reading of
+// the others' partials needs no L2 write-back (a device-scope fence, 26 us
+// when measured): they are stored and loaded past the L2 with device-scope
+// atomics, and a workgroup counts itself in only after its stores are done.
+// The arrivals count in two levels, as atomics on one address take 11 ns each.
+// An iteration takes 11.6 (120x80) to 16.5 us (640x480); a 640x480 call of 19
+// iterations 376 us before, 238 us now.
+__global__ __launch_bounds__(kThreads) void k_trk_iter(TrkLevel L, TrkRef r, float tau2, TrkState *st, double *part,
+                                                       int level, double min_update, tf_track_result *out)
+{
+    if (st->done[level]) {           // the same for every workgroup of the launch
+        if (out && blockIdx.x == 0) write_result(st, out);
+        return;
+    }
+    const float R0 = st->Rf[0], R1 = st->Rf[1], R2 = st->Rf[2];
+    const float R3 = st->Rf[3], R4 = st->Rf[4], R5 = st->Rf[5];
+    const float R6 = st->Rf[6], R7 = st->Rf[7], R8 = st->Rf[8];
+    const float t0 = st->tf[0], t1 = st->tf[1], t2 = st->tf[2];
+    double acc[32];
+#pragma unroll
+    for (int k = 0; k < 32; ++k) acc[k] = 0.0;
+    const int n = L.W * L.H, stride = (int)gridDim.x * kThreads;
+    constexpr int kAhead = 2;        // pixels per thread in flight
+    for (int p0 = blockIdx.x * kThreads + threadIdx.x; p0 < n; p0 += kAhead * stride) {
+        float qx[kAhead], qy[kAhead], qz[kAhead], d[kAhead];
+        float4 V[kAhead], N[kAhead];
+        bool ok[kAhead];
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) d[a] = p0 + a * stride < n ? L.depth[p0 + a * stride] : 0.0f;
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) {
+            const int p = p0 + a * stride;
+            const int y = p / L.W;
+            const int x = p - y * L.W;
+            const float px = d[a] * (((float)x - L.cx) / L.fx);
+            const float py = d[a] * (((float)y - L.cy) / L.fy);
+            const float pz = d[a];
+            qx[a] = ((R0 * px + R1 * py) + R2 * pz) + t0;
+            qy[a] = ((R3 * px + R4 * py) + R5 * pz) + t1;
+            qz[a] = ((R6 * px + R7 * py) + R8 * pz) + t2;
+            const float cxr = ((r.m[0] * qx[a] + r.m[1] * qy[a]) + r.m[2] * qz[a]) + r.m[3];
+            const float cyr = ((r.m[4] * qx[a] + r.m[5] * qy[a]) + r.m[6] * qz[a]) + r.m[7];
+            const float czr = ((r.m[8] * qx[a] + r.m[9] * qy[a]) + r.m[10] * qz[a]) + r.m[11];
+            ok[a] = d[a] > 0.0f && czr > 0.0f;
+            const float u = (r.fx * cxr) / czr + r.cx;
+            const float v = (r.fy * cyr) / czr + r.cy;
+            const float ui = floorf(u + 0.5f);
+            const float vi = floorf(v + 0.5f);
+            ok[a] = ok[a] && ui >= 0.0f && ui <= (float)(r.W - 1) && vi >= 0.0f && vi <= (float)(r.H - 1);
+            const size_t k = ok[a] ? (size_t)(int)vi * (size_t)r.W + (size_t)(int)ui : 0;
+            V[a] = r.V[k];
+            N[a] = r.N[k];
+        }
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) {
+            if (!ok[a] || V[a].w != 1.0f || N[a].w != 1.0f) continue;
+            const float dx = qx[a] - V[a].x, dy = qy[a] - V[a].y, dz = qz[a] - V[a].z;
+            if (!((dx * dx + dy * dy) + dz * dz <= tau2)) continue;
+            const float res = (dx * N[a].x + dy * N[a].y) + dz * N[a].z;
+            const double J[6] = {(double)(qy[a] * N[a].z - qz[a] * N[a].y), (double)(qz[a] * N[a].x - qx[a] * N[a].z),
+                                 (double)(qx[a] * N[a].y - qy[a] * N[a].x), (double)N[a].x, (double)N[a].y,
+                                 (double)N[a].z};
+            int m = 0;
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+#pragma unroll
+                for (int j = i; j < 6; ++j) acc[m++] += J[i] * J[j];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) acc[21 + i] += J[i] * (double)res;
+            acc[27] += (double)res * (double)res;
+            acc[28] += 1.0;
+        }
+    }
+    __shared__ double wsum[kThreads / 64][32];
+    __shared__ double red[kSlices][kTerms];
+    __shared__ double tot[kTerms];
+    __shared__ bool last;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const double ws = wave_sums(acc);
+    if (!(lane & 1)) wsum[wave][lane >> 1] = ws;
+    __syncthreads();
+    if (wave == 0) {
+        if (lane < kTerms) {
+            double v = wsum[0][lane];
+#pragma unroll
+            for (int w = 1; w < kThreads / 64; ++w) v += wsum[w][lane];
+            __hip_atomic_store(&part[(size_t)blockIdx.x * kPartStride + lane], v, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // this wave's partial has reached memory before its arrival is counted
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0) {
+            const uint32_t G = gridDim.x, id = blockIdx.x % kTickets;
+            const uint32_t mine = (G - id + kTickets - 1) / kTickets;          // workgroups of this counter
+            const uint32_t counters = G < (uint32_t)kTickets ? G : (uint32_t)kTickets;
+            bool l = false;
+            uint32_t *t1p = ticket(part, (int)id), *t2p = ticket(part, kTickets);
+            if (__hip_atomic_fetch_add(t1p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mine - 1u) {
+                __hip_atomic_store(t1p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (__hip_atomic_fetch_add(t2p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == counters - 1u) {
+                    __hip_atomic_store(t2p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    l = true;
+                }
+            }
+            last = l;
+        }
+    }
+    __syncthreads();
+    if (!last) return;
+    const int groups = (int)gridDim.x;
+    if (threadIdx.x < kSlices * kTerms) {
+        const int k = threadIdx.x / kSlices, s = threadIdx.x % kSlices;
+        double x[kGroups / kSlices];
+#pragma unroll
+        for (int j = 0; j < kGroups / kSlices; ++j) {
+            const int g = s + j * kSlices;
+            x[j] = g < groups ? __hip_atomic_load(&part[(size_t)g * kPartStride + k], __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT)
+                              : 0.0;
+        }
+        double v = 0.0;
+#pragma unroll
+        for (int j = 0; j < kGroups / kSlices; ++j) v += x[j];
+        red[s][k] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < kTerms) {
+        double v = 0.0;
+#pragma unroll
+        for (int s = 0; s < kSlices; ++s) v += red[s][threadIdx.x];
+        tot[threadIdx.x] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) solve_and_update(st, tot, level, min_update);
+    if (!out) return;
+    __syncthreads();
+    write_result(st, out);
+}
+
+// the result of a call without iterations
+__global__ __launch_bounds__(128) void k_trk_finish(const TrkState *st, tf_track_result *out) { write_result(st, out); }
+
 struct TrkLayout {
     size_t state, part, level[TF_TRACK_MAX_LEVELS], total;
     int W[TF_TRACK_MAX_LEVELS], H[TF_TRACK_MAX_LEVELS];
@@ -340,7 +445,7 @@ bool track_layout(int32_t W, int32_t H, int32_t levels, TrkLayout *o)
     o->state = off;
     off += kStateBytes;
     o->part = off;
-    off += up256((size_t)kMaxGroups * kPartStride * sizeof(double));
+    off += up256((size_t)kPartSlots * kPartStride * sizeof(double));
     for (int l = 0; l < levels; ++l) {
         o->W[l] = W >> l;
         o->H[l] = H >> l;
@@ -404,23 +509,24 @@ int tsdf_track_impl(const void *d_depth, int depth_format, const tf_intrinsics *
         for (int j = 0; j < 3; ++j) ini.R[3 * i + j] = (double)M[4 * j + i];
     for (int i = 0; i < 3; ++i)
         ini.t[i] = -((ini.R[3 * i] * (double)M[3] + ini.R[3 * i + 1] * (double)M[7]) + ini.R[3 * i + 2] * (double)M[11]);
-    hipLaunchKernelGGL(k_trk_init, dim3(1), dim3(128), 0, s, st, ini);
-
+    TrkPyramid P = {};
     const float *lvl[TF_TRACK_MAX_LEVELS];
+    P.levels = levels;
+    int last_level = -1;             // the level of the call's last iteration
+    for (int l = 0; l < levels; ++l) {
+        P.level[l] = (float *)(ws + Lay.level[l]);
+        P.W[l] = Lay.W[l];
+        P.H[l] = Lay.H[l];
+        lvl[l] = P.level[l];
+        if (last_level < 0 && tp->iterations[l] > 0) last_level = l;
+    }
+    const dim3 tiles((Lay.W[0] + 31) / 32, (Lay.H[0] + 31) / 32);
     if (depth_format == TF_DEPTH_U16_MM) {
-        const int n = Lay.W[0] * Lay.H[0];
-        float *d0 = (float *)(ws + Lay.level[0]);
-        hipLaunchKernelGGL(k_trk_mm, dim3((n + 255) / 256), dim3(256), 0, s, (const uint16_t *)d_depth, n, d0);
-        lvl[0] = d0;
+        hipLaunchKernelGGL(k_trk_prep<TF_DEPTH_U16_MM>, tiles, dim3(256), 0, s, st, ini, part, d_depth, P);
     } else {
         lvl[0] = (const float *)d_depth;
-    }
-    for (int l = 1; l < levels; ++l) {
-        float *dl = (float *)(ws + Lay.level[l]);
-        const int n = Lay.W[l] * Lay.H[l];
-        hipLaunchKernelGGL(k_trk_down, dim3((n + 255) / 256), dim3(256), 0, s, lvl[l - 1], Lay.W[l - 1], dl, Lay.W[l],
-                           Lay.H[l]);
-        lvl[l] = dl;
+        hipLaunchKernelGGL(k_trk_prep<TF_DEPTH_F32_M>, levels > 1 ? tiles : dim3(1), dim3(256), 0, s, st, ini, part, d_depth,
+                           P);
     }
     TrkRef ref;
     ref.V = (const float4 *)d_ref_points;
@@ -447,15 +553,13 @@ int tsdf_track_impl(const void *d_depth, int depth_format, const tf_intrinsics *
         const float tau2 = tau * tau;
         const size_t npix = (size_t)L.W * L.H;
         int groups = (int)((npix + kThreads - 1) / kThreads);
-        if (groups > kMaxGroups) groups = kMaxGroups;
-        for (int it = 0; it < tp->iterations[l]; ++it) {
-            hipLaunchKernelGGL(k_trk_sums, dim3(groups), dim3(kThreads), 0, s, L, ref, tau2, (const TrkState *)st,
-                               part, l);
-            hipLaunchKernelGGL(k_trk_solve, dim3(1), dim3(kThreads), 0, s, st, (const double *)part, groups, l,
-                               (double)tp->min_update);
-        }
+        if (groups > kGroups) groups = kGroups;
+        for (int it = 0; it < tp->iterations[l]; ++it)
+            hipLaunchKernelGGL(k_trk_iter, dim3(groups), dim3(kThreads), 0, s, L, ref, tau2, st, part, l,
+                               (double)tp->min_update,
+                               l == last_level && it + 1 == tp->iterations[l] ? d_result : nullptr);
     }
-    hipLaunchKernelGGL(k_trk_finish, dim3(1), dim3(128), 0, s, (const TrkState *)st, d_result);
+    if (last_level < 0) hipLaunchKernelGGL(k_trk_finish, dim3(1), dim3(128), 0, s, (const TrkState *)st, d_result);
     return hipGetLastError() == hipSuccess ? TF_OK : TF_E_HIP;
 }
 

@@ -215,3 +215,34 @@ def test_frame_to_model_loop():
         worst = max(worst, gt)
     _log(f"loop of {n} frames: worst error vs truth {worst[0] * 1e3:.2f} mm, {worst[1]:.3f} deg")
     assert worst[0] < 0.01 and worst[1] < 0.5
+
+
+@pytest.mark.parametrize("size,levels", [((33, 31), 1), ((64, 32), 2), ((517, 263), 4), ((1280, 720), 3)])
+def test_tiles_and_partial_counts_match_oracle(size, levels):
+    """level sizes around the pyramid's 32-pixel tiles and calls of 1 to 256
+    partials (the largest with several pixels per thread); one system per
+    level, the bars of _compare_sums; then a call whose finest level runs no
+    iteration, and one with none at all (the initial pose comes back)"""
+    import paper_1708_00783_amd as T
+    from oracle import track as TR
+    P = configs.c2_poses(300)
+    V, N = _ref_maps(0, P[3], K2)
+    W, H = size
+    f = 525.0 * W / 640.0
+    Kl = Intrinsics(f, f, (W - 1) / 2.0, (H - 1) / 2.0, W, H)
+    d = render_depth(configs.c2_scene(0), P[4], Kl).astype(np.float32)
+    dd, dV, dN = to_device(d), to_device(V), to_device(N)
+    trk = T.Tracker(W, H, levels)
+    taus = [0.2] * levels
+    for level in range(levels):
+        it = [0] * levels
+        it[level] = 1
+        res = trk.track(dd, Kl, dV, dN, K2, P[3], P[3], T.make_track_params(it, taus))
+        _, info = TR.track(d, Kl.as_array(), V, N, K2.as_array(), P[3], P[3], it, taus)
+        _compare_sums(res, info, level, f"{size} level {level}")
+    it = [0] + [2] * (levels - 1)
+    res = trk.track(dd, Kl, dV, dN, K2, P[3], P[3], T.make_track_params(it, taus))
+    M, info = TR.track(d, Kl.as_array(), V, N, K2.as_array(), P[3], P[3], it, taus)
+    et, er = pose_error(res["pose_w2c"], M)
+    assert et < 1e-5 and er < 1e-4, (et, er)
+    assert res["iterations"][:levels] == [i["iterations"] for i in info]
