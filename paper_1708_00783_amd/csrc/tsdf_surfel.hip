@@ -1,19 +1,21 @@
 // tsdf_surfel.hip -- surfel fusion (Sec. 7.3) on gfx950.
 //
-// Per frame, six launches, none waiting for the host:
+// Per frame, four launches, none waiting for the host (eight before, half of
+// them 1 to 4 us of counting between launch gaps):
 //   k_sf_points  per pixel: world point, normal (forward differences), alpha,
-//                validity; clears the pixel's z-buffer word
+//                validity; clears the pixel's z-buffer word; the previous
+//                frame's new surfels join the count
 //   k_sf_splat   per surfel: project, and for every pixel of its circle an
 //                atomicMin of (camera z bits << 32 | index) -- the index map is
 //                the low half, independent of the order of the atomics
 //   k_sf_assoc   per pixel: the index map's surfel if the depth and normal
-//                gates pass, else a new surfel, else nothing
-//   k_sf_update  per surfel: walks its own circle again in raster order and
-//                sums the points that chose it (fixed order, no atomics), then
+//                gates pass, else a new surfel, else nothing; counts the new
+//                ones per 256 pixels
+//   k_sf_update  new surfels in pixel raster order (a workgroup's place is the
+//                sum of the counts before it, then ballot ranks); and per
+//                surfel: walks its own circle again in raster order and sums
+//                the points that chose it (fixed order, no atomics), then
 //                applies the weighted average
-//   k_sf_count / k_sf_scan / k_sf_append / k_sf_finish: new surfels in pixel
-//                raster order (per-256-pixel counts, one-workgroup scan,
-//                ballot ranks), then the count
 // The surfel count stays on the device; grid-stride loops read it.
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -28,13 +30,21 @@ constexpr int kSurfGrid = 2048;        // workgroups of the per-surfel launches
 constexpr float kRhoMax = 8.0f;
 constexpr int kFaceCorr = -2;          // corr: no input point
 constexpr int kNewCorr = -1;           // corr: new surfel
+constexpr int kSumBlocks = 4096;       // pixel blocks whose counts an appending workgroup sums by itself
 
 struct alignas(256) SfState {
-    uint32_t n;                        // surfels in the map
+    uint32_t n;                        // surfels in the map before the last frame's new ones
     uint32_t flags;
-    uint32_t n_new;                    // new surfels of the current frame
+    uint32_t n_new;                    // new surfels of the last frame
     uint32_t pad;
 };
+
+// surfels in the map, the last frame's new ones included
+__host__ __device__ inline uint32_t sf_count(const SfState &st, uint32_t cap)
+{
+    const uint32_t n = st.n + st.n_new;
+    return n < cap ? n : cap;
+}
 
 struct SfMap {
     SfState *st;
@@ -45,7 +55,7 @@ struct SfMap {
     float4 *inr;                       // per pixel: world normal, camera depth (0: no input point)
     unsigned long long *zbuf;          // per pixel: (z bits << 32) | surfel
     int32_t *corr;                     // per pixel: surfel, kNewCorr or kFaceCorr
-    uint32_t *blk;                     // per 256 pixels: new surfels, then their offset
+    uint32_t *blk;                     // per 256 pixels: new surfels (after k_sf_scan: their offset)
     uint32_t cap;
 };
 
@@ -67,6 +77,10 @@ template <int FMT>
 __global__ __launch_bounds__(256) void k_sf_points(const void *depth, SfCam c, float alpha_k, float norm_r, SfMap m)
 {
     const int p = blockIdx.x * 256 + threadIdx.x;
+    if (p == 0) {
+        m.st->n = sf_count(*m.st, m.cap);
+        m.st->n_new = 0u;
+    }
     if (p >= c.W * c.H) return;
     const int y = p / c.W, x = p - y * c.W;
     m.zbuf[p] = ~0ull;
@@ -145,9 +159,10 @@ __global__ __launch_bounds__(256) void k_sf_splat(SfCam c, SfMap m)
 
 __global__ __launch_bounds__(256) void k_sf_assoc(SfCam c, float max_dz, float min_dot, SfMap m)
 {
+    __shared__ uint32_t wc[4];
     const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= c.W * c.H) return;
-    const float4 N = m.inr[p];
+    const bool in = p < c.W * c.H;
+    const float4 N = in ? m.inr[p] : make_float4(0.f, 0.f, 0.f, 0.f);
     int r = kFaceCorr;
     if (N.w > 0.0f) {
         r = kNewCorr;
@@ -161,13 +176,89 @@ __global__ __launch_bounds__(256) void k_sf_assoc(SfCam c, float max_dz, float m
             if (fabsf(N.w - Z) <= max_dz && dot >= min_dot * len) r = (int)s;
         }
     }
-    m.corr[p] = r;
+    if (in) m.corr[p] = r;
+    const unsigned long long b = __ballot(r == kNewCorr);
+    if ((threadIdx.x & 63) == 0) wc[threadIdx.x >> 6] = (uint32_t)__popcll(b);
+    __syncthreads();
+    if (threadIdx.x == 0) m.blk[blockIdx.x] = ((wc[0] + wc[1]) + wc[2]) + wc[3];
 }
 
-__global__ __launch_bounds__(256) void k_sf_update(SfCam c, SfMap m, int frame)
+// exclusive offsets of the per-block counts, the frame's total in st->n_new
+// (one workgroup; images of more than kSumBlocks blocks)
+__global__ __launch_bounds__(1024) void k_sf_scan(int nblk, SfMap m)
 {
+    __shared__ uint32_t part[1024];
+    const int t = threadIdx.x;
+    const int per = (nblk + 1023) / 1024;
+    const int b = t * per, e = min(b + per, nblk);
+    uint32_t s = 0;
+    for (int i = b; i < e; ++i) s += m.blk[i];
+    part[t] = s;
+    __syncthreads();
+    for (int d = 1; d < 1024; d <<= 1) {
+        const uint32_t x = t >= d ? part[t - d] : 0u;
+        __syncthreads();
+        part[t] += x;
+        __syncthreads();
+    }
+    uint32_t run = part[t] - s;
+    for (int i = b; i < e; ++i) {
+        const uint32_t k = m.blk[i];
+        m.blk[i] = run;
+        run += k;
+    }
+    if (t == 1023) m.st->n_new = part[1023];
+}
+
+// New surfels of pixel block `b` (256 pixels), in raster order after those of
+// the blocks before it: their counts are summed here, or scanned into offsets
+// by a launch before.  Up to kSumBlocks blocks the sum (a 640x480 image: 5
+// reads per thread) costs less than that launch and its gap (3.3 us and 2 us);
+// its cost grows with the square of the blocks.
+__device__ __forceinline__ void sf_append(const SfCam &c, const SfMap &m, int b, int nblk, bool scanned, int frame)
+{
+    __shared__ uint32_t wc[4], wp[4];
+    const int p = b * 256 + (int)threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t before = 0u;
+    if (scanned)
+        before = threadIdx.x == 0 ? m.blk[b] : 0u;
+    else
+        for (int i = (int)threadIdx.x; i < b; i += 256) before += m.blk[i];
+    const bool nw = p < c.W * c.H && m.corr[p] == kNewCorr;
+    const unsigned long long bm = __ballot(nw);
+#pragma unroll
+    for (int d = 32; d; d >>= 1) before += __shfl_xor(before, d, 64);
+    if (lane == 0) {
+        wc[wave] = (uint32_t)__popcll(bm);
+        wp[wave] = before;
+    }
+    __syncthreads();
+    uint32_t off = ((wp[0] + wp[1]) + wp[2]) + wp[3];
+    if (!scanned && b == nblk - 1 && threadIdx.x == 0) m.st->n_new = off + (((wc[0] + wc[1]) + wc[2]) + wc[3]);
+    if (!nw) return;
+    for (int w = 0; w < wave; ++w) off += wc[w];
+    off += (uint32_t)__popcll(bm & ((1ull << lane) - 1ull));
+    const uint32_t idx = m.st->n + off;
+    if (idx >= m.cap) {
+        atomicOr(&m.st->flags, (uint32_t)TF_FLAG_SURFEL_OVERFLOW);
+        return;
+    }
+    const float4 P = m.ipt[p];
+    const float4 N = m.inr[p];
+    m.pos[idx] = make_float4(P.x, P.y, P.z, (N.w * 0.70710677f) / c.fx);
+    m.nrm[idx] = make_float4(N.x, N.y, N.z, P.w);
+    m.time[idx] = frame;
+}
+
+__global__ __launch_bounds__(256) void k_sf_update(SfCam c, SfMap m, int nblk, int scanned, int frame)
+{
+    if ((int)blockIdx.x < nblk) {
+        sf_append(c, m, (int)blockIdx.x, nblk, scanned != 0, frame);
+        return;
+    }
     const uint32_t n = m.st->n;
-    for (uint32_t s = blockIdx.x * 256 + threadIdx.x; s < n; s += gridDim.x * 256) {
+    for (uint32_t s = (blockIdx.x - (uint32_t)nblk) * 256 + threadIdx.x; s < n; s += (gridDim.x - (uint32_t)nblk) * 256) {
         const float4 q = m.pos[s];
         float u, v, rho, Z;
         if (!sf_project(c, q, u, v, rho, Z)) continue;
@@ -210,75 +301,6 @@ __global__ __launch_bounds__(256) void k_sf_update(SfCam c, SfMap m, int frame)
             m.time[s] = frame;
         }
     }
-}
-
-__global__ __launch_bounds__(256) void k_sf_count(int npix, SfMap m)
-{
-    __shared__ uint32_t wc[4];
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    const bool nw = p < npix && m.corr[p] == kNewCorr;
-    const unsigned long long b = __ballot(nw);
-    if ((threadIdx.x & 63) == 0) wc[threadIdx.x >> 6] = (uint32_t)__popcll(b);
-    __syncthreads();
-    if (threadIdx.x == 0) m.blk[blockIdx.x] = ((wc[0] + wc[1]) + wc[2]) + wc[3];
-}
-
-// exclusive offsets of the per-block counts, the frame's total in st->n_new
-__global__ __launch_bounds__(1024) void k_sf_scan(int nblk, SfMap m)
-{
-    __shared__ uint32_t part[1024];
-    const int t = threadIdx.x;
-    const int per = (nblk + 1023) / 1024;
-    const int b = t * per, e = min(b + per, nblk);
-    uint32_t s = 0;
-    for (int i = b; i < e; ++i) s += m.blk[i];
-    part[t] = s;
-    __syncthreads();
-    for (int d = 1; d < 1024; d <<= 1) {
-        const uint32_t x = t >= d ? part[t - d] : 0u;
-        __syncthreads();
-        part[t] += x;
-        __syncthreads();
-    }
-    uint32_t run = part[t] - s;
-    for (int i = b; i < e; ++i) {
-        const uint32_t k = m.blk[i];
-        m.blk[i] = run;
-        run += k;
-    }
-    if (t == 1023) m.st->n_new = part[1023];
-}
-
-__global__ __launch_bounds__(256) void k_sf_append(SfCam c, SfMap m, int frame)
-{
-    __shared__ uint32_t wc[4];
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    const int npix = c.W * c.H;
-    const bool nw = p < npix && m.corr[p] == kNewCorr;
-    const unsigned long long b = __ballot(nw);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) wc[wave] = (uint32_t)__popcll(b);
-    __syncthreads();
-    if (!nw) return;
-    uint32_t off = m.blk[blockIdx.x];
-    for (int w = 0; w < wave; ++w) off += wc[w];
-    off += (uint32_t)__popcll(b & ((1ull << lane) - 1ull));
-    const uint32_t idx = m.st->n + off;
-    if (idx >= m.cap) {
-        atomicOr(&m.st->flags, (uint32_t)TF_FLAG_SURFEL_OVERFLOW);
-        return;
-    }
-    const float4 P = m.ipt[p];
-    const float4 N = m.inr[p];
-    m.pos[idx] = make_float4(P.x, P.y, P.z, (N.w * 0.70710677f) / c.fx);
-    m.nrm[idx] = make_float4(N.x, N.y, N.z, P.w);
-    m.time[idx] = frame;
-}
-
-__global__ void k_sf_finish(SfMap m)
-{
-    const uint32_t n = m.st->n + m.st->n_new;
-    m.st->n = n < m.cap ? n : m.cap;
 }
 
 __global__ __launch_bounds__(256) void k_sf_init(SfMap m)
@@ -439,11 +461,9 @@ int tf_surfel_fuse(tf_surfels *m, const void *d_depth, int depth_format, const t
         hipLaunchKernelGGL(k_sf_points<TF_DEPTH_F32_M>, dim3(nblk), dim3(256), 0, s, d_depth, c, alpha_k, norm_r, m->m);
     hipLaunchKernelGGL(k_sf_splat, dim3(kSurfGrid), dim3(256), 0, s, c, m->m);
     hipLaunchKernelGGL(k_sf_assoc, dim3(nblk), dim3(256), 0, s, c, m->p.max_depth_diff, m->p.min_normal_dot, m->m);
-    hipLaunchKernelGGL(k_sf_update, dim3(kSurfGrid), dim3(256), 0, s, c, m->m, frame);
-    hipLaunchKernelGGL(k_sf_count, dim3(nblk), dim3(256), 0, s, npix, m->m);
-    hipLaunchKernelGGL(k_sf_scan, dim3(1), dim3(1024), 0, s, nblk, m->m);
-    hipLaunchKernelGGL(k_sf_append, dim3(nblk), dim3(256), 0, s, c, m->m, frame);
-    hipLaunchKernelGGL(k_sf_finish, dim3(1), dim3(1), 0, s, m->m);
+    if (nblk > kSumBlocks) hipLaunchKernelGGL(k_sf_scan, dim3(1), dim3(1024), 0, s, nblk, m->m);
+    hipLaunchKernelGGL(k_sf_update, dim3(nblk + kSurfGrid), dim3(256), 0, s, c, m->m, nblk, nblk > kSumBlocks ? 1 : 0,
+                       frame);
     if (hipGetLastError() != hipSuccess) return TF_E_HIP;
     m->frames += 1;
     m->last_w = c.W;
@@ -458,7 +478,7 @@ int tf_surfel_stats(tf_surfels *m, uint32_t *h_count, uint32_t *h_flags, uint32_
     if (hipMemcpyAsync(&st, m->m.st, sizeof(st), hipMemcpyDeviceToHost, (hipStream_t)stream) != hipSuccess ||
         hipStreamSynchronize((hipStream_t)stream) != hipSuccess)
         return TF_E_HIP;
-    if (h_count) *h_count = st.n;
+    if (h_count) *h_count = sf_count(st, m->p.capacity);
     if (h_flags) *h_flags = st.flags;
     if (h_frames) *h_frames = m->frames;
     return TF_OK;

@@ -111,3 +111,32 @@ def test_capacity_and_empty_frames():
     g.fuse(torch.zeros((K2.height, K2.width), dtype=torch.int16, device="cuda"), K2, configs.c2_poses(300)[0])
     st = g.stats()
     assert st["count"] == 0 and st["flags"] == 0 and st["frames"] == 1
+
+
+@pytest.mark.parametrize("size", [(1, 1), (255, 2), (1024, 1024), (1280, 832)])
+def test_append_order_of_small_and_large_images(size):
+    """new surfels in raster order with contiguous indices, at 1, 2 and 4096
+    blocks of 256 pixels and at 4160 (counts scanned by a launch of their own):
+    an empty map takes every pixel with a normal"""
+    import paper_1708_00783_amd as T
+    from synth.scenes import Intrinsics
+    W, H = size
+    rng = np.random.default_rng(W)
+    K = Intrinsics(0.8 * W, 0.8 * W, (W - 1) / 2.0, (H - 1) / 2.0, W, H)
+    d = rng.uniform(1.0, 1.2, size=(H, W)).astype(np.float32)
+    d[rng.uniform(size=(H, W)) < 0.1] = 0.0
+    P = np.eye(4, dtype=np.float32)
+    g = T.SurfelMap(W * H, W, H)
+    g.fuse(to_device(d), K, P)
+    valid = np.zeros((H, W), bool)
+    valid[:-1, :-1] = (d[:-1, :-1] > 0) & (d[:-1, 1:] > 0) & (d[1:, :-1] > 0)
+    n = int(valid.sum())
+    assert g.stats()["count"] == n and g.stats()["flags"] == 0
+    pos, _, tm = g.export()
+    assert np.array_equal(pos[:, 2], d[valid]) and np.all(tm == 0)
+    _, corr = g.export_frame()
+    assert np.array_equal(corr == -1, valid) and np.all(corr[~valid] == -2)
+    g.fuse(to_device(d), K, P)      # the second frame starts from the whole first one
+    im, _ = g.export_frame()
+    assert int(im.max()) == n - 1 if n else True
+    assert g.stats()["count"] >= n
