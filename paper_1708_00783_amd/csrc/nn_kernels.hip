@@ -226,9 +226,12 @@ __device__ __forceinline__ void pack_g(const float *w, int cin, int cinp, int co
     g[i] = (tap < 9 && ci < cin) ? f2bf(w[(co * 9 + tap) * cin + ci]) : (uint16_t)0;
 }
 
-__device__ __forceinline__ void pack_t(const float *w, int cin, int cout, int i, uint16_t *t)
+// backward-data operand in the same order: K step tap * cout / 32 + co / 32, the B column is input channel ci
+__device__ __forceinline__ void pack_t(const float *w, int cin, int cinp, int cout, int i, uint16_t *t)
 {
-    const int ci = i / (9 * cout), k = i % (9 * cout), tap = k / cout, co = k % cout;
+    int ci, k;
+    frag_coords(i, cinp, ci, k);
+    const int tap = k / cout, co = k % cout;
     t[i] = ci < cin ? f2bf(w[(co * 9 + tap) * cin + ci]) : (uint16_t)0;
 }
 
@@ -276,12 +279,15 @@ __device__ __forceinline__ void pack_up(const float *w, int cin, int cinp, int c
     gu[i] = folded_weight(w, cin, par, co, q, ci, lo);
 }
 
-// backward-data operand of the same folded weights: tu[lo][ci][(par * 4 + q) * cout + co]
+// backward-data operand of the same folded weights, in fragment order: K step
+// st = (par * 4 + q) * cout / 32 + co / 32, the B column is input channel ci
 __device__ __forceinline__ void pack_tu(const float *w, int cin, int cinp, int cout, int i, uint16_t *tu)
 {
     const int half = cinp * 16 * cout;
     const int lo = i / half, j = i - lo * half;
-    const int ci = j / (16 * cout), rem = j - ci * 16 * cout, pq = rem / cout, co = rem - (rem / cout) * cout;
+    int ci, k;
+    frag_coords(j, cinp, ci, k);
+    const int pq = k / cout, co = k - (k / cout) * cout;
     tu[i] = folded_weight(w, cin, pq >> 2, co, pq & 3, ci, lo);
 }
 
@@ -305,7 +311,7 @@ __global__ __launch_bounds__(256) void k_pack(PackJobs J)
         if (p.up)
             pack_tu(p.w, p.cin, p.cinp, p.cout, li, p.t);
         else
-            pack_t(p.w, p.cin, p.cout, li, p.t);
+            pack_t(p.w, p.cin, p.cinp, p.cout, li, p.t);
     }
 }
 
@@ -323,8 +329,10 @@ __device__ __forceinline__ long xcd_band_tile(long ntiles)
 }
 
 // stage rows iy0 .. iy0 + IR - 1, columns ix0 .. ix0 + IC - 1 of one image's
-// NHWC bf16 tensor (CINP channels) in LDS, RS bytes per pixel, zeros outside
-template <int CINP, int IR, int IC, int RS>
+// NHWC bf16 tensor (CINP channels) in LDS, RS bytes per pixel, zeros outside;
+// SPLIT keeps the even columns before the odd ones, so that pixels two apart
+// are RS bytes apart (IC even)
+template <int CINP, int IR, int IC, int RS, bool SPLIT = false>
 __device__ __forceinline__ void stage_tile(unsigned char *tile, const uint16_t *in, int nimg, int Hs, int Ws,
                                            int iy0, int ix0, bool live)
 {
@@ -335,7 +343,8 @@ __device__ __forceinline__ void stage_tile(unsigned char *tile, const uint16_t *
         u32x4 v = {0u, 0u, 0u, 0u};
         if (live && sy >= 0 && sy < Hs && sx >= 0 && sx < Ws)
             v = ld16(in + (((size_t)nimg * Hs + sy) * Ws + sx) * CINP + ch * 8);
-        *reinterpret_cast<u32x4 *>(tile + (rr * IC + c) * RS + ch * 16) = v;
+        const int cs = SPLIT ? (c & 1) * (IC / 2) + (c >> 1) : c;
+        *reinterpret_cast<u32x4 *>(tile + (rr * IC + cs) * RS + ch * 16) = v;
     }
     __syncthreads();
 }
@@ -492,76 +501,79 @@ __global__ __launch_bounds__(256) void k_conv_fwd_up(const uint16_t *in, int Hs,
 // and source offset (a, b), the output pixel (2 m' + py, 2 n' + px) with
 // m' = m + 1 - py - a, n' = n + 1 - px - b, on the same split folded
 // weights as the forward (high and low halves; 28 COUT multiply-adds per
-// source channel instead of 36 COUT).  Then the source's relu mask.  A wave
-// takes 32 source pixels and CIN / NS channels.
-template <int CIN, int COUT, int NS>
+// source channel instead of 36 COUT).  Then the source's relu mask.
+//
+// A workgroup takes R = 4 / NS source rows x 16 T columns; it stages the
+// (2 R + 2) x (32 T + 2) output pixels those collect from in LDS once (each is
+// read by four source pixels), and each wave computes one row x CIN / NS
+// channels, the weights in fragment order so that a load reads whole lines.
+// Bound by the latency of a K step (weights from L2), so the steps are unrolled
+// in full: where the low half is loaded is then known, no branch ends a block,
+// and the loads of several steps are in flight.  Layers d1, d2, d3 at
+// 8 x 256 x 256: 31, 22 and 20 us; in a loop with that branch 37, 43 and 51;
+// gathered from global memory per tap, the 16 rows of a weight fragment apart,
+// 72, 77 and 43.
+template <int CIN, int COUT, int T, int NS>
 __global__ __launch_bounds__(256) void k_conv_bwd_data_up(const uint16_t *gpre, const uint16_t *tu,
                                                           const uint16_t *act, uint16_t *gout, int N, int Hs, int Ws)
 {
     static_assert(NS == 1 || NS == 2 || NS == 4, "channel split must divide the 4 waves of a workgroup");
     static_assert(COUT % 32 == 0, "a K step is 32 output channels of one (parity, offset)");
     constexpr int K16 = 16 * COUT;
-    constexpr int NT = CIN / 16 / NS;
-    const int lane = (int)threadIdx.x & 63, r = lane & 15, gq = lane >> 4;
-    const long P = (long)N * Hs * Ws;
+    constexpr int NT = CIN / 16 / NS, R = 4 / NS;
+    constexpr int IR = 2 * R + 2, IC = 32 * T + 2;
+    constexpr int RS = COUT * 2 + 16;   // +16 bytes: neighbouring pixels' fragments start on different banks
+    __shared__ __attribute__((aligned(16))) unsigned char tile[IR * IC * RS];
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6, r = lane & 15, gq = lane >> 4;
     const int Ho = 2 * Hs, Wo = 2 * Ws;
-    const int wid = (int)blockIdx.x * 4 + ((int)threadIdx.x >> 6);
-    const int cbase = (wid % NS) * (CIN / NS);
-    const long p0 = (long)(wid / NS) * 32;   // waves past P load nothing and store nothing
-    int pn[2], pm[2], pnn[2];
-    bool pv[2];
+    const int tx = (Ws + 16 * T - 1) / (16 * T), ty = (Hs + R - 1) / R;
+    const long ntiles = (long)N * ty * tx;
+    const long wt = xcd_band_tile(ntiles);
+    const bool live = wt < ntiles;
+    const long gt = live ? wt : 0;
+    const int xt = (int)(gt % tx);
+    const long nyt = gt / tx;
+    const int nimg = (int)(nyt / ty), m0 = (int)(nyt - (long)nimg * ty) * R, n0 = xt * 16 * T;
+    stage_tile<COUT, IR, IC, RS, true>(tile, gpre, nimg, Ho, Wo, 2 * m0 - 1, 2 * n0 - 1, live);
+    const int yy = w / NS, cbase = (w % NS) * (CIN / NS);
+    f32x4 acc[T][NT];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        long p = p0 + t * 16 + r;
-        pv[t] = p < P;
-        if (!pv[t]) p = 0;
-        pn[t] = (int)(p / ((long)Hs * Ws));
-        const int rem = (int)(p - (long)pn[t] * Hs * Ws);
-        pm[t] = rem / Ws;
-        pnn[t] = rem - pm[t] * Ws;
-    }
-    f32x4 acc[2][NT];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < T; ++t)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint16_t *tl = tu + (size_t)CIN * K16;   // low halves
-    for (int pq = 0; pq < 16; ++pq) {
+    const uint16_t *th = tu + (size_t)cbase / 16 * 512 + lane * 8;
+    const uint16_t *tl = th + (size_t)CIN * K16;   // low halves
+#pragma unroll
+    for (int st = 0; st < K16 / 32; ++st) {
+        const int pq = st / (COUT / 32), co = (st - pq * (COUT / 32)) * 32 + gq * 8;
         const int py = pq >> 3, px = (pq >> 2) & 1, a = (pq >> 1) & 1, b = pq & 1;
         const bool split = (pq & 3) != (pq >> 2);   // offset (a, b) != (py, px): two or four taps
-#pragma unroll 2
-        for (int co0 = 0; co0 < COUT; co0 += 32) {
-            const int co = co0 + gq * 8;
-            bf16x8 av[2];
+        // output row 2 m' + py = 2 m + 2 - py - 2 a of source row m, counted from 2 m0 - 1; columns likewise
+        const unsigned char *src = tile + ((2 * yy + 3 - py - 2 * a) * IC + (1 - px) * (IC / 2) + r + 1 - b) * RS + co * 2;
+        bf16x8 av[T];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int mo = pm[t] + 1 - py - a, no = pnn[t] + 1 - px - b;
-                u32x4 v = {0u, 0u, 0u, 0u};
-                if (pv[t] && mo >= 0 && mo < Hs && no >= 0 && no < Ws)
-                    v = ld16(gpre + (((size_t)pn[t] * Ho + 2 * mo + py) * Wo + 2 * no + px) * COUT + co);
-                av[t] = as_bf(v);
-            }
+        for (int t = 0; t < T; ++t) av[t] = as_bf(*reinterpret_cast<const u32x4 *>(src + 16 * t * RS));
 #pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const size_t wo = (size_t)(cbase + j * 16 + r) * K16 + pq * COUT + co;
-                const bf16x8 bv = as_bf(ld16(tu + wo));
-                acc[0][j] = mfma(av[0], bv, acc[0][j]);
-                acc[1][j] = mfma(av[1], bv, acc[1][j]);
-                if (split) {
-                    const bf16x8 bl = as_bf(ld16(tl + wo));
-                    acc[0][j] = mfma(av[0], bl, acc[0][j]);
-                    acc[1][j] = mfma(av[1], bl, acc[1][j]);
-                }
+        for (int j = 0; j < NT; ++j) {
+            const size_t wo = (size_t)(st * (CIN / 16) + j) * 512;
+            const bf16x8 bv = as_bf(ld16(th + wo));
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc[t][j] = mfma(av[t], bv, acc[t][j]);
+            if (split) {
+                const bf16x8 bl = as_bf(ld16(tl + wo));
+#pragma unroll
+                for (int t = 0; t < T; ++t) acc[t][j] = mfma(av[t], bl, acc[t][j]);
             }
         }
     }
     __shared__ EpiTile<NT> st[4];
+    const int m = m0 + yy;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-        epilogue_tile(st[threadIdx.x >> 6], acc[t], lane, [&](int pix, int c8, f32x4 lo, f32x4 hi) {
-            const long p = p0 + t * 16 + pix;
-            if (p >= P) return;
-            const size_t o = (size_t)p * CIN + cbase + c8;
+    for (int t = 0; t < T; ++t)
+        epilogue_tile(st[w], acc[t], lane, [&](int pix, int c8, f32x4 lo, f32x4 hi) {
+            const int n = n0 + t * 16 + pix;
+            if (!live || m >= Hs || n >= Ws) return;
+            const size_t o = (((size_t)nimg * Hs + m) * Ws + n) * CIN + cbase + c8;
             bwd_store8<false>(gout + o, lo, hi, nullptr, act + o);
         });
 }
@@ -569,74 +581,87 @@ __global__ __launch_bounds__(256) void k_conv_bwd_data_up(const uint16_t *gpre, 
 // backward data of a stride-2 layer by input parity: input pixel
 // (2m + py, 2n + px) receives gradient only through the taps ky = 1 (py = 0)
 // or ky in {0, 2} (py = 1), likewise kx, from output pixel
-// ((iy + 1 - ky) / 2, (ix + 1 - kx) / 2) -- 1, 2 or 4 of the 9 taps.  A wave
-// takes 32 same-parity columns of one input row and CIN / NS channels; the
-// skip gradient and the relu mask are fused as in k_conv_bwd_data.
-template <int CIN, int COUT, bool SKIP, int NS>
+// ((iy + 1 - ky) / 2, (ix + 1 - kx) / 2) -- 1, 2 or 4 of the 9 taps; so the
+// four parities of (m, n) use every tap once, on the gradients of output
+// pixels (m, n) to (m + 1, n + 1).  The skip gradient and the relu mask are
+// fused into the store.
+//
+// A workgroup takes R = 4 / NS rows m x 16 T columns n; it stages their
+// (R + 1) x (16 T + 1) gradient pixels in LDS once, and each wave computes the
+// four parities of one row for CIN / NS channels: a weight fragment (in
+// fragment order, whole lines a load) serves T products, a 2 x 2 of input pixels
+// leaves one wave.  Layers e2, e3, e4 at 8 x 256 x 256: 30, 15 and 11 us
+// (per parity and from global memory, the 16 rows of a weight fragment apart:
+// 66, 22 and 15); e2 moves 117 MB, 23 us at a copy's rate.
+template <int CIN, int COUT, bool SKIP, int T, int NS>
 __global__ __launch_bounds__(256) void k_conv_bwd_data_s2(const uint16_t *gpre, int Ho, int Wo, const uint16_t *tw,
                                                           const uint16_t *skipg, const uint16_t *act, uint16_t *gout,
                                                           int N, int Hq, int Wq)
 {
     static_assert(NS == 1 || NS == 2 || NS == 4, "channel split must divide the 4 waves of a workgroup");
     static_assert(COUT % 32 == 0, "a K step is 32 output channels of one tap");
-    constexpr int K9 = 9 * COUT;
-    constexpr int NT = CIN / 16 / NS;
-    const int lane = (int)threadIdx.x & 63, r = lane & 15, gq = lane >> 4;
-    const int Wh = (Wq + 1) >> 1, runs = (Wh + 31) >> 5;
-    const long wid = (long)blockIdx.x * 4 + ((int)threadIdx.x >> 6);
-    const bool live = wid / NS < (long)N * Hq * 2 * runs;   // dead waves still join the epilogue barriers
-    const long grp = live ? wid / NS : 0;
-    const int cbase = (int)(wid % NS) * (CIN / NS);
-    const int run = (int)(grp % runs);
-    const long rp = grp / runs;
-    const int px = (int)(rp & 1);
-    const long ni = rp >> 1;   // image * Hq + input row
-    const int nimg = (int)(ni / Hq), iy = (int)(ni - (long)nimg * Hq);
-    const int py = iy & 1;
-    f32x4 acc[2][NT];
+    constexpr int NT = CIN / 16 / NS, R = 4 / NS;
+    constexpr int IR = R + 1, IC = 16 * T + 1;
+    constexpr int RS = COUT * 2 + 16;   // +16 bytes: neighbouring pixels' fragments start on different banks
+    __shared__ __attribute__((aligned(16))) unsigned char tile[IR * IC * RS];
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6, r = lane & 15, gq = lane >> 4;
+    const int Hh = (Hq + 1) >> 1, Wh = (Wq + 1) >> 1;
+    const int tx = (Wh + 16 * T - 1) / (16 * T), ty = (Hh + R - 1) / R;
+    const long ntiles = (long)N * ty * tx;
+    const long wt = xcd_band_tile(ntiles);
+    const bool live = wt < ntiles;
+    const long gt = live ? wt : 0;
+    const int xt = (int)(gt % tx);
+    const long nyt = gt / tx;
+    const int nimg = (int)(nyt / ty), m0 = (int)(nyt - (long)nimg * ty) * R, n0 = xt * 16 * T;
+    stage_tile<COUT, IR, IC, RS>(tile, gpre, nimg, Ho, Wo, m0, n0, live);
+    const int yy = w / NS, cbase = (w % NS) * (CIN / NS);
+    f32x4 acc[4][T][NT];   // [py * 2 + px]
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int p = 0; p < 4; ++p)
 #pragma unroll
-        for (int j = 0; j < NT; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int nty = py ? 2 : 1, ntx = px ? 2 : 1;
-    for (int a = 0; a < nty; ++a) {
-        const int ky = py ? 2 * a : 1;
-        const int oy = (iy + 1 - ky) >> 1;
-        const bool rowok = oy >= 0 && oy < Ho;
-        for (int b = 0; b < ntx; ++b) {
-            const int kx = px ? 2 * b : 1;
-            const int tap = ky * 3 + kx;
-            for (int co0 = 0; co0 < COUT; co0 += 32) {
-                const int co = co0 + gq * 8;
-                bf16x8 av[2];
+        for (int t = 0; t < T; ++t)
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int ix = 2 * (run * 32 + t * 16 + r) + px;
-                    const int ox = (ix + 1 - kx) >> 1;
-                    u32x4 v = {0u, 0u, 0u, 0u};
-                    if (rowok && ix < Wq && ox >= 0 && ox < Wo)
-                        v = ld16(gpre + (((size_t)nimg * Ho + oy) * Wo + ox) * COUT + co);
-                    av[t] = as_bf(v);
-                }
+            for (int j = 0; j < NT; ++j) acc[p][t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const unsigned char *src = tile + (yy * IC + r) * RS + gq * 16;
+    const uint16_t *tf = tw + (size_t)cbase / 16 * 512 + lane * 8;
+#pragma unroll
+    for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) {
+            const int par = (ky != 1) * 2 + (kx != 1);
+            const int off = ((ky == 0) * IC + (kx == 0)) * RS;   // tap 0 reads the next output row / column
+#pragma unroll
+            for (int c = 0; c < COUT / 32; ++c) {
+                bf16x8 av[T];
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+                    av[t] = as_bf(*reinterpret_cast<const u32x4 *>(src + off + c * 64 + 16 * t * RS));
 #pragma unroll
                 for (int j = 0; j < NT; ++j) {
-                    const bf16x8 bv = as_bf(ld16(tw + (size_t)(cbase + j * 16 + r) * K9 + tap * COUT + co));
-                    acc[0][j] = mfma(av[0], bv, acc[0][j]);
-                    acc[1][j] = mfma(av[1], bv, acc[1][j]);
+                    const size_t wo = (size_t)(((ky * 3 + kx) * (COUT / 32) + c) * (CIN / 16) + j) * 512;
+                    const bf16x8 bv = as_bf(ld16(tf + wo));
+#pragma unroll
+                    for (int t = 0; t < T; ++t) acc[par][t][j] = mfma(av[t], bv, acc[par][t][j]);
                 }
             }
         }
-    }
-    const size_t prow = ((size_t)nimg * Hq + iy) * Wq;
     __shared__ EpiTile<NT> st[4];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-        epilogue_tile(st[threadIdx.x >> 6], acc[t], lane, [&](int pix, int c8, f32x4 lo, f32x4 hi) {
-            const int ix = 2 * (run * 32 + t * 16 + pix) + px;
-            if (!live || ix >= Wq) return;
-            const size_t o = (prow + ix) * CIN + cbase + c8;
-            bwd_store8<SKIP>(gout + o, lo, hi, SKIP ? skipg + o : nullptr, act + o);
-        });
+    for (int py = 0; py < 2; ++py) {
+        const int iy = 2 * (m0 + yy) + py;
+        const size_t prow = ((size_t)nimg * Hq + iy) * Wq;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int px = 0; px < 2; ++px)
+                epilogue_tile(st[w], acc[py * 2 + px][t], lane, [&](int pix, int c8, f32x4 lo, f32x4 hi) {
+                    const int ix = 2 * (n0 + t * 16 + pix) + px;
+                    if (!live || iy >= Hq || ix >= Wq) return;
+                    const size_t o = (prow + ix) * CIN + cbase + c8;
+                    bwd_store8<SKIP>(gout + o, lo, hi, SKIP ? skipg + o : nullptr, act + o);
+                });
+    }
 }
 
 // ============================================================================
@@ -1320,29 +1345,28 @@ hipError_t launch_head_wgrad(const float *ddelta, const uint16_t *d1, int N, int
     return hipGetLastError();
 }
 
-// workgroups of k_conv_bwd_data_s2: N Hq input rows x 2 column parities x runs of 32 x NS waves
-static dim3 s2_grid(int N, int Hq, int Wq, int NS)
-{
-    const long waves = (long)N * Hq * 2 * ((((Wq + 1) >> 1) + 31) >> 5) * NS;
-    return dim3((unsigned)((waves + 3) / 4));
-}
-
 hipError_t launch_conv_bwd_data(int layer, const uint16_t *gpre, int Ho, int Wo, const uint16_t *t,
                                 const uint16_t *skipg, const uint16_t *act, uint16_t *gout, int N, int Hq, int Wq,
                                 hipStream_t s)
 {
-    const long P = (long)N * Hq * Wq;
-    const dim3 g1 = grid1(P, 128), g4 = grid1(P, 32), b(256);
+    const dim3 b(256);
+    // 4 / NS rows x 16 T columns per workgroup: of source pixels (upsampled layers) or of 2 x 2 input pixels (stride 2)
+    auto tiles = [&](int h, int w, int T, int NS) {
+        const long nt = (long)N * ((h + 4 / NS - 1) / (4 / NS)) * ((w + 16 * T - 1) / (16 * T));
+        return dim3((unsigned)((nt + 7) / 8 * 8));
+    };
+    auto up_grid = [&](int T, int NS) { return tiles(Hq, Wq, T, NS); };
+    auto s2_grid = [&](int T, int NS) { return tiles((Hq + 1) >> 1, (Wq + 1) >> 1, T, NS); };
     if (layer >= 4 && (Ho != 2 * Hq || Wo != 2 * Wq)) return hipErrorInvalidValue;
     switch (layer) {
     // stride-2 layers: only the taps of each input parity
-    case 1: hipLaunchKernelGGL((k_conv_bwd_data_s2<32, 64, true, 1>), s2_grid(N, Hq, Wq, 1), b, 0, s, gpre, Ho, Wo, t, skipg, act, gout, N, Hq, Wq); break;
-    case 2: hipLaunchKernelGGL((k_conv_bwd_data_s2<64, 64, true, 1>), s2_grid(N, Hq, Wq, 1), b, 0, s, gpre, Ho, Wo, t, skipg, act, gout, N, Hq, Wq); break;
-    case 3: hipLaunchKernelGGL((k_conv_bwd_data_s2<64, 128, true, 2>), s2_grid(N, Hq, Wq, 2), b, 0, s, gpre, Ho, Wo, t, skipg, act, gout, N, Hq, Wq); break;
+    case 1: hipLaunchKernelGGL((k_conv_bwd_data_s2<32, 64, true, 1, 2>), s2_grid(1, 2), b, 0, s, gpre, Ho, Wo, t, skipg, act, gout, N, Hq, Wq); break;
+    case 2: hipLaunchKernelGGL((k_conv_bwd_data_s2<64, 64, true, 1, 2>), s2_grid(1, 2), b, 0, s, gpre, Ho, Wo, t, skipg, act, gout, N, Hq, Wq); break;
+    case 3: hipLaunchKernelGGL((k_conv_bwd_data_s2<64, 128, true, 1, 4>), s2_grid(1, 4), b, 0, s, gpre, Ho, Wo, t, skipg, act, gout, N, Hq, Wq); break;
     // upsampled layers: the adjoint of the parity-folded forward (t holds the folded weights)
-    case 4: hipLaunchKernelGGL((k_conv_bwd_data_up<128, 64, 4>), g4, b, 0, s, gpre, t, act, gout, N, Hq, Wq); break;
-    case 5: hipLaunchKernelGGL((k_conv_bwd_data_up<64, 64, 1>), g1, b, 0, s, gpre, t, act, gout, N, Hq, Wq); break;
-    case 6: hipLaunchKernelGGL((k_conv_bwd_data_up<64, 32, 1>), g1, b, 0, s, gpre, t, act, gout, N, Hq, Wq); break;
+    case 4: hipLaunchKernelGGL((k_conv_bwd_data_up<128, 64, 1, 4>), up_grid(1, 4), b, 0, s, gpre, t, act, gout, N, Hq, Wq); break;
+    case 5: hipLaunchKernelGGL((k_conv_bwd_data_up<64, 64, 1, 2>), up_grid(1, 2), b, 0, s, gpre, t, act, gout, N, Hq, Wq); break;
+    case 6: hipLaunchKernelGGL((k_conv_bwd_data_up<64, 32, 2, 2>), up_grid(2, 2), b, 0, s, gpre, t, act, gout, N, Hq, Wq); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -157,6 +157,28 @@ def test_backward_layers_match_oracle(shape):
         _close(_bf(net, "grad_" + src), dx * (a > 0), "grad_" + src)
 
 
+@pytest.mark.parametrize("shape", [(1, 8, 8), (3, 24, 136), (1, 136, 72)])
+def test_backward_data_at_tile_edges(shape):
+    """Gradients at the conv inputs where the backward tiles end: the smallest
+    image (sources of 1 x 1, less than a tile in both directions), and widths
+    and heights one past 1, 2 and 4 tiles of 16 columns or of 2 or 4 rows, with
+    3 images (the tiles are not a multiple of the 8 they are dealt in)."""
+    import torch
+    T, net, P, depth, target, out = _setup(11, shape)
+    net.backward(torch.from_numpy(target).cuda())
+    skip_to = {"e1": "d1", "e2": "d2", "e3": "d3"}
+    for name, (src, stride, up, _) in reversed(list(LAYER_IO.items())):
+        if name == "e1":
+            continue
+        a = _bf(net, src)
+        dx = D.conv_backward(D.up2(a) if up else a, _rb(P[name + ".w"]), _bf(net, "grad_" + name), stride)[0]
+        if up:
+            dx = D.up2_backward(dx)
+        if src in skip_to:
+            dx = dx + _bf(net, "grad_" + skip_to[src])
+        _close(_bf(net, "grad_" + src), dx * (a > 0), f"{shape} grad_{src}")
+
+
 def test_end_to_end_gradient_cosine():
     import torch
     T, net, P, depth, target, out = _setup(3)
