@@ -248,9 +248,8 @@ int tf_nn_forward(tf_nn *nn, const void *d_depth, int fmt, uint32_t batch, float
     }
     const LayerDesc &Hd = nn->net.L[kLayers - 1];
     if (e == hipSuccess)
-        e = launch_head_fwd(nn->act[7], nn->params + Hd.w_off, nn->params + Hd.b_off, nn->dm, nn->out, N, H, W, s);
-    if (e == hipSuccess && d_out != nn->out)
-        e = hipMemcpyAsync(d_out, nn->out, 4 * (size_t)N * H * W, hipMemcpyDeviceToDevice, s);
+        e = launch_head_fwd(nn->act[7], nn->params + Hd.w_off, nn->params + Hd.b_off, nn->dm, nn->out,
+                            d_out != nn->out ? d_out : nullptr, N, H, W, s);
     nn->batch = batch;
     nn->have_forward = e == hipSuccess;
     return hs(e);
