@@ -160,38 +160,51 @@ struct Timed {
     }
 };
 
-// swap-in after the visible list (Sec. 5): the device lists the visible
+// swap-in after the visible list (Sec. 5): the device notes the visible
 // entries whose host store holds data; the host takes the lowest entry
-// indices up to the transfer capacity, gathers their blocks into the pinned
-// transfer buffer and sends it; one kernel fuses them into the device blocks.
+// indices up to the transfer capacity and gathers their blocks into the
+// pinned transfer buffer, part by part; a kernel fuses each part, as it is
+// there, into the device blocks, reading it from the host.
 hipError_t swap_in(tf_ctx *ctx, hipStream_t s)
 {
     Vol &v = ctx->v;
+    SwapHost &h = *ctx->swap;
     hipError_t e = launch_swap_candidates(v, s);
-    Ctrl c;
-    if (e == hipSuccess) e = hipMemcpyAsync(&c, v.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess || c.n_swap_cand == 0) return e;
-    ctx->cand.resize(c.n_swap_cand);
-    e = hipMemcpyAsync(ctx->cand.data(), v.ret, (size_t)c.n_swap_cand * 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
-    std::sort(ctx->cand.begin(), ctx->cand.end());
-    const uint32_t T = ctx->p.swap_transfer_blocks;
-    const uint32_t m = c.n_swap_cand < T ? c.n_swap_cand : T;
-    if (c.n_swap_cand > T) ctx->host_flags |= TF_FLAG_TRANSFER_OVERFLOW;
-    int32_t *hidx = (int32_t *)ctx->h_transfer;
-    uint8_t *hvox = (uint8_t *)ctx->h_transfer + (size_t)T * 4;
-    const uint8_t *store = (const uint8_t *)ctx->h_store;
-    for (uint32_t k = 0; k < m; ++k) {
-        const int32_t idx = ctx->cand[k];
-        hidx[k] = idx;
-        memcpy(hvox + (size_t)k * kBlockBytes, store + (size_t)idx * kBlockBytes, kBlockBytes);
-        ctx->host_has[idx] = 0;
+    SwapInCopy job;
+    job.idx = h.idx;
+    job.store = (const uint8_t *)ctx->h_store;
+    job.vox = h.vox;
+    bool helped = SwapHost::many(h.last_in);
+    if (helped) h.pool.start(job);
+    e = hipStreamSynchronize(s);
+    const uint32_t T = ctx->p.swap_transfer_blocks, n = e == hipSuccess ? (uint32_t)h.note[0] : 0u;
+    const uint32_t m = std::min(n, T);
+    h.last_in = m;
+    if (m) {
+        for (uint32_t k = 0; k < m; ++k) h.idx[k] = (int32_t)h.note[1 + k];
+        if (n > T) {   // the order of those taken is of no account
+            std::vector<int32_t> &cand = ctx->cand;
+            cand.resize(n);
+            for (uint32_t k = 0; k < n; ++k) cand[k] = (int32_t)h.note[1 + k];
+            std::nth_element(cand.begin(), cand.begin() + T, cand.end());
+            memcpy(h.idx, cand.data(), (size_t)T * 4);
+            ctx->host_flags |= TF_FLAG_TRANSFER_OVERFLOW;
+        }
+        job.per = SwapHost::part(m);
+        job.n.store(m, std::memory_order_release);
+        if (!helped && SwapHost::many(m)) {
+            helped = true;
+            h.pool.start(job);
+        }
+        for (uint32_t k = 0; k < m; ++k) ctx->host_has[h.idx[k]] = 0;
+        for (uint32_t k = 0, at = 0; at < m; ++k, at += job.per) {
+            const uint32_t cnt = std::min(job.per, m - at);
+            CopyPool::finish_part(job, k, cnt);
+            if (e == hipSuccess) e = launch_swap_merge(v, at, cnt, s);
+        }
     }
-    e = hipMemcpyAsync(v.xfer_idx, hidx, (size_t)m * 4, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(v.xfer_vox, hvox, (size_t)m * kBlockBytes, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = launch_swap_merge(v, m, s);
+    if (helped) h.pool.finish();
     return e;
 }
 
@@ -263,6 +276,9 @@ int tf_create(const tf_params *p, void *d_workspace, size_t bytes, void *h_store
     v.xfer_host = p->swap_transfer_blocks ? b + L.xfer_host : nullptr;
     v.xfer_pend = p->swap_transfer_blocks ? (int32_t *)(b + L.xfer_pend) : nullptr;
     v.swap_chunks = p->swap_transfer_blocks ? (uint32_t *)(b + L.swap_chunks) : nullptr;
+    v.note = nullptr;
+    v.hx_vox = nullptr;
+    v.hx_idx = nullptr;
     v.alist = nullptr;
     v.n_buckets = p->n_buckets;
     v.n_excess = p->n_excess;
@@ -274,7 +290,15 @@ int tf_create(const tf_params *p, void *d_workspace, size_t bytes, void *h_store
     v.voxel = p->voxel_size;
     v.mu = p->mu;
     v.max_w = p->max_w;
-    int st = tf_reset(ctx, stream);
+    int st = TF_OK;
+    if (p->swap_transfer_blocks) {
+        ctx->swap.reset(new (std::nothrow) SwapHost());
+        if (!ctx->swap)
+            st = TF_E_INVAL;
+        else if (ctx->swap->init(*p, h_transfer, tf_host_transfer_bytes(p), v) != hipSuccess)
+            st = TF_E_HIP;
+    }
+    if (st == TF_OK) st = tf_reset(ctx, stream);
     if (st != TF_OK) {
         delete ctx;
         return st;
@@ -477,32 +501,34 @@ int tf_swap_out(tf_ctx *ctx, tf_stream stream)
     hipStream_t s = (hipStream_t)stream;
     Vol &v = ctx->v;
     Timed t(ctx, TF_K_SWAP, s);
-    hipError_t e = launch_swap_select(v, s);
-    Ctrl c;
-    if (e == hipSuccess) e = hipMemcpyAsync(&c, v.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    SwapHost &h = *ctx->swap;
+    uint8_t *store = (uint8_t *)ctx->h_store;
+    hipError_t e = launch_swap_out(v, ++h.call, s);
     if (e != hipSuccess) return TF_E_HIP;
-    const uint32_t T = ctx->p.swap_transfer_blocks;
-    const uint32_t m = c.n_swap_cand < T ? c.n_swap_cand : T;
-    int32_t *hidx = (int32_t *)ctx->h_transfer;
-    uint8_t *hvox = (uint8_t *)ctx->h_transfer + (size_t)T * 4;
+    // blocks whose host copy never came back in are fused with it (the
+    // secondary integration, on the device, below); the others are copied
+    SwapOutCopy job;
+    job.note = h.note;
+    job.call = h.call;
+    job.cap = ctx->p.swap_transfer_blocks;
+    job.held = ctx->host_has.data();
+    job.store = store;
+    job.vox = h.vox;
+    const bool helped = SwapHost::many(h.last_out);
+    if (helped) h.pool.start(job);
+    e = hipStreamSynchronize(s);
+    job.synced.store(true, std::memory_order_release);
+    const uint32_t m = job.size();
+    h.last_out = m;
+    if (e == hipSuccess) CopyPool::finish_part(job, 0, m);
+    if (helped) h.pool.finish();
+    if (e != hipSuccess || job.lost.load()) return TF_E_HIP;
     if (m) {
-        e = launch_swap_gather(v, m, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(hidx, v.xfer_idx, (size_t)m * 4, hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(hvox, v.xfer_vox, (size_t)m * kBlockBytes, hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return TF_E_HIP;
-        uint8_t *store = (uint8_t *)ctx->h_store;
-        // blocks whose host copy never came back in are fused with it (the
-        // secondary integration, on the device, below); the others are copied
         std::vector<int32_t> &pend = ctx->cand;
         pend.clear();
         for (uint32_t k = 0; k < m; ++k) {
-            const int32_t idx = hidx[k];
-            if (ctx->host_has[idx])
-                pend.push_back((int32_t)k);
-            else
-                memcpy(store + (size_t)idx * kBlockBytes, hvox + (size_t)k * kBlockBytes, kBlockBytes);
+            const uint32_t idx = (uint32_t)h.note[1 + k];
+            if (ctx->host_has[idx]) pend.push_back((int32_t)k);
             ctx->host_has[idx] = 1;
         }
         const uint32_t np = (uint32_t)pend.size();
@@ -512,24 +538,23 @@ int tf_swap_out(tf_ctx *ctx, tf_stream stream)
             // and bring the results back
             std::vector<int32_t> entry(np);
             for (uint32_t j = 0; j < np; ++j) {
-                entry[j] = hidx[pend[j]];
-                memcpy(hvox + (size_t)j * kBlockBytes, store + (size_t)entry[j] * kBlockBytes, kBlockBytes);
-                hidx[j] = pend[j];
+                entry[j] = (int32_t)(uint32_t)h.note[1 + pend[j]];
+                memcpy(h.vox + (size_t)j * kBlockBytes, store + (size_t)entry[j] * kBlockBytes, kBlockBytes);
+                h.idx[j] = pend[j];
             }
-            e = hipMemcpyAsync(v.xfer_pend, hidx, (size_t)np * 4, hipMemcpyHostToDevice, s);
+            e = hipMemcpyAsync(v.xfer_pend, h.idx, (size_t)np * 4, hipMemcpyHostToDevice, s);
             if (e == hipSuccess)
-                e = hipMemcpyAsync(v.xfer_host, hvox, (size_t)np * kBlockBytes, hipMemcpyHostToDevice, s);
+                e = hipMemcpyAsync(v.xfer_host, h.vox, (size_t)np * kBlockBytes, hipMemcpyHostToDevice, s);
             if (e == hipSuccess) e = launch_swap_merge_out(v, np, s);
             if (e == hipSuccess)
-                e = hipMemcpyAsync(hvox, v.xfer_host, (size_t)np * kBlockBytes, hipMemcpyDeviceToHost, s);
+                e = hipMemcpyAsync(h.vox, v.xfer_host, (size_t)np * kBlockBytes, hipMemcpyDeviceToHost, s);
             if (e == hipSuccess) e = hipStreamSynchronize(s);
             if (e != hipSuccess) return TF_E_HIP;
             for (uint32_t j = 0; j < np; ++j)
-                memcpy(store + (size_t)entry[j] * kBlockBytes, hvox + (size_t)j * kBlockBytes, kBlockBytes);
+                memcpy(store + (size_t)entry[j] * kBlockBytes, h.vox + (size_t)j * kBlockBytes, kBlockBytes);
         }
     }
-    e = launch_swap_release(v, m, s);
-    return hip_status(e);
+    return TF_OK;
 }
 
 int tf_export_host_voxels(tf_ctx *ctx, const int32_t *h_entries, uint32_t n, int16_t *h_sdf, uint8_t *h_w,

@@ -2,10 +2,12 @@
 // API (tsdf_api.hip) and the batched submaps (tsdf_multi_api.hip).  Internal.
 #pragma once
 
+#include <memory>
 #include <vector>
 
 #include "tsdf.h"
 #include "tsdf_internal.h"
+#include "tsdf_swap.h"
 
 // ring of HIP event pairs per kernel class; a slot is harvested before reuse
 struct Profiler {
@@ -38,7 +40,8 @@ struct tf_ctx {
     int alloc_fmt;
     uint32_t host_flags;              // flags raised on the host (transfer overflow)
     std::vector<uint8_t> host_has;    // host mirror: the store holds data for the entry
-    std::vector<int32_t> cand;        // swap-in candidates of the current frame
+    std::vector<int32_t> cand;        // entries, or transfer slots, of the current swap
+    std::unique_ptr<tsdf::SwapHost> swap;   // swapping volumes only
 };
 
 namespace tsdf {

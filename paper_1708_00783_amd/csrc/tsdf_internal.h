@@ -106,6 +106,9 @@ struct Vol {
     uint8_t *xfer_host;             // swapping: host-store copies fused into swap-out blocks
     int32_t *xfer_pend;             // swapping: transfer-buffer slot of each such copy
     uint32_t *swap_chunks;          // swapping: per-chunk candidate counts, then offsets
+    unsigned long long *note;       // swapping: host memory: [0] candidates, then their entries
+    uint8_t *hx_vox;                // swapping: the host's transfer buffer: blocks ...
+    int32_t *hx_idx;                // ... and entry indices
     int4 *alist;                    // submap volumes: allocated blocks {x | y << 16, z, ptr, entry}
     uint32_t n_buckets, n_excess, n_entries, n_blocks;
     uint32_t reqset_mask, max_req;
@@ -147,10 +150,8 @@ hipError_t launch_raycast(const Vol &v, const Cam &c, bool all_blocks, float4 *p
 hipError_t launch_range_write(const Vol &v, const Cam &c, float *zmin, float *zmax, hipStream_t s);
 constexpr int kSwapChunk = 4096;        // entries per workgroup of the ordered swap-out selection
 hipError_t launch_swap_candidates(const Vol &v, hipStream_t s);
-hipError_t launch_swap_merge(const Vol &v, uint32_t n, hipStream_t s);
-hipError_t launch_swap_select(const Vol &v, hipStream_t s);
-hipError_t launch_swap_gather(const Vol &v, uint32_t n, hipStream_t s);
-hipError_t launch_swap_release(const Vol &v, uint32_t n, hipStream_t s);
+hipError_t launch_swap_merge(const Vol &v, uint32_t at, uint32_t n, hipStream_t s);
+hipError_t launch_swap_out(const Vol &v, uint32_t call, hipStream_t s);
 hipError_t launch_swap_merge_out(const Vol &v, uint32_t n, hipStream_t s);
 hipError_t launch_camera_depth(const float4 *pts, int n, const float *M, float *depth, hipStream_t s);
 hipError_t launch_export_voxels(const Vol &v, const int32_t *ids, uint32_t n, int16_t *sdf,

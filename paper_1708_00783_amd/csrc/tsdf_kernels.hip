@@ -1004,7 +1004,8 @@ __device__ __forceinline__ void merge_voxel(int &sa, int &wa, int sb, int wb, in
     wa = w;
 }
 
-// visible entries whose host store holds data: swap-in candidates
+// visible entries whose host store holds data: swap-in candidates, written
+// to the host's note; k_swap_note adds their number once all are there
 __global__ __launch_bounds__(256) void k_swap_candidates(Vol v)
 {
     const uint32_t n = v.ctrl->n_vis;
@@ -1012,33 +1013,64 @@ __global__ __launch_bounds__(256) void k_swap_candidates(Vol v)
         const int e = v.vlist[i];
         if (v.host_has[e]) {
             const uint32_t k = atomicAdd(&v.ctrl->n_swap_cand, 1u);
-            v.ret[k] = e;
+            v.note[1 + k] = (unsigned long long)e;
         }
     }
 }
 
-// fuse the transferred host blocks into their device blocks; one wave per block
-__global__ __launch_bounds__(256) void k_swap_merge(Vol v, uint32_t n)
+__global__ void k_swap_note(Vol v) { v.note[0] = v.ctrl->n_swap_cand; }
+
+// eight voxels of a block: 16-bit distances and 8-bit weights
+struct Voxels8 {
+    uint4 s;
+    uint2 w;
+};
+
+__device__ __forceinline__ Voxels8 load_voxels8(const uint8_t *block, uint32_t lane)
+{
+    return {reinterpret_cast<const uint4 *>(block)[lane], reinterpret_cast<const uint2 *>(block + 1024)[lane]};
+}
+
+__device__ __forceinline__ void store_voxels8(uint8_t *block, uint32_t lane, const Voxels8 &a)
+{
+    reinterpret_cast<uint4 *>(block)[lane] = a.s;
+    reinterpret_cast<uint2 *>(block + 1024)[lane] = a.w;
+}
+
+// secondary integration of eight voxels: b into a
+__device__ __forceinline__ void merge_voxels8(Voxels8 &a, const Voxels8 &b, int max_w)
+{
+    uint32_t as[4] = {a.s.x, a.s.y, a.s.z, a.s.w}, aw[2] = {a.w.x, a.w.y};
+    const uint32_t bs[4] = {b.s.x, b.s.y, b.s.z, b.s.w}, bw[2] = {b.w.x, b.w.y};
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int hs = 16 * (q & 1), hw = 8 * (q & 3);
+        int sa = (int16_t)(as[q >> 1] >> hs), wa = (int)((aw[q >> 2] >> hw) & 255u);
+        merge_voxel(sa, wa, (int16_t)(bs[q >> 1] >> hs), (int)((bw[q >> 2] >> hw) & 255u), max_w);
+        as[q >> 1] = (as[q >> 1] & ~(0xffffu << hs)) | ((uint32_t)(uint16_t)sa << hs);
+        aw[q >> 2] = (aw[q >> 2] & ~(0xffu << hw)) | (((uint32_t)wa & 255u) << hw);
+    }
+    a.s = make_uint4(as[0], as[1], as[2], as[3]);
+    a.w = make_uint2(aw[0], aw[1]);
+}
+
+// fuse blocks at .. at + n - 1 of the host's transfer buffer into their
+// device blocks, read over the link where they lie (each byte once, whole
+// lines: a copy to the device first would only add its launch and a pass);
+// one wave per block
+__global__ __launch_bounds__(256) void k_swap_merge(Vol v, uint32_t at, uint32_t n)
 {
     const uint32_t lane = lane_id();
     const uint32_t gwave = (blockIdx.x * 256u + threadIdx.x) / kWave;
     const uint32_t nwaves = gridDim.x * (256u / kWave);
-    if (blockIdx.x == 0 && threadIdx.x == 0) v.ctrl->n_swapped_in = n;
-    for (uint32_t k = gwave; k < n; k += nwaves) {
-        const int e = v.xfer_idx[k];
-        const int ptr = load_entry(v.entries, (uint32_t)e).w;
-        uint8_t *dst = v.voxels + (size_t)ptr * kBlockBytes;
-        const uint8_t *src = v.xfer_vox + (size_t)k * kBlockBytes;
-        const int16_t *ss = reinterpret_cast<const int16_t *>(src);
-        int16_t *ds = reinterpret_cast<int16_t *>(dst);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int j = (int)lane * 8 + q;
-            int sa = ds[j], wa = dst[1024 + j];
-            merge_voxel(sa, wa, ss[j], src[1024 + j], v.max_w);
-            ds[j] = (int16_t)sa;
-            dst[1024 + j] = (uint8_t)wa;
-        }
+    if (blockIdx.x == 0 && threadIdx.x == 0) v.ctrl->n_swapped_in = at + n;
+    for (uint32_t k = at + gwave; k < at + n; k += nwaves) {
+        const int e = v.hx_idx[k];
+        const Voxels8 b = load_voxels8(v.hx_vox + (size_t)k * kBlockBytes, lane);
+        uint8_t *dst = v.voxels + (size_t)load_entry(v.entries, (uint32_t)e).w * kBlockBytes;
+        Voxels8 a = load_voxels8(dst, lane);
+        merge_voxels8(a, b, v.max_w);
+        store_voxels8(dst, lane, a);
         if (lane == 0) v.host_has[e] = 0;
     }
 }
@@ -1055,25 +1087,20 @@ __global__ __launch_bounds__(256) void k_swap_merge_out(Vol v, uint32_t n)
     for (uint32_t k = gwave; k < n; k += nwaves) {
         uint8_t *a = v.xfer_host + (size_t)k * kBlockBytes;
         const uint8_t *b = v.xfer_vox + (size_t)v.xfer_pend[k] * kBlockBytes;
-        int16_t *as = reinterpret_cast<int16_t *>(a);
-        const int16_t *bs = reinterpret_cast<const int16_t *>(b);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int j = (int)lane * 8 + q;
-            int sa = as[j], wa = a[1024 + j];
-            merge_voxel(sa, wa, bs[j], b[1024 + j], v.max_w);
-            as[j] = (int16_t)sa;
-            a[1024 + j] = (uint8_t)wa;
-        }
+        Voxels8 x = load_voxels8(a, lane);
+        merge_voxels8(x, load_voxels8(b, lane), v.max_w);
+        store_voxels8(a, lane, x);
     }
 }
 
 // marks the visible entries (val = 1) or clears the marks (val = 0)
-__global__ __launch_bounds__(256) void k_mark_visible(Vol v, uint8_t val)
+__device__ __forceinline__ void mark_visible(const Vol &v, uint8_t val)
 {
     const uint32_t n = v.ctrl->n_vis;
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) v.vis[v.vlist[i]] = val;
 }
+
+__global__ __launch_bounds__(256) void k_mark_visible(Vol v) { mark_visible(v, (uint8_t)1); }
 
 // swap-out candidates: a device block and not visible.  Ordered selection of
 // the lowest entry indices: per-chunk counts, a scan, then in-order writes.
@@ -1104,19 +1131,35 @@ __device__ __forceinline__ uint32_t wg_exclusive_scan(uint32_t x, uint32_t *lds,
 }
 
 // a chunk is 16 slices of 256 consecutive entries, one entry per thread in a
-// slice (coalesced reads)
+// slice (coalesced reads, those of all slices in flight); the thread's
+// candidates, bit k = slice k
+__device__ __forceinline__ uint32_t swap_slices(const Vol &v, uint32_t e0)
+{
+    uint32_t c = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) c |= (swap_out_candidate(v, e0 + 256u * (uint32_t)k) ? 1u : 0u) << k;
+    return c;
+}
+
 __global__ __launch_bounds__(256) void k_swap_count(Vol v)
 {
     __shared__ uint32_t lds[4];
-    const uint32_t e0 = blockIdx.x * (uint32_t)kSwapChunk + threadIdx.x;
-    uint32_t cnt = 0;
-    for (int k = 0; k < 16; ++k) cnt += swap_out_candidate(v, e0 + 256u * (uint32_t)k) ? 1u : 0u;
+    const uint32_t c = swap_slices(v, blockIdx.x * (uint32_t)kSwapChunk + threadIdx.x);
     uint32_t total;
-    wg_exclusive_scan(cnt, lds, total);
+    wg_exclusive_scan((uint32_t)__popc(c), lds, total);
     if (threadIdx.x == 0) v.swap_chunks[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(256) void k_swap_scan(Vol v, uint32_t nchunks)
+// a word of the host's note, seen by the host before the kernel ends
+__device__ __forceinline__ void note_word(unsigned long long *p, uint32_t value, uint32_t call)
+{
+    __hip_atomic_store(p, (unsigned long long)value | ((unsigned long long)call << 32), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// offsets of the chunks, and the free stack's new height: the blocks that
+// leave (the gather puts them there)
+__global__ __launch_bounds__(256) void k_swap_scan(Vol v, uint32_t nchunks, uint32_t call)
 {
     __shared__ uint32_t lds[4];
     uint32_t carry = 0;
@@ -1128,57 +1171,82 @@ __global__ __launch_bounds__(256) void k_swap_scan(Vol v, uint32_t nchunks)
         if (i < nchunks) v.swap_chunks[i] = carry + ex;
         carry += total;
     }
-    if (threadIdx.x == 0) v.ctrl->n_swap_cand = carry;
-}
-
-// in entry order: slice by slice, a workgroup scan of the candidate flags
-__global__ __launch_bounds__(256) void k_swap_pick(Vol v)
-{
-    __shared__ uint32_t lds[4];
-    uint32_t base = v.swap_chunks[blockIdx.x];
-    if (base >= v.transfer_blocks) return;   // uniform: every pick of this chunk is past the capacity
-    const uint32_t e0 = blockIdx.x * (uint32_t)kSwapChunk + threadIdx.x;
-    for (int k = 0; k < 16; ++k) {
-        const uint32_t e = e0 + 256u * (uint32_t)k;
-        const bool c = swap_out_candidate(v, e);
-        uint32_t total;
-        const uint32_t pos = base + wg_exclusive_scan(c ? 1u : 0u, lds, total);
-        if (c && pos < v.transfer_blocks) v.xfer_idx[pos] = (int32_t)e;
-        base += total;
+    if (threadIdx.x == 0) {
+        const uint32_t n = carry < v.transfer_blocks ? carry : v.transfer_blocks;
+        v.ctrl->n_swap_cand = carry;
+        v.ctrl->free_blocks += (int32_t)n;
+        v.ctrl->n_swapped_out = n;
+        note_word(v.note, carry, call);
     }
 }
 
-// device blocks of the selected entries into the transfer buffer; one wave per block
-__global__ __launch_bounds__(256) void k_swap_gather(Vol v, uint32_t n)
+// in entry order: slice by slice, and within a slice thread by thread
+__global__ __launch_bounds__(256) void k_swap_pick(Vol v)
+{
+    __shared__ uint32_t cnt[16][4];   // candidates of a slice's waves
+    const uint32_t base = v.swap_chunks[blockIdx.x];
+    if (base >= v.transfer_blocks) return;   // uniform: every pick of this chunk is past the capacity
+    const uint32_t e0 = blockIdx.x * (uint32_t)kSwapChunk + threadIdx.x;
+    const uint32_t c = swap_slices(v, e0), lane = lane_id(), w = threadIdx.x / kWave;
+    uint32_t before[16];   // lanes of this wave before this one, per slice
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const unsigned long long m = __ballot((c >> k) & 1u);
+        before[k] = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        if (lane == 0) cnt[k][w] = (uint32_t)__popcll(m);
+    }
+    __syncthreads();
+    uint32_t pos = base;
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) {
+            const uint32_t p = pos + before[k];
+            if (u == w && ((c >> k) & 1u) && p < v.transfer_blocks) v.xfer_idx[p] = (int32_t)(e0 + 256u * (uint32_t)k);
+            pos += cnt[k][u];
+        }
+}
+
+// The selected entries' device blocks into the host's transfer buffer, over
+// the link from here, and into the device's for the secondary integration;
+// their blocks back onto the free stack, the entries marked swapped out, the
+// visibility marks cleared on the side.  One wave per block, which notes its
+// entry when the block is on the host: the host's copy into its store runs
+// while later blocks are on the link.  The block's stores go through the
+// caches (system scope), so that waiting for them is all the note needs.
+// Bound by the link (4.8 MB in 144 us, 33 GB/s); the launch is small, so that
+// blocks arrive one after the other: with a wave for each block they all
+// arrive at the end, and the host was 186 us behind instead of 109.
+__global__ __launch_bounds__(256) void k_swap_gather(Vol v, uint32_t call)
 {
     const uint32_t lane = lane_id();
     const uint32_t gwave = (blockIdx.x * 256u + threadIdx.x) / kWave;
     const uint32_t nwaves = gridDim.x * (256u / kWave);
+    const uint32_t n = v.ctrl->n_swapped_out;
+    const int32_t head = v.ctrl->free_blocks - (int32_t)n;
     for (uint32_t k = gwave; k < n; k += nwaves) {
-        const int ptr = load_entry(v.entries, (uint32_t)v.xfer_idx[k]).w;
-        const uint8_t *src = v.voxels + (size_t)ptr * kBlockBytes;
-        uint8_t *dst = v.xfer_vox + (size_t)k * kBlockBytes;
-        reinterpret_cast<uint4 *>(dst)[lane] = reinterpret_cast<const uint4 *>(src)[lane];
-        reinterpret_cast<uint2 *>(dst + 1024)[lane] = reinterpret_cast<const uint2 *>(src + 1024)[lane];
+        const uint32_t e = (uint32_t)v.xfer_idx[k];
+        const int ptr = load_entry(v.entries, e).w;
+        const unsigned long long *src = reinterpret_cast<const unsigned long long *>(v.voxels + (size_t)ptr * kBlockBytes);
+        unsigned long long *dev = reinterpret_cast<unsigned long long *>(v.xfer_vox + (size_t)k * kBlockBytes);
+        unsigned long long *host = reinterpret_cast<unsigned long long *>(v.hx_vox + (size_t)k * kBlockBytes);
+        unsigned long long x[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) x[q] = src[lane + 64u * q];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            __hip_atomic_store(host + lane + 64u * q, x[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            dev[lane + 64u * q] = x[q];
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0) {
+            note_word(v.note + 1 + k, e, call);
+            v.free_blocks[head + (int32_t)k] = ptr;
+            v.entries[e].ptr = kPtrSwapped;
+            v.host_has[e] = 1;
+        }
     }
-}
-
-// return the blocks to the free stack and mark the entries swapped out (one workgroup)
-__global__ __launch_bounds__(256) void k_swap_release(Vol v, uint32_t n)
-{
-    const int32_t head = v.ctrl->free_blocks;
-    __syncthreads();
-    for (uint32_t k = threadIdx.x; k < n; k += 256u) {
-        const int e = v.xfer_idx[k];
-        v.free_blocks[head + (int32_t)k] = v.entries[e].ptr;
-        v.entries[e].ptr = kPtrSwapped;
-        v.host_has[e] = 1;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        v.ctrl->free_blocks = head + (int32_t)n;
-        v.ctrl->n_swapped_out = n;
-    }
+    mark_visible(v, (uint8_t)0);
 }
 
 // ============================================================================
@@ -1332,41 +1400,31 @@ namespace tsdf {
 hipError_t launch_swap_candidates(const Vol &v, hipStream_t s)
 {
     hipLaunchKernelGGL(k_swap_candidates, dim3(256), dim3(256), 0, s, v);
+    hipLaunchKernelGGL(k_swap_note, dim3(1), dim3(1), 0, s, v);
     return hipGetLastError();
 }
 
-hipError_t launch_swap_merge(const Vol &v, uint32_t n, hipStream_t s)
+hipError_t launch_swap_merge(const Vol &v, uint32_t at, uint32_t n, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_swap_merge, dim3(cu_grid((size_t)n * 64, 256, 2048)), dim3(256), 0, s, v, n);
+    hipLaunchKernelGGL(k_swap_merge, dim3(cu_grid((size_t)n * 64, 256, 2048)), dim3(256), 0, s, v, at, n);
     return hipGetLastError();
 }
 
-hipError_t launch_swap_select(const Vol &v, hipStream_t s)
+hipError_t launch_swap_out(const Vol &v, uint32_t call, hipStream_t s)
 {
     const uint32_t nchunks = (v.n_entries + kSwapChunk - 1) / kSwapChunk;
-    hipLaunchKernelGGL(k_mark_visible, dim3(256), dim3(256), 0, s, v, (uint8_t)1);
+    hipLaunchKernelGGL(k_mark_visible, dim3(256), dim3(256), 0, s, v);
     hipLaunchKernelGGL(k_swap_count, dim3(nchunks), dim3(256), 0, s, v);
-    hipLaunchKernelGGL(k_swap_scan, dim3(1), dim3(256), 0, s, v, nchunks);
+    hipLaunchKernelGGL(k_swap_scan, dim3(1), dim3(256), 0, s, v, nchunks, call);
     hipLaunchKernelGGL(k_swap_pick, dim3(nchunks), dim3(256), 0, s, v);
-    hipLaunchKernelGGL(k_mark_visible, dim3(256), dim3(256), 0, s, v, (uint8_t)0);
-    return hipGetLastError();
-}
-
-hipError_t launch_swap_gather(const Vol &v, uint32_t n, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_swap_gather, dim3(cu_grid((size_t)n * 64, 256, 2048)), dim3(256), 0, s, v, n);
+    // 256 waves of 1.5 KB each cover the link's latency several times
+    hipLaunchKernelGGL(k_swap_gather, dim3(64), dim3(256), 0, s, v, call);
     return hipGetLastError();
 }
 
 hipError_t launch_swap_merge_out(const Vol &v, uint32_t n, hipStream_t s)
 {
     hipLaunchKernelGGL(k_swap_merge_out, dim3(cu_grid((size_t)n * 64, 256, 2048)), dim3(256), 0, s, v, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_swap_release(const Vol &v, uint32_t n, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_swap_release, dim3(1), dim3(256), 0, s, v, n);
     return hipGetLastError();
 }
 }  // namespace tsdf

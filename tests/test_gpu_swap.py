@@ -180,3 +180,56 @@ def test_swap_out_merges_pending_host_copies():
         n_lsb += int((dsdf > 0).sum())
     print(f"pending host copies merged at swap-out: {pending_at_swap}; blocks {len(a)}; "
           f"1-LSB SDF differences {n_lsb}", flush=True)
+
+
+@pytest.mark.parametrize("buffer", ["pageable", "odd"])
+def test_transfer_buffers_the_device_cannot_use_as_given(buffer):
+    """a pageable transfer buffer, and a pinned one four bytes off alignment,
+    swap as Volume's own does: several hundred blocks out, back in, and out
+    again onto their host copies"""
+    import ctypes
+    import torch
+    import paper_1708_00783_amd as T
+    from synth import configs
+    cap = 4096
+    d, p, K, _ = configs.c1_frames(8)
+    a = T.Volume(configs.C1_VOLUME, K.width, K.height, swap_transfer_blocks=cap)
+    L, par = T.lib(), a.params
+    ws = torch.empty(T.tf_workspace_bytes(par), dtype=torch.uint8, device="cuda")
+    store = np.zeros(int(L.tf_host_store_bytes(ctypes.byref(par))), np.uint8)
+    n = int(L.tf_host_transfer_bytes(ctypes.byref(par)))
+    if buffer == "pageable":
+        held = np.zeros(n, np.uint8)
+        xfer = held.ctypes.data
+    else:
+        held = torch.empty(n + 64, dtype=torch.uint8, pin_memory=True)
+        xfer = held.data_ptr() + 4
+    ctx = T.tf_create(par, ws.data_ptr(), ws.numel(), ctypes.c_void_p(store.ctypes.data), ctypes.c_void_p(xfer), None)
+    b = T.Volume.borrowed(ctx, par, (ws, store, held))
+    try:
+        out = inn = 0
+        for k in (0, 1, 0, 7, 0, 1):
+            for g in (a, b):
+                g.frame(to_device(d[k]), K, p[k])
+            sa, sb = a.stats(), b.stats()
+            assert sa["n_swapped_in"] == sb["n_swapped_in"]
+            inn += sa["n_swapped_in"]
+            for g in (a, b):
+                g.alloc_and_visible(to_device(np.zeros_like(d[k])), T.make_intrinsics(K), _away(p[k]))
+                g.swap_out()
+            sa, sb = a.stats(), b.stats()
+            assert sa["n_swapped_out"] == sb["n_swapped_out"]
+            out += sa["n_swapped_out"]
+            ra, rb = _state(vol_g=a), _state(vol_g=b)   # by position: excess slots differ
+            assert ra.keys() == rb.keys()
+            for q in ra:
+                assert all(np.array_equal(x, y) for x, y in zip(ra[q], rb[q]))
+        print(f"{buffer}: {out} blocks out, {inn} in", flush=True)
+        assert out > 6 * 128 and inn > 128
+    finally:
+        L.tf_destroy(ctx)
+
+
+def _away(P):
+    """the same camera turned around: it sees none of what it saw"""
+    return (np.diag([-1.0, 1.0, -1.0, 1.0]) @ np.asarray(P, np.float64)).astype(np.float32)
