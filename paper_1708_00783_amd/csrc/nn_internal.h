@@ -30,14 +30,27 @@ constexpr float kDepthScale = 4.0f;     // metres: input normalisation (d / 4 m)
 constexpr float kCorrScale = 0.05f;     // metres: unit of the head's depth correction
 constexpr int kWgradStep = 64;          // pixels per LDS staging round of the conv weight gradient
 constexpr int kWgradChunkPix = 512;     // target pixels per chunk of a conv weight-gradient reduction
-
-constexpr int kWgradFoldChunkPix = 2048; // the same for the folded decoder layers (16 taps per chunk)
+constexpr int kWgradRows = 4, kWgradCols = 32;   // block of pixels the decoder's weight gradient stages
 
 // pixel chunks of a conv weight-gradient reduction over P pixels
-inline int wgrad_chunks(long P, int pix_per_chunk = kWgradChunkPix)
+inline int wgrad_chunks(long P)
 {
-    const long c = P / pix_per_chunk;
+    const long c = P / kWgradChunkPix;
     return (int)(c < 64 ? 64 : (c > 512 ? 512 : c));
+}
+
+// the decoder layers: blocks of the source grid, and their chunks.  A chunk
+// is the work of 4 parities x cinp / 64 workgroups; at least 256 of these,
+// and at most 8 blocks a chunk up to 512 chunks (the partial sums, one set a
+// chunk, cost as much as the products do where chunks are smaller)
+inline long wgrad_blocks(long N, long H, long W)
+{
+    return N * ((H + kWgradRows - 1) / kWgradRows) * ((W + kWgradCols - 1) / kWgradCols);
+}
+inline int wgrad_up_chunks(long blocks, int cinp)
+{
+    const long least = 64 * 64 / cinp, c = blocks / 8;
+    return (int)(c < least ? least : (c > 512 ? 512 : c));
 }
 
 constexpr int kHeadChunks = 1024;       // pixel chunks of the head's weight-gradient reduction

@@ -16,6 +16,8 @@
 //   k_conv_wgrad        M = cout, N = cin of one tap, K = pixels of one chunk:
 //                       both operands are staged transposed in LDS; per-chunk
 //                       partial sums are reduced in a fixed order
+//   k_conv_wgrad_up     decoder: the same for the four offsets of a parity,
+//                       staged as they lie and transposed by the LDS reads
 // Bias, skip add / skip gradient and relu (mask) are fused into every
 // epilogue, which is staged in LDS and written as 16-byte pixel vectors.
 // The 32->1 head, the loss, input packing and Adam are plain VALU kernels.
@@ -685,14 +687,13 @@ __global__ __launch_bounds__(256) void k_conv_bwd_data_s2(const uint16_t *gpre, 
 // partial[chunk][co][tap][ci] = sum_p gpre[p][co] * in_tap(p)[ci]; the bias
 // gradient partial[chunk][co] comes from the tap-0 workgroups
 // ============================================================================
-template <int CINP, int COUT, int STRIDE, bool UP, bool FOLD>
+template <int CINP, int COUT, int STRIDE>
 __global__ __launch_bounds__(256) void k_conv_wgrad(const uint16_t *gpre, const uint16_t *in, int Hs, int Ws, int N,
                                                     int Ho, int Wo, float *partial, float *partial_b, int chunk_pix,
                                                     int nchunk)
 {
-    static_assert(!FOLD || (UP && STRIDE == 1), "the parity fold is for upsampled stride-1 layers");
     constexpr int CT = CINP < 16 ? 16 : CINP;
-    constexpr int NTAP = FOLD ? 16 : 9;   // taps, or (output parity, source offset) pairs
+    constexpr int NTAP = 9;
     constexpr int MT = COUT / 16, NTT = CT / 16, TILES = MT * NTT, TPW = (TILES + 3) / 4;
     constexpr int KS = kWgradStep;   // pixels staged per round (4 MFMA k-steps)
     constexpr int LD = KS + 8;       // LDS row pitch in bf16 elements (16-byte aligned rows)
@@ -712,15 +713,10 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(const uint16_t *gpre, const 
     const int chunk = (id & 7) + 8 * (slot / NTAP), tap = slot - (slot / NTAP) * NTAP;
     if (chunk >= nchunk) return;
     const int ky = tap / 3, kx = tap - (tap / 3) * 3;
-    // FOLD: tap = (py * 2 + px) * 4 + a * 2 + b; the pixels are the source
-    // grid (m, n), read at output (2m + py, 2n + px) and source
-    // (m + py - 1 + a, n + px - 1 + b)
-    const int fpy = tap >> 3, fpx = (tap >> 2) & 1, fa = (tap >> 1) & 1, fb = tap & 1;
-    const long P = FOLD ? (long)N * Hs * Ws : (long)N * Ho * Wo;
+    const long P = (long)N * Ho * Wo;
     const long c0 = (long)chunk * chunk_pix;
     const long c1 = c0 + chunk_pix < P ? c0 + chunk_pix : P;
     const int w = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63, r = lane & 15, gq = lane >> 4;
-    const int Hc = UP ? 2 * Hs : Hs, Wc = UP ? 2 * Ws : Ws;
     f32x4 acc[TPW];
 #pragma unroll
     for (int j = 0; j < TPW; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -733,16 +729,7 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(const uint16_t *gpre, const 
             const int pi = v / (COUT / 8), cv = (v - pi * (COUT / 8)) * 8;
             const long p = pb + pi;
             gv[q] = u32x4{0u, 0u, 0u, 0u};
-            if (v < GV && p < c1) {
-                size_t po = (size_t)p;
-                if (FOLD) {
-                    const int n = (int)(p / ((long)Hs * Ws));
-                    const int rem = (int)(p - (long)n * Hs * Ws);
-                    const int m = rem / Ws, nn = rem - (rem / Ws) * Ws;
-                    po = ((size_t)n * Ho + 2 * m + fpy) * Wo + 2 * nn + fpx;
-                }
-                gv[q] = ld16(gpre + po * COUT + cv);
-            }
+            if (v < GV && p < c1) gv[q] = ld16(gpre + (size_t)p * COUT + cv);
         }
 #pragma unroll
         for (int q = 0; q < (IV + 255) / 256; ++q) {
@@ -750,22 +737,12 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(const uint16_t *gpre, const 
             const int pi = v / (CT / 8), cv = (v - pi * (CT / 8)) * 8;
             const long p = pb + pi;
             iv[q] = u32x4{0u, 0u, 0u, 0u};
-            if (FOLD && v < IV && p < c1 && cv < CINP) {
-                const int n = (int)(p / ((long)Hs * Ws));
-                const int rem = (int)(p - (long)n * Hs * Ws);
-                const int m = rem / Ws, nn = rem - (rem / Ws) * Ws;
-                const int sy = m + fpy - 1 + fa, sx = nn + fpx - 1 + fb;
-                if (sy >= 0 && sy < Hs && sx >= 0 && sx < Ws)
-                    iv[q] = ld16(in + (((size_t)n * Hs + sy) * Ws + sx) * CINP + cv);
-            } else if (!FOLD && v < IV && p < c1 && cv < CINP) {
+            if (v < IV && p < c1 && cv < CINP) {
                 const int n = (int)(p / ((long)Ho * Wo));
                 const int rem = (int)(p - (long)n * Ho * Wo);
                 const int oy = rem / Wo, ox = rem - (rem / Wo) * Wo;
                 const int iy = STRIDE * oy + ky - 1, ix = STRIDE * ox + kx - 1;
-                if (iy >= 0 && iy < Hc && ix >= 0 && ix < Wc) {
-                    const int sy = UP ? (iy >> 1) : iy, sx = UP ? (ix >> 1) : ix;
-                    iv[q] = ld16(in + (((size_t)n * Hs + sy) * Ws + sx) * CINP + cv);
-                }
+                if (iy >= 0 && iy < Hs && ix >= 0 && ix < Ws) iv[q] = ld16(in + (((size_t)n * Hs + iy) * Ws + ix) * CINP + cv);
             }
         }
 #pragma unroll
@@ -785,7 +762,7 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(const uint16_t *gpre, const 
                 for (int e = 0; e < 8; ++e) iT[cv + e][pi ^ swz(cv + e)] = (uint16_t)(iv[q][e >> 1] >> (16 * (e & 1)));
         }
         __syncthreads();
-        if ((FOLD ? (tap & 3) : tap) == 0 && (int)threadIdx.x < COUT)
+        if (tap == 0 && (int)threadIdx.x < COUT)
             for (int k = 0; k < KS; ++k) bpart += bf2f(gT[threadIdx.x][k ^ swz((int)threadIdx.x)]);
 #pragma unroll
         for (int kk = 0; kk < KS; kk += 32)
@@ -814,10 +791,131 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(const uint16_t *gpre, const 
             partial[(((size_t)chunk * COUT + co) * NTAP + tap) * CINP + ci] = acc[j][i];
         }
     }
-    // bias partials: one per chunk, or one per chunk and output parity (FOLD)
-    if (FOLD && (tap & 3) == 0 && (int)threadIdx.x < COUT)
-        partial_b[((size_t)chunk * 4 + (tap >> 2)) * COUT + threadIdx.x] = bpart;
-    if (!FOLD && tap == 0 && (int)threadIdx.x < COUT) partial_b[(size_t)chunk * COUT + threadIdx.x] = bpart;
+    if (tap == 0 && (int)threadIdx.x < COUT) partial_b[(size_t)chunk * COUT + threadIdx.x] = bpart;
+}
+
+// MFMA operands along pixels from a tile that is kept pixel by pixel, as it
+// lies in memory: ds_read_tr16_b64 gives lane i of each 16 column i of four
+// rows, whose 8-byte pieces the lanes address (lane i: row i / 4, columns
+// 4 (i % 4) .. + 3).  Two reads make the operand: channel r of pixels gq * 8 ..
+// + 7, `pitch` bytes apart from `base`.  The pitch is an odd number of 32
+// bytes, so the four rows of a read lie on different banks.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bf16x8 pixel_operand(const unsigned char *base, int pitch, int lane)
+{
+    const int i = lane & 15, gq = lane >> 4;
+    const unsigned char *p = base + (gq * 8 + (i >> 2)) * pitch + (i & 3) * 8;
+    typedef __attribute__((address_space(3))) s16x4 *lds_s16x4;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(p + 4 * pitch));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// Weight gradient of an upsampled layer on its parity-folded taps:
+// partial[chunk][co][tap][ci], tap = (py * 2 + px) * 4 + a * 2 + b, over source
+// pixels (m, n), the gradient at (2m + py, 2n + px) times the source at
+// (m + py - 1 + a, n + px - 1 + b).
+//
+// A workgroup takes one chunk (a run of blocks of 4 rows x 32 columns), one
+// output parity and 64 input channels; wave (a, b) takes that offset.  Of a
+// block it stages 4 x 32 gradient and 5 x 33 source pixels, which the four
+// offsets share, as they lie in memory, and the transposing LDS reads turn them
+// into operands along the pixels; the next block's loads are in flight
+// meanwhile.  Bound by those loads' latency.  Tap by tap, with 2-byte
+// transposed writes to LDS, d1 / d2 / d3 at 8 x 256 x 256 took 84.5, 33.8 and
+// 24.2 us; now 25.3, 17.8 and 12.6.  The bias gradient is one more product, with ones.
+template <int CIN, int COUT>
+__global__ __launch_bounds__(256) void k_conv_wgrad_up(const uint16_t *gpre, const uint16_t *in, int Hs, int Ws, int N,
+                                                       float *partial, float *partial_b, int per, int nchunk)
+{
+    constexpr int R = kWgradRows, C = kWgradCols, MT = COUT / 16, NT = 4, NG = CIN / 64;
+    constexpr int GP = COUT * 2 + 32, IP = 64 * 2 + 32;   // bytes per pixel in LDS
+    constexpr int GV = R * C * (COUT / 8), IV = (R + 1) * (C + 1) * 8;   // 16-byte vectors of a block
+    constexpr int GQ = (GV + 255) / 256, IQ = (IV + 255) / 256;
+    __shared__ __attribute__((aligned(16))) unsigned char gt[R * C * GP];
+    __shared__ __attribute__((aligned(16))) unsigned char it[(R + 1) * (C + 1) * IP];
+    // the parities and channel groups of a chunk get linear indices of one
+    // residue mod 8: one XCD, whose L2 they share the chunk's pixels in
+    const int id = (int)blockIdx.x, slot = id >> 3;
+    const int chunk = (id & 7) + 8 * (slot / (4 * NG)), sub = slot % (4 * NG);
+    if (chunk >= nchunk) return;
+    const int par = sub & 3, py = par >> 1, px = par & 1, cg = (sub >> 2) * 64;
+    const int w = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63, r = lane & 15, gq = lane >> 4;
+    const int bx = (Ws + C - 1) / C, by = (Hs + R - 1) / R;
+    const long nb = (long)N * by * bx, b0 = (long)chunk * per, b1 = b0 + per < nb ? b0 + per : nb;
+    u32x4 gv[GQ], iv[IQ];
+    auto load = [&](long blk) {
+        const int xb = (int)(blk % bx);
+        const long yb = blk / bx;
+        const int n = (int)(yb / by), m0 = (int)(yb - (long)n * by) * R, c0 = xb * C;
+#pragma unroll
+        for (int q = 0; q < GQ; ++q) {
+            const int v = (int)threadIdx.x + 256 * q, pix = v / (COUT / 8), cv = (v % (COUT / 8)) * 8;
+            const int m = m0 + pix / C, c = c0 + pix % C;
+            gv[q] = u32x4{0u, 0u, 0u, 0u};
+            if (v < GV && m < Hs && c < Ws)
+                gv[q] = ld16(gpre + (((size_t)n * 2 * Hs + 2 * m + py) * (2 * (size_t)Ws) + 2 * c + px) * COUT + cv);
+        }
+#pragma unroll
+        for (int q = 0; q < IQ; ++q) {
+            const int v = (int)threadIdx.x + 256 * q, pix = v / 8, cv = (v % 8) * 8;
+            const int sy = m0 + py - 1 + pix / (C + 1), sx = c0 + px - 1 + pix % (C + 1);
+            iv[q] = u32x4{0u, 0u, 0u, 0u};
+            if (v < IV && sy >= 0 && sy < Hs && sx >= 0 && sx < Ws)
+                iv[q] = ld16(in + (((size_t)n * Hs + sy) * Ws + sx) * CIN + cg + cv);
+        }
+    };
+    f32x4 acc[MT][NT], accb[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        accb[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const u32x4 one2 = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+    const bf16x8 ones = as_bf(one2);
+    const unsigned char *ip = it + ((w >> 1) * (C + 1) + (w & 1)) * IP;
+    if (b0 < b1) load(b0);
+    for (long blk = b0; blk < b1; ++blk) {
+#pragma unroll
+        for (int q = 0; q < GQ; ++q) {
+            const int v = (int)threadIdx.x + 256 * q;
+            if (v < GV) *reinterpret_cast<u32x4 *>(gt + (v / (COUT / 8)) * GP + (v % (COUT / 8)) * 16) = gv[q];
+        }
+#pragma unroll
+        for (int q = 0; q < IQ; ++q) {
+            const int v = (int)threadIdx.x + 256 * q;
+            if (v < IV) *reinterpret_cast<u32x4 *>(it + (v / 8) * IP + (v % 8) * 16) = iv[q];
+        }
+        __syncthreads();
+        if (blk + 1 < b1) load(blk + 1);
+#pragma unroll
+        for (int y = 0; y < R; ++y) {
+            bf16x8 a[MT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[i] = pixel_operand(gt + y * C * GP + i * 32, GP, lane);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const bf16x8 b = pixel_operand(ip + y * (C + 1) * IP + j * 32, IP, lane);
+#pragma unroll
+                for (int i = 0; i < MT; ++i) acc[i][j] = mfma(a[i], b, acc[i][j]);
+            }
+            if (w == 0 && cg == 0)
+#pragma unroll
+                for (int i = 0; i < MT; ++i) accb[i] = mfma(a[i], ones, accb[i]);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int co = i * 16 + gq * 4 + e;
+            float *o = partial + (((size_t)chunk * COUT + co) * 16 + par * 4 + w) * CIN + cg + r;
+#pragma unroll
+            for (int j = 0; j < NT; ++j) o[j * 16] = acc[i][j][e];
+            if (w == 0 && cg == 0 && r == 0) partial_b[((size_t)chunk * 4 + par) * COUT + co] = accb[i][e];
+        }
 }
 
 // weight gradient of the first layer (8 padded input channels, stride 1):
@@ -924,13 +1022,17 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_c8(const uint16_t *gpre, con
 
 // fixed-order sum of the chunk partials into the fp32 gradient vector: a
 // workgroup takes 64 consecutive partial entries j (weights with the padded
-// input channels, then the biases); wave sl sums chunks sl, sl + 4, ... with
-// eight loads in flight per lane, and the four wave sums are added in LDS
+// input channels, then the biases); wave sl sums chunks sl, sl + 16, ... with
+// eight or sixteen loads in flight per lane, and the wave sums are added in
+// LDS.  Bound by the latency of those loads, so a workgroup has 16 waves: the
+// folded layers at 8 x 256 x 256 9.6 us (with 4 waves, and half the chunks, 12.7).
+constexpr int kReduceWaves = 16;
 template <bool FOLD>
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float *partial, const float *partial_b, int chunks,
+__global__ __launch_bounds__(64 * kReduceWaves) void k_wgrad_reduce(const float *partial, const float *partial_b, int chunks,
                                                       int cout, int cin, int cinp, float *dw, float *db)
 {
-    __shared__ float red[4][64];
+    constexpr int S = kReduceWaves;
+    __shared__ float red[S][64];
     const int nw = cout * 9 * cinp;
     const int j = (int)blockIdx.x * 64 + ((int)threadIdx.x & 63), sl = (int)threadIdx.x >> 6;
     const bool isw = j < nw, valid = j < nw + cout;
@@ -942,10 +1044,12 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(const float *partial, cons
 #pragma unroll
         for (int k = 0; k < 8; ++k) a[k] = 0.0f;
         int c = sl;
-        for (; c + 28 < chunks; c += 32)
+        for (; c + 7 * S < chunks; c += 8 * S)
 #pragma unroll
-            for (int k = 0; k < 8; ++k) a[k] += src[(size_t)(c + 4 * k) * stride];
-        for (; c < chunks; c += 4) a[0] += src[(size_t)c * stride];
+            for (int k = 0; k < 8; ++k) a[k] += src[(size_t)(c + S * k) * stride];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (c + S * k < chunks) a[k] += src[(size_t)(c + S * k) * stride];
         s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
     } else if (valid) {
         // FOLD: partial[chunk][co][16][cinp] over (output parity, source
@@ -974,23 +1078,27 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(const float *partial, cons
         }
         float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         int c = sl;
-        for (; c + 12 < chunks; c += 16)
+        for (; c + 3 * S < chunks; c += 4 * S)
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const float *q = src + (size_t)(c + 4 * k) * stride;
+                const float *q = src + (size_t)(c + S * k) * stride;
                 a[k] += (q[off[0]] + q[off[1]]) + (q[off[2]] + q[off[3]]);
             }
-        for (; c < chunks; c += 4) {
-            const float *q = src + (size_t)c * stride;
-            a[0] += (q[off[0]] + q[off[1]]) + (q[off[2]] + q[off[3]]);
-        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (c + S * k < chunks) {
+                const float *q = src + (size_t)(c + S * k) * stride;
+                a[k] += (q[off[0]] + q[off[1]]) + (q[off[2]] + q[off[3]]);
+            }
         s = (a[0] + a[1]) + (a[2] + a[3]);
     }
     red[sl][threadIdx.x & 63] = s;
     __syncthreads();
     if (sl != 0 || !valid) return;
     const int l = (int)threadIdx.x;
-    const float t = (red[0][l] + red[1][l]) + (red[2][l] + red[3][l]);
+    float t = 0.0f;
+#pragma unroll
+    for (int k = 0; k < S; k += 4) t += (red[k][l] + red[k + 1][l]) + (red[k + 2][l] + red[k + 3][l]);
     if (isw) {
         const int co = j / (9 * cinp), rem = j - co * 9 * cinp, tap = rem / cinp, ci = rem - (rem / cinp) * cinp;
         if (ci < cin) dw[(co * 9 + tap) * cin + ci] = t;
@@ -1406,41 +1514,42 @@ hipError_t launch_conv_bwd_data(int layer, const uint16_t *gpre, int Ho, int Wo,
 hipError_t launch_conv_wgrad(int layer, const uint16_t *gpre, const uint16_t *in, int Hs, int Ws, int N, int Ho,
                              int Wo, float *partial, int chunks, float *dw, float *db, hipStream_t s)
 {
-    // the decoder layers (4-6) run folded: 16 (parity, offset) taps over the source grid
+    // the decoder layers (4-6) run folded: 16 (parity, offset) taps over the
+    // source grid, their chunks counted in blocks of pixels
     const bool fold = layer >= 4;
-    const int ntap = fold ? 16 : 9;
-    const long P = fold ? (long)N * Hs * Ws : (long)N * Ho * Wo;
+    const long P = fold ? wgrad_blocks(N, Hs, Ws) : (long)N * Ho * Wo;
     if (fold && (Ho != 2 * Hs || Wo != 2 * Ws)) return hipErrorInvalidValue;
     int per = (int)((P + chunks - 1) / chunks);
-    per = ((per + kWgradStep - 1) / kWgradStep) * kWgradStep;
+    if (!fold) per = ((per + kWgradStep - 1) / kWgradStep) * kWgradStep;
     const int nc = (int)((P + per - 1) / per);
     float *pb = partial;   // bias partials after the weight partials
-    const dim3 gr(ntap * ((nc + 7) / 8) * 8), b(256);   // (tap, chunk) pairs, chunks padded to a multiple of 8
+    const int nc8 = (nc + 7) / 8 * 8;
+    const dim3 gr(9 * nc8), b(256);   // (tap, chunk) pairs, chunks padded to a multiple of 8
     int cout = 0, cin = 0, cinp = 0;
     switch (layer) {
     case 0: cout = 32; cin = 3; cinp = 8; pb += (size_t)nc * 32 * 9 * 8;   // all taps per workgroup
         hipLaunchKernelGGL((k_conv_wgrad_c8<32>), dim3(nc), b, 0, s, gpre, in, Ho, Wo, N, partial, pb, per, nc); break;
     case 1: cout = 64; cin = cinp = 32; pb += (size_t)nc * 64 * 9 * 32;
-        hipLaunchKernelGGL((k_conv_wgrad<32, 64, 2, false, false>), gr, b, 0, s, gpre, in, Hs, Ws, N, Ho, Wo, partial, pb, per, nc); break;
+        hipLaunchKernelGGL((k_conv_wgrad<32, 64, 2>), gr, b, 0, s, gpre, in, Hs, Ws, N, Ho, Wo, partial, pb, per, nc); break;
     case 2: cout = 64; cin = cinp = 64; pb += (size_t)nc * 64 * 9 * 64;
-        hipLaunchKernelGGL((k_conv_wgrad<64, 64, 2, false, false>), gr, b, 0, s, gpre, in, Hs, Ws, N, Ho, Wo, partial, pb, per, nc); break;
+        hipLaunchKernelGGL((k_conv_wgrad<64, 64, 2>), gr, b, 0, s, gpre, in, Hs, Ws, N, Ho, Wo, partial, pb, per, nc); break;
     case 3: cout = 128; cin = cinp = 64; pb += (size_t)nc * 128 * 9 * 64;
-        hipLaunchKernelGGL((k_conv_wgrad<64, 128, 2, false, false>), gr, b, 0, s, gpre, in, Hs, Ws, N, Ho, Wo, partial, pb, per, nc); break;
+        hipLaunchKernelGGL((k_conv_wgrad<64, 128, 2>), gr, b, 0, s, gpre, in, Hs, Ws, N, Ho, Wo, partial, pb, per, nc); break;
     case 4: cout = 64; cin = cinp = 128; pb += (size_t)nc * 64 * 16 * 128;
-        hipLaunchKernelGGL((k_conv_wgrad<128, 64, 1, true, true>), gr, b, 0, s, gpre, in, Hs, Ws, N, Ho, Wo, partial, pb, per, nc); break;
+        hipLaunchKernelGGL((k_conv_wgrad_up<128, 64>), dim3(8 * nc8), b, 0, s, gpre, in, Hs, Ws, N, partial, pb, per, nc); break;
     case 5: cout = 64; cin = cinp = 64; pb += (size_t)nc * 64 * 16 * 64;
-        hipLaunchKernelGGL((k_conv_wgrad<64, 64, 1, true, true>), gr, b, 0, s, gpre, in, Hs, Ws, N, Ho, Wo, partial, pb, per, nc); break;
+        hipLaunchKernelGGL((k_conv_wgrad_up<64, 64>), dim3(4 * nc8), b, 0, s, gpre, in, Hs, Ws, N, partial, pb, per, nc); break;
     case 6: cout = 32; cin = cinp = 64; pb += (size_t)nc * 32 * 16 * 64;
-        hipLaunchKernelGGL((k_conv_wgrad<64, 32, 1, true, true>), gr, b, 0, s, gpre, in, Hs, Ws, N, Ho, Wo, partial, pb, per, nc); break;
+        hipLaunchKernelGGL((k_conv_wgrad_up<64, 32>), dim3(4 * nc8), b, 0, s, gpre, in, Hs, Ws, N, partial, pb, per, nc); break;
     default: return hipErrorInvalidValue;
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (fold)
-        hipLaunchKernelGGL(k_wgrad_reduce<true>, grid1((long)cout * 9 * cinp + cout, 64), dim3(256), 0, s, partial, pb,
+        hipLaunchKernelGGL(k_wgrad_reduce<true>, grid1((long)cout * 9 * cinp + cout, 64), dim3(64 * kReduceWaves), 0, s, partial, pb,
                            nc, cout, cin, cinp, dw, db);
     else
-        hipLaunchKernelGGL(k_wgrad_reduce<false>, grid1((long)cout * 9 * cinp + cout, 64), dim3(256), 0, s, partial, pb,
+        hipLaunchKernelGGL(k_wgrad_reduce<false>, grid1((long)cout * 9 * cinp + cout, 64), dim3(64 * kReduceWaves), 0, s, partial, pb,
                            nc, cout, cin, cinp, dw, db);
     return hipGetLastError();
 }

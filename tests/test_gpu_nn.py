@@ -158,20 +158,29 @@ def test_backward_layers_match_oracle(shape):
 
 
 @pytest.mark.parametrize("shape", [(1, 8, 8), (3, 24, 136), (1, 136, 72)])
-def test_backward_data_at_tile_edges(shape):
-    """Gradients at the conv inputs where the backward tiles end: the smallest
-    image (sources of 1 x 1, less than a tile in both directions), and widths
-    and heights one past 1, 2 and 4 tiles of 16 columns or of 2 or 4 rows, with
-    3 images (the tiles are not a multiple of the 8 they are dealt in)."""
+def test_tiles_and_blocks_at_their_edges(shape):
+    """Activations, gradients at the conv inputs and weight gradients where the
+    kernels' tiles and blocks end: the smallest image (sources of 1 x 1, less
+    than a tile in both directions), and widths and heights one past 1, 2 and 4
+    tiles of 16 columns, of blocks of 32 columns and of 2 or 4 rows, with 3
+    images (the tiles are not a multiple of the 8 they are dealt in).  The
+    bounds are those of the tests of whole layers."""
     import torch
     T, net, P, depth, target, out = _setup(11, shape)
     net.backward(torch.from_numpy(target).cuda())
+    grads = T.nn_unflatten(net.tensor("grads").cpu().numpy().reshape(-1))
     skip_to = {"e1": "d1", "e2": "d2", "e3": "d3"}
-    for name, (src, stride, up, _) in reversed(list(LAYER_IO.items())):
+    for name, (src, stride, up, skip) in reversed(list(LAYER_IO.items())):
+        a = _bf(net, src)
+        if name == "e1":
+            a = a[..., :3]
+        y = D.conv(D.up2(a) if up else a, _rb(P[name + ".w"]), P[name + ".b"], stride)
+        _close(_bf(net, name), np.maximum(y + _bf(net, skip) if skip else y, 0), f"{shape} {name}")
+        dx, dw, db = D.conv_backward(D.up2(a) if up else a, _rb(P[name + ".w"]), _bf(net, "grad_" + name), stride)
+        assert np.linalg.norm(grads[name + ".w"] - dw) < 1e-3 * np.linalg.norm(dw), (shape, name)
+        assert np.allclose(grads[name + ".b"], db, rtol=1e-3, atol=1e-6 * max(1e-9, np.abs(db).max())), (shape, name)
         if name == "e1":
             continue
-        a = _bf(net, src)
-        dx = D.conv_backward(D.up2(a) if up else a, _rb(P[name + ".w"]), _bf(net, "grad_" + name), stride)[0]
         if up:
             dx = D.up2_backward(dx)
         if src in skip_to:
