@@ -98,9 +98,8 @@ bool nlayout(const Net &net, uint32_t B, uint32_t H, uint32_t W, int training, N
         for (int l = 0; l < kLayers - 1; ++l) {
             // the decoder layers reduce 16 (parity, offset) taps over the source grid, 4 bias partials
             const LayerDesc &Ll = net.L[l];
-            const long h = (long)(H / Ll.scale), w = (long)(W / Ll.scale);
-            const int chunks = Ll.up ? wgrad_up_chunks(wgrad_blocks((long)B, h / 2, w / 2), Ll.cinp)
-                                     : wgrad_chunks((long)B * h * w);
+            const int chunks = wgrad_layer_chunks(l, Ll.up, Ll.cinp, Ll.cout, (long)B, (long)(H / Ll.scale),
+                                                  (long)(W / Ll.scale));
             const size_t e = (size_t)chunks *
                              ((size_t)Ll.cout * (Ll.up ? 16 : 9) * Ll.cinp + (Ll.up ? 4 : 1) * Ll.cout);
             if (e > mx) mx = e;
@@ -278,7 +277,7 @@ int tf_nn_backward(tf_nn *nn, const float *d_target, float *d_loss, tf_stream st
         const int Hs = H / ss, Ws = W / ss, Ho = H / L.scale, Wo = W / L.scale;
         uint16_t *gpre = nn->grad[l + 1];
         e = launch_conv_wgrad(l, gpre, nn->act[L.src], Hs, Ws, N, Ho, Wo, nn->partial,
-                              L.up ? wgrad_up_chunks(wgrad_blocks(N, Hs, Ws), L.cinp) : wgrad_chunks((long)N * Ho * Wo),
+                              wgrad_layer_chunks(l, L.up, L.cinp, L.cout, N, Ho, Wo),
                               nn->grads + L.w_off, nn->grads + L.b_off, s);
         if (e == hipSuccess && l > 0)
             e = launch_conv_bwd_data(l, gpre, Ho, Wo, nn->t + L.t_off,

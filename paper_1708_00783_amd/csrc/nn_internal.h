@@ -30,27 +30,35 @@ constexpr float kDepthScale = 4.0f;     // metres: input normalisation (d / 4 m)
 constexpr float kCorrScale = 0.05f;     // metres: unit of the head's depth correction
 constexpr int kWgradStep = 64;          // pixels per LDS staging round of the conv weight gradient
 constexpr int kWgradChunkPix = 512;     // target pixels per chunk of a conv weight-gradient reduction
-constexpr int kWgradRows = 4, kWgradCols = 32;   // block of pixels the decoder's weight gradient stages
+constexpr int kWgradRows = 4, kWgradCols = 32;   // block of pixels the weight gradients stage
 
-// pixel chunks of a conv weight-gradient reduction over P pixels
+// pixel chunks of the first layer's weight-gradient reduction over P pixels
 inline int wgrad_chunks(long P)
 {
     const long c = P / kWgradChunkPix;
     return (int)(c < 64 ? 64 : (c > 512 ? 512 : c));
 }
 
-// the decoder layers: blocks of the source grid, and their chunks.  A chunk
-// is the work of 4 parities x cinp / 64 workgroups; at least 256 of these,
-// and at most 8 blocks a chunk up to 512 chunks (the partial sums, one set a
-// chunk, cost as much as the products do where chunks are smaller)
+// The other layers: blocks of the reduced grid (the source grid of a decoder
+// layer), and their chunks.  A chunk is the work of `groups` workgroups; at
+// least 256 of these, and at most 8 blocks of a decoder layer or 4 of a
+// stride-2 layer a chunk, up to 512 chunks (the partial sums, one set a chunk,
+// cost as much as the products do where chunks are smaller)
 inline long wgrad_blocks(long N, long H, long W)
 {
     return N * ((H + kWgradRows - 1) / kWgradRows) * ((W + kWgradCols - 1) / kWgradCols);
 }
-inline int wgrad_up_chunks(long blocks, int cinp)
+inline int wgrad_block_chunks(long blocks, int up, int cinp, int cout)
 {
-    const long least = 64 * 64 / cinp, c = blocks / 8;
+    const long groups = up ? 4 * (cinp / 64) : (cinp / 32) * (cout / 64);
+    const long least = 256 / groups, c = blocks / (up ? 8 : 4);
     return (int)(c < least ? least : (c > 512 ? 512 : c));
+}
+// of layer l (0: the first) over N images of h x w outputs
+inline int wgrad_layer_chunks(int l, int up, int cinp, int cout, long N, long h, long w)
+{
+    if (l == 0) return wgrad_chunks(N * h * w);
+    return wgrad_block_chunks(up ? wgrad_blocks(N, h / 2, w / 2) : wgrad_blocks(N, h, w), up, cinp, cout);
 }
 
 constexpr int kHeadChunks = 1024;       // pixel chunks of the head's weight-gradient reduction
