@@ -98,8 +98,8 @@ bool nlayout(const Net &net, uint32_t B, uint32_t H, uint32_t W, int training, N
         for (int l = 0; l < kLayers - 1; ++l) {
             // the decoder layers reduce 16 (parity, offset) taps over the source grid, 4 bias partials
             const LayerDesc &Ll = net.L[l];
-            const int chunks = wgrad_layer_chunks(l, Ll.up, Ll.cinp, Ll.cout, (long)B, (long)(H / Ll.scale),
-                                                  (long)(W / Ll.scale));
+            const int chunks = wgrad_chunks(l, Ll.up, Ll.cinp, Ll.cout, (long)B, (long)(H / Ll.scale),
+                                            (long)(W / Ll.scale));
             const size_t e = (size_t)chunks *
                              ((size_t)Ll.cout * (Ll.up ? 16 : 9) * Ll.cinp + (Ll.up ? 4 : 1) * Ll.cout);
             if (e > mx) mx = e;
@@ -264,10 +264,9 @@ int tf_nn_backward(tf_nn *nn, const float *d_target, float *d_loss, tf_stream st
     const Net &net = nn->net;
     const LayerDesc &Hd = net.L[kLayers - 1];
     hipError_t e = launch_loss(nn->out, nn->dm, d_target, N * H * W, nn->ddelta, nn->scratch, d_loss, s);
-    if (e == hipSuccess) e = launch_head_bwd(nn->ddelta, nn->params + Hd.w_off, nn->act[7], nn->grad[7], N, H, W, s);
     if (e == hipSuccess)
-        e = launch_head_wgrad(nn->ddelta, nn->act[7], N, H, W, nn->hpartial, kHeadChunks, nn->grads + Hd.w_off,
-                              nn->grads + Hd.b_off, s);
+        e = launch_head_bwd(nn->ddelta, nn->params + Hd.w_off, nn->act[7], nn->grad[7], N, H, W, nn->hpartial,
+                            kHeadChunks, nn->grads + Hd.w_off, nn->grads + Hd.b_off, s);
     // conv layers from the last to the first: weight gradient, then the
     // gradient at the source (skip gradient and relu mask fused)
     static const int skipg_of[kLayers] = {-1, 7, 6, 5, -1, -1, -1, -1};   // gradient added at the source
@@ -277,7 +276,7 @@ int tf_nn_backward(tf_nn *nn, const float *d_target, float *d_loss, tf_stream st
         const int Hs = H / ss, Ws = W / ss, Ho = H / L.scale, Wo = W / L.scale;
         uint16_t *gpre = nn->grad[l + 1];
         e = launch_conv_wgrad(l, gpre, nn->act[L.src], Hs, Ws, N, Ho, Wo, nn->partial,
-                              wgrad_layer_chunks(l, L.up, L.cinp, L.cout, N, Ho, Wo),
+                              wgrad_chunks(l, L.up, L.cinp, L.cout, N, Ho, Wo),
                               nn->grads + L.w_off, nn->grads + L.b_off, s);
         if (e == hipSuccess && l > 0)
             e = launch_conv_bwd_data(l, gpre, Ho, Wo, nn->t + L.t_off,

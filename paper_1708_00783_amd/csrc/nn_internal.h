@@ -28,37 +28,25 @@ namespace nn {
 constexpr int kLayers = 8;              // e1 e2 e3 e4 d3 d2 d1 head
 constexpr float kDepthScale = 4.0f;     // metres: input normalisation (d / 4 m)
 constexpr float kCorrScale = 0.05f;     // metres: unit of the head's depth correction
-constexpr int kWgradStep = 64;          // pixels per LDS staging round of the conv weight gradient
-constexpr int kWgradChunkPix = 512;     // target pixels per chunk of a conv weight-gradient reduction
-constexpr int kWgradRows = 4, kWgradCols = 32;   // block of pixels the weight gradients stage
+// block of pixels the weight gradients stage (kWgradRows0: the first layer's)
+constexpr int kWgradRows = 4, kWgradRows0 = 8, kWgradCols = 32;
 
-// pixel chunks of the first layer's weight-gradient reduction over P pixels
-inline int wgrad_chunks(long P)
+// Weight gradient of layer l (0: the first): blocks of the grid it sums over
+// (the source grid of a decoder layer), and their chunks.  A chunk is the work
+// of `groups` workgroups; at least 256 of these, and at most 8 blocks of a
+// decoder layer or 4 of another a chunk, up to 512 chunks (the partial sums,
+// one set a chunk, cost as much as the products do where chunks are smaller).
+inline long wgrad_blocks(int l, long N, long H, long W)
 {
-    const long c = P / kWgradChunkPix;
-    return (int)(c < 64 ? 64 : (c > 512 ? 512 : c));
+    const int rows = l == 0 ? kWgradRows0 : kWgradRows;
+    return N * ((H + rows - 1) / rows) * ((W + kWgradCols - 1) / kWgradCols);
 }
-
-// The other layers: blocks of the reduced grid (the source grid of a decoder
-// layer), and their chunks.  A chunk is the work of `groups` workgroups; at
-// least 256 of these, and at most 8 blocks of a decoder layer or 4 of a
-// stride-2 layer a chunk, up to 512 chunks (the partial sums, one set a chunk,
-// cost as much as the products do where chunks are smaller)
-inline long wgrad_blocks(long N, long H, long W)
+// over N images of h x w outputs
+inline int wgrad_chunks(int l, int up, int cinp, int cout, long N, long h, long w)
 {
-    return N * ((H + kWgradRows - 1) / kWgradRows) * ((W + kWgradCols - 1) / kWgradCols);
-}
-inline int wgrad_block_chunks(long blocks, int up, int cinp, int cout)
-{
-    const long groups = up ? 4 * (cinp / 64) : (cinp / 32) * (cout / 64);
-    const long least = 256 / groups, c = blocks / (up ? 8 : 4);
+    const long groups = l == 0 ? 1 : up ? 4 * (cinp / 64) : (cinp / 32) * (cout / 64);
+    const long least = 256 / groups, c = wgrad_blocks(l, N, up ? h / 2 : h, up ? w / 2 : w) / (up ? 8 : 4);
     return (int)(c < least ? least : (c > 512 ? 512 : c));
-}
-// of layer l (0: the first) over N images of h x w outputs
-inline int wgrad_layer_chunks(int l, int up, int cinp, int cout, long N, long h, long w)
-{
-    if (l == 0) return wgrad_chunks(N * h * w);
-    return wgrad_block_chunks(up ? wgrad_blocks(N, h / 2, w / 2) : wgrad_blocks(N, h, w), up, cinp, cout);
 }
 
 constexpr int kHeadChunks = 1024;       // pixel chunks of the head's weight-gradient reduction
@@ -114,9 +102,7 @@ inline size_t loss_scratch_words(long n_pix) { return 4 + 2 * (size_t)((n_pix + 
 hipError_t launch_loss(const float *out, const float *dm, const float *target, int n_pix, float *ddelta,
                        float *scratch, float *loss, hipStream_t s);
 hipError_t launch_head_bwd(const float *ddelta, const float *w, const uint16_t *d1, uint16_t *g_d1, int N, int H,
-                           int W, hipStream_t s);
-hipError_t launch_head_wgrad(const float *ddelta, const uint16_t *d1, int N, int H, int W, float *partial,
-                             int chunks, float *dw, float *db, hipStream_t s);
+                           int W, float *partial, int chunks, float *dw, float *db, hipStream_t s);
 hipError_t launch_conv_bwd_data(int layer, const uint16_t *gpre, int Ho, int Wo, const uint16_t *t,
                                 const uint16_t *skipg, const uint16_t *act, uint16_t *gout, int N, int Hq, int Wq,
                                 hipStream_t s);

@@ -692,14 +692,17 @@ __global__ __launch_bounds__(256) void k_conv_bwd_data_s2(const uint16_t *gpre, 
 // + 7, `pitch` bytes apart from `base`.  The pitch is an odd number of 32
 // bytes, so the four rows of a read lie on different banks.
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ bf16x8 pixel_operand(const unsigned char *base, int pitch, int lane)
+__device__ __forceinline__ bf16x8 pixel_pieces(const unsigned char *p, int pitch)   // p: this lane's first piece
 {
-    const int i = lane & 15, gq = lane >> 4;
-    const unsigned char *p = base + (gq * 8 + (i >> 2)) * pitch + (i & 3) * 8;
     typedef __attribute__((address_space(3))) s16x4 *lds_s16x4;
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)p);
     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(p + 4 * pitch));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+__device__ __forceinline__ bf16x8 pixel_operand(const unsigned char *base, int pitch, int lane)
+{
+    const int i = lane & 15, gq = lane >> 4;
+    return pixel_pieces(base + (gq * 8 + (i >> 2)) * pitch + (i & 3) * 8, pitch);
 }
 
 // Weight gradient of an upsampled layer on its parity-folded taps:
@@ -921,106 +924,113 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_s2(const uint16_t *gpre, con
     }
 }
 
-// weight gradient of the first layer (8 padded input channels, stride 1):
-// all 9 taps in one workgroup as the N rows tap * 8 + ci (72 rows, padded to
-// 80 with zeros), so the gradient operand is staged once per chunk instead of
-// once per tap; partial layout [chunk][co][tap][ci]
+// Weight gradient of the first layer (8 padded input channels, stride 1):
+// partial[chunk][co][tap][ci].  A workgroup takes blocks of 8 rows x 32
+// columns, staged as they lie, and all 9 taps: a tile of 16 columns is two
+// taps of 8 channels, whose pixels the lanes of a transposing read address
+// each for itself (the tenth tap repeats the ninth and is dropped).  Wave w
+// takes rows 2 w and 2 w + 1, and the four sums are added at the end.
+// Staged per tap with 2-byte transposed writes to LDS it took 38.3 us at
+// 8 x 256 x 256, now 13.3.
 template <int COUT>
 __global__ __launch_bounds__(256) void k_conv_wgrad_c8(const uint16_t *gpre, const uint16_t *in, int H, int W, int N,
-                                                       float *partial, float *partial_b, int chunk_pix, int nchunk)
+                                                       float *partial, float *partial_b, int per)
 {
-    constexpr int KS = kWgradStep;
-    constexpr int LD = KS + 8;
-    constexpr int NR = 80;   // 72 (tap, ci) rows + 8 zero rows
-    constexpr int MT = COUT / 16, NTT = NR / 16, TILES = MT * NTT, TPW = (TILES + 3) / 4;
-    constexpr int GV = KS * (COUT / 8), IV = KS * 9;   // 16-byte vectors staged per round
-    static_assert(KS == 64, "one staging vector per (tap, pixel): pixel = v % 64");
-    auto swz = [](int row) { return ((row >> 3) & 7) << 3; };
-    __shared__ uint16_t gT[COUT][LD];
-    __shared__ uint16_t iT[NR][LD];
-    const int chunk = (int)blockIdx.x;
-    if (chunk >= nchunk) return;
-    const long P = (long)N * H * W;
-    const long c0 = (long)chunk * chunk_pix;
-    const long c1 = c0 + chunk_pix < P ? c0 + chunk_pix : P;
+    constexpr int R = kWgradRows0, C = kWgradCols, MT = COUT / 16, NT = 5;
+    constexpr int GP = COUT * 2 + 32;   // bytes per gradient pixel in LDS; an input pixel has 16
+    constexpr int IC = C + 2;
+    constexpr int GV = R * C * (COUT / 8), IV = (R + 2) * IC;   // 16-byte vectors of a block
+    constexpr int GQ = (GV + 255) / 256, IQ = (IV + 255) / 256;
+    constexpr int NA = MT * (NT + 1);   // the products and the bias
+    static_assert(R == 8, "two rows a wave");
+    constexpr int TILE = R * C * GP + IV * 16, SUMS = 4 * NA * 64 * 16;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[TILE > SUMS ? TILE : SUMS];
+    unsigned char *const gt = lds, *const it = lds + R * C * GP;
     const int w = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63, r = lane & 15, gq = lane >> 4;
-    for (int i = (int)threadIdx.x; i < 8 * LD; i += 256) iT[72 + i / LD][i % LD] = 0;
-    f32x4 acc[TPW];
+    const int bx = (W + C - 1) / C, by = (H + R - 1) / R;
+    const long nb = (long)N * by * bx, b0 = (long)blockIdx.x * per, b1 = b0 + per < nb ? b0 + per : nb;
+    u32x4 gv[GQ], iv[IQ];
+    auto load = [&](long blk) {
+        const int xb = (int)(blk % bx);
+        const long yb = blk / bx;
+        const int n = (int)(yb / by), m0 = (int)(yb - (long)n * by) * R, c0 = xb * C;
 #pragma unroll
-    for (int j = 0; j < TPW; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bpart = 0.0f;
-    for (long pb = c0; pb < c1; pb += KS) {
-        u32x4 gv[(GV + 255) / 256], iv[(IV + 255) / 256];
-#pragma unroll
-        for (int q = 0; q < (GV + 255) / 256; ++q) {
-            const int v = (int)threadIdx.x + 256 * q;
-            const int pi = v / (COUT / 8), cv = (v - pi * (COUT / 8)) * 8;
-            const long p = pb + pi;
+        for (int q = 0; q < GQ; ++q) {
+            const int v = (int)threadIdx.x + 256 * q, pix = v / (COUT / 8), cv = (v % (COUT / 8)) * 8;
+            const int m = m0 + pix / C, c = c0 + pix % C;
             gv[q] = u32x4{0u, 0u, 0u, 0u};
-            if (v < GV && p < c1) gv[q] = ld16(gpre + (size_t)p * COUT + cv);
+            if (v < GV && m < H && c < W) gv[q] = ld16(gpre + (((size_t)n * H + m) * W + c) * COUT + cv);
         }
 #pragma unroll
-        for (int q = 0; q < (IV + 255) / 256; ++q) {
+        for (int q = 0; q < IQ; ++q) {
             const int v = (int)threadIdx.x + 256 * q;
-            const int tap = v / KS, pi = v - (v / KS) * KS;
-            const long p = pb + pi;
+            const int sy = m0 - 1 + v / IC, sx = c0 - 1 + v % IC;
             iv[q] = u32x4{0u, 0u, 0u, 0u};
-            if (v < IV && p < c1) {
-                const int n = (int)(p / ((long)H * W));
-                const int rem = (int)(p - (long)n * H * W);
-                const int y = rem / W, x = rem - (rem / W) * W;
-                const int iy = y + tap / 3 - 1, ix = x + tap % 3 - 1;
-                if (iy >= 0 && iy < H && ix >= 0 && ix < W) iv[q] = ld16(in + (((size_t)n * H + iy) * W + ix) * 8);
-            }
+            if (v < IV && sy >= 0 && sy < H && sx >= 0 && sx < W) iv[q] = ld16(in + (((size_t)n * H + sy) * W + sx) * 8);
+        }
+    };
+    // where this lane's piece of tile j lies, from a row's first pixel: tap 2 j
+    // or 2 j + 1 by its column, 4 channels of it
+    int off[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const int tp = 2 * j + ((lane >> 1) & 1), tap = tp < 9 ? tp : 8;
+        off[j] = ((tap / 3) * IC + tap % 3 + gq * 8 + ((lane & 15) >> 2)) * 16 + (lane & 1) * 8;
+    }
+    f32x4 acc[NA];
+#pragma unroll
+    for (int j = 0; j < NA; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const u32x4 one2 = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+    const bf16x8 ones = as_bf(one2);
+    if (b0 < b1) load(b0);
+    for (long blk = b0; blk < b1; ++blk) {
+#pragma unroll
+        for (int q = 0; q < GQ; ++q) {
+            const int v = (int)threadIdx.x + 256 * q;
+            if (v < GV) *reinterpret_cast<u32x4 *>(gt + (v / (COUT / 8)) * GP + (v % (COUT / 8)) * 16) = gv[q];
         }
 #pragma unroll
-        for (int q = 0; q < (GV + 255) / 256; ++q) {
+        for (int q = 0; q < IQ; ++q) {
             const int v = (int)threadIdx.x + 256 * q;
-            const int pi = v / (COUT / 8), cv = (v - pi * (COUT / 8)) * 8;
-            if (v < GV)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) gT[cv + e][pi ^ swz(cv + e)] = (uint16_t)(gv[q][e >> 1] >> (16 * (e & 1)));
-        }
-#pragma unroll
-        for (int q = 0; q < (IV + 255) / 256; ++q) {
-            const int v = (int)threadIdx.x + 256 * q;
-            const int tap = v / KS, pi = v - (v / KS) * KS;
-            if (v < IV)
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    iT[tap * 8 + e][pi ^ swz(tap * 8 + e)] = (uint16_t)(iv[q][e >> 1] >> (16 * (e & 1)));
+            if (v < IV) *reinterpret_cast<u32x4 *>(it + v * 16) = iv[q];
         }
         __syncthreads();
-        if ((int)threadIdx.x < COUT)
-            for (int k = 0; k < KS; ++k) bpart += bf2f(gT[threadIdx.x][k ^ swz((int)threadIdx.x)]);
+        if (blk + 1 < b1) load(blk + 1);
 #pragma unroll
-        for (int kk = 0; kk < KS; kk += 32)
+        for (int y = 0; y < 2; ++y) {
+            const int row = 2 * w + y;
+            bf16x8 a[MT];
 #pragma unroll
-            for (int j = 0; j < TPW; ++j) {
-                const int tile = w * TPW + j;
-                if (tile < TILES) {
-                    const int mt = tile / NTT, nt = tile - (tile / NTT) * NTT;
-                    const bf16x8 a = as_bf(*reinterpret_cast<const u32x4 *>(&gT[mt * 16 + r][(kk + gq * 8) ^ swz(mt * 16 + r)]));
-                    const bf16x8 b = as_bf(*reinterpret_cast<const u32x4 *>(&iT[nt * 16 + r][(kk + gq * 8) ^ swz(nt * 16 + r)]));
-                    acc[j] = mfma(a, b, acc[j]);
-                }
+            for (int i = 0; i < MT; ++i) a[i] = pixel_operand(gt + row * C * GP + i * 32, GP, lane);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const bf16x8 b = pixel_pieces(it + row * IC * 16 + off[j], 16);
+#pragma unroll
+                for (int i = 0; i < MT; ++i) acc[i * (NT + 1) + j] = mfma(a[i], b, acc[i * (NT + 1) + j]);
             }
+#pragma unroll
+            for (int i = 0; i < MT; ++i) acc[i * (NT + 1) + NT] = mfma(a[i], ones, acc[i * (NT + 1) + NT]);
+        }
         __syncthreads();
     }
+    f32x4 *const sums = reinterpret_cast<f32x4 *>(lds);
 #pragma unroll
-    for (int j = 0; j < TPW; ++j) {
-        const int tile = w * TPW + j;
-        if (tile >= TILES) continue;
-        const int mt = tile / NTT, nt = tile - (tile / NTT) * NTT;
-        const int row = nt * 16 + r;   // tap * 8 + ci
-        if (row >= 72) continue;
+    for (int j = 0; j < NA; ++j) sums[(w * NA + j) * 64 + lane] = acc[j];
+    __syncthreads();
+    for (int j = w; j < NA; j += 4) {
+        const f32x4 s = (sums[j * 64 + lane] + sums[(NA + j) * 64 + lane]) +
+                        (sums[(2 * NA + j) * 64 + lane] + sums[(3 * NA + j) * 64 + lane]);
+        const int i = j / (NT + 1), nt = j % (NT + 1), col = nt * 16 + r;   // col = tap * 8 + ci
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int co = mt * 16 + gq * 4 + i;
-            partial[((size_t)chunk * COUT + co) * 72 + row] = acc[j][i];
+        for (int e = 0; e < 4; ++e) {
+            const int co = i * 16 + gq * 4 + e;
+            if (nt == NT) {
+                if (r == 0) partial_b[(size_t)blockIdx.x * COUT + co] = s[e];
+            } else if (col < 72) {
+                partial[((size_t)blockIdx.x * COUT + co) * 72 + col] = s[e];
+            }
         }
     }
-    if ((int)threadIdx.x < COUT) partial_b[(size_t)chunk * COUT + threadIdx.x] = bpart;
 }
 
 // fixed-order sum of the chunk partials into the fp32 gradient vector: a
@@ -1231,110 +1241,114 @@ __global__ __launch_bounds__(256) void k_loss_final(const float *part, int nwg, 
     }
 }
 
-// gradient at d1 through the head: g[p][c] = sum_tap ddelta[p - tap + 1] w[tap][c], relu mask of d1
-__global__ __launch_bounds__(256) void k_head_bwd(const float *ddelta, const float *w, const uint16_t *d1,
-                                                  uint16_t *g_d1, int N, int H, int W)
+// Backward of the head over one chunk of rows, d1 and ddelta read once for both:
+// the gradient at d1, g[p][c] = sum_tap ddelta[p - off(tap)] w[tap][c] with the
+// relu mask of d1, and the weight gradient gathered from the input side,
+// dw[tap][c] = sum_p ddelta[p] d1[p + off(tap)][c] = sum_q d1[q][c] ddelta[q - off(tap)].
+//
+// A workgroup takes segments of 64 pixels of a row, their ddelta with the rows
+// and columns around in LDS (zeros outside the image), the next segment's loads
+// in flight.  Gradient: four lanes a pixel with eight channels each, whose 72
+// weights stay in registers; their loads and stores are one run a wave.  Weight
+// gradient: on the matrix cores in fp32 (v_mfma_f32_16x16x4_f32: A row l % 16,
+// k = l / 16; B column l % 16, same k; D as above): M = tap (rows past 8 are not
+// used), K = pixels, N = channels 2 c and 2 c + 1 of the 32 in two products, so
+// that a lane's load is the 4 bytes of its column and a wave's the 256 of four
+// pixels; wave w takes pixels 16 w .. + 15.
+// partial[j * nchunk + chunk]: j = tap * 32 + c, j = 288 the bias, the sum of
+// ddelta.  Bound by the gradient's vector instructions (18 a channel and pixel
+// beside the unpacking) and memory; at 8 x 256 x 256 a kernel each, with a pixel
+// a lane 64 bytes apart and the weight gradient on the vector units, took 29.7
+// and 52.6 us, now 38 together.
+__global__ __launch_bounds__(256) void k_head_bwd(const float *ddelta, const float *__restrict__ wt,
+                                                  const uint16_t *__restrict__ d1, uint16_t *__restrict__ g_d1, int N,
+                                                  int H, int W, float *__restrict__ partial, int per)
 {
-    __shared__ float ws[288];
-    for (int k = threadIdx.x; k < 288; k += 256) ws[k] = w[k];
-    __syncthreads();
-    const long P = (long)N * H * W;
-    const long p = (long)blockIdx.x * 256 + threadIdx.x;
-    if (p >= P) return;
-    const int n = (int)(p / ((long)H * W));
-    const int rem = (int)(p - (long)n * H * W);
-    const int y = rem / W, x = rem - (rem / W) * W;
-    float g[32];
-#pragma unroll
-    for (int c = 0; c < 32; ++c) g[c] = 0.0f;
-    for (int tap = 0; tap < 9; ++tap) {
-        const int oy = y - tap / 3 + 1, ox = x - tap % 3 + 1;
-        if (oy < 0 || oy >= H || ox < 0 || ox >= W) continue;
-        const float dd = ddelta[((size_t)n * H + oy) * W + ox];
-        if (dd == 0.0f) continue;
-#pragma unroll
-        for (int c = 0; c < 32; ++c) g[c] += dd * ws[tap * 32 + c];
-    }
-    const uint16_t *a = d1 + (size_t)p * 32;
-    uint16_t *o = g_d1 + (size_t)p * 32;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const u32x4 av = ld16(a + 8 * q);
-        u32x4 ov;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint16_t a0 = (uint16_t)(av[e] & 0xffffu), a1 = (uint16_t)(av[e] >> 16);
-            const uint16_t v0 = bf2f(a0) > 0.0f ? f2bf(g[8 * q + 2 * e]) : (uint16_t)0;
-            const uint16_t v1 = bf2f(a1) > 0.0f ? f2bf(g[8 * q + 2 * e + 1]) : (uint16_t)0;
-            ov[e] = (uint32_t)v0 | ((uint32_t)v1 << 16);
-        }
-        *reinterpret_cast<u32x4 *>(o + 8 * q) = ov;
-    }
-}
-
-// head weight gradient of one pixel chunk, gathered from the input side:
-// dw[tap][c] = sum_p ddelta[p] d1[p + off(tap)][c] = sum_q d1[q][c] ddelta[q - off(tap)],
-// so every d1 pixel is read once.  Thread t takes pixel t / 4 of each
-// 64-pixel pass and channels 8 (t % 4) .. +7; the 16 lanes of a wave with the
-// same channel octet are summed by a fixed butterfly, the 4 waves in LDS.
-// partial[j * nchunk + chunk]: j = tap * 32 + c, j = 288 the bias (the sum of
-// ddelta, from the octet-0 lanes)
-__global__ __launch_bounds__(256) void k_head_wgrad(const float *ddelta, const uint16_t *d1, int N, int H, int W,
-                                                    float *partial, int chunk_pix)
-{
-    __shared__ float red[4][4][73];
-    const long P = (long)N * H * W;
-    const long c0 = (long)blockIdx.x * chunk_pix;
-    const long c1 = c0 + chunk_pix < P ? c0 + chunk_pix : P;
-    const int oct = (int)threadIdx.x & 3, lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
-    float acc[9][8], bsum = 0.0f;
+    constexpr int SP = 64, DW = SP + 2;
+    __shared__ float dl[2][3 * DW];
+    __shared__ float red[4][289];
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6, r = lane & 15, gq = lane >> 4;
+    const int bx = (W + SP - 1) / SP;
+    const long ns = (long)N * H * bx, s0 = (long)blockIdx.x * per, s1 = s0 + per < ns ? s0 + per : ns;
+    const int px = (int)threadIdx.x >> 2, oct = (int)threadIdx.x & 3;
+    float ws[9][8];
 #pragma unroll
     for (int k = 0; k < 9; ++k)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[k][e] = 0.0f;
-    for (long q = c0 + ((int)threadIdx.x >> 2); q < c1; q += 64) {
-        const int n = (int)(q / ((long)H * W));
-        const int rem = (int)(q - (long)n * H * W);
-        const int y = rem / W, x = rem - (rem / W) * W;
-        const u32x4 v = ld16(d1 + (size_t)q * 32 + 8 * oct);
-        float a[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) a[e] = bf2f((uint16_t)(v[e >> 1] >> (16 * (e & 1))));
-        const float *drow = ddelta + (size_t)n * H * W;
-#pragma unroll
-        for (int tap = 0; tap < 9; ++tap) {
-            const int py = y - tap / 3 + 1, px = x - tap % 3 + 1;
-            if (py < 0 || py >= H || px < 0 || px >= W) continue;
-            const float dd = drow[(size_t)py * W + px];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[tap][e] += dd * a[e];
-            if (tap == 4 && oct == 0) bsum += dd;
+        for (int e = 0; e < 8; ++e) ws[k][e] = wt[k * 32 + 8 * oct + e];
+    const int tap = r < 9 ? r : 0;
+    const int at = (2 - tap / 3) * DW + 2 - tap % 3 + 16 * w + gq;   // ddelta of q - off(tap), q = 16 w + gq + 4 k
+    float dv = 0.0f;
+    uint32_t v[4];
+    u32x4 av;
+    auto load = [&](long s) {
+        const int c0 = (int)(s % bx) * SP;
+        const long row = s / bx;   // image * H + row
+        const int n = (int)(row / H), y = (int)(row - (long)n * H);
+        dv = 0.0f;
+        if ((int)threadIdx.x < 3 * DW) {
+            const int oy = y - 1 + (int)threadIdx.x / DW, ox = c0 - 1 + (int)threadIdx.x % DW;
+            if (oy >= 0 && oy < H && ox >= 0 && ox < W) dv = ddelta[((size_t)n * H + oy) * W + ox];
         }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int x = c0 + 16 * w + 4 * k + gq;
+            v[k] = 0u;
+            if (x < W) v[k] = *reinterpret_cast<const uint32_t *>(d1 + ((size_t)row * W + x) * 32 + 2 * r);
+        }
+        av = u32x4{0u, 0u, 0u, 0u};
+        if (c0 + px < W) av = ld16(d1 + ((size_t)row * W + c0 + px) * 32 + 8 * oct);
+    };
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    float bsum = 0.0f;
+    if (s0 < s1) load(s0);
+    for (long s = s0; s < s1; ++s) {
+        float *const d = dl[s & 1];
+        if ((int)threadIdx.x < 3 * DW) d[threadIdx.x] = dv;
+        uint32_t u[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) u[k] = v[k];
+        const u32x4 act = av;
+        __syncthreads();   // two tiles of ddelta, so that this one barrier also guards the one before
+        if (s + 1 < s1) load(s + 1);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float a = d[at + 4 * k];
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, __uint_as_float(u[k] << 16), acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, __uint_as_float(u[k] & 0xffff0000u), acc[1], 0, 0, 0);
+            bsum += a;   // of use where the tap is the centre
+        }
+        float g[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) g[e] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            const float a = d[(2 - k / 3) * DW + 2 - k % 3 + px];
+            if (a != 0.0f)   // a gradient of zero is left out, whatever the weight
+#pragma unroll
+                for (int e = 0; e < 8; ++e) g[e] += a * ws[k][e];
+        }
+        u32x4 ov;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float v0 = bf2f((uint16_t)(act[e] & 0xffffu)) > 0.0f ? g[2 * e] : 0.0f;
+            const float v1 = bf2f((uint16_t)(act[e] >> 16)) > 0.0f ? g[2 * e + 1] : 0.0f;
+            ov[e] = bf2(v0, v1);
+        }
+        const int c0 = (int)(s % bx) * SP;
+        if (c0 + px < W) *reinterpret_cast<u32x4 *>(g_d1 + ((size_t)(s / bx) * W + c0 + px) * 32 + 8 * oct) = ov;
     }
+    bsum += __shfl_xor(bsum, 16);
+    bsum += __shfl_xor(bsum, 32);
+    if (lane == 4) red[w][288] = bsum;
 #pragma unroll
-    for (int m = 4; m < 64; m <<= 1) {
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int k = 0; k < 9; ++k)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[k][e] += __shfl_xor(acc[k][e], m);
-        bsum += __shfl_xor(bsum, m);
-    }
-    if (lane < 4) {
-#pragma unroll
-        for (int k = 0; k < 9; ++k)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) red[wv][oct][k * 8 + e] = acc[k][e];
-        red[wv][oct][72] = bsum;
-    }
+        for (int i = 0; i < 4; ++i)
+            if (gq * 4 + i < 9) red[w][(gq * 4 + i) * 32 + 2 * r + j] = acc[j][i];
     __syncthreads();
-    const int nchunk = (int)gridDim.x;
-    for (int j = (int)threadIdx.x; j < 289; j += 256) {
-        // j = tap * 32 + c (c = 8 oct + e); the bias sits at octet 0, slot 72
-        const int tap = j >> 5, c = j & 31;
-        const int o = j < 288 ? c >> 3 : 0, k = j < 288 ? tap * 8 + (c & 7) : 72;
-        const float s = (red[0][o][k] + red[1][o][k]) + (red[2][o][k] + red[3][o][k]);
-        partial[(size_t)j * nchunk + blockIdx.x] = s;
-    }
+    for (int j = (int)threadIdx.x; j < 289; j += 256)
+        partial[(size_t)j * gridDim.x + blockIdx.x] = (red[0][j] + red[1][j]) + (red[2][j] + red[3][j]);
 }
 
 // fixed-order sum of the head partials: workgroup j sums row j of partial
@@ -1470,19 +1484,12 @@ hipError_t launch_loss(const float *out, const float *dm, const float *target, i
 }
 
 hipError_t launch_head_bwd(const float *ddelta, const float *w, const uint16_t *d1, uint16_t *g_d1, int N, int H,
-                           int W, hipStream_t s)
+                           int W, float *partial, int chunks, float *dw, float *db, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_head_bwd, grid1((long)N * H * W, 256), dim3(256), 0, s, ddelta, w, d1, g_d1, N, H, W);
-    return hipGetLastError();
-}
-
-hipError_t launch_head_wgrad(const float *ddelta, const uint16_t *d1, int N, int H, int W, float *partial,
-                             int chunks, float *dw, float *db, hipStream_t s)
-{
-    const long P = (long)N * H * W;
-    const int per = (int)((P + chunks - 1) / chunks);
-    const int nc = (int)((P + per - 1) / per);
-    hipLaunchKernelGGL(k_head_wgrad, dim3(nc), dim3(256), 0, s, ddelta, d1, N, H, W, partial, per);
+    const long segs = (long)N * H * ((W + 63) / 64);
+    const int per = (int)((segs + chunks - 1) / chunks);
+    const int nc = (int)((segs + per - 1) / per);
+    hipLaunchKernelGGL(k_head_bwd, dim3(nc), dim3(256), 0, s, ddelta, w, d1, g_d1, N, H, W, partial, per);
     hipLaunchKernelGGL(k_head_reduce, dim3(289), dim3(256), 0, s, partial, nc, dw, db);
     return hipGetLastError();
 }
@@ -1518,12 +1525,11 @@ hipError_t launch_conv_wgrad(int layer, const uint16_t *gpre, const uint16_t *in
                              int Wo, float *partial, int chunks, float *dw, float *db, hipStream_t s)
 {
     // the decoder layers (4-6) run folded: 16 (parity, offset) taps over the
-    // source grid; chunks are counted in blocks of pixels, layer 0's in pixels
+    // source grid
     const bool fold = layer >= 4;
-    const long P = layer == 0 ? (long)N * Ho * Wo : fold ? wgrad_blocks(N, Hs, Ws) : wgrad_blocks(N, Ho, Wo);
+    const long P = wgrad_blocks(layer, N, fold ? Hs : Ho, fold ? Ws : Wo);
     if (fold && (Ho != 2 * Hs || Wo != 2 * Ws)) return hipErrorInvalidValue;
-    int per = (int)((P + chunks - 1) / chunks);
-    if (layer == 0) per = ((per + kWgradStep - 1) / kWgradStep) * kWgradStep;
+    const int per = (int)((P + chunks - 1) / chunks);
     const int nc = (int)((P + per - 1) / per);
     float *pb = partial;   // bias partials after the weight partials
     const int nc8 = (nc + 7) / 8 * 8;   // chunks padded to a multiple of 8, the XCDs they are dealt to
@@ -1531,7 +1537,7 @@ hipError_t launch_conv_wgrad(int layer, const uint16_t *gpre, const uint16_t *in
     int cout = 0, cin = 0, cinp = 0;
     switch (layer) {
     case 0: cout = 32; cin = 3; cinp = 8; pb += (size_t)nc * 32 * 9 * 8;   // all taps per workgroup
-        hipLaunchKernelGGL((k_conv_wgrad_c8<32>), dim3(nc), b, 0, s, gpre, in, Ho, Wo, N, partial, pb, per, nc); break;
+        hipLaunchKernelGGL((k_conv_wgrad_c8<32>), dim3(nc), b, 0, s, gpre, in, Ho, Wo, N, partial, pb, per); break;
     case 1: cout = 64; cin = cinp = 32; pb += (size_t)nc * 64 * 9 * 32;
         hipLaunchKernelGGL((k_conv_wgrad_s2<32, 64>), dim3(1 * nc8), dim3(512), 0, s, gpre, in, Hs, Ws, N, Ho, Wo, partial, pb, per, nc); break;
     case 2: cout = 64; cin = cinp = 64; pb += (size_t)nc * 64 * 9 * 64;
