@@ -2,10 +2,15 @@
 // stage (Sec. 4; Sec. 6 useBilateralFilter) on gfx950.
 //
 // One workgroup per 16x16 output tile: the tile and its halo of `radius`
-// pixels are staged in LDS once (u16 millimetres converted on the way), the
-// spatial weights too, and each thread forms one output pixel's weighted
-// mean from LDS.  The work is a small stencil: HBM traffic is one read and
-// one write of the image.
+// pixels are staged in LDS once (u16 millimetres converted on the way), and
+// each thread forms one output pixel's weighted mean from LDS.  The work is a
+// small stencil: HBM traffic is one read and one write of the image, and the
+// images of a depth camera leave the time to one pixel's chain of taps.  So
+// the window of the usual radii is unrolled: its LDS reads and exponentials
+// overlap, the weights come with the arguments, and a tap without depth is
+// selected away instead of branched around.  333x251, radius 2: 7.1 -> 4.6 us;
+// from some 300000 pixels on bound by vector instructions: 1280x720, radius 2
+// 17.9 -> 14.3, radius 3 29.5 -> 24.3, radius 5 63.5 -> 57.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -15,13 +20,14 @@
 namespace {
 
 constexpr int kTile = 16;
-constexpr int kMaxSide = kTile + 2 * TF_BILATERAL_MAX_RADIUS;
-constexpr int kMaxTaps = (2 * TF_BILATERAL_MAX_RADIUS + 1) * (2 * TF_BILATERAL_MAX_RADIUS + 1);
+constexpr int taps_of(int r) { return (2 * r + 1) * (2 * r + 1); }
 
+// by value to the kernel, so no longer than the window needs
+template <int MAXR>
 struct BilArgs {
     int r;
     float inv2sr2;                 // 1 / (2 sigma_range^2)
-    float ws[kMaxTaps];            // spatial weights, row-major over (dy, dx)
+    float ws[taps_of(MAXR)];       // spatial weights, row-major over (dy, dx)
 };
 
 template <int FMT>
@@ -31,12 +37,41 @@ __device__ __forceinline__ float load_depth(const void *src, size_t i)
     return ((const float *)src)[i];
 }
 
-template <int FMT>
-__global__ __launch_bounds__(256) void k_bilateral(const void *src, int W, int H, BilArgs a, float *out)
+// exp(t) for t <= 0: 2^(t log2 e) by the hardware's exponential of the product's
+// high part, and the low part (the product's rounding error and log2 e's own)
+// to first order.  Within 2 ulp down to the smallest normal number, zero below:
+// expf's steps for overflow and subnormals are not needed beside a weight of 1
+// (1280x720, radius 5: 66.6 us with it, 57 without).
+__device__ __forceinline__ float exp_neg(float t)
 {
-    __shared__ float tile[kMaxSide * kMaxSide];
-    __shared__ float ws[kMaxTaps];
-    const int r = a.r, side = kTile + 2 * r, taps = (2 * r + 1) * (2 * r + 1);
+    constexpr float c = 1.44269502162933350f, cl = 1.92596299112661746e-8f;   // log2 e = c + cl
+    constexpr float ln2 = 0.693147180559945309f;
+    if (t < -1000.0f) t = -1000.0f;   // no infinity below; NaN stays
+    const float hi = t * c;
+    const float lo = fmaf(t, c, -hi) + t * cl;
+    const float p = __builtin_amdgcn_exp2f(hi);
+    return fmaf(p, lo * ln2, p);
+}
+
+// one tap of the window into the sums; a neighbour without depth leaves them as they are
+__device__ __forceinline__ void tap(float dq, float dp, float ws, float inv2sr2, float &sw, float &swd)
+{
+    const float e = dq - dp;
+    const float w = ws * exp_neg(-(e * e) * inv2sr2);
+    const float sw1 = sw + w, swd1 = swd + w * e;
+    sw = dq > 0.0f ? sw1 : sw;
+    swd = dq > 0.0f ? swd1 : swd;
+}
+
+// R: the radius, or 0 for any
+template <int FMT, int R>
+__global__ __launch_bounds__(256) void k_bilateral(const void *src, int W, int H,
+                                                   BilArgs<R ? R : TF_BILATERAL_MAX_RADIUS> a, float *out)
+{
+    constexpr int kMaxR = R ? R : TF_BILATERAL_MAX_RADIUS, kSide = kTile + 2 * kMaxR;
+    __shared__ float tile[kSide * kSide];
+    __shared__ float ws[R ? 1 : taps_of(kMaxR)];
+    const int r = R ? R : a.r, side = kTile + 2 * r, taps = (2 * r + 1) * (2 * r + 1);
     const int x0 = (int)blockIdx.x * kTile - r, y0 = (int)blockIdx.y * kTile - r;
     for (int i = threadIdx.x; i < side * side; i += 256) {
         const int ty = i / side, tx = i - ty * side;
@@ -44,7 +79,8 @@ __global__ __launch_bounds__(256) void k_bilateral(const void *src, int W, int H
         // outside the image reads as invalid, which the window skips
         tile[i] = (gx >= 0 && gx < W && gy >= 0 && gy < H) ? load_depth<FMT>(src, (size_t)gy * W + gx) : 0.0f;
     }
-    for (int i = threadIdx.x; i < taps; i += 256) ws[i] = a.ws[i];
+    if (!R)
+        for (int i = threadIdx.x; i < taps; i += 256) ws[i] = a.ws[i];
     __syncthreads();
     const int lx = threadIdx.x & 15, ly = threadIdx.x >> 4;
     const int x = (int)blockIdx.x * kTile + lx, y = (int)blockIdx.y * kTile + ly;
@@ -54,22 +90,45 @@ __global__ __launch_bounds__(256) void k_bilateral(const void *src, int W, int H
     float res = 0.0f;
     if (dp > 0.0f) {
         float sw = 0.0f, swd = 0.0f;
-        int k = 0;
-        for (int dy = -r; dy <= r; ++dy) {
-            const float *row = c + dy * side;
-            for (int dx = -r; dx <= r; ++dx, ++k) {
-                const float dq = row[dx];
-                if (dq > 0.0f) {
-                    const float e = dq - dp;
-                    const float w = ws[k] * expf(-(e * e) * a.inv2sr2);
-                    sw += w;
-                    swd += w * e;
-                }
-            }
+        if (R) {
+#pragma unroll
+            for (int k = 0; k < (2 * R + 1) * (2 * R + 1); ++k)
+                tap(c[(k / (2 * R + 1) - R) * side + k % (2 * R + 1) - R], dp, a.ws[k], a.inv2sr2, sw, swd);
+        } else {
+            int k = 0;
+            for (int dy = -r; dy <= r; ++dy)
+                for (int dx = -r; dx <= r; ++dx, ++k) tap(c[dy * side + dx], dp, ws[k], a.inv2sr2, sw, swd);
         }
         res = dp + swd / sw;       // sw >= 1: the centre's own weight
     }
     out[(size_t)y * W + x] = res;
+}
+
+template <int FMT, int R>
+void launch(dim3 grid, hipStream_t s, const void *src, int W, int H, const tf_bilateral_params &p, float *out)
+{
+    BilArgs<R ? R : TF_BILATERAL_MAX_RADIUS> a;
+    a.r = p.radius;
+    const double ss = p.sigma_space, sr = p.sigma_range;
+    a.inv2sr2 = (float)(1.0 / (2.0 * sr * sr));
+    float by_d2[2 * TF_BILATERAL_MAX_RADIUS * TF_BILATERAL_MAX_RADIUS + 1];
+    for (int q = 0; q <= 2 * a.r * a.r; ++q) by_d2[q] = (float)exp(-(double)q / (2.0 * ss * ss));
+    int k = 0;
+    for (int dy = -a.r; dy <= a.r; ++dy)
+        for (int dx = -a.r; dx <= a.r; ++dx) a.ws[k++] = by_d2[dx * dx + dy * dy];
+    hipLaunchKernelGGL((k_bilateral<FMT, R>), grid, dim3(256), 0, s, src, W, H, a, out);
+}
+
+template <int FMT>
+void launch_radius(dim3 grid, hipStream_t s, const void *src, int W, int H, const tf_bilateral_params &p, float *out)
+{
+    // unrolled up to 49 taps; past that the code outgrows what the overlap gives
+    switch (p.radius) {
+    case 1: launch<FMT, 1>(grid, s, src, W, H, p, out); break;
+    case 2: launch<FMT, 2>(grid, s, src, W, H, p, out); break;
+    case 3: launch<FMT, 3>(grid, s, src, W, H, p, out); break;
+    default: launch<FMT, 0>(grid, s, src, W, H, p, out); break;
+    }
 }
 
 }  // namespace
@@ -90,18 +149,10 @@ extern "C" int tf_bilateral(const void *d_depth, int depth_format, int32_t width
     const uintptr_t a0 = (uintptr_t)d_depth, a1 = a0 + in_bytes;
     const uintptr_t b0 = (uintptr_t)d_out, b1 = b0 + (size_t)width * height * 4;
     if (a0 < b1 && b0 < a1) return TF_E_INVAL;
-    BilArgs a;
-    a.r = p->radius;
-    const double ss = p->sigma_space, sr = p->sigma_range;
-    a.inv2sr2 = (float)(1.0 / (2.0 * sr * sr));
-    int k = 0;
-    for (int dy = -a.r; dy <= a.r; ++dy)
-        for (int dx = -a.r; dx <= a.r; ++dx) a.ws[k++] = (float)exp(-(double)(dx * dx + dy * dy) / (2.0 * ss * ss));
-    const dim3 grid((width + kTile - 1) / kTile, (height + kTile - 1) / kTile), block(256);
-    hipStream_t s = (hipStream_t)stream;
+    const dim3 grid((width + kTile - 1) / kTile, (height + kTile - 1) / kTile);
     if (depth_format == TF_DEPTH_U16_MM)
-        hipLaunchKernelGGL(k_bilateral<TF_DEPTH_U16_MM>, grid, block, 0, s, d_depth, width, height, a, d_out);
+        launch_radius<TF_DEPTH_U16_MM>(grid, (hipStream_t)stream, d_depth, width, height, *p, d_out);
     else
-        hipLaunchKernelGGL(k_bilateral<TF_DEPTH_F32_M>, grid, block, 0, s, d_depth, width, height, a, d_out);
+        launch_radius<TF_DEPTH_F32_M>(grid, (hipStream_t)stream, d_depth, width, height, *p, d_out);
     return hipGetLastError() == hipSuccess ? TF_OK : TF_E_HIP;
 }

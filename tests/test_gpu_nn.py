@@ -186,6 +186,11 @@ def test_tiles_and_blocks_at_their_edges(shape):
         if src in skip_to:
             dx = dx + _bf(net, "grad_" + skip_to[src])
         _close(_bf(net, "grad_" + src), dx * (a > 0), f"{shape} grad_{src}")
+    d1, dd = _bf(net, "d1"), net.tensor("ddelta").cpu().numpy().astype(np.float64).reshape(shape)
+    dx, dw, db = D.conv_backward(d1, P["head.w"], dd[..., None])
+    _close(_bf(net, "grad_d1"), dx * (d1 > 0), f"{shape} grad_d1")
+    assert np.allclose(grads["head.w"], dw, rtol=1e-3, atol=1e-6 * np.abs(dw).max()), shape
+    assert np.allclose(grads["head.b"], db, rtol=1e-4, atol=1e-9), shape
 
 
 def test_end_to_end_gradient_cosine():
