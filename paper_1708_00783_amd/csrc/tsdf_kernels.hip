@@ -336,12 +336,23 @@ __device__ __forceinline__ int table_find(const TileTable *tt, int bx, int by, i
 // device pointer of a block (coordinates in the 16-bit range; -1 = absent or
 // not on the device) from its occupancy brick and its bucket entry, loaded
 // together; the chain beyond the bucket only when the entry is another block's
-__device__ __forceinline__ int map_find(const Vol &v, int bx, int by, int bz)
+struct MapProbe {
+    uint32_t bw;
+    int4 w;
+};
+
+__device__ __forceinline__ MapProbe map_probe(const Vol &v, int bx, int by, int bz)
 {
-    const uint32_t h = hash_index(bx, by, bz, v.n_buckets - 1u);
-    const uint32_t bw = gload(v.brick + brick_word(bx, by, bz));
-    const int4 w = load_entry(v.entries, h);
-    if (!(bw & brick_bit(bx, by, bz))) return -1;
+    MapProbe m;
+    m.bw = gload(v.brick + brick_word(bx, by, bz));
+    m.w = load_entry(v.entries, hash_index(bx, by, bz, v.n_buckets - 1u));
+    return m;
+}
+
+__device__ __forceinline__ int map_resolve(const Vol &v, const MapProbe &m, int bx, int by, int bz)
+{
+    const int4 w = m.w;
+    if (!(m.bw & brick_bit(bx, by, bz))) return -1;
     const uint32_t kxy = (uint32_t)(uint16_t)bx | ((uint32_t)(uint16_t)by << 16);
     if ((uint32_t)w.x == kxy && (int16_t)(w.y & 0xffff) == (int16_t)bz && w.w >= 0) return w.w;
     if (w.z < 1 || (uint32_t)(w.z - 1) >= v.n_excess) return -1;
@@ -349,6 +360,11 @@ __device__ __forceinline__ int map_find(const Vol &v, int bx, int by, int bz)
     const int e = find_entry_from(v.entries, v.n_buckets, v.n_excess, v.n_buckets + (uint32_t)(w.z - 1), bx, by, bz, 0,
                                   &ptr);
     return e >= 0 ? ptr : -1;
+}
+
+__device__ __forceinline__ int map_find(const Vol &v, int bx, int by, int bz)
+{
+    return map_resolve(v, map_probe(v, bx, by, bz), bx, by, bz);
 }
 
 // The tile's block table and the search range of pixel (px, py) from the
@@ -407,14 +423,23 @@ __device__ __forceinline__ void tile_range(const Vol &v, int tile, int tx0, int 
         __syncthreads();
         // the order of a wave's list varies with the atomics; min and max do not
         const int nw = __builtin_amdgcn_readfirstlane(tt->wcnt[wave]);
-        for (int i = 0; i < nw; ++i) {
-            const uint4 b = tt->r.box[tt->r.wlist[wave][i]];
-            const int x0 = (int16_t)(b.x & 0xffffu), y0 = (int16_t)(b.x >> 16);
-            const int x1 = (int16_t)(b.y & 0xffffu), y1 = (int16_t)(b.y >> 16);
-            if (px >= x0 && px <= x1 && py >= y0 && py <= y1) {
-                const float zl = __uint_as_float(b.z), zh = __uint_as_float(b.w);
-                lo = zl < lo ? zl : lo;
-                hi = zh > hi ? zh : hi;
+        // kBatch boxes at a time, their LDS reads (list, then box) in flight
+        // together; past the end the last one again, which changes nothing
+        constexpr int kBatch = 4;
+        for (int i = 0; i < nw; i += kBatch) {
+            uint4 bb[kBatch];
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) bb[k] = tt->r.box[tt->r.wlist[wave][i + k < nw ? i + k : nw - 1]];
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) {
+                const uint4 b = bb[k];
+                const int x0 = (int16_t)(b.x & 0xffffu), y0 = (int16_t)(b.x >> 16);
+                const int x1 = (int16_t)(b.y & 0xffffu), y1 = (int16_t)(b.y >> 16);
+                if (px >= x0 && px <= x1 && py >= y0 && py <= y1) {
+                    const float zl = __uint_as_float(b.z), zh = __uint_as_float(b.w);
+                    lo = zl < lo ? zl : lo;
+                    hi = zh > hi ? zh : hi;
+                }
             }
         }
         // this wave's list is consumed; the next chunk's staging starts after the barrier above
@@ -437,19 +462,39 @@ __device__ __forceinline__ void tile_range(const Vol &v, int tile, int tx0, int 
         tt->nb[j][2] = own[h].y;
     }
     __syncthreads();
+    // A thread takes kLook of them at a time: the table first, then the map
+    // reads of all that are not in it, together.
+    constexpr int kLook = 2;
     const int nn = (int)threadIdx.x & 7;
-    for (int i = (int)threadIdx.x; i < 8 * n; i += 256) {
-        const int j = i >> 3;
-        const int kxy = tt->nb[j][1], bz = tt->nb[j][2] + (nn >> 2);
-        const int bx = (int16_t)(kxy & 0xffff) + (nn & 1), by = (int16_t)((uint32_t)kxy >> 16) + ((nn >> 1) & 1);
-        __builtin_amdgcn_wave_barrier();   // the record's eight lanes have read its key
-        if (nn == 0) continue;
-        int p = -1;
-        if (in_short_range(bx) && in_short_range(by) && in_short_range(bz)) {
-            const int k = table_find(tt, bx, by, bz);
-            p = k >= 0 ? tt->nb[k][0] : map_find(v, bx, by, bz);
+    for (int i0 = (int)threadIdx.x; i0 < 8 * n; i0 += kLook * 256) {
+        int kxy[kLook], bz[kLook], p[kLook];
+        bool ask[kLook];
+        MapProbe m[kLook];
+#pragma unroll
+        for (int u = 0; u < kLook; ++u) {
+            const int i = i0 + 256 * u, j = (i < 8 * n ? i : i0) >> 3;
+            kxy[u] = tt->nb[j][1];
+            bz[u] = tt->nb[j][2] + (nn >> 2);
         }
-        tt->nb[j][nn] = p;
+        __builtin_amdgcn_wave_barrier();   // the records' eight lanes have read their keys
+#pragma unroll
+        for (int u = 0; u < kLook; ++u) {
+            const int bx = (int16_t)(kxy[u] & 0xffff) + (nn & 1), by = (int16_t)((uint32_t)kxy[u] >> 16) + ((nn >> 1) & 1);
+            p[u] = -1;
+            ask[u] = false;
+            if (nn != 0 && i0 + 256 * u < 8 * n && in_short_range(bx) && in_short_range(by) && in_short_range(bz[u])) {
+                const int k = table_find(tt, bx, by, bz[u]);
+                ask[u] = k < 0;
+                if (k >= 0) p[u] = tt->nb[k][0];
+            }
+            if (ask[u]) m[u] = map_probe(v, bx, by, bz[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kLook; ++u) {
+            const int bx = (int16_t)(kxy[u] & 0xffff) + (nn & 1), by = (int16_t)((uint32_t)kxy[u] >> 16) + ((nn >> 1) & 1);
+            if (ask[u]) p[u] = map_resolve(v, m[u], bx, by, bz[u]);
+            if (nn != 0 && i0 + 256 * u < 8 * n) tt->nb[(i0 + 256 * u) >> 3][nn] = p[u];
+        }
     }
     __syncthreads();   // before any lookup
 }
@@ -696,13 +741,43 @@ __device__ __forceinline__ bool normal_gradient(const Vol &v, const TileTable *t
     const int az = (iz & 7) == 0 ? -1 : ((iz & 7) >= 6 ? 1 : 0);
     int pb[8];
     pb[0] = cached_block(v, tt, Bx, By, Bz, cc);
-    const bool lc = cc.local;
+    // the lowest block of the range: its record's row holds all of them (seven
+    // lookups one after the other were 5 to 8% of the kernel)
+    const int lx = ax < 0 ? 1 : 0, ly = ay < 0 ? 1 : 0, lz0 = az < 0 ? 1 : 0;
+    int rec = cc.rec;
+    if (lx | ly | lz0)
+        rec = (in_short_range(Bx - lx) && in_short_range(By - ly) && in_short_range(Bz - lz0))
+                  ? table_find(tt, Bx - lx, By - ly, Bz - lz0)
+                  : -1;
+    if (rec >= 0) {
+        // a step along an axis leads from the own block (lx, ly, lz0) to the other of the two
 #pragma unroll
-    for (int c = 1; c < 8; ++c) {
-        const int sx = c & 1, sy = (c >> 1) & 1, sz = c >> 2;
-        pb[c] = ((sx && !ax) || (sy && !ay) || (sz && !az))
-                    ? -1
-                    : lookup_block(v, tt, Bx + (sx ? ax : 0), By + (sy ? ay : 0), Bz + (sz ? az : 0), lc);
+        for (int c = 1; c < 8; ++c) {
+            const int o = (((c & 1) ^ lx) | ((((c >> 1) & 1) ^ ly) << 1) | (((c >> 2) ^ lz0) << 2));
+            pb[c] = tt->nb[rec][o];
+        }
+    } else {
+        int q1 = -1, q2 = -1, q3 = -1, q4 = -1, q5 = -1, q6 = -1, q7 = -1;
+#pragma unroll 1
+        for (int c = 1; c < 8; ++c) {
+            const int sx = c & 1, sy = (c >> 1) & 1, sz = c >> 2;
+            if ((sx && !ax) || (sy && !ay) || (sz && !az)) continue;
+            const int q = lookup_block(v, tt, Bx + (sx ? ax : 0), By + (sy ? ay : 0), Bz + (sz ? az : 0), cc.local);
+            q1 = c == 1 ? q : q1;
+            q2 = c == 2 ? q : q2;
+            q3 = c == 3 ? q : q3;
+            q4 = c == 4 ? q : q4;
+            q5 = c == 5 ? q : q5;
+            q6 = c == 6 ? q : q6;
+            q7 = c == 7 ? q : q7;
+        }
+        pb[1] = q1;
+        pb[2] = q2;
+        pb[3] = q3;
+        pb[4] = q4;
+        pb[5] = q5;
+        pb[6] = q6;
+        pb[7] = q7;
     }
     // columns 0..3: (dx, dy) = (c & 1, c >> 1), z - 1 .. z + 2; 4..7: dx -1 / 2
     // (c & 1), dy 0 / 1 (c >> 1 & 1), and 8..11: dx 0 / 1, dy -1 / 2, z .. z + 1
