@@ -498,6 +498,9 @@ int tf_multi_autotune(tf_multi *m, const void *d_depth, int fmt, const tf_intrin
     // out), each keeping its better median; a later candidate replaces the
     // best only when it is faster by more than 2%, so near-ties keep the
     // earlier (default-first) order and repeated runs pick the same shape.
+    // Smaller tiles must win by 10%: a block enters more of their bins, and
+    // that cost grows with the map (at 7.3 M blocks 16x16 tiles took 36.4 ms of
+    // raycast, 32x8 37.9 and 16x8 51.5, after near-ties at 1.3 M).
     auto pick = [&](const std::vector<tf_multi_config> &cand, bool integ, tf_multi_config &bc, float &bt) -> int {
         std::vector<float> best(cand.size(), 3.4e38f);
         for (int pass = 0; pass < 2; ++pass)
@@ -509,7 +512,8 @@ int tf_multi_autotune(tf_multi *m, const void *d_depth, int fmt, const tf_intrin
             }
         size_t bi = 0;
         for (size_t i = 1; i < cand.size(); ++i)
-            if (best[i] < 0.98f * best[bi]) bi = i;
+            if (best[i] < (cand[i].tile_w * cand[i].tile_h < cand[bi].tile_w * cand[bi].tile_h ? 0.9f : 0.98f) * best[bi])
+                bi = i;
         bc = cand[bi];
         bt = best[bi];
         return TF_OK;
