@@ -426,15 +426,16 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t *in, int Hs, in
 // Forward of an upsampled layer on the parity-folded weights (split into
 // high and low halves; the one-tap offset has no low half: 7 cinp
 // multiply-adds per output instead of 9 cinp).  A workgroup = the 4 output
-// parities (one per wave) of one (image, source row m, run of 16 T source
-// columns) and one of NS shares of the output channels; it stages source
-// rows m - 1 .. m + 1 and columns c0 - 1 .. c0 + 16 T, which every parity's
-// 2x2 offsets read, in LDS.  The K loop is written out for each parity: which
-// steps have a low half is then known, no branch ends a step, and the weight
-// loads (from L2, whose latency bounds the loop) of several steps are in
-// flight.  d1, d2, d3 at 8 x 256 x 256: 38.7, 24.5 and 17.8 us with the branch,
-// 28.7, 19.5 and 15.2 now.
-template <int CINP, int COUT, bool SKIP, int T, int NS>
+// parities (one per wave) of one (image, band of R source rows, run of 16 T
+// source columns) and one of NS shares of the output channels; it stages the
+// R + 2 source rows and 16 T + 2 columns that every parity's 2x2 offsets read in
+// LDS (a square stages less a pixel than a strip and serves more products with a
+// weight load).  The K loop is written out for each parity: which steps have
+// a low half is then known, no branch ends a step, and the weight loads (from
+// L2, whose latency bounds the loop) of several steps are in flight.  d1, d2,
+// d3 at 8 x 256 x 256: 38.7, 24.5 and 17.8 us with the branch, 28.5, 19.1 and 14.6
+// without it on strips of one row, 25.0, 15.2 and 11.0 now.
+template <int CINP, int COUT, bool SKIP, int T, int NS, int R>
 __global__ __launch_bounds__(256) void k_conv_fwd_up(const uint16_t *in, int Hs, int Ws, const uint16_t *gu,
                                                      const float *bias, const uint16_t *skip, uint16_t *out, int N)
 {
@@ -443,25 +444,26 @@ __global__ __launch_bounds__(256) void k_conv_fwd_up(const uint16_t *in, int Hs,
     constexpr int TC = 16 * T + 2;
     constexpr int RS = CINP * 2 + 16;
     static_assert(CINP % 32 == 0, "a K step stays inside one source offset");
-    __shared__ __attribute__((aligned(16))) unsigned char tile[3 * TC * RS];
+    __shared__ __attribute__((aligned(16))) unsigned char tile[(R + 2) * TC * RS];
     const int lane = (int)threadIdx.x & 63, r = lane & 15, gq = lane >> 4;
     const int runs = (Ws + 16 * T - 1) / (16 * T);
-    const long ntiles = (long)N * Hs * runs * NS;
+    const int bands = (Hs + R - 1) / R;
+    const long ntiles = (long)N * bands * runs * NS;
     const long wt = xcd_band_tile(ntiles);
     const bool live = wt < ntiles;
     const int cbase = (int)(wt % NS) * (COUT / NS);
     const long gt = live ? wt / NS : 0;
     const int run = (int)(gt % runs);
     const long nm = gt / runs;
-    const int nimg = (int)(nm / Hs), m = (int)(nm - (long)nimg * Hs);
+    const int nimg = (int)(nm / bands), m0 = (int)(nm - (long)nimg * bands) * R;
     const int c0 = run * 16 * T;
-    stage_tile<CINP, 3, TC, RS>(tile, in, nimg, Hs, Ws, m - 1, c0 - 1, live);
+    stage_tile<CINP, R + 2, TC, RS>(tile, in, nimg, Hs, Ws, m0 - 1, c0 - 1, live);
     const int par = (int)threadIdx.x >> 6;
     const int py = par >> 1, px = par & 1;
     const int Ho = 2 * Hs, Wo = 2 * Ws;
-    f32x4 acc[T][NT];
+    f32x4 acc[R * T][NT];   // [row * T + run of 16 columns]
 #pragma unroll
-    for (int t = 0; t < T; ++t)
+    for (int t = 0; t < R * T; ++t)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const uint16_t *gp = gu + (size_t)par * COUT * K4;
@@ -471,21 +473,21 @@ __global__ __launch_bounds__(256) void k_conv_fwd_up(const uint16_t *in, int Hs,
 #pragma unroll
         for (int st = 0; st < K4 / 32; ++st) {
             const int q = st / (CINP / 32), ci = (st - q * (CINP / 32)) * 32 + gq * 8;
-            bf16x8 av[T];
+            bf16x8 av[R * T];
 #pragma unroll
-            for (int t = 0; t < T; ++t)
+            for (int t = 0; t < R * T; ++t)
                 av[t] = as_bf(*reinterpret_cast<const u32x4 *>(
-                    tile + (((PAR >> 1) + (q >> 1)) * TC + t * 16 + r + (PAR & 1) + (q & 1)) * RS + ci * 2));
+                    tile + ((t / T + (PAR >> 1) + (q >> 1)) * TC + t % T * 16 + r + (PAR & 1) + (q & 1)) * RS + ci * 2));
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 const size_t wo = ((size_t)(st * (COUT / 16) + cbase / 16 + j) * 64 + lane) * 8;
                 const bf16x8 b = as_bf(ld16(gp + wo));
 #pragma unroll
-                for (int t = 0; t < T; ++t) acc[t][j] = mfma(av[t], b, acc[t][j]);
+                for (int t = 0; t < R * T; ++t) acc[t][j] = mfma(av[t], b, acc[t][j]);
                 if (q != PAR) {
                     const bf16x8 bl = as_bf(ld16(gl + wo));
 #pragma unroll
-                    for (int t = 0; t < T; ++t) acc[t][j] = mfma(av[t], bl, acc[t][j]);
+                    for (int t = 0; t < R * T; ++t) acc[t][j] = mfma(av[t], bl, acc[t][j]);
                 }
             }
         }
@@ -496,14 +498,13 @@ __global__ __launch_bounds__(256) void k_conv_fwd_up(const uint16_t *in, int Hs,
     case 2: contract(Const<2>{}); break;
     default: contract(Const<3>{}); break;
     }
-    const size_t orow = ((size_t)nimg * Ho + 2 * m + py) * Wo;
     __shared__ EpiTile<NT> st[4];
 #pragma unroll
-    for (int t = 0; t < T; ++t)
+    for (int t = 0; t < R * T; ++t)
         epilogue_tile(st[par], acc[t], lane, [&](int pix, int c8, f32x4 lo, f32x4 hi) {
-            const int nn = c0 + t * 16 + pix;
-            if (!live || nn >= Ws) return;
-            const size_t p = orow + 2 * nn + px;
+            const int nn = c0 + t % T * 16 + pix, m = m0 + t / T;
+            if (!live || nn >= Ws || m >= Hs) return;
+            const size_t p = ((size_t)nimg * Ho + 2 * m + py) * Wo + 2 * nn + px;
             const int co = cbase + c8;
             fwd_store8<SKIP>(out + p * COUT + co, lo, hi, bias + co, SKIP ? skip + p * COUT + co : nullptr);
         });
@@ -1433,16 +1434,16 @@ hipError_t launch_conv_fwd(int layer, const uint16_t *in, int Hs, int Ws, const 
 {
     // encoder tiles: 4 / NS output rows x 16 T columns per workgroup, the
     // stride-2 layers splitting their output channels over the 4 waves (one
-    // output row per workgroup); decoder tiles: one source row x 16 T
-    // columns, the smaller layers' channels split over NS workgroups (shapes
-    // measured at 640x480)
+    // output row per workgroup); decoder tiles: R source rows x 16 T columns,
+    // the smaller layers' channels split over NS workgroups (shapes measured
+    // at 640x480 and 8 x 256 x 256)
     const dim3 b(256);
     auto enc_grid = [&](int T, int NS) {
         const long nt = (long)N * ((Ho + 4 / NS - 1) / (4 / NS)) * ((Wo + 16 * T - 1) / (16 * T));
         return dim3((unsigned)((nt + 7) / 8 * 8));
     };
-    auto up_grid = [&](int T, int NS) {
-        const long nt = (long)N * Hs * ((Ws + 16 * T - 1) / (16 * T)) * NS;
+    auto up_grid = [&](int T, int NS, int R) {
+        const long nt = (long)N * ((Hs + R - 1) / R) * ((Ws + 16 * T - 1) / (16 * T)) * NS;
         return dim3((unsigned)((nt + 7) / 8 * 8));
     };
     if (layer < 4 && skip) return hipErrorInvalidValue;
@@ -1452,9 +1453,9 @@ hipError_t launch_conv_fwd(int layer, const uint16_t *in, int Hs, int Ws, const 
     case 1: hipLaunchKernelGGL((k_conv_fwd<32, 64, 2, 2, 4>), enc_grid(2, 4), b, 0, s, in, Hs, Ws, g, bias, out, N, Ho, Wo); break;
     case 2: hipLaunchKernelGGL((k_conv_fwd<64, 64, 2, 2, 4>), enc_grid(2, 4), b, 0, s, in, Hs, Ws, g, bias, out, N, Ho, Wo); break;
     case 3: hipLaunchKernelGGL((k_conv_fwd<64, 128, 2, 1, 4>), enc_grid(1, 4), b, 0, s, in, Hs, Ws, g, bias, out, N, Ho, Wo); break;
-    case 4: hipLaunchKernelGGL((k_conv_fwd_up<128, 64, true, 1, 2>), up_grid(1, 2), b, 0, s, in, Hs, Ws, g, bias, skip, out, N); break;
-    case 5: hipLaunchKernelGGL((k_conv_fwd_up<64, 64, true, 2, 2>), up_grid(2, 2), b, 0, s, in, Hs, Ws, g, bias, skip, out, N); break;
-    case 6: hipLaunchKernelGGL((k_conv_fwd_up<64, 32, true, 4, 1>), up_grid(4, 1), b, 0, s, in, Hs, Ws, g, bias, skip, out, N); break;
+    case 4: hipLaunchKernelGGL((k_conv_fwd_up<128, 64, true, 1, 4, 2>), up_grid(1, 4, 2), b, 0, s, in, Hs, Ws, g, bias, skip, out, N); break;
+    case 5: hipLaunchKernelGGL((k_conv_fwd_up<64, 64, true, 1, 2, 4>), up_grid(1, 2, 4), b, 0, s, in, Hs, Ws, g, bias, skip, out, N); break;
+    case 6: hipLaunchKernelGGL((k_conv_fwd_up<64, 32, true, 1, 1, 4>), up_grid(1, 1, 4), b, 0, s, in, Hs, Ws, g, bias, skip, out, N); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
