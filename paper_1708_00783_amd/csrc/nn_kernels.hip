@@ -354,22 +354,24 @@ __device__ __forceinline__ void stage_tile(unsigned char *tile, const uint16_t *
 }
 
 // ============================================================================
-// forward 3x3 convolution (no skip input): a workgroup takes ROWS = 4 / NS
+// forward 3x3 convolution (no skip input): a workgroup takes ROWS = 4 R / NS
 // output rows x 16 T columns; it stages the input rows and columns those
 // reach (with the stride) in LDS with coalesced 16-byte loads, then each
-// wave computes 16 T pixels of one row x COUT / NS channels, A fragments
+// wave computes 16 T pixels of R rows x COUT / NS channels, A fragments
 // from LDS, B fragments (fragment order) from global memory.  The K steps are
 // unrolled in full, so that the weight loads of several steps are in flight:
-// e4 at 8 x 256 x 256 12.2 -> 8.2 us against steps two at a time
+// e4 at 8 x 256 x 256 12.2 -> 8.2 us against steps two at a time.  Two rows
+// where the channels are split over the waves stage 5 input rows for 2 outputs
+// instead of 3 for 1 (640x480: e2 13.0 -> 11.5 us, e3 8.2 -> 7.8)
 // ============================================================================
-template <int CINP, int COUT, int STRIDE, int T, int NS>
+template <int CINP, int COUT, int STRIDE, int T, int NS, int R>
 __global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t *in, int Hs, int Ws, const uint16_t *g,
                                                   const float *bias, uint16_t *out, int N, int Ho, int Wo)
 {
     static_assert(NS == 1 || NS == 2 || NS == 4, "channel split must divide the 4 waves of a workgroup");
     constexpr int KP = ((9 * CINP + 31) / 32) * 32;
     constexpr int NT = COUT / 16 / NS;
-    constexpr int ROWS = 4 / NS;
+    constexpr int ROWS = R * (4 / NS);
     constexpr int IR = STRIDE * (ROWS - 1) + 3, IC = STRIDE * (16 * T - 1) + 3;
     constexpr int RS = CINP * 2 + 16;   // +16 bytes: neighbouring pixels' fragments start on different banks
     __shared__ __attribute__((aligned(16))) unsigned char tile[IR * IC * RS];
@@ -383,10 +385,10 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t *in, int Hs, in
     const long nyt = gt / tx;
     const int nimg = (int)(nyt / ty), y0 = (int)(nyt - (long)nimg * ty) * ROWS, x0 = xt * 16 * T;
     stage_tile<CINP, IR, IC, RS>(tile, in, nimg, Hs, Ws, STRIDE * y0 - 1, STRIDE * x0 - 1, live);
-    const int yy = w / NS, cbase = (w % NS) * (COUT / NS);
-    f32x4 acc[T][NT];
+    const int yy = w / NS * R, cbase = (w % NS) * (COUT / NS);
+    f32x4 acc[R * T][NT];   // [row * T + run of 16 columns]
 #pragma unroll
-    for (int t = 0; t < T; ++t)
+    for (int t = 0; t < R * T; ++t)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -394,12 +396,12 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t *in, int Hs, in
         const int k = k0 + gq * 8;
         const int tap = k / CINP, ci = k - (k / CINP) * CINP;
         const int ky = tap / 3, kx = tap - (tap / 3) * 3;
-        bf16x8 a[T];
+        bf16x8 a[R * T];
 #pragma unroll
-        for (int t = 0; t < T; ++t) {
+        for (int t = 0; t < R * T; ++t) {
             u32x4 v = {0u, 0u, 0u, 0u};
             if (tap < 9)   // K padding past the 9 taps multiplies zeros
-                v = *reinterpret_cast<const u32x4 *>(tile + ((STRIDE * yy + ky) * IC + STRIDE * (t * 16 + r) + kx) * RS +
+                v = *reinterpret_cast<const u32x4 *>(tile + ((STRIDE * (yy + t / T) + ky) * IC + STRIDE * (t % T * 16 + r) + kx) * RS +
                                                      ci * 2);
             a[t] = as_bf(v);
         }
@@ -407,15 +409,14 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t *in, int Hs, in
         for (int j = 0; j < NT; ++j) {
             const bf16x8 b = as_bf(ld16(g + ((size_t)((k0 / 32) * (COUT / 16) + cbase / 16 + j) * 64 + lane) * 8));
 #pragma unroll
-            for (int t = 0; t < T; ++t) acc[t][j] = mfma(a[t], b, acc[t][j]);
+            for (int t = 0; t < R * T; ++t) acc[t][j] = mfma(a[t], b, acc[t][j]);
         }
     }
     __shared__ EpiTile<NT> st[4];
-    const int oy = y0 + yy;
 #pragma unroll
-    for (int t = 0; t < T; ++t)
+    for (int t = 0; t < R * T; ++t)
         epilogue_tile(st[w], acc[t], lane, [&](int pix, int c8, f32x4 lo, f32x4 hi) {
-            const int ox = x0 + t * 16 + pix;
+            const int ox = x0 + t % T * 16 + pix, oy = y0 + yy + t / T;
             if (!live || oy >= Ho || ox >= Wo) return;
             const size_t p = ((size_t)nimg * Ho + oy) * Wo + ox;
             const int co = cbase + c8;
@@ -1432,14 +1433,15 @@ hipError_t launch_pack(const Net &net, const float *params, uint16_t *g, uint16_
 hipError_t launch_conv_fwd(int layer, const uint16_t *in, int Hs, int Ws, const uint16_t *g, const float *bias,
                            const uint16_t *skip, uint16_t *out, int N, int Ho, int Wo, hipStream_t s)
 {
-    // encoder tiles: 4 / NS output rows x 16 T columns per workgroup, the
-    // stride-2 layers splitting their output channels over the 4 waves (one
-    // output row per workgroup); decoder tiles: R source rows x 16 T columns,
+    // encoder tiles: 4 R / NS output rows x 16 T columns per workgroup, the
+    // stride-2 layers splitting their output channels over the 4 waves (R
+    // output rows per workgroup); decoder tiles: R source rows x 16 T columns,
     // the smaller layers' channels split over NS workgroups (shapes measured
     // at 640x480 and 8 x 256 x 256)
     const dim3 b(256);
-    auto enc_grid = [&](int T, int NS) {
-        const long nt = (long)N * ((Ho + 4 / NS - 1) / (4 / NS)) * ((Wo + 16 * T - 1) / (16 * T));
+    auto enc_grid = [&](int T, int NS, int R) {
+        const int rows = R * (4 / NS);
+        const long nt = (long)N * ((Ho + rows - 1) / rows) * ((Wo + 16 * T - 1) / (16 * T));
         return dim3((unsigned)((nt + 7) / 8 * 8));
     };
     auto up_grid = [&](int T, int NS, int R) {
@@ -1449,10 +1451,10 @@ hipError_t launch_conv_fwd(int layer, const uint16_t *in, int Hs, int Ws, const 
     if (layer < 4 && skip) return hipErrorInvalidValue;
     if (layer >= 4 && (Ho != 2 * Hs || Wo != 2 * Ws)) return hipErrorInvalidValue;
     switch (layer) {
-    case 0: hipLaunchKernelGGL((k_conv_fwd<8, 32, 1, 2, 1>), enc_grid(2, 1), b, 0, s, in, Hs, Ws, g, bias, out, N, Ho, Wo); break;
-    case 1: hipLaunchKernelGGL((k_conv_fwd<32, 64, 2, 2, 4>), enc_grid(2, 4), b, 0, s, in, Hs, Ws, g, bias, out, N, Ho, Wo); break;
-    case 2: hipLaunchKernelGGL((k_conv_fwd<64, 64, 2, 2, 4>), enc_grid(2, 4), b, 0, s, in, Hs, Ws, g, bias, out, N, Ho, Wo); break;
-    case 3: hipLaunchKernelGGL((k_conv_fwd<64, 128, 2, 1, 4>), enc_grid(1, 4), b, 0, s, in, Hs, Ws, g, bias, out, N, Ho, Wo); break;
+    case 0: hipLaunchKernelGGL((k_conv_fwd<8, 32, 1, 2, 1, 1>), enc_grid(2, 1, 1), b, 0, s, in, Hs, Ws, g, bias, out, N, Ho, Wo); break;
+    case 1: hipLaunchKernelGGL((k_conv_fwd<32, 64, 2, 2, 4, 2>), enc_grid(2, 4, 2), b, 0, s, in, Hs, Ws, g, bias, out, N, Ho, Wo); break;
+    case 2: hipLaunchKernelGGL((k_conv_fwd<64, 64, 2, 1, 4, 2>), enc_grid(1, 4, 2), b, 0, s, in, Hs, Ws, g, bias, out, N, Ho, Wo); break;
+    case 3: hipLaunchKernelGGL((k_conv_fwd<64, 128, 2, 1, 4, 1>), enc_grid(1, 4, 1), b, 0, s, in, Hs, Ws, g, bias, out, N, Ho, Wo); break;
     case 4: hipLaunchKernelGGL((k_conv_fwd_up<128, 64, true, 1, 4, 2>), up_grid(1, 4, 2), b, 0, s, in, Hs, Ws, g, bias, skip, out, N); break;
     case 5: hipLaunchKernelGGL((k_conv_fwd_up<64, 64, true, 1, 2, 4>), up_grid(1, 2, 4), b, 0, s, in, Hs, Ws, g, bias, skip, out, N); break;
     case 6: hipLaunchKernelGGL((k_conv_fwd_up<64, 32, true, 1, 1, 4>), up_grid(1, 1, 4), b, 0, s, in, Hs, Ws, g, bias, skip, out, N); break;
