@@ -6,11 +6,12 @@
 // each thread forms one output pixel's weighted mean from LDS.  The work is a
 // small stencil: HBM traffic is one read and one write of the image, and the
 // images of a depth camera leave the time to one pixel's chain of taps.  So
-// the window of the usual radii is unrolled: its LDS reads and exponentials
+// the window is unrolled for each radius: its LDS reads and exponentials
 // overlap, the weights come with the arguments, and a tap without depth is
 // selected away instead of branched around.  333x251, radius 2: 7.1 -> 4.6 us;
 // from some 300000 pixels on bound by vector instructions: 1280x720, radius 2
-// 17.9 -> 14.3, radius 3 29.5 -> 24.3, radius 5 63.5 -> 57.
+// 17.9 -> 14.3, radius 3 29.5 -> 24.3, radius 5 63.5 -> 53
+// (57 in a loop); 640x480, radius 7 47 -> 36 (40).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -23,11 +24,10 @@ constexpr int kTile = 16;
 constexpr int taps_of(int r) { return (2 * r + 1) * (2 * r + 1); }
 
 // by value to the kernel, so no longer than the window needs
-template <int MAXR>
+template <int R>
 struct BilArgs {
-    int r;
     float inv2sr2;                 // 1 / (2 sigma_range^2)
-    float ws[taps_of(MAXR)];       // spatial weights, row-major over (dy, dx)
+    float ws[taps_of(R)];          // spatial weights, row-major over (dy, dx)
 };
 
 template <int FMT>
@@ -63,15 +63,11 @@ __device__ __forceinline__ void tap(float dq, float dp, float ws, float inv2sr2,
     swd = dq > 0.0f ? swd1 : swd;
 }
 
-// R: the radius, or 0 for any
 template <int FMT, int R>
-__global__ __launch_bounds__(256) void k_bilateral(const void *src, int W, int H,
-                                                   BilArgs<R ? R : TF_BILATERAL_MAX_RADIUS> a, float *out)
+__global__ __launch_bounds__(256) void k_bilateral(const void *src, int W, int H, BilArgs<R> a, float *out)
 {
-    constexpr int kMaxR = R ? R : TF_BILATERAL_MAX_RADIUS, kSide = kTile + 2 * kMaxR;
-    __shared__ float tile[kSide * kSide];
-    __shared__ float ws[R ? 1 : taps_of(kMaxR)];
-    const int r = R ? R : a.r, side = kTile + 2 * r, taps = (2 * r + 1) * (2 * r + 1);
+    constexpr int r = R, side = kTile + 2 * R;
+    __shared__ float tile[side * side];
     const int x0 = (int)blockIdx.x * kTile - r, y0 = (int)blockIdx.y * kTile - r;
     for (int i = threadIdx.x; i < side * side; i += 256) {
         const int ty = i / side, tx = i - ty * side;
@@ -79,8 +75,6 @@ __global__ __launch_bounds__(256) void k_bilateral(const void *src, int W, int H
         // outside the image reads as invalid, which the window skips
         tile[i] = (gx >= 0 && gx < W && gy >= 0 && gy < H) ? load_depth<FMT>(src, (size_t)gy * W + gx) : 0.0f;
     }
-    if (!R)
-        for (int i = threadIdx.x; i < taps; i += 256) ws[i] = a.ws[i];
     __syncthreads();
     const int lx = threadIdx.x & 15, ly = threadIdx.x >> 4;
     const int x = (int)blockIdx.x * kTile + lx, y = (int)blockIdx.y * kTile + ly;
@@ -90,15 +84,9 @@ __global__ __launch_bounds__(256) void k_bilateral(const void *src, int W, int H
     float res = 0.0f;
     if (dp > 0.0f) {
         float sw = 0.0f, swd = 0.0f;
-        if (R) {
 #pragma unroll
-            for (int k = 0; k < (2 * R + 1) * (2 * R + 1); ++k)
-                tap(c[(k / (2 * R + 1) - R) * side + k % (2 * R + 1) - R], dp, a.ws[k], a.inv2sr2, sw, swd);
-        } else {
-            int k = 0;
-            for (int dy = -r; dy <= r; ++dy)
-                for (int dx = -r; dx <= r; ++dx, ++k) tap(c[dy * side + dx], dp, ws[k], a.inv2sr2, sw, swd);
-        }
+        for (int k = 0; k < taps_of(R); ++k)
+            tap(c[(k / (2 * R + 1) - R) * side + k % (2 * R + 1) - R], dp, a.ws[k], a.inv2sr2, sw, swd);
         res = dp + swd / sw;       // sw >= 1: the centre's own weight
     }
     out[(size_t)y * W + x] = res;
@@ -107,27 +95,29 @@ __global__ __launch_bounds__(256) void k_bilateral(const void *src, int W, int H
 template <int FMT, int R>
 void launch(dim3 grid, hipStream_t s, const void *src, int W, int H, const tf_bilateral_params &p, float *out)
 {
-    BilArgs<R ? R : TF_BILATERAL_MAX_RADIUS> a;
-    a.r = p.radius;
+    BilArgs<R> a;
     const double ss = p.sigma_space, sr = p.sigma_range;
     a.inv2sr2 = (float)(1.0 / (2.0 * sr * sr));
-    float by_d2[2 * TF_BILATERAL_MAX_RADIUS * TF_BILATERAL_MAX_RADIUS + 1];
-    for (int q = 0; q <= 2 * a.r * a.r; ++q) by_d2[q] = (float)exp(-(double)q / (2.0 * ss * ss));
+    float by_d2[2 * R * R + 1];
+    for (int q = 0; q <= 2 * R * R; ++q) by_d2[q] = (float)exp(-(double)q / (2.0 * ss * ss));
     int k = 0;
-    for (int dy = -a.r; dy <= a.r; ++dy)
-        for (int dx = -a.r; dx <= a.r; ++dx) a.ws[k++] = by_d2[dx * dx + dy * dy];
+    for (int dy = -R; dy <= R; ++dy)
+        for (int dx = -R; dx <= R; ++dx) a.ws[k++] = by_d2[dx * dx + dy * dy];
     hipLaunchKernelGGL((k_bilateral<FMT, R>), grid, dim3(256), 0, s, src, W, H, a, out);
 }
 
 template <int FMT>
 void launch_radius(dim3 grid, hipStream_t s, const void *src, int W, int H, const tf_bilateral_params &p, float *out)
 {
-    // unrolled up to 49 taps; past that the code outgrows what the overlap gives
+    static_assert(TF_BILATERAL_MAX_RADIUS == 7, "a kernel for each radius");
     switch (p.radius) {
     case 1: launch<FMT, 1>(grid, s, src, W, H, p, out); break;
     case 2: launch<FMT, 2>(grid, s, src, W, H, p, out); break;
     case 3: launch<FMT, 3>(grid, s, src, W, H, p, out); break;
-    default: launch<FMT, 0>(grid, s, src, W, H, p, out); break;
+    case 4: launch<FMT, 4>(grid, s, src, W, H, p, out); break;
+    case 5: launch<FMT, 5>(grid, s, src, W, H, p, out); break;
+    case 6: launch<FMT, 6>(grid, s, src, W, H, p, out); break;
+    default: launch<FMT, 7>(grid, s, src, W, H, p, out); break;
     }
 }
 

@@ -75,8 +75,7 @@ def test_rejects_bad_arguments():
 
 @pytest.mark.parametrize("radius", [1, 2, 3, 4, 5, 6, 7])
 def test_every_radius_and_a_range_that_overflows(radius):
-    """the unrolled windows (radius 1 to 3) and the loop, on an image of ragged
-    tiles; and with a range so narrow that the exponent of a far neighbour
+    """the window of each radius has its own kernel: on an image of ragged tiles; and with a range so narrow that the exponent of a far neighbour
     overflows, where only equal depths count"""
     rng = np.random.default_rng(radius)
     d = rng.choice([0.0, 0.5, 0.5625, 12.0], size=(35, 50), p=[0.1, 0.4, 0.3, 0.2]).astype(np.float32)
