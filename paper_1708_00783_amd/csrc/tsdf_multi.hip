@@ -498,13 +498,14 @@ __device__ __forceinline__ void m_pixel_range(const MTiles &t, uint32_t g, int t
     const int n = m_bin_range(t, g, o0);
     zmin = __builtin_inff();
     zmax = -__builtin_inff();
+    unsigned long long mask = 0ull;   // submaps of this thread's records
     for (int b0 = 0; b0 < n; b0 += kStage) {
         const int m = n - b0 < kStage ? n - b0 : kStage;
         __syncthreads();   // the lists are empty, the previous records consumed
         for (int j = (int)threadIdx.x; j < m; j += NT) {
             const uint4 b = *reinterpret_cast<const uint4 *>(t.bins + o0 + (uint32_t)(b0 + j));
             L.r.box[j] = b;
-            atomicOr(&L.mask, 1ull << (uint32_t)t.bins[o0 + (uint32_t)(b0 + j)].pad);
+            mask |= 1ull << (uint32_t)t.bins[o0 + (uint32_t)(b0 + j)].pad;
             const int x0 = (int16_t)(b.x & 0xffffu), y0 = (int16_t)(b.x >> 16);
             const int x1 = (int16_t)(b.y & 0xffffu), y1 = (int16_t)(b.y >> 16);
 #pragma unroll
@@ -517,18 +518,35 @@ __device__ __forceinline__ void m_pixel_range(const MTiles &t, uint32_t g, int t
         __syncthreads();
         // the order of a wave's list varies with the atomics; min and max do not
         const int nw = __builtin_amdgcn_readfirstlane(L.wcnt[wave]);
-        for (int i = 0; i < nw; ++i) {
-            const uint4 b = L.r.box[L.r.wlist[wave][i]];
-            const int x0 = (int16_t)(b.x & 0xffffu), y0 = (int16_t)(b.x >> 16);
-            const int x1 = (int16_t)(b.y & 0xffffu), y1 = (int16_t)(b.y >> 16);
-            if (px >= x0 && px <= x1 && py >= y0 && py <= y1) {
-                const float zl = __uint_as_float(b.z), zh = __uint_as_float(b.w);
-                zmin = zl < zmin ? zl : zmin;
-                zmax = zh > zmax ? zh : zmax;
+        // kBatch boxes at a time, their LDS reads (list, then box) in flight
+        // together; past the end the last one again, which changes nothing
+        // (12 submaps, 4 views: with the mask below 3028 -> 2954 us)
+        constexpr int kBatch = 4;
+        for (int i = 0; i < nw; i += kBatch) {
+            uint4 bb[kBatch];
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) bb[k] = L.r.box[L.r.wlist[wave][i + k < nw ? i + k : nw - 1]];
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) {
+                const uint4 b = bb[k];
+                const int x0 = (int16_t)(b.x & 0xffffu), y0 = (int16_t)(b.x >> 16);
+                const int x1 = (int16_t)(b.y & 0xffffu), y1 = (int16_t)(b.y >> 16);
+                if (px >= x0 && px <= x1 && py >= y0 && py <= y1) {
+                    const float zl = __uint_as_float(b.z), zh = __uint_as_float(b.w);
+                    zmin = zl < zmin ? zl : zmin;
+                    zmax = zh > zmax ? zh : zmax;
+                }
             }
         }
         if ((threadIdx.x & 63) == 0) L.wcnt[wave] = 0;
     }
+    // one atomic a wave: those of a wave's lanes on one word wait for each other
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t lo = __shfl_xor((uint32_t)mask, d), hi = __shfl_xor((uint32_t)(mask >> 32), d);
+        mask |= (unsigned long long)lo | ((unsigned long long)hi << 32);
+    }
+    if ((threadIdx.x & 63) == 0 && mask) atomicOr(&L.mask, mask);
     __syncthreads();   // the boxes are read: their bytes become the table
 }
 
