@@ -442,6 +442,8 @@ struct MTileLds {
 // multiplication, so the neighbours' hashes are sums as well: a cell that
 // crosses block faces finds its seven blocks with a few additions and seven
 // reads in flight, where one lookup after another cost ~70 instructions each.
+// A block outside the window gets the valid bit alone: its fields would run into
+// one another, and a neighbour's sum could then come to 0, an empty slot's key.
 constexpr uint32_t kHashMul = 0x9e3779b1u;
 
 __device__ __forceinline__ uint32_t m_neighbour(int n)   // key offset of neighbour n at (n & 1, n >> 1 & 1, n >> 2)
@@ -454,9 +456,10 @@ __device__ __forceinline__ bool m_key(const MTileLds<NT> &L, int k, int bx, int 
 {
     const uint32_t rx = (uint32_t)(bx - L.org[k][0]), ry = (uint32_t)(by - L.org[k][1]),
                    rz = (uint32_t)(bz - L.org[k][2]);
-    key = 0x80000000u | ((uint32_t)k << 24) | (rz << 16) | (ry << 8) | rx;
     const uint32_t m = rx > ry ? rx : ry;
-    return (m > rz ? m : rz) <= 254u;
+    const bool in = (m > rz ? m : rz) <= 254u;
+    key = 0x80000000u | (in ? ((uint32_t)k << 24) | (rz << 16) | (ry << 8) | rx : 0u);
+    return in;
 }
 
 template <int NT>

@@ -231,6 +231,52 @@ def test_close_view_blocks_over_many_tiles():
     assert nhit > 0.2 * VIEW2.width * VIEW2.height
 
 
+def _facing(axis, sign):
+    """submap pose that turns the camera's forward axis (world z) to +- `axis` of the submap"""
+    P = np.eye(4)
+    z, x = np.zeros(3), np.zeros(3)
+    z[axis], x[(axis + 1) % 3] = sign, 1.0
+    P[:3, :3] = np.stack([x, np.cross(z, x), z], axis=1)
+    return P.astype(np.float32)
+
+
+@pytest.mark.parametrize("axis", [0, 1, 2])
+@pytest.mark.parametrize("sign", [-1, 1])
+def test_views_past_the_block_table_s_window(axis, sign):
+    """A tile's block table takes blocks in a window of 254 per axis, centred
+    120 out on the tile's ray: at 2 mm it ends 3.9 to 4.0 m out.  A slanted
+    wall from 3.84 to 4.08 m, seen along each axis of a submap and each way,
+    lies on both sides of the end: blocks left out of the table, cells whose
+    own block is outside with neighbours inside and the reverse."""
+    from oracle import oracle as O
+    from synth.configs import VolumeParams
+    import paper_1708_00783_amd as T
+    import torch
+    vp = VolumeParams(0.002, 0.008, 100, 1 << 16, 1 << 14, 1 << 15)
+    Kw = Intrinsics(320.0, 320.0, 47.5, 35.5, 96, 72)
+    pose = np.eye(4, dtype=np.float32)
+    subs = _facing(axis, sign)[None]
+    u, v = np.meshgrid(np.arange(96), np.arange(72))
+    depth = (3.84 + 0.24 * (0.75 * u / 95 + 0.25 * v / 71)).astype(np.float32)
+    ov = O.Volume.from_params(vp)
+    o = O.Multi([ov], subs)
+    g = T.MultiMap(vp, subs, 96, 72, 96, 72, 1 << 20)
+    for k in range(2):
+        o.integrate_frame(0, depth, Kw.as_array(), pose)
+        g.integrate(to_device(depth), Kw, pose, [0])
+    nblk, _ = compare_tables(g.submap(0), ov, "wall")
+    op, on = o.raycast(96, 72, Kw.as_array(), pose)
+    for tw, th in ((16, 16), (32, 8), (16, 8), (8, 8)):
+        g.set_config(tile_w=tw, tile_h=th)
+        pts = torch.full((72, 96, 4), -7.0, dtype=torch.float32, device="cuda")
+        nrm = torch.full_like(pts, -7.0)
+        g.raycast([(Kw, pose, pts, nrm)])
+        nhit, flips = compare_raycast(pts.cpu().numpy(), nrm.cpu().numpy(), op, on, f"{tw}x{th}")
+        _log(f"axis {axis} sign {sign} {tw}x{th}: blocks {nblk} hits {nhit} flips {flips}")
+        assert nhit > 0.9 * 96 * 72
+    assert g.stats()["flags"] == 0
+
+
 def _pool_map(fn, items):
     import multiprocessing as mp
     import os
