@@ -1,130 +1,20 @@
 // tsdf_swap.h -- host side of block swapping: the note kernels leave for the
-// host, the transfer buffer, and the threads that move blocks between it and
-// the host store.  Internal.
+// host, the transfer buffer, and the copies between it and the host store.
+// Internal.
 #pragma once
 
 #include <emmintrin.h>
-#include <sched.h>
 #include <stdint.h>
 #include <string.h>
 #include <unistd.h>
 
 #include <atomic>
-#include <condition_variable>
-#include <mutex>
-#include <thread>
-#include <vector>
 
 #include "tsdf.h"
+#include "tsdf_copy_pool.h"
 #include "tsdf_internal.h"
 
 namespace tsdf {
-
-// Copies of single blocks by the calling thread and up to kHelpers others.  A
-// block is 1.5 KB somewhere in a store of hundreds of megabytes, so one thread
-// moves them at what its own cache misses allow: 17 GB/s, 280 us for 3000
-// blocks, twice their time on the link.  The helpers sleep between jobs:
-// start() wakes them (they may wait for the job's size there) and finish()
-// returns only once each has put the job down.
-class CopyPool {
-public:
-    static constexpr uint32_t kHelpers = 3, kParts = 8, kGrab = 16;
-
-    struct Job {
-        virtual ~Job() {}
-        virtual uint32_t size() const = 0;        // blocks of the job; 0 while that is not known
-        virtual void block(uint32_t k) = 0;       // copy block k; waits until it can be
-        uint32_t per = ~0u;                       // blocks per part
-        std::atomic<uint32_t> next{0};            // first block nobody has taken
-        std::atomic<uint32_t> done[kParts] = {};  // blocks copied, by part
-    };
-
-    ~CopyPool()
-    {
-        if (th_.empty()) return;
-        if (getpid() != pid_) {   // a forked child has the handles but not the threads
-            for (std::thread &t : th_) t.detach();
-            return;
-        }
-        {
-            std::lock_guard<std::mutex> g(m_);
-            stop_ = true;
-        }
-        cv_.notify_all();
-        for (std::thread &t : th_) t.join();
-    }
-
-    void start(Job &job)
-    {
-        if (!tried_) {
-            tried_ = true;
-            pid_ = getpid();
-            cpu_set_t set;
-            const int cpus = sched_getaffinity(0, sizeof(set), &set) == 0 ? CPU_COUNT(&set) : 1;
-            try {
-                for (int k = 0; k < (int)kHelpers && k < cpus - 1; ++k) th_.emplace_back([this] { helper(); });
-            } catch (...) {   // no more threads to be had: the caller copies what they would have
-            }
-        }
-        {
-            std::lock_guard<std::mutex> g(m_);
-            job_.store(&job, std::memory_order_seq_cst);
-        }
-        cv_.notify_all();
-    }
-
-    // the next few blocks of a job, if there are any
-    static bool take(Job &job)
-    {
-        uint32_t i = job.next.load(std::memory_order_relaxed);
-        const uint32_t n = job.size();
-        if (i >= n) return false;
-        const uint32_t part = i / job.per, rest = job.per - i % job.per;
-        const uint32_t cnt = rest < n - i ? (rest < kGrab ? rest : kGrab) : (n - i < kGrab ? n - i : kGrab);
-        if (!job.next.compare_exchange_weak(i, i + cnt, std::memory_order_acq_rel)) return true;
-        for (uint32_t k = i; k < i + cnt; ++k) job.block(k);
-        job.done[part].fetch_add(cnt, std::memory_order_release);
-        return true;
-    }
-
-    // returns when the `blocks` blocks of a part are copied
-    static void finish_part(Job &job, uint32_t part, uint32_t blocks)
-    {
-        while (job.done[part].load(std::memory_order_acquire) < blocks)
-            if (!take(job)) _mm_pause();
-    }
-
-    void finish()
-    {
-        job_.store(nullptr, std::memory_order_seq_cst);
-        while (busy_.load(std::memory_order_seq_cst) != 0) _mm_pause();
-    }
-
-private:
-    void helper()
-    {
-        for (;;) {
-            {
-                std::unique_lock<std::mutex> g(m_);
-                cv_.wait(g, [this] { return stop_ || job_.load(std::memory_order_seq_cst); });
-                if (stop_) return;
-            }
-            // announced before the look at job_, so that finish() waits for whoever saw a job
-            busy_.fetch_add(1, std::memory_order_seq_cst);
-            while (Job *job = job_.load(std::memory_order_seq_cst))
-                if (!take(*job)) _mm_pause();
-            busy_.fetch_sub(1, std::memory_order_seq_cst);
-        }
-    }
-
-    std::vector<std::thread> th_;
-    std::mutex m_;
-    std::condition_variable cv_;
-    bool stop_ = false, tried_ = false;
-    pid_t pid_ = 0;
-    std::atomic<Job *> job_{nullptr};
-    std::atomic<int> busy_{0};
-};
 
 // swap-in: store blocks idx[k] into slots k of the transfer buffer
 struct SwapInCopy : CopyPool::Job {
