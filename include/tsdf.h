@@ -176,7 +176,7 @@ int tf_range_image(tf_ctx *ctx, const float pose_w2c[16], const tf_intrinsics *i
  * swap_transfer_blocks per call); their device blocks return to the free
  * stack and the entries are marked ptr = -1.  Synchronises `stream` (the
  * host copies the transfer buffer into the store).  TF_E_INVAL if swapping is
- * disabled. */
+ * disabled; after TF_E_HIP the map is as it was before the call. */
 int tf_swap_out(tf_ctx *ctx, tf_stream stream);
 
 /* Copies of host-store blocks (swapping only; synchronous host work): for

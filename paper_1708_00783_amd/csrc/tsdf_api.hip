@@ -523,37 +523,35 @@ int tf_swap_out(tf_ctx *ctx, tf_stream stream)
     if (e == hipSuccess) CopyPool::finish_part(job, 0, m);
     if (helped) h.pool.finish();
     if (e != hipSuccess || job.lost.load()) return TF_E_HIP;
-    if (m) {
-        std::vector<int32_t> &pend = ctx->cand;
-        pend.clear();
-        for (uint32_t k = 0; k < m; ++k) {
-            const uint32_t idx = (uint32_t)h.note[1 + k];
-            if (ctx->host_has[idx]) pend.push_back((int32_t)k);
-            ctx->host_has[idx] = 1;
+    std::vector<int32_t> &pend = ctx->cand;
+    pend.clear();
+    for (uint32_t k = 0; k < m; ++k)
+        if (ctx->host_has[(uint32_t)h.note[1 + k]]) pend.push_back((int32_t)k);
+    const uint32_t np = (uint32_t)pend.size();
+    const auto stored = [&](uint32_t j) { return store + (size_t)(uint32_t)h.note[1 + pend[j]] * kBlockBytes; };
+    if (np) {
+        // the pinned buffer's blocks are consumed: stage the store copies
+        // there (slot j), upload them with their transfer-buffer slots, fuse,
+        // and bring the results back
+        for (uint32_t j = 0; j < np; ++j) {
+            memcpy(h.vox + (size_t)j * kBlockBytes, stored(j), kBlockBytes);
+            h.idx[j] = pend[j];
         }
-        const uint32_t np = (uint32_t)pend.size();
-        if (np) {
-            // the pinned buffer's blocks are consumed: stage the store copies
-            // there (slot j), upload them with their transfer-buffer slots, fuse,
-            // and bring the results back
-            std::vector<int32_t> entry(np);
-            for (uint32_t j = 0; j < np; ++j) {
-                entry[j] = (int32_t)(uint32_t)h.note[1 + pend[j]];
-                memcpy(h.vox + (size_t)j * kBlockBytes, store + (size_t)entry[j] * kBlockBytes, kBlockBytes);
-                h.idx[j] = pend[j];
-            }
-            e = hipMemcpyAsync(v.xfer_pend, h.idx, (size_t)np * 4, hipMemcpyHostToDevice, s);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(v.xfer_host, h.vox, (size_t)np * kBlockBytes, hipMemcpyHostToDevice, s);
-            if (e == hipSuccess) e = launch_swap_merge_out(v, np, s);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(h.vox, v.xfer_host, (size_t)np * kBlockBytes, hipMemcpyDeviceToHost, s);
-            if (e == hipSuccess) e = hipStreamSynchronize(s);
-            if (e != hipSuccess) return TF_E_HIP;
-            for (uint32_t j = 0; j < np; ++j)
-                memcpy(store + (size_t)entry[j] * kBlockBytes, h.vox + (size_t)j * kBlockBytes, kBlockBytes);
-        }
+        e = hipMemcpyAsync(v.xfer_pend, h.idx, (size_t)np * 4, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(v.xfer_host, h.vox, (size_t)np * kBlockBytes, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = launch_swap_merge_out(v, np, s);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(h.vox, v.xfer_host, (size_t)np * kBlockBytes, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return TF_E_HIP;
     }
+    // the host has every block: only now do they leave the device, and only
+    // with that launched do the store's copies count
+    e = launch_swap_release(v, m, s);
+    if (e != hipSuccess) return TF_E_HIP;
+    for (uint32_t j = 0; j < np; ++j) memcpy(stored(j), h.vox + (size_t)j * kBlockBytes, kBlockBytes);
+    for (uint32_t k = 0; k < m; ++k) ctx->host_has[(uint32_t)h.note[1 + k]] = 1;
     return TF_OK;
 }
 

@@ -1244,8 +1244,7 @@ __device__ __forceinline__ void note_word(unsigned long long *p, uint32_t value,
                        __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// offsets of the chunks, and the free stack's new height: the blocks that
-// leave (the gather puts them there)
+// offsets of the chunks, and the number of candidates for the host
 __global__ __launch_bounds__(256) void k_swap_scan(Vol v, uint32_t nchunks, uint32_t call)
 {
     __shared__ uint32_t lds[4];
@@ -1259,10 +1258,8 @@ __global__ __launch_bounds__(256) void k_swap_scan(Vol v, uint32_t nchunks, uint
         carry += total;
     }
     if (threadIdx.x == 0) {
-        const uint32_t n = carry < v.transfer_blocks ? carry : v.transfer_blocks;
         v.ctrl->n_swap_cand = carry;
-        v.ctrl->free_blocks += (int32_t)n;
-        v.ctrl->n_swapped_out = n;
+        v.ctrl->n_swapped_out = 0u;
         note_word(v.note, carry, call);
     }
 }
@@ -1295,8 +1292,7 @@ __global__ __launch_bounds__(256) void k_swap_pick(Vol v)
 }
 
 // The selected entries' device blocks into the host's transfer buffer, over
-// the link from here, and into the device's for the secondary integration;
-// their blocks back onto the free stack, the entries marked swapped out, the
+// the link from here, and into the device's for the secondary integration; the
 // visibility marks cleared on the side.  One wave per block, which notes its
 // entry when the block is on the host: the host's copy into its store runs
 // while later blocks are on the link.  The block's stores go through the
@@ -1309,8 +1305,8 @@ __global__ __launch_bounds__(256) void k_swap_gather(Vol v, uint32_t call)
     const uint32_t lane = lane_id();
     const uint32_t gwave = (blockIdx.x * 256u + threadIdx.x) / kWave;
     const uint32_t nwaves = gridDim.x * (256u / kWave);
-    const uint32_t n = v.ctrl->n_swapped_out;
-    const int32_t head = v.ctrl->free_blocks - (int32_t)n;
+    const uint32_t cand = v.ctrl->n_swap_cand;
+    const uint32_t n = cand < v.transfer_blocks ? cand : v.transfer_blocks;
     for (uint32_t k = gwave; k < n; k += nwaves) {
         const uint32_t e = (uint32_t)v.xfer_idx[k];
         const int ptr = load_entry(v.entries, e).w;
@@ -1326,14 +1322,28 @@ __global__ __launch_bounds__(256) void k_swap_gather(Vol v, uint32_t call)
             dev[lane + 64u * q] = x[q];
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (lane == 0) {
-            note_word(v.note + 1 + k, e, call);
-            v.free_blocks[head + (int32_t)k] = ptr;
-            v.entries[e].ptr = kPtrSwapped;
-            v.host_has[e] = 1;
-        }
+        if (lane == 0) note_word(v.note + 1 + k, e, call);
     }
     mark_visible(v, (uint8_t)0);
+}
+
+// The first n selected entries' blocks back onto the free stack, the entries
+// marked swapped out (one workgroup).  A launch of its own, made once the host
+// holds the blocks: until then the map is as it was, whatever fails.
+__global__ __launch_bounds__(1024) void k_swap_release(Vol v, uint32_t n)
+{
+    const int32_t head = v.ctrl->free_blocks;
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < n; k += 1024u) {
+        const int e = v.xfer_idx[k];
+        v.free_blocks[head + (int32_t)k] = v.entries[e].ptr;
+        v.entries[e].ptr = kPtrSwapped;
+        v.host_has[e] = 1;
+    }
+    if (threadIdx.x == 0) {
+        v.ctrl->free_blocks = head + (int32_t)n;
+        v.ctrl->n_swapped_out = n;
+    }
 }
 
 // ============================================================================
@@ -1506,6 +1516,12 @@ hipError_t launch_swap_out(const Vol &v, uint32_t call, hipStream_t s)
     hipLaunchKernelGGL(k_swap_pick, dim3(nchunks), dim3(256), 0, s, v);
     // 256 waves of 1.5 KB each cover the link's latency several times
     hipLaunchKernelGGL(k_swap_gather, dim3(64), dim3(256), 0, s, v, call);
+    return hipGetLastError();
+}
+
+hipError_t launch_swap_release(const Vol &v, uint32_t n, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_swap_release, dim3(1), dim3(1024), 0, s, v, n);
     return hipGetLastError();
 }
 

@@ -233,3 +233,109 @@ def test_transfer_buffers_the_device_cannot_use_as_given(buffer):
 def _away(P):
     """the same camera turned around: it sees none of what it saw"""
     return (np.diag([-1.0, 1.0, -1.0, 1.0]) @ np.asarray(P, np.float64)).astype(np.float32)
+
+
+_FAILING = r"""
+import ctypes, os, sys
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)      # before anything that uses the HIP runtime
+sys.path[:0] = [sys.argv[2], os.path.join(sys.argv[2], "tests")]
+import numpy as np
+import torch
+torch.zeros(1, device="cuda")
+hip = [l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l][0]
+assert shim.shim_init(hip.encode()) == 0
+import paper_1708_00783_amd as T
+from synth import configs
+from test_gpu_swap import _away, _state
+from gpu_helpers import to_device
+
+nth, cap = int(sys.argv[3]), int(sys.argv[4])
+d, p, K, _ = configs.c1_frames(3)
+vols = [T.Volume(configs.C1_VOLUME, K.width, K.height, swap_transfer_blocks=cap) for _ in range(2)]
+failed = 0
+
+def out_all(g, fail):
+    global failed
+    for _ in range(500):
+        if fail:
+            pos, off, ptr = g.entries()
+            host = g.host_voxels(np.arange(g.n_entries, dtype=np.int32)[ptr != -2])
+            st = g.stats()
+            shim.shim_fail(nth)
+            try:
+                g.swap_out()
+            except T.TsdfError:
+                failed += 1
+                pos2, off2, ptr2 = g.entries()
+                host2 = g.host_voxels(np.arange(g.n_entries, dtype=np.int32)[ptr2 != -2])
+                assert np.array_equal(ptr, ptr2), "a failed call moved blocks"
+                assert all(np.array_equal(a, b) for a, b in zip(host, host2)), "a failed call changed the store"
+                assert g.stats()["n_allocated"] == st["n_allocated"]
+            shim.shim_fail(0)
+        g.swap_out()
+        if g.stats()["n_swapped_out"] == 0:
+            return
+    raise AssertionError("blocks stay on the device")
+
+# Both volumes start as one map and see only what is in it: two runs of the same
+# frames give the blocks of a bucket their entries in the order of a race, and a
+# small transfer takes blocks by entry, so that they would be fused at other times.
+for k in range(3):
+    vols[0].alloc_and_visible(to_device(d[k]), K, p[k])
+    vols[0].integrate(to_device(d[k]), p[k])
+vols[0].save(sys.argv[5])
+vols[1].load(sys.argv[5])
+for k, away in ((1, False), (1, True), (2, False), (2, False), (2, True)):
+    for i, g in enumerate(vols):
+        pose = _away(p[k]) if away else p[k]
+        g.alloc_and_visible(to_device(np.zeros_like(d[k]) if away else d[k]), K, pose)
+        if away:
+            out_all(g, i == 1)
+        else:
+            g.integrate(to_device(d[k]), pose)
+a, b = (_state(vol_g=g) for g in vols)
+assert a.keys() == b.keys() and len(a) > 500
+for q in a:
+    assert all(np.array_equal(x, y) for x, y in zip(a[q], b[q])), q
+print("failed calls", failed, "blocks", len(a), flush=True)
+assert failed >= 2
+"""
+
+_SHIM = r"""
+#include <dlfcn.h>
+static int (*real)(void *);
+static int left;
+extern "C" int shim_init(const char *path)
+{
+    real = (int (*)(void *))dlsym(dlopen(path, RTLD_NOLOAD | RTLD_LAZY), "hipStreamSynchronize");
+    return real ? 0 : 1;
+}
+extern "C" void shim_fail(int nth) { left = nth; }
+extern "C" int hipStreamSynchronize(void *s)
+{
+    if (!real) real = (int (*)(void *))dlsym(RTLD_NEXT, "hipStreamSynchronize");
+    const int e = real(s);
+    return left && --left == 0 ? 999 : e;
+}
+"""
+
+
+@pytest.mark.parametrize("nth,cap", [(1, 4096), (1, 100), (2, 100)])
+def test_a_failed_swap_out_leaves_the_map(nth, cap, tmp_path):
+    """tf_swap_out whose first wait (for the blocks) or second (for pending
+    host copies fused with them) reports an error: no block has left the
+    device, the store is unchanged, and the calls that follow end in the map of
+    a volume without failures.  The error comes from a stand-in for
+    hipStreamSynchronize, which waits and then reports it, in a process of its own."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src, so, script = tmp_path / "shim.cpp", tmp_path / "shim.so", tmp_path / "failing.py"
+    src.write_text(_SHIM)
+    script.write_text(_FAILING)
+    subprocess.run(["g++", "-shared", "-fPIC", "-O1", "-o", str(so), str(src), "-ldl"], check=True)
+    r = subprocess.run([sys.executable, "-u", str(script), str(so), root, str(nth), str(cap),
+                        str(tmp_path / "map")], timeout=100, capture_output=True, text=True)
+    print(r.stdout, flush=True)
+    assert r.returncode == 0, r.stderr[-2000:]
