@@ -171,38 +171,32 @@ hipError_t swap_in(tf_ctx *ctx, hipStream_t s)
     SwapHost &h = *ctx->swap;
     hipError_t e = launch_swap_candidates(v, s);
     if (e != hipSuccess) return e;
+    e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return e;
+    const uint32_t T = ctx->p.swap_transfer_blocks, n = (uint32_t)h.note[0], m = std::min(n, T);
+    if (m == 0) return hipSuccess;
+    for (uint32_t k = 0; k < m; ++k) h.idx[k] = (int32_t)h.note[1 + k];
+    if (n > T) {   // the order of those taken is of no account
+        std::vector<int32_t> &cand = ctx->cand;
+        cand.resize(n);
+        for (uint32_t k = 0; k < n; ++k) cand[k] = (int32_t)h.note[1 + k];
+        std::nth_element(cand.begin(), cand.begin() + T, cand.end());
+        memcpy(h.idx, cand.data(), (size_t)T * 4);
+        ctx->host_flags |= TF_FLAG_TRANSFER_OVERFLOW;
+    }
     SwapInCopy job;
+    job.n = m;
+    job.per = SwapHost::part(m);
     job.idx = h.idx;
     job.store = (const uint8_t *)ctx->h_store;
     job.vox = h.vox;
-    bool helped = SwapHost::many(h.last_in);
+    const bool helped = SwapHost::many(m);
     if (helped) h.pool.start(job);
-    e = hipStreamSynchronize(s);
-    const uint32_t T = ctx->p.swap_transfer_blocks, n = e == hipSuccess ? (uint32_t)h.note[0] : 0u;
-    const uint32_t m = std::min(n, T);
-    h.last_in = m;
-    if (m) {
-        for (uint32_t k = 0; k < m; ++k) h.idx[k] = (int32_t)h.note[1 + k];
-        if (n > T) {   // the order of those taken is of no account
-            std::vector<int32_t> &cand = ctx->cand;
-            cand.resize(n);
-            for (uint32_t k = 0; k < n; ++k) cand[k] = (int32_t)h.note[1 + k];
-            std::nth_element(cand.begin(), cand.begin() + T, cand.end());
-            memcpy(h.idx, cand.data(), (size_t)T * 4);
-            ctx->host_flags |= TF_FLAG_TRANSFER_OVERFLOW;
-        }
-        job.per = SwapHost::part(m);
-        job.n.store(m, std::memory_order_release);
-        if (!helped && SwapHost::many(m)) {
-            helped = true;
-            h.pool.start(job);
-        }
-        for (uint32_t k = 0; k < m; ++k) ctx->host_has[h.idx[k]] = 0;
-        for (uint32_t k = 0, at = 0; at < m; ++k, at += job.per) {
-            const uint32_t cnt = std::min(job.per, m - at);
-            CopyPool::finish_part(job, k, cnt);
-            if (e == hipSuccess) e = launch_swap_merge(v, at, cnt, s);
-        }
+    for (uint32_t k = 0; k < m; ++k) ctx->host_has[h.idx[k]] = 0;
+    for (uint32_t k = 0, at = 0; at < m; ++k, at += job.per) {
+        const uint32_t cnt = std::min(job.per, m - at);
+        CopyPool::finish_part(job, k, cnt);
+        if (e == hipSuccess) e = launch_swap_merge(v, at, cnt, s);
     }
     if (helped) h.pool.finish();
     return e;
@@ -503,23 +497,29 @@ int tf_swap_out(tf_ctx *ctx, tf_stream stream)
     Timed t(ctx, TF_K_SWAP, s);
     SwapHost &h = *ctx->swap;
     uint8_t *store = (uint8_t *)ctx->h_store;
-    hipError_t e = launch_swap_out(v, ++h.call, s);
+    hipError_t e = launch_swap_select(v, ++h.call, s);
+    if (e == hipSuccess) e = hipEventRecord(h.counted, s);
+    if (e == hipSuccess) e = launch_swap_gather(v, h.call, s);
+    // the helpers are woken for blocks that are on their way, not for the wait
+    // for what the stream still has to do before them
+    if (e == hipSuccess) e = hipEventSynchronize(h.counted);
     if (e != hipSuccess) return TF_E_HIP;
+    const uint64_t w = SwapOutCopy::word(h.note);
+    if ((uint32_t)(w >> 32) != h.call) return TF_E_HIP;
+    const uint32_t m = std::min((uint32_t)w, ctx->p.swap_transfer_blocks);
     // blocks whose host copy never came back in are fused with it (the
     // secondary integration, on the device, below); the others are copied
     SwapOutCopy job;
     job.note = h.note;
     job.call = h.call;
-    job.cap = ctx->p.swap_transfer_blocks;
+    job.n = m;
     job.held = ctx->host_has.data();
     job.store = store;
     job.vox = h.vox;
-    const bool helped = SwapHost::many(h.last_out);
+    const bool helped = SwapHost::many(m);
     if (helped) h.pool.start(job);
     e = hipStreamSynchronize(s);
     job.synced.store(true, std::memory_order_release);
-    const uint32_t m = job.size();
-    h.last_out = m;
     if (e == hipSuccess) CopyPool::finish_part(job, 0, m);
     if (helped) h.pool.finish();
     if (e != hipSuccess || job.lost.load()) return TF_E_HIP;

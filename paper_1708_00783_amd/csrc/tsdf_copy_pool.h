@@ -21,19 +21,34 @@ namespace tsdf {
 // block is 1.5 KB somewhere in a store of hundreds of megabytes, so one thread
 // moves them at what its own cache misses allow: 17 GB/s, 280 us for 3000
 // blocks, twice their time on the link.  The helpers sleep between jobs:
-// start() wakes them (they may wait for the job's size there) and finish()
-// returns only once each has put the job down.
+// start() wakes them, each goes back to sleep when a job has no more blocks to
+// take, and finish() returns only once each has put the job down.
 class CopyPool {
 public:
     static constexpr uint32_t kHelpers = 3, kParts = 8, kGrab = 16;
 
     struct Job {
         virtual ~Job() {}
-        virtual uint32_t size() const = 0;        // blocks of the job; 0 while that is not known
+        virtual uint32_t size() const = 0;        // blocks of the job
         virtual void block(uint32_t k) = 0;       // copy block k; waits until it can be
         uint32_t per = ~0u;                       // blocks per part
         std::atomic<uint32_t> next{0};            // first block nobody has taken
         std::atomic<uint32_t> done[kParts] = {};  // blocks copied, by part
+    };
+
+    // One turn of a wait for another thread or the device: a pause for some tens
+    // of microseconds, then sleep.  What is waited for is due within that; where
+    // it is not (a busy device, a container short of CPU time), a thread that
+    // goes on spinning takes the time from those that get on with the work.
+    struct Turn {
+        uint32_t n = 0;
+        void operator()()
+        {
+            if (++n < 1024u)
+                _mm_pause();
+            else
+                usleep(20);
+        }
     };
 
     ~CopyPool()
@@ -70,7 +85,8 @@ public:
         }
         {
             std::lock_guard<std::mutex> g(s_->m);
-            s_->job.store(&job, std::memory_order_seq_cst);
+            s_->job = &job;
+            ++s_->jobs;
         }
         s_->cv.notify_all();
     }
@@ -92,15 +108,19 @@ public:
     // returns when the `blocks` blocks of a part are copied
     static void finish_part(Job &job, uint32_t part, uint32_t blocks)
     {
+        Turn turn;
         while (job.done[part].load(std::memory_order_acquire) < blocks)
-            if (!take(job)) _mm_pause();
+            if (!take(job)) turn();
     }
 
     void finish()
     {
         if (!s_) return;
-        s_->job.store(nullptr, std::memory_order_seq_cst);
-        while (s_->busy.load(std::memory_order_seq_cst) != 0) _mm_pause();
+        {
+            std::lock_guard<std::mutex> g(s_->m);
+            s_->job = nullptr;
+        }
+        for (Turn turn; s_->busy.load(std::memory_order_acquire) != 0;) turn();
     }
 
 private:
@@ -111,23 +131,25 @@ private:
         std::condition_variable cv;
         bool stop = false;
         const pid_t pid = getpid();
-        std::atomic<Job *> job{nullptr};
-        std::atomic<int> busy{0};
+        Job *job = nullptr;
+        uint64_t jobs = 0;           // jobs started
+        std::atomic<int> busy{0};    // helpers that hold the job
     };
 
     static void helper(Shared &s)
     {
-        for (;;) {
+        for (uint64_t seen = 0;;) {
+            Job *job;
             {
                 std::unique_lock<std::mutex> g(s.m);
-                s.cv.wait(g, [&s] { return s.stop || s.job.load(std::memory_order_seq_cst); });
+                s.cv.wait(g, [&] { return s.stop || (s.job && s.jobs != seen); });
                 if (s.stop) return;
+                seen = s.jobs;
+                job = s.job;
+                s.busy.fetch_add(1, std::memory_order_relaxed);   // under the lock: finish() sees it or we see no job
             }
-            // announced before the look at the job, so that finish() waits for whoever saw one
-            s.busy.fetch_add(1, std::memory_order_seq_cst);
-            while (Job *job = s.job.load(std::memory_order_seq_cst))
-                if (!take(*job)) _mm_pause();
-            s.busy.fetch_sub(1, std::memory_order_seq_cst);
+            while (take(*job)) {}
+            s.busy.fetch_sub(1, std::memory_order_release);
         }
     }
 

@@ -151,7 +151,8 @@ hipError_t launch_range_write(const Vol &v, const Cam &c, float *zmin, float *zm
 constexpr int kSwapChunk = 4096;        // entries per workgroup of the ordered swap-out selection
 hipError_t launch_swap_candidates(const Vol &v, hipStream_t s);
 hipError_t launch_swap_merge(const Vol &v, uint32_t at, uint32_t n, hipStream_t s);
-hipError_t launch_swap_out(const Vol &v, uint32_t call, hipStream_t s);
+hipError_t launch_swap_select(const Vol &v, uint32_t call, hipStream_t s);
+hipError_t launch_swap_gather(const Vol &v, uint32_t call, hipStream_t s);
 hipError_t launch_swap_release(const Vol &v, uint32_t n, hipStream_t s);
 hipError_t launch_swap_merge_out(const Vol &v, uint32_t n, hipStream_t s);
 hipError_t launch_camera_depth(const float4 *pts, int n, const float *M, float *depth, hipStream_t s);

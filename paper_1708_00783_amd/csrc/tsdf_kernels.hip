@@ -1507,12 +1507,18 @@ hipError_t launch_swap_merge(const Vol &v, uint32_t at, uint32_t n, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t launch_swap_out(const Vol &v, uint32_t call, hipStream_t s)
+hipError_t launch_swap_select(const Vol &v, uint32_t call, hipStream_t s)
 {
     const uint32_t nchunks = (v.n_entries + kSwapChunk - 1) / kSwapChunk;
     hipLaunchKernelGGL(k_mark_visible, dim3(256), dim3(256), 0, s, v);
     hipLaunchKernelGGL(k_swap_count, dim3(nchunks), dim3(256), 0, s, v);
     hipLaunchKernelGGL(k_swap_scan, dim3(1), dim3(256), 0, s, v, nchunks, call);
+    return hipGetLastError();
+}
+
+hipError_t launch_swap_gather(const Vol &v, uint32_t call, hipStream_t s)
+{
+    const uint32_t nchunks = (v.n_entries + kSwapChunk - 1) / kSwapChunk;
     hipLaunchKernelGGL(k_swap_pick, dim3(nchunks), dim3(256), 0, s, v);
     // 256 waves of 1.5 KB each cover the link's latency several times
     hipLaunchKernelGGL(k_swap_gather, dim3(64), dim3(256), 0, s, v, call);

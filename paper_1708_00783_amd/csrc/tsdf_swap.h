@@ -18,11 +18,11 @@ namespace tsdf {
 
 // swap-in: store blocks idx[k] into slots k of the transfer buffer
 struct SwapInCopy : CopyPool::Job {
-    std::atomic<uint32_t> n{0};
+    uint32_t n = 0;
     const int32_t *idx = nullptr;
     const uint8_t *store = nullptr;
     uint8_t *vox = nullptr;
-    uint32_t size() const override { return n.load(std::memory_order_acquire); }
+    uint32_t size() const override { return n; }
     void block(uint32_t k) override
     {
         memcpy(vox + (size_t)k * kBlockBytes, store + (size_t)idx[k] * kBlockBytes, kBlockBytes);
@@ -34,21 +34,17 @@ struct SwapInCopy : CopyPool::Job {
 // blocks the store already holds.  A note word is entry | call << 32.
 struct SwapOutCopy : CopyPool::Job {
     const uint64_t *note = nullptr;
-    uint32_t call = 0, cap = 0;
+    uint32_t call = 0, n = 0;
     const uint8_t *held = nullptr;
     uint8_t *store = nullptr;
     const uint8_t *vox = nullptr;
     std::atomic<bool> synced{false}, lost{false};
     static uint64_t word(const uint64_t *p) { return __atomic_load_n(p, __ATOMIC_ACQUIRE); }
-    uint32_t size() const override
-    {
-        const uint64_t w = word(note);
-        return (uint32_t)(w >> 32) == call ? ((uint32_t)w < cap ? (uint32_t)w : cap) : 0u;
-    }
+    uint32_t size() const override { return n; }
     void block(uint32_t k) override
     {
         uint64_t w;
-        for (;;) {
+        for (CopyPool::Turn turn;;) {
             const bool last = synced.load(std::memory_order_acquire);
             w = word(note + 1 + k);
             if ((uint32_t)(w >> 32) == call) break;
@@ -56,7 +52,7 @@ struct SwapOutCopy : CopyPool::Job {
                 lost.store(true, std::memory_order_relaxed);
                 return;
             }
-            _mm_pause();
+            turn();
         }
         const size_t e = (uint32_t)w;
         if (!held[e]) memcpy(store + e * kBlockBytes, vox + (size_t)k * kBlockBytes, kBlockBytes);
@@ -69,7 +65,7 @@ struct SwapHost {
     int32_t *idx = nullptr;
     void *own = nullptr;        // it, where the caller's is not one the device can use
     uint32_t call = 0;          // of swap-out, in the words of its note
-    uint32_t last_in = 0, last_out = 0;   // blocks the last call moved
+    hipEvent_t counted = nullptr;   // swap-out: the note has the number of blocks
     CopyPool pool;
     pid_t pid = getpid();
 
@@ -80,7 +76,7 @@ struct SwapHost {
         return per < 256u ? 256u : per;
     }
 
-    // helpers are woken ahead of a wait for the device that is likely to end in as many blocks again
+    // blocks that are worth waking the helpers for
     static bool many(uint32_t blocks) { return blocks >= 8 * CopyPool::kGrab; }
 
     hipError_t init(const tf_params &p, void *h_transfer, size_t bytes, Vol &v)
@@ -90,6 +86,7 @@ struct SwapHost {
         const size_t most = p.n_blocks > p.swap_transfer_blocks ? p.n_blocks : p.swap_transfer_blocks;
         hipError_t e = hipHostMalloc((void **)&note, 8 * (1 + most), hipHostMallocCoherent);
         if (e == hipSuccess) e = hipHostGetDevicePointer(&d, note, 0);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&counted, hipEventDisableTiming);
         if (e != hipSuccess) return e;
         memset(note, 0, 8 * (1 + most));
         v.note = (unsigned long long *)d;
@@ -119,6 +116,7 @@ struct SwapHost {
         if (getpid() != pid) return;   // a forked child: the parent's to give back
         if (own) (void)hipHostFree(own);
         if (note) (void)hipHostFree(note);
+        if (counted) (void)hipEventDestroy(counted);
     }
 };
 

@@ -92,3 +92,59 @@ int main()
 }
 """)
     assert r.returncode == 0, r.stderr
+
+
+def test_helpers_sleep_when_a_job_has_no_more_blocks(tmp_path):
+    """Between the last block taken and finish() -- a wait for the device -- the helpers use no CPU time."""
+    r = run(tmp_path, r"""
+int main()
+{
+    CopyPool pool;
+    if (!copy_all(pool, 500)) return 1;
+    Count job(500);
+    pool.start(job);
+    CopyPool::finish_part(job, 0, 500);
+    struct rusage a, b;
+    getrusage(RUSAGE_SELF, &a);
+    usleep(400000);
+    getrusage(RUSAGE_SELF, &b);
+    pool.finish();
+    const double used = (b.ru_utime.tv_sec - a.ru_utime.tv_sec) + 1e-6 * (b.ru_utime.tv_usec - a.ru_utime.tv_usec);
+    printf("%.3f s\n", used);
+    return job.whole() && used < 0.1 ? 0 : 2;
+}
+""")
+    assert r.returncode == 0, r.stdout
+
+
+def test_a_wait_for_a_block_gives_up_its_core(tmp_path):
+    """Blocks that come late are waited for asleep, not spinning."""
+    r = run(tmp_path, r"""
+struct Late : Count {
+    std::atomic<bool> there{false};
+    using Count::Count;
+    void block(uint32_t k) override
+    {
+        for (CopyPool::Turn turn; !there.load();) turn();
+        Count::block(k);
+    }
+};
+int main()
+{
+    CopyPool pool;
+    if (!copy_all(pool, 500)) return 1;
+    Late job(500);
+    pool.start(job);
+    struct rusage a, b;
+    getrusage(RUSAGE_SELF, &a);
+    usleep(400000);
+    getrusage(RUSAGE_SELF, &b);
+    job.there = true;
+    CopyPool::finish_part(job, 0, 500);
+    pool.finish();
+    const double used = (b.ru_utime.tv_sec - a.ru_utime.tv_sec) + 1e-6 * (b.ru_utime.tv_usec - a.ru_utime.tv_usec);
+    printf("%.3f s\n", used);
+    return job.whole() && used < 0.3 ? 0 : 2;
+}
+""")
+    assert r.returncode == 0, r.stdout

@@ -339,3 +339,44 @@ def test_a_failed_swap_out_leaves_the_map(nth, cap, tmp_path):
                         str(tmp_path / "map")], timeout=100, capture_output=True, text=True)
     print(r.stdout, flush=True)
     assert r.returncode == 0, r.stderr[-2000:]
+
+
+def test_waits_for_the_stream_keep_the_helpers_asleep():
+    """Swap calls that move nothing behind some 150 ms of work on their stream:
+    beside the caller's own wait, no thread spins.  (The calls before moved
+    hundreds of blocks each way, for which the copy threads were woken.)"""
+    import time
+    import torch
+    import paper_1708_00783_amd as T
+    from synth import configs
+    d, p, K, _ = configs.c1_frames(2)
+    g = T.Volume(configs.C1_VOLUME, K.width, K.height, swap_transfer_blocks=4096)
+    dd, zero = to_device(d[0]), to_device(np.zeros_like(d[0]))
+    a = torch.zeros((4096, 4096), dtype=torch.float32, device="cuda")
+
+    def busy():
+        for _ in range(100):
+            torch.mm(a, a)
+
+    def timed(call):
+        torch.cuda.synchronize()
+        busy()
+        t0, c0 = time.perf_counter(), time.process_time()
+        call()
+        return time.perf_counter() - t0, time.process_time() - c0
+
+    busy()
+    for _ in range(2):                     # out, in, and out again
+        g.alloc_and_visible(dd, K, p[0])
+        g.integrate(dd, p[0])
+        g.alloc_and_visible(zero, K, _away(p[0]))
+        g.swap_out()
+    assert g.stats()["n_swapped_out"] > 128
+    w, c = timed(g.swap_out)
+    print(f"swap_out behind busy stream: wall {w * 1e3:.1f} ms, CPU {c * 1e3:.1f} ms", flush=True)
+    assert w > 0.02 and c < 2 * w + 0.01
+    g.alloc_and_visible(dd, K, p[0])
+    assert g.stats()["n_swapped_in"] > 128
+    w, c = timed(lambda: g.alloc_and_visible(dd, K, p[0]))
+    print(f"alloc_and_visible behind busy stream: wall {w * 1e3:.1f} ms, CPU {c * 1e3:.1f} ms", flush=True)
+    assert w > 0.02 and c < 2 * w + 0.01
