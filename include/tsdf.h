@@ -132,8 +132,12 @@ size_t tf_host_transfer_bytes(const tf_params *p);
 /* Create a volume in d_workspace (256-byte aligned, `bytes` >= tf_workspace_bytes).
  * With swapping enabled, h_store (tf_host_store_bytes, any host memory) and
  * h_transfer (tf_host_transfer_bytes, pinned: hipHostMalloc) are required;
- * both stay owned by the caller and must outlive the context.  The workspace
- * is initialised on `stream` (every entry unallocated, free lists full). */
+ * both stay owned by the caller and must outlive the context.  Kernels use
+ * h_transfer where it lies if it is 16-byte aligned and of hipHostMalloc's
+ * default flags or hipHostMallocCoherent; in place of any other buffer the
+ * context pins one of its own.  The workspace is initialised on `stream` (every
+ * entry unallocated, free lists full).  tf_destroy of a swapping volume gives
+ * pinned memory back, which waits for the device. */
 int tf_create(const tf_params *p, void *d_workspace, size_t bytes, void *h_store,
               void *h_transfer, tf_stream stream, tf_ctx **out);
 int tf_destroy(tf_ctx *ctx);

@@ -90,17 +90,22 @@ struct SwapHost {
         if (e != hipSuccess) return e;
         memset(note, 0, 8 * (1 + most));
         v.note = (unsigned long long *)d;
-        // kernels write and read the transfer buffer as vectors: the caller's
-        // if it is pinned and aligned, else one of its size
+        // Kernels write and read the transfer buffer as vectors, while the host
+        // reads other blocks of it, and writes other parts: the caller's if it is
+        // pinned, coherent (as hipHostMalloc's default is) and aligned, else one
+        // of its size.
         hipPointerAttribute_t a;
+        unsigned flags = hipHostMallocNonCoherent;
         d = nullptr;
-        if (hipPointerGetAttributes(&a, h_transfer) == hipSuccess && a.type == hipMemoryTypeHost)
+        if (hipPointerGetAttributes(&a, h_transfer) == hipSuccess && a.type == hipMemoryTypeHost &&
+            hipHostGetFlags(&flags, h_transfer) == hipSuccess &&
+            (flags == hipHostMallocDefault || ((flags & hipHostMallocCoherent) && !(flags & hipHostMallocNonCoherent))))
             d = a.devicePointer;
         else
             (void)hipGetLastError();
         vox = (uint8_t *)h_transfer;
         if (!d || ((uintptr_t)d & 15u) || ((uintptr_t)h_transfer & 15u)) {
-            e = hipHostMalloc(&own, bytes, hipHostMallocDefault);
+            e = hipHostMalloc(&own, bytes, hipHostMallocCoherent);
             if (e == hipSuccess) e = hipHostGetDevicePointer(&d, own, 0);
             if (e != hipSuccess) return e;
             vox = (uint8_t *)own;

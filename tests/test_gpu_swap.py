@@ -380,3 +380,42 @@ def test_waits_for_the_stream_keep_the_helpers_asleep():
     w, c = timed(lambda: g.alloc_and_visible(dd, K, p[0]))
     print(f"alloc_and_visible behind busy stream: wall {w * 1e3:.1f} ms, CPU {c * 1e3:.1f} ms", flush=True)
     assert w > 0.02 and c < 2 * w + 0.01
+
+
+def test_a_transfer_buffer_that_is_not_coherent_is_left_alone():
+    """The host reads and writes parts of the transfer buffer while kernels use
+    others, which only coherent memory allows: a buffer pinned as non-coherent
+    is not touched, and blocks swap out, in and out again as with Volume's own."""
+    import ctypes
+    import torch
+    import paper_1708_00783_amd as T
+    from synth import configs
+    d, p, K, _ = configs.c1_frames(8)
+    a = T.Volume(configs.C1_VOLUME, K.width, K.height, swap_transfer_blocks=4096)
+    L, par = T.lib(), a.params
+    hip = ctypes.CDLL([x.split()[-1] for x in open("/proc/self/maps") if "libamdhip64" in x][0])
+    ws = torch.empty(T.tf_workspace_bytes(par), dtype=torch.uint8, device="cuda")
+    store = np.zeros(int(L.tf_host_store_bytes(ctypes.byref(par))), np.uint8)
+    n = int(L.tf_host_transfer_bytes(ctypes.byref(par)))
+    xfer = ctypes.c_void_p()
+    assert hip.hipHostMalloc(ctypes.byref(xfer), ctypes.c_size_t(n), ctypes.c_uint(0x80000000)) == 0
+    held = np.ctypeslib.as_array((ctypes.c_uint8 * n).from_address(xfer.value))
+    held[:] = 0xa5
+    ctx = T.tf_create(par, ws.data_ptr(), ws.numel(), ctypes.c_void_p(store.ctypes.data), xfer, None)
+    b = T.Volume.borrowed(ctx, par, (ws, store))
+    try:
+        for k in (0, 1, 0, 7):
+            for g in (a, b):
+                g.frame(to_device(d[k]), K, p[k])
+                g.alloc_and_visible(to_device(np.zeros_like(d[k])), T.make_intrinsics(K), _away(p[k]))
+                g.swap_out()
+            assert b.stats()["n_swapped_out"] == a.stats()["n_swapped_out"] > 128
+            ra, rb = _state(vol_g=a), _state(vol_g=b)
+            assert ra.keys() == rb.keys()
+            for q in ra:
+                assert all(np.array_equal(x, y) for x, y in zip(ra[q], rb[q]))
+        torch.cuda.synchronize()
+        assert (held == 0xa5).all()
+    finally:
+        L.tf_destroy(ctx)
+        hip.hipHostFree(xfer)
