@@ -8,10 +8,11 @@
 // images of a depth camera leave the time to one pixel's chain of taps.  So
 // the window is unrolled for each radius: its LDS reads and exponentials
 // overlap, the weights come with the arguments, and a tap without depth is
-// selected away instead of branched around.  333x251, radius 2: 7.1 -> 4.6 us;
-// from some 300000 pixels on bound by vector instructions: 1280x720, radius 2
-// 17.9 -> 14.3, radius 3 29.5 -> 24.3, radius 5 63.5 -> 53
-// (57 in a loop); 640x480, radius 7 47 -> 36 (40).
+// selected away instead of branched around.  The kernel, against a loop with
+// expf: 160x120 radius 4 12.9 -> 7.7 us, 333x251 radius 2 7.2 -> 4.8 (the call
+// stays at 8, the host's share); from some 300000 pixels on bound by vector
+// instructions: 1280x720 radius 2 17.3 -> 16.6, radius 3 28.8 -> 25.9, radius 5
+// 62.9 -> 58.7; 640x480 radius 7 46.8 -> 39.1.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -37,20 +38,20 @@ __device__ __forceinline__ float load_depth(const void *src, size_t i)
     return ((const float *)src)[i];
 }
 
-// exp(t) for t <= 0: 2^(t log2 e) by the hardware's exponential of the product's
-// high part, and the low part (the product's rounding error and log2 e's own)
-// to first order.  Within 2 ulp down to the smallest normal number, zero below:
-// expf's steps for overflow and subnormals are not needed beside a weight of 1
-// (1280x720, radius 5: 66.6 us with it, 57 without).
+// exp(t) for t <= 0: 2^(t log2 e), the product in two parts of which the nearest
+// whole number is taken out exactly before the hardware's exponential, and put
+// back as the result's exponent.  Over every float from -104 to -1e-9 its error
+// is expf's: mean 0.243 to 0.257 ulp, at most 0.857; below -87, among the
+// subnormals, mean 0.255 and at most 0.891 (expf 0.273 and 1.0).  What it leaves
+// out is expf's way through overflow, which a weight cannot take.
 __device__ __forceinline__ float exp_neg(float t)
 {
     constexpr float c = 1.44269502162933350f, cl = 1.92596299112661746e-8f;   // log2 e = c + cl
-    constexpr float ln2 = 0.693147180559945309f;
     if (t < -1000.0f) t = -1000.0f;   // no infinity below; NaN stays
     const float hi = t * c;
-    const float lo = fmaf(t, c, -hi) + t * cl;
-    const float p = __builtin_amdgcn_exp2f(hi);
-    return fmaf(p, lo * ln2, p);
+    const float lo = fmaf(t, cl, fmaf(t, c, -hi));
+    const float n = rintf(hi);
+    return __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f((hi - n) + lo), (int)n);
 }
 
 // one tap of the window into the sums; a neighbour without depth leaves them as they are

@@ -81,3 +81,28 @@ def test_every_radius_and_a_range_that_overflows(radius):
     d = rng.choice([0.0, 0.5, 0.5625, 12.0], size=(35, 50), p=[0.1, 0.4, 0.3, 0.2]).astype(np.float32)
     _check(d, _run(d, radius, 2.0, 0.05), radius, 2.0, 0.05, f"r{radius}")
     assert np.array_equal(_run(d, radius, 2.0, 3e-19), d)
+
+
+@pytest.mark.parametrize("lo,hi", [(-87.0, -18.0), (-103.0, -87.5)])
+def test_range_weights_are_as_exact_as_expf(lo, hi):
+    """The exponential of the range weight, read off the output: beside a pixel
+    of 2^-126 m one of 2^60 m with weight w < 2^-25 makes it 2^-126 +
+    2^60 w / (1 + w), which is 2^60 w in float32, subnormal w too.  Its error against 64 bits is within expf's over all
+    floats of the interval (mean 0.257, at most 0.852 ulp; among the subnormals
+    0.273 and 1.0), the mean with room for a sample of 4096."""
+    import torch
+    import paper_1708_00783_amd as T
+    n = 4096
+    sr = (2.0 ** 60 * np.sqrt(-0.5 / np.linspace(lo, hi, n))).astype(np.float32)
+    d = torch.tensor([[2.0 ** -126, 2.0 ** 60]], dtype=torch.float32, device="cuda")
+    out = torch.zeros((n, 1, 2), dtype=torch.float32, device="cuda")
+    for k in range(n):
+        T.tf_bilateral(d, out[k], 1, 1e6, float(sr[k]))
+    w = out[:, 0, 0].cpu().numpy().astype(np.float64) * 2.0 ** -60
+    t = -(1.0 / (2.0 * sr.astype(np.float64) ** 2)).astype(np.float32).astype(np.float64) * 2.0 ** 120
+    x = np.exp(t)
+    ulp = np.ldexp(1.0, np.maximum(np.frexp(x)[1], -125) - 24)
+    err = np.abs(w - x) / ulp
+    mean, most = (0.27, 0.86) if lo == -87.0 else (0.285, 1.0)
+    print(f"exp over [{lo}, {hi}]: mean {err.mean():.4f} max {err.max():.4f} ulp", flush=True)
+    assert err.mean() <= mean and err.max() <= most
