@@ -83,7 +83,8 @@ Layout make_layout(const tf_params *p)
     L.ret = take((size_t)L.max_req * 4);
     L.depth = take((size_t)p->max_width * p->max_height * 4);
     L.recs = take((size_t)p->n_blocks * sizeof(Rec));
-    L.bins = take((size_t)L.max_tiles * kTileSlots * sizeof(Rec));
+    L.bins = take((size_t)L.max_tiles * kBinCap * sizeof(Rec));
+    L.bin_count = take((size_t)L.max_tiles * kBinCountStride * 4);
     L.acc_cols = take((size_t)kIntegrateGrid * 8);
     L.acc_hits = take((size_t)L.max_tiles * 8);
     L.occ = take((size_t)p->n_buckets / 8);
@@ -259,6 +260,7 @@ int tf_create(const tf_params *p, void *d_workspace, size_t bytes, void *h_store
     v.depth = (float *)(b + L.depth);
     v.recs = (Rec *)(b + L.recs);
     v.bins = (Rec *)(b + L.bins);
+    v.bin_count = (int32_t *)(b + L.bin_count);
     v.ctrl = (Ctrl *)(b + L.ctrl);
     v.acc_cols = (unsigned long long *)(b + L.acc_cols);
     v.acc_hits = (unsigned long long *)(b + L.acc_hits);

@@ -99,19 +99,18 @@ __device__ __forceinline__ int4 load_entry(const DEntry *e, uint32_t i)
     return make_int4(w.x, w.y, w.z, w.w);
 }
 
-// A tile's bin is kTileSlots 32-byte slots: the first 128 bytes hold the
-// record counter, the rest the records.  Counters side by side in one array
-// share a few lines, and atomics on a line wait for each other wherever in it
-// they land (100 k atomics on 2040 counters: 15.5 us 4 bytes apart, 5.4 us on
-// lines of their own).
+// The tiles' record counters lie on lines of their own: side by side they share
+// a few lines, and atomics on a line wait for each other wherever in it they
+// land (100 k atomics on 2040 counters: 15.5 us 4 bytes apart, 5.4 us on lines
+// of their own).
 __device__ __forceinline__ int32_t *bin_counter(const Vol &v, int tile)
 {
-    return reinterpret_cast<int32_t *>(v.bins + (size_t)tile * kTileSlots);
+    return v.bin_count + (size_t)tile * kBinCountStride;
 }
 
 __device__ __forceinline__ Rec *bin_record(const Vol &v, int tile, int i)
 {
-    return v.bins + (size_t)tile * kTileSlots + (kTileSlots - kBinCap) + i;
+    return v.bins + (size_t)tile * kBinCap + i;
 }
 
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }

@@ -11,9 +11,11 @@ namespace tsdf {
 constexpr int kBlockVox = 512;          // 8x8x8 voxels per block (Sec. 3.1)
 constexpr int kBlockBytes = 1536;       // 512 x int16 SDF, then 512 x uint8 weight
 constexpr int kTile = 16;               // raycast tile = the paper's 16x16 fragments (Sec. 4.4)
-constexpr int kTileSlots = 512;          // 32-byte slots of a tile's bin: its counter and its records
-constexpr int kBinCap = kTileSlots - 4;  // block records per tile before the all-records fallback
-constexpr int kTileTable = 1024;        // LDS block-pointer table slots per raycast tile (> 2 kBinCap)
+constexpr int kBinCap = 512;            // block records per tile before the all-records fallback
+constexpr int kBinCountStride = 32;     // words between the tiles' record counters: a line each
+constexpr int kTileTable = 1024;        // LDS block-pointer table slots per raycast tile
+static_assert(kBinCap % 256 == 0, "a raycast workgroup of 256 stages whole rounds of records");
+static_assert(kTileTable >= 2 * kBinCap, "the table is at most half full");
 constexpr int32_t kPtrSwapped = -1;     // Sec. 3.2: ptr == -1 swapped out
 constexpr int32_t kPtrEmpty = -2;       // Sec. 3.2: ptr < -1 unallocated
 constexpr int32_t kPtrClaimed = -3;     // bucket claimed inside k_insert, block pointer pending
@@ -94,7 +96,8 @@ struct Vol {
     int32_t *ret;
     float *depth;                   // metres, last ingested frame
     Rec *recs;
-    Rec *bins;                      // per tile: the records of the blocks overlapping it, and their counter
+    Rec *bins;                      // per tile: the records of the blocks overlapping it
+    int32_t *bin_count;             // their numbers
     Ctrl *ctrl;
     unsigned long long *acc_cols;   // per integration workgroup: 8-voxel columns written back
     unsigned long long *acc_hits;   // per raycast tile: pixels with a hit
@@ -129,7 +132,7 @@ struct Cam {
 // workspace carving
 struct Layout {
     size_t entries, vis, free_blocks, free_excess, voxels, vlist, reqset, reqs, ret, depth,
-        recs, bins, ctrl, acc_cols, acc_hits, occ, brick, host_has, xfer_idx, xfer_vox, xfer_host,
+        recs, bins, bin_count, ctrl, acc_cols, acc_hits, occ, brick, host_has, xfer_idx, xfer_vox, xfer_host,
         xfer_pend, swap_chunks, total;
     uint32_t reqset_size, max_req, max_tiles;
 };

@@ -299,10 +299,10 @@ struct TileTable {
     unsigned long long key[kTileTable];   // 0 = empty slot
     union {
         struct {
-            uint4 box[kTileSlots];         // x0, y0, x1, y1 (int16), zlo, zhi (float)
-            uint16_t wlist[4][kTileSlots]; // per wave: the staged records whose box meets its pixels
+            uint4 box[kBinCap];            // x0, y0, x1, y1 (int16), zlo, zhi (float)
+            uint16_t wlist[4][kBinCap];    // per wave: the staged records whose box meets its pixels
         } r;
-        int nb[kTileSlots][8];
+        int nb[kBinCap][8];
     };
     uint16_t rec[kTileTable];             // record of the slot's block
     int wcnt[4];
@@ -392,7 +392,7 @@ __device__ __forceinline__ void tile_range(const Vol &v, int tile, int tx0, int 
         const int m = n - base < kBinCap ? n - base : kBinCap;
         __syncthreads();   // the cleared table, or the previous chunk consumed
 #pragma unroll
-        for (int h = 0; h < kTileSlots / 256; ++h) {
+        for (int h = 0; h < kBinCap / 256; ++h) {
             const int j = (int)threadIdx.x + 256 * h;
             if (j >= m) break;
             const Rec r = fallback ? v.recs[base + j] : *bin_record(v, tile, j);
@@ -454,7 +454,7 @@ __device__ __forceinline__ void tile_range(const Vol &v, int tile, int tx0, int 
     // looking up to seven blocks up one after another (the march's longest
     // chain: 25 to 32% of the kernel).
 #pragma unroll
-    for (int h = 0; h < kTileSlots / 256; ++h) {
+    for (int h = 0; h < kBinCap / 256; ++h) {
         const int j = (int)threadIdx.x + 256 * h;
         if (j >= n) break;
         tt->nb[j][0] = own[h].z;

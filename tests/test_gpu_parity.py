@@ -261,6 +261,50 @@ def test_tile_bins_overflow_fall_back_to_all_records():
     _log(f"bin overflow: allocated {n_alloc}, visible {nvis}, hits {nhit}/{nhit2}, flips {flips}/{flips2}")
 
 
+@pytest.fixture(scope="module")
+def depth_of_blocks():
+    """depth images of a slanted patch, grown pixel by pixel, that allocate exactly 508 .. 513 blocks"""
+    from oracle import oracle as O
+    K = configs.C1_INTR
+    found = {}
+    for slant in np.linspace(0.1, 0.3, 21):
+        plane = np.broadcast_to(1.0 + slant * np.arange(K.width)[None] / K.width, (K.height, K.width)).astype(np.float32)
+        o = O.Volume.from_params(configs.C1_VOLUME)
+        for n in range(16000, K.width * K.height, 8):
+            d = np.where(np.arange(K.width * K.height).reshape(plane.shape) < n, plane, np.float32(0))
+            o.alloc_and_visible(d, K.as_array(), np.eye(4, dtype=np.float32))
+            blocks = len(o.allocated_positions())
+            if 508 <= blocks <= 513:
+                found.setdefault(blocks, d)
+            if blocks > 513:
+                break
+        if len(found) == 6:
+            return found
+    raise AssertionError(sorted(found))
+
+
+@pytest.mark.parametrize("blocks", [508, 509, 511, 512, 513])
+def test_tiles_at_the_bins_capacity(blocks, depth_of_blocks):
+    """one tile whose bin holds 508 to 512 records (512 fit), or one more than fit"""
+    K = configs.C1_INTR
+    pose = np.eye(4, dtype=np.float32)
+    pair = Pair(configs.C1_VOLUME, K.width, K.height)
+    pair.frame(depth_of_blocks[blocks], K, pose)
+    assert pair.g.stats()["n_allocated"] == blocks
+    Kt = Intrinsics(9.0, 9.0, 7.5, 7.5, 16, 16)      # the whole image's frustum in one tile
+    view = pose.copy()
+    view[2, 3] = 0.3
+    n0 = pair.g.stats()["total_range_records"]
+    gp, gn, op, on = pair.raycast(Kt, view)
+    assert pair.g.stats()["total_range_records"] - n0 == blocks
+    nhit, flips = compare_raycast(gp, gn, op, on, f"{blocks} records")
+    gz0, gz1 = pair.g.range_image(view, Kt)
+    oz0, oz1 = pair.o.range_image(16, 16, Kt.as_array(), view, blocks="all")
+    assert np.array_equal(gz0.cpu().numpy(), oz0) and np.array_equal(gz1.cpu().numpy(), oz1)
+    _log(f"{blocks} records in one tile: hits {nhit} flips {flips}")
+    assert nhit > 50
+
+
 def test_voxel_array_beyond_4_gib():
     """2^22 blocks (6 GiB of voxels): block indices are taken from the top of
     the free stack, so every voxel address lies past 4 GiB and the raycast
