@@ -305,6 +305,34 @@ def test_tiles_at_the_bins_capacity(blocks, depth_of_blocks):
     assert nhit > 50
 
 
+def test_view_of_a_table_of_many_strips():
+    """Binning a view over 2560 strips of 256 entries on a grid of 512: every
+    workgroup takes five, in two turns, and with some 200000 live blocks it has
+    whole rounds of 256 to bin after the first and a rest to carry over.
+    Another view's range is exact and its raycast matches the oracle's."""
+    from synth.configs import VolumeParams
+    K = configs.KINECT_INTR
+    vp = VolumeParams(0.002, 0.008, 100, 1 << 19, 1 << 17, 1 << 18)
+    pair = Pair(vp, K.width, K.height)
+    u = np.arange(K.width, dtype=np.float32)[None] / K.width
+    v = np.arange(K.height, dtype=np.float32)[:, None] / K.height
+    poses = [look_at([0.0, 0.0, 0.0], [np.cos(a), np.sin(a), 0.0]).astype(np.float32) for a in (0.0, 1.3, 2.6)]
+    for k, pose in enumerate(poses):
+        pair.frame((2.9 + 0.2 * u + (0.1 * k - 0.1) * v).astype(np.float32), K, pose)
+    n = pair.g.stats()["n_allocated"]
+    assert n == len(pair.o.allocated_positions()) and n > 150000 and pair.g.stats()["flags"] == 0
+    for tag, eye, at, Kv in (("all of it", [-6.0, -3.0, 0.5], [0.0, 1.0, 0.0], Intrinsics(150.0, 150.0, 159.5, 119.5, 320, 240)),
+                             ("part of it", [0.3, 0.2, 0.1], [2.0, 2.5, 0.0], Intrinsics(300.0, 300.0, 165.5, 124.5, 333, 251))):
+        view = look_at(eye, at).astype(np.float32)
+        gz0, gz1 = pair.g.range_image(view, Kv)
+        oz0, oz1 = pair.o.range_image(Kv.width, Kv.height, Kv.as_array(), view, blocks="all")
+        assert np.array_equal(gz0.cpu().numpy(), oz0) and np.array_equal(gz1.cpu().numpy(), oz1)
+        gp, gn, op, on = pair.raycast(Kv, view)
+        nhit, flips = compare_raycast(gp, gn, op, on, tag)
+        _log(f"{n} blocks, {tag}: hits {nhit} flips {flips}")
+        assert nhit > 2000
+
+
 def test_voxel_array_beyond_4_gib():
     """2^22 blocks (6 GiB of voxels): block indices are taken from the top of
     the free stack, so every voxel address lies past 4 GiB and the raycast
