@@ -874,22 +874,6 @@ __device__ __forceinline__ bool outside_frustum(const Frustum &f, const float *M
 // ============================================================================
 __device__ __forceinline__ int block_of(float X) { return ((int)floorf(X)) >> 3; }
 
-// in-block indices of the cell's corners: base voxel (ix, iy, iz), corner c
-// at + (c & 1, c >> 1 & 1, c >> 2); a step across a block face (local index
-// 7, flagged by sx, sy, sz) wraps to index 0 of the neighbouring block
-__device__ __forceinline__ void cell_index(int ix, int iy, int iz, bool sx, bool sy, bool sz, int (&j)[8])
-{
-    j[0] = (iz & 7) + 8 * (iy & 7) + 64 * (ix & 7);
-    const int dx = sx ? -448 : 64, dy = sy ? -56 : 8, dz = sz ? -7 : 1;
-    j[1] = j[0] + dx;
-    j[2] = j[0] + dy;
-    j[3] = j[1] + dy;
-    j[4] = j[0] + dz;
-    j[5] = j[1] + dz;
-    j[6] = j[2] + dz;
-    j[7] = j[3] + dz;
-}
-
 // lerp a + (b - a) t of a cell's corners along x, then y, then z
 __device__ __forceinline__ float lerp8(const float (&f)[8], float tx, float ty, float tz)
 {
