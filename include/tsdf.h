@@ -328,7 +328,10 @@ int tf_multi_frame(tf_multi *m, const void *d_depth, int depth_format, const tf_
 int tf_multi_range_image(tf_multi *m, const tf_view *view, float *d_zmin, float *d_zmax, tf_stream stream);
 
 /* Time every supported launch shape on this frame and these views (reps
- * timed repetitions each) and keep the fastest.  Integration shapes are timed
+ * timed repetitions each) and keep the fastest, where a shape replaces one
+ * tried before it only if it is faster by more than 2%, and one of smaller
+ * tiles by more than 10%: a block enters more bins of smaller tiles, which
+ * costs more as the map grows.  Integration shapes are timed
  * with a dry pass that computes every update and stores none; the frame's
  * allocation runs once, as the frame's own integration would run it, so the
  * map changes only by the blocks this frame allocates.  The views' outputs
