@@ -707,6 +707,20 @@ __device__ __forceinline__ bf16x8 pixel_operand(const unsigned char *base, int p
     return pixel_pieces(base + (gq * 8 + (i >> 2)) * pitch + (i & 3) * 8, pitch);
 }
 
+// Past the right and lower border a block's gradient pixels are zeros, but a tap
+// still leads from some of them to input pixels of the image, and a zero times
+// an infinity or a NaN there would spoil a sum it has no part in.  In blocks
+// across a border (`ragged`) the operand keeps the first `left` pixels of its
+// row, and rows past the border are left out.
+__device__ __forceinline__ bf16x8 first_pixels(bf16x8 b, int left, int lane)
+{
+    const int n = left - (lane >> 4) * 8;
+    u32x4 v = __builtin_bit_cast(u32x4, b);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] &= n >= 2 * i + 2 ? 0xffffffffu : (n == 2 * i + 1 ? 0xffffu : 0u);
+    return as_bf(v);
+}
+
 // Weight gradient of an upsampled layer on its parity-folded taps:
 // partial[chunk][co][tap][ci], tap = (py * 2 + px) * 4 + a * 2 + b, over source
 // pixels (m, n), the gradient at (2m + py, 2n + px) times the source at
@@ -719,7 +733,7 @@ __device__ __forceinline__ bf16x8 pixel_operand(const unsigned char *base, int p
 // into operands along the pixels; the next block's loads are in flight
 // meanwhile.  Bound by those loads' latency.  Tap by tap, with 2-byte
 // transposed writes to LDS, d1 / d2 / d3 at 8 x 256 x 256 took 84.5, 33.8 and
-// 24.2 us; now 25.3, 17.8 and 12.6.  The bias gradient is one more product, with ones.
+// 24.2 us; now 26.0, 18.2 and 13.4.  The bias gradient is one more product, with ones.
 template <int CIN, int COUT>
 __global__ __launch_bounds__(256) void k_conv_wgrad_up(const uint16_t *gpre, const uint16_t *in, int Hs, int Ws, int N,
                                                        float *partial, float *partial_b, int per, int nchunk)
@@ -740,10 +754,13 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_up(const uint16_t *gpre, con
     const int bx = (Ws + C - 1) / C, by = (Hs + R - 1) / R;
     const long nb = (long)N * by * bx, b0 = (long)chunk * per, b1 = b0 + per < nb ? b0 + per : nb;
     u32x4 gv[GQ], iv[IQ];
+    int m0 = 0, c0 = 0;   // first row and column of the block loaded last
     auto load = [&](long blk) {
         const int xb = (int)(blk % bx);
         const long yb = blk / bx;
-        const int n = (int)(yb / by), m0 = (int)(yb - (long)n * by) * R, c0 = xb * C;
+        const int n = (int)(yb / by);
+        m0 = (int)(yb - (long)n * by) * R;
+        c0 = xb * C;
 #pragma unroll
         for (int q = 0; q < GQ; ++q) {
             const int v = (int)threadIdx.x + 256 * q, pix = v / (COUT / 8), cv = (v % (COUT / 8)) * 8;
@@ -784,22 +801,31 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_up(const uint16_t *gpre, con
             if (v < IV) *reinterpret_cast<u32x4 *>(it + (v / 8) * IP + (v % 8) * 16) = iv[q];
         }
         __syncthreads();
+        const int rows = Hs - m0, cols = Ws - c0;
         if (blk + 1 < b1) load(blk + 1);
+        auto products = [&](auto ragged) {
 #pragma unroll
-        for (int y = 0; y < R; ++y) {
-            bf16x8 a[MT];
+            for (int y = 0; y < R; ++y) {
+                if (decltype(ragged)::v && y >= rows) continue;
+                bf16x8 a[MT];
 #pragma unroll
-            for (int i = 0; i < MT; ++i) a[i] = pixel_operand(gt + y * C * GP + i * 32, GP, lane);
+                for (int i = 0; i < MT; ++i) a[i] = pixel_operand(gt + y * C * GP + i * 32, GP, lane);
 #pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const bf16x8 b = pixel_operand(ip + y * (C + 1) * IP + j * 32, IP, lane);
+                for (int j = 0; j < NT; ++j) {
+                    bf16x8 b = pixel_operand(ip + y * (C + 1) * IP + j * 32, IP, lane);
+                    if (decltype(ragged)::v) b = first_pixels(b, cols, lane);
 #pragma unroll
-                for (int i = 0; i < MT; ++i) acc[i][j] = mfma(a[i], b, acc[i][j]);
+                    for (int i = 0; i < MT; ++i) acc[i][j] = mfma(a[i], b, acc[i][j]);
+                }
+                if (w == 0 && cg == 0)
+#pragma unroll
+                    for (int i = 0; i < MT; ++i) accb[i] = mfma(a[i], ones, accb[i]);
             }
-            if (w == 0 && cg == 0)
-#pragma unroll
-                for (int i = 0; i < MT; ++i) accb[i] = mfma(a[i], ones, accb[i]);
-        }
+        };
+        if (rows >= R && cols >= C)
+            products(Const<0>{});
+        else
+            products(Const<1>{});
         __syncthreads();
     }
 #pragma unroll
@@ -824,7 +850,7 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_up(const uint16_t *gpre, con
 // channels 16 i .. + 15 of rows 2 h and 2 h + 1, and the two halves are added
 // at the end.  The next block's loads are in flight meanwhile.  Tap by tap, with
 // 2-byte transposed writes to LDS, e2 / e3 / e4 at 8 x 256 x 256 took 33.9,
-// 22.6 and 13.5 us; now 19.4, 14.2 and 13.4.  The bias gradient is one more product, with ones.
+// 22.6 and 13.5 us; now 19.8, 13.7 and 13.8.  The bias gradient is one more product, with ones.
 template <int CIN, int COUT>
 __global__ __launch_bounds__(512) void k_conv_wgrad_s2(const uint16_t *gpre, const uint16_t *in, int Hs, int Ws, int N,
                                                        int Ho, int Wo, float *partial, float *partial_b, int per,
@@ -850,10 +876,13 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_s2(const uint16_t *gpre, con
     const int bx = (Wo + C - 1) / C, by = (Ho + R - 1) / R;
     const long nb = (long)N * by * bx, b0 = (long)chunk * per, b1 = b0 + per < nb ? b0 + per : nb;
     u32x4 gv[GQ], iv[IQ];
+    int m0 = 0, c0 = 0;   // first row and column of the block loaded last
     auto load = [&](long blk) {
         const int xb = (int)(blk % bx);
         const long yb = blk / bx;
-        const int n = (int)(yb / by), m0 = (int)(yb - (long)n * by) * R, c0 = xb * C;
+        const int n = (int)(yb / by);
+        m0 = (int)(yb - (long)n * by) * R;
+        c0 = xb * C;
 #pragma unroll
         for (int q = 0; q < GQ; ++q) {
             const int v = (int)threadIdx.x + NB * q, pix = v / 8, cv = (v % 8) * 8;
@@ -889,20 +918,31 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_s2(const uint16_t *gpre, con
                 *reinterpret_cast<u32x4 *>(it + ((pix / IC) * IC + (x & 1) * ODD + (x >> 1)) * IP + (v % 4) * 16) = iv[q];
         }
         __syncthreads();
+        const int rows = Ho - m0, cols = Wo - c0;
         if (blk + 1 < b1) load(blk + 1);
+        auto products = [&](auto ragged) {
 #pragma unroll
-        for (int y = 0; y < 2; ++y) {
-            const bf16x8 a = pixel_operand(gt + (2 * h + y) * C * GP + mt * 32, GP, lane);
+            for (int y = 0; y < 2; ++y) {
+                if (decltype(ragged)::v && 2 * h + y >= rows) continue;
+                const bf16x8 a = pixel_operand(gt + (2 * h + y) * C * GP + mt * 32, GP, lane);
 #pragma unroll
-            for (int tap = 0; tap < 9; ++tap) {
-                const int ky = tap / 3, kx = tap % 3;
-                const unsigned char *p = it + ((2 * (2 * h + y) + ky) * IC + (kx & 1) * ODD + (kx >> 1)) * IP;
+                for (int tap = 0; tap < 9; ++tap) {
+                    const int ky = tap / 3, kx = tap % 3;
+                    const unsigned char *p = it + ((2 * (2 * h + y) + ky) * IC + (kx & 1) * ODD + (kx >> 1)) * IP;
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[tap * 2 + j] = mfma(a, pixel_operand(p + j * 32, IP, lane), acc[tap * 2 + j]);
+                    for (int j = 0; j < 2; ++j) {
+                        bf16x8 b = pixel_operand(p + j * 32, IP, lane);
+                        if (decltype(ragged)::v) b = first_pixels(b, cols, lane);
+                        acc[tap * 2 + j] = mfma(a, b, acc[tap * 2 + j]);
+                    }
+                }
+                if (ci0 == 0) acc[18] = mfma(a, ones, acc[18]);
             }
-            if (ci0 == 0) acc[18] = mfma(a, ones, acc[18]);
-        }
+        };
+        if (rows >= R && cols >= C)
+            products(Const<0>{});
+        else
+            products(Const<1>{});
         __syncthreads();
     }
     f32x4 *const sums = reinterpret_cast<f32x4 *>(lds);
@@ -933,7 +973,7 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_s2(const uint16_t *gpre, con
 // each for itself (the tenth tap repeats the ninth and is dropped).  Wave w
 // takes rows 2 w and 2 w + 1, and the four sums are added at the end.
 // Staged per tap with 2-byte transposed writes to LDS it took 38.3 us at
-// 8 x 256 x 256, now 13.3.
+// 8 x 256 x 256, now 14.9.
 template <int COUT>
 __global__ __launch_bounds__(256) void k_conv_wgrad_c8(const uint16_t *gpre, const uint16_t *in, int H, int W, int N,
                                                        float *partial, float *partial_b, int per)
@@ -952,10 +992,13 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_c8(const uint16_t *gpre, con
     const int bx = (W + C - 1) / C, by = (H + R - 1) / R;
     const long nb = (long)N * by * bx, b0 = (long)blockIdx.x * per, b1 = b0 + per < nb ? b0 + per : nb;
     u32x4 gv[GQ], iv[IQ];
+    int m0 = 0, c0 = 0;   // first row and column of the block loaded last
     auto load = [&](long blk) {
         const int xb = (int)(blk % bx);
         const long yb = blk / bx;
-        const int n = (int)(yb / by), m0 = (int)(yb - (long)n * by) * R, c0 = xb * C;
+        const int n = (int)(yb / by);
+        m0 = (int)(yb - (long)n * by) * R;
+        c0 = xb * C;
 #pragma unroll
         for (int q = 0; q < GQ; ++q) {
             const int v = (int)threadIdx.x + 256 * q, pix = v / (COUT / 8), cv = (v % (COUT / 8)) * 8;
@@ -997,22 +1040,31 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_c8(const uint16_t *gpre, con
             if (v < IV) *reinterpret_cast<u32x4 *>(it + v * 16) = iv[q];
         }
         __syncthreads();
+        const int rows = H - m0, cols = W - c0;
         if (blk + 1 < b1) load(blk + 1);
+        auto products = [&](auto ragged) {
 #pragma unroll
-        for (int y = 0; y < 2; ++y) {
-            const int row = 2 * w + y;
-            bf16x8 a[MT];
+            for (int y = 0; y < 2; ++y) {
+                const int row = 2 * w + y;
+                if (decltype(ragged)::v && row >= rows) continue;
+                bf16x8 a[MT];
 #pragma unroll
-            for (int i = 0; i < MT; ++i) a[i] = pixel_operand(gt + row * C * GP + i * 32, GP, lane);
+                for (int i = 0; i < MT; ++i) a[i] = pixel_operand(gt + row * C * GP + i * 32, GP, lane);
 #pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const bf16x8 b = pixel_pieces(it + row * IC * 16 + off[j], 16);
+                for (int j = 0; j < NT; ++j) {
+                    bf16x8 b = pixel_pieces(it + row * IC * 16 + off[j], 16);
+                    if (decltype(ragged)::v) b = first_pixels(b, cols, lane);
 #pragma unroll
-                for (int i = 0; i < MT; ++i) acc[i * (NT + 1) + j] = mfma(a[i], b, acc[i * (NT + 1) + j]);
+                    for (int i = 0; i < MT; ++i) acc[i * (NT + 1) + j] = mfma(a[i], b, acc[i * (NT + 1) + j]);
+                }
+#pragma unroll
+                for (int i = 0; i < MT; ++i) acc[i * (NT + 1) + NT] = mfma(a[i], ones, acc[i * (NT + 1) + NT]);
             }
-#pragma unroll
-            for (int i = 0; i < MT; ++i) acc[i * (NT + 1) + NT] = mfma(a[i], ones, acc[i * (NT + 1) + NT]);
-        }
+        };
+        if (rows >= R && cols >= C)
+            products(Const<0>{});
+        else
+            products(Const<1>{});
         __syncthreads();
     }
     f32x4 *const sums = reinterpret_cast<f32x4 *>(lds);
@@ -1258,10 +1310,13 @@ __global__ __launch_bounds__(256) void k_loss_final(const float *part, int nwg, 
 // that a lane's load is the 4 bytes of its column and a wave's the 256 of four
 // pixels; wave w takes pixels 16 w .. + 15.
 // partial[j * nchunk + chunk]: j = tap * 32 + c, j = 288 the bias, the sum of
-// ddelta.  Bound by the gradient's vector instructions (18 a channel and pixel
+// ddelta.  A pixel on the image's border has no part in the taps whose ddelta
+// lies outside, zero here.  That zero times an infinity or a NaN would spread
+// it, so a chunk whose sums are not all finite is taken again with the terms of
+// such activations on the border led past the products.  Bound by the gradient's vector instructions (18 a channel and pixel
 // beside the unpacking) and memory; at 8 x 256 x 256 a kernel each, with a pixel
 // a lane 64 bytes apart and the weight gradient on the vector units, took 29.7
-// and 52.6 us, now 38 together.
+// and 52.6 us, now 39 together.
 __global__ __launch_bounds__(256) void k_head_bwd(const float *ddelta, const float *__restrict__ wt,
                                                   const uint16_t *__restrict__ d1, uint16_t *__restrict__ g_d1, int N,
                                                   int H, int W, float *__restrict__ partial, int per)
@@ -1269,6 +1324,7 @@ __global__ __launch_bounds__(256) void k_head_bwd(const float *ddelta, const flo
     constexpr int SP = 64, DW = SP + 2;
     __shared__ float dl[2][3 * DW];
     __shared__ float red[4][289];
+    __shared__ float past[288];   // terms of non-finite activations on the border
     const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6, r = lane & 15, gq = lane >> 4;
     const int bx = (W + SP - 1) / SP;
     const long ns = (long)N * H * bx, s0 = (long)blockIdx.x * per, s1 = s0 + per < ns ? s0 + per : ns;
@@ -1278,15 +1334,21 @@ __global__ __launch_bounds__(256) void k_head_bwd(const float *ddelta, const flo
     for (int k = 0; k < 9; ++k)
 #pragma unroll
         for (int e = 0; e < 8; ++e) ws[k][e] = wt[k * 32 + 8 * oct + e];
+    for (int j = (int)threadIdx.x; j < 288; j += 256) past[j] = 0.0f;
     const int tap = r < 9 ? r : 0;
     const int at = (2 - tap / 3) * DW + 2 - tap % 3 + 16 * w + gq;   // ddelta of q - off(tap), q = 16 w + gq + 4 k
     float dv = 0.0f;
     uint32_t v[4];
     u32x4 av;
+    int c0n = 0, yn = 0;   // the segment loaded last: its first column, row, and image * H + row
+    long rown = 0;
     auto load = [&](long s) {
-        const int c0 = (int)(s % bx) * SP;
-        const long row = s / bx;   // image * H + row
+        const long row = s / bx;
+        const int c0 = (int)(s - row * bx) * SP;
         const int n = (int)(row / H), y = (int)(row - (long)n * H);
+        c0n = c0;
+        yn = y;
+        rown = row;
         dv = 0.0f;
         if ((int)threadIdx.x < 3 * DW) {
             const int oy = y - 1 + (int)threadIdx.x / DW, ox = c0 - 1 + (int)threadIdx.x % DW;
@@ -1301,45 +1363,74 @@ __global__ __launch_bounds__(256) void k_head_bwd(const float *ddelta, const flo
         av = u32x4{0u, 0u, 0u, 0u};
         if (c0 + px < W) av = ld16(d1 + ((size_t)row * W + c0 + px) * 32 + 8 * oct);
     };
-    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-    float bsum = 0.0f;
-    if (s0 < s1) load(s0);
-    for (long s = s0; s < s1; ++s) {
-        float *const d = dl[s & 1];
-        if ((int)threadIdx.x < 3 * DW) d[threadIdx.x] = dv;
-        uint32_t u[4];
+    f32x4 acc[2];
+    float bsum;
+    auto pass = [&](auto border) {
+        acc[0] = acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        bsum = 0.0f;
+        if (s0 < s1) load(s0);
+        for (long s = s0; s < s1; ++s) {
+            float *const d = dl[s & 1];
+            if ((int)threadIdx.x < 3 * DW) d[threadIdx.x] = dv;
+            uint32_t u[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) u[k] = v[k];
-        const u32x4 act = av;
-        __syncthreads();   // two tiles of ddelta, so that this one barrier also guards the one before
-        if (s + 1 < s1) load(s + 1);
+            for (int k = 0; k < 4; ++k) u[k] = v[k];
+            const u32x4 act = av;
+            __syncthreads();   // two tiles of ddelta, so that this one barrier also guards the one before
+            const int c0 = c0n, y = yn;
+            const long row = rown;
+            if (s + 1 < s1) load(s + 1);
+            if (decltype(border)::v) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float a = d[at + 4 * k];
-            acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, __uint_as_float(u[k] << 16), acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, __uint_as_float(u[k] & 0xffff0000u), acc[1], 0, 0, 0);
-            bsum += a;   // of use where the tap is the centre
+                for (int k = 0; k < 4; ++k) {
+                    const int q = 16 * w + 4 * k + gq, x = c0 + q;
+                    const bool edge = x < W && (y == 0 || y == H - 1 || x == 0 || x == W - 1);
+                    const bool lo = edge && (u[k] & 0x7f80u) == 0x7f80u, hi = edge && (u[k] & 0x7f800000u) == 0x7f800000u;
+                    if (!__any(lo || hi)) continue;
+#pragma unroll 1
+                    for (int t = 0; t < 9; ++t) {
+                        const int oy = y - t / 3 + 1, ox = x - t % 3 + 1;
+                        if (oy < 0 || oy >= H || ox < 0 || ox >= W) continue;
+                        const float a = d[(2 - t / 3) * DW + 2 - t % 3 + q];
+                        if (lo) atomicAdd(&past[t * 32 + 2 * r], a * __uint_as_float(u[k] << 16));
+                        if (hi) atomicAdd(&past[t * 32 + 2 * r + 1], a * __uint_as_float(u[k] & 0xffff0000u));
+                    }
+                    u[k] &= (lo ? 0xffff0000u : ~0u) & (hi ? 0xffffu : ~0u);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float a = d[at + 4 * k];
+                acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, __uint_as_float(u[k] << 16), acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, __uint_as_float(u[k] & 0xffff0000u), acc[1], 0, 0, 0);
+                bsum += a;   // of use where the tap is the centre
+            }
+            float g[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) g[e] = 0.0f;
+#pragma unroll
+            for (int k = 0; k < 9; ++k) {
+                const float a = d[(2 - k / 3) * DW + 2 - k % 3 + px];
+                if (a != 0.0f)   // a gradient of zero is left out, whatever the weight
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) g[e] += a * ws[k][e];
+            }
+            u32x4 ov;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float v0 = bf2f((uint16_t)(act[e] & 0xffffu)) > 0.0f ? g[2 * e] : 0.0f;
+                const float v1 = bf2f((uint16_t)(act[e] >> 16)) > 0.0f ? g[2 * e + 1] : 0.0f;
+                ov[e] = bf2(v0, v1);
+            }
+            if (c0 + px < W) *reinterpret_cast<u32x4 *>(g_d1 + ((size_t)row * W + c0 + px) * 32 + 8 * oct) = ov;
         }
-        float g[8];
+    };
+    pass(Const<0>{});
+    bool finite = true;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) g[e] = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            const float a = d[(2 - k / 3) * DW + 2 - k % 3 + px];
-            if (a != 0.0f)   // a gradient of zero is left out, whatever the weight
-#pragma unroll
-                for (int e = 0; e < 8; ++e) g[e] += a * ws[k][e];
-        }
-        u32x4 ov;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float v0 = bf2f((uint16_t)(act[e] & 0xffffu)) > 0.0f ? g[2 * e] : 0.0f;
-            const float v1 = bf2f((uint16_t)(act[e] >> 16)) > 0.0f ? g[2 * e + 1] : 0.0f;
-            ov[e] = bf2(v0, v1);
-        }
-        const int c0 = (int)(s % bx) * SP;
-        if (c0 + px < W) *reinterpret_cast<u32x4 *>(g_d1 + ((size_t)(s / bx) * W + c0 + px) * 32 + 8 * oct) = ov;
-    }
+    for (int i = 0; i < 4; ++i)
+        if (gq * 4 + i < 9) finite = finite && isfinite(acc[0][i]) && isfinite(acc[1][i]);
+    if (__syncthreads_or(!finite)) pass(Const<1>{});
     bsum += __shfl_xor(bsum, 16);
     bsum += __shfl_xor(bsum, 32);
     if (lane == 4) red[w][288] = bsum;
@@ -1349,8 +1440,10 @@ __global__ __launch_bounds__(256) void k_head_bwd(const float *ddelta, const flo
         for (int i = 0; i < 4; ++i)
             if (gq * 4 + i < 9) red[w][(gq * 4 + i) * 32 + 2 * r + j] = acc[j][i];
     __syncthreads();
-    for (int j = (int)threadIdx.x; j < 289; j += 256)
-        partial[(size_t)j * gridDim.x + blockIdx.x] = (red[0][j] + red[1][j]) + (red[2][j] + red[3][j]);
+    for (int j = (int)threadIdx.x; j < 289; j += 256) {
+        const float sum = (red[0][j] + red[1][j]) + (red[2][j] + red[3][j]), p = j < 288 ? past[j] : 0.0f;
+        partial[(size_t)j * gridDim.x + blockIdx.x] = p != 0.0f ? sum + p : sum;
+    }
 }
 
 // fixed-order sum of the head partials: workgroup j sums row j of partial

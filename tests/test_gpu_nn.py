@@ -193,6 +193,40 @@ def test_tiles_and_blocks_at_their_edges(shape):
     assert np.allclose(grads["head.b"], db, rtol=1e-4, atol=1e-9), shape
 
 
+@pytest.mark.parametrize("name", ["e1", "e2", "e3", "e4", "d3", "d2", "d1", "head"])
+def test_a_non_finite_activation_spoils_only_its_own_taps(name):
+    """An infinity in the last pixel of a layer's input and a NaN in the first:
+    of the layer's weight gradients, those of their channels and of the taps
+    that lead to them from an output inside the image are not finite, all
+    others are as before (24 x 40: blocks and tiles reach past every border,
+    where zeros stand for the outputs)."""
+    import torch
+    T, net, P, depth, target, out = _setup(13, (1, 24, 40))
+    t = torch.from_numpy(target).cuda()
+    src, stride, up, _ = LAYER_IO.get(name, ("d1", 1, False, None))
+
+    def weight_grads():
+        net.backward(t)
+        return T.nn_unflatten(net.tensor("grads").cpu().numpy().reshape(-1))[name + ".w"].copy()
+
+    before = weight_grads()
+    x = net.tensor(src)
+    mark = np.zeros(x.shape)
+    for pixel, channel, bits in ((-1, 1, 0x7f80), (0, 2, 0x7fc0)):
+        x[0, pixel, pixel, channel] = bits
+        mark[0, pixel, pixel, channel] = 1.0
+    after = weight_grads()
+    if name == "e1":
+        mark = mark[..., :3]
+    mark = D.up2(mark) if up else mark
+    g = np.ones((1, *[-(-n // stride) for n in mark.shape[1:3]], before.shape[0]))
+    spoilt = D.conv_backward(mark, np.zeros_like(before, dtype=np.float64), g, stride)[1] > 0
+    assert np.isfinite(before).all() and spoilt.any() and not spoilt.all()
+    _log(f"{name}: {int(spoilt.sum())} of {spoilt.size} weights read the two pixels")
+    assert np.array_equal(~np.isfinite(after), spoilt)
+    assert np.array_equal(after[~spoilt], before[~spoilt])
+
+
 def test_end_to_end_gradient_cosine():
     import torch
     T, net, P, depth, target, out = _setup(3)
