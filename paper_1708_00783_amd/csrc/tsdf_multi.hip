@@ -417,6 +417,7 @@ struct MTileLds {
         struct {
             uint4 box[kStage];                  // x0, y0, x1, y1 (int16), zlo, zhi (float)
             uint16_t wlist[NT / 64][kStage];    // per wave: the staged records whose box meets its pixels
+            uint32_t zlo[NT], zhi[NT];          // per pixel of the tile, row by row: from boxes of a few pixels
         } r;                                    // before the table is filled
     };
     float Rs[kMaxSubmaps][12];                  // rotation rows, then translation (voxel units)
@@ -479,12 +480,19 @@ __device__ __forceinline__ int m_bin_range(const MTiles &t, uint32_t g, uint32_t
 
 // Search range of pixel (px, py) -- the calling thread's, in its wave's 8 x 8
 // square of the tile [tx0, tx0 + TW) x [ty0, ty0 + TH) -- and the tile's
-// submap set from its bin.  Every thread of the workgroup calls it.  The range is a min / max over the records covering the
-// pixel: the records' boxes are staged in LDS (in the bytes of the block table,
-// filled afterwards), each listed for the waves whose pixels it meets, and
-// every thread goes through its wave's list.  Scattering each record to the
-// pixels of its box instead took two LDS atomics per pixel and record, with a
-// few lanes at work on the largest boxes.
+// submap set from its bin.  Every thread of the workgroup calls it.  The range
+// is a min / max over the records covering the pixel.  A record whose box holds
+// at most kScatter pixels updates those of the tile in LDS (positive floats order
+// like their bits); the others' boxes are staged in LDS (in the bytes of the
+// block table, filled afterwards), each listed for the waves whose pixels it
+// meets, and every thread goes through its wave's list.  Scattered, a large box
+// leaves one lane with two atomics for each of its pixels; listed, every lane
+// looks at a box that few of them need, and a view that has a whole map in a
+// few tiles has 100 k of those in a bin: six submaps of 2.5 mm voxels 12 m away,
+// 64x48 pixels, 22.4 ms with all of them listed, 4.8 with all scattered, 2.8
+// with boxes of 9 or of 16 pixels as the line.
+constexpr int kScatter = 16;
+
 template <int NT, int TW, int TH>
 __device__ __forceinline__ void m_pixel_range(const MTiles &t, uint32_t g, int tx0, int ty0, int px, int py,
                                               MTileLds<NT> &L, float &zmin, float &zmax)
@@ -492,6 +500,9 @@ __device__ __forceinline__ void m_pixel_range(const MTiles &t, uint32_t g, int t
     constexpr int kStage = MTileLds<NT>::kStage, kWaves = NT / 64;
     const int wave = (int)threadIdx.x >> 6;
     if (threadIdx.x < kWaves) L.wcnt[threadIdx.x] = 0;
+    const int at = (py - ty0) * TW + (px - tx0);
+    L.r.zlo[at] = 0x7f800000u;   // +inf
+    L.r.zhi[at] = 0u;            // below every depth
     if (threadIdx.x == 0) {
         L.mask = 0ull;
         L.n_tab = 0u;
@@ -507,10 +518,20 @@ __device__ __forceinline__ void m_pixel_range(const MTiles &t, uint32_t g, int t
         __syncthreads();   // the lists are empty, the previous records consumed
         for (int j = (int)threadIdx.x; j < m; j += NT) {
             const uint4 b = *reinterpret_cast<const uint4 *>(t.bins + o0 + (uint32_t)(b0 + j));
-            L.r.box[j] = b;
             mask |= 1ull << (uint32_t)t.bins[o0 + (uint32_t)(b0 + j)].pad;
             const int x0 = (int16_t)(b.x & 0xffffu), y0 = (int16_t)(b.x >> 16);
             const int x1 = (int16_t)(b.y & 0xffffu), y1 = (int16_t)(b.y >> 16);
+            if ((x1 - x0 + 1) * (y1 - y0 + 1) <= kScatter) {   // (a record without a range has an empty box)
+                const int u0 = x0 > tx0 ? x0 : tx0, u1 = x1 < tx0 + TW - 1 ? x1 : tx0 + TW - 1;
+                const int v0 = y0 > ty0 ? y0 : ty0, v1 = y1 < ty0 + TH - 1 ? y1 : ty0 + TH - 1;
+                for (int v = v0; v <= v1; ++v)
+                    for (int u = u0; u <= u1; ++u) {
+                        atomicMin(&L.r.zlo[(v - ty0) * TW + u - tx0], b.z);
+                        atomicMax(&L.r.zhi[(v - ty0) * TW + u - tx0], b.w);
+                    }
+                continue;
+            }
+            L.r.box[j] = b;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) {
                 const int wx0 = tx0 + (w % (TW / 8)) * 8, wy0 = ty0 + (w / (TW / 8)) * 8;
@@ -543,6 +564,10 @@ __device__ __forceinline__ void m_pixel_range(const MTiles &t, uint32_t g, int t
         }
         if ((threadIdx.x & 63) == 0) L.wcnt[wave] = 0;
     }
+    // after the last chunk's barriers (without records, as this thread left them)
+    const float slo = __uint_as_float(L.r.zlo[at]), shi = __uint_as_float(L.r.zhi[at]);
+    zmin = slo < zmin ? slo : zmin;
+    if (shi > 0.0f) zmax = shi > zmax ? shi : zmax;
     // one atomic a wave: those of a wave's lanes on one word wait for each other
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
@@ -635,18 +660,31 @@ __device__ __forceinline__ void m_table(const MSub *subs, const MTiles &t, uint3
     __syncthreads();
 }
 
-// device pointer of block (bx, by, bz) of the k-th submap of the tile (-1 =
-// absent) from the submap's bucket bitmap and hash table: the bucket's
-// occupancy bit and its entry, loaded together; the chain beyond the bucket
-// only when the entry is another block's
+// Device pointer of block (bx, by, bz) of the k-th submap of the tile (-1 =
+// absent) from the submap's bucket bitmap and hash table, in two halves, so that
+// lookups can be in flight together: the bucket's occupancy bit and its entry,
+// loaded at once; then the answer, along the chain beyond the bucket only when
+// the entry is another block's.
+struct MProbe {
+    uint32_t h, ow;
+    int4 w;
+};
+
 template <int NT>
-__device__ __forceinline__ int m_map_find(const MTileLds<NT> &L, int k, int bx, int by, int bz)
+__device__ __forceinline__ MProbe m_map_probe(const MTileLds<NT> &L, int k, int bx, int by, int bz)
 {
-    if (!in_short_range(bx) || !in_short_range(by) || !in_short_range(bz)) return -1;
-    const uint32_t h = hash_index(bx, by, bz, L.nb[k] - 1u);
-    const uint32_t ow = gload(L.occ[k] + (h >> 5));
-    const int4 w = load_entry(L.ent[k], h);
-    if (!((ow >> (h & 31u)) & 1u)) return -1;
+    MProbe q;
+    q.h = hash_index(bx, by, bz, L.nb[k] - 1u);
+    q.ow = gload(L.occ[k] + (q.h >> 5));
+    q.w = load_entry(L.ent[k], q.h);
+    return q;
+}
+
+template <int NT>
+__device__ __forceinline__ int m_map_resolve(const MTileLds<NT> &L, int k, const MProbe &q, int bx, int by, int bz)
+{
+    const int4 w = q.w;
+    if (!((q.ow >> (q.h & 31u)) & 1u)) return -1;
     const uint32_t kxy = (uint32_t)(uint16_t)bx | ((uint32_t)(uint16_t)by << 16);
     if ((uint32_t)w.x == kxy && (int16_t)(w.y & 0xffff) == (int16_t)bz && w.w >= 0) return w.w;
     if (w.z < 1 || (uint32_t)(w.z - 1) >= L.ne[k]) return -1;
@@ -682,7 +720,8 @@ __device__ __forceinline__ int m_lookup(const MTileLds<NT> &L, int k, int bx, in
     uint32_t key;
     int p = -1;
     if (m_key(L, k, bx, by, bz, key)) p = m_table_find(L, key, key * kHashMul);
-    return p >= 0 || local ? p : m_map_find(L, k, bx, by, bz);
+    if (p >= 0 || local || !in_short_range(bx) || !in_short_range(by) || !in_short_range(bz)) return p;
+    return m_map_resolve(L, k, m_map_probe(L, k, bx, by, bz), bx, by, bz);
 }
 
 template <int NT>
@@ -704,22 +743,45 @@ __device__ __forceinline__ unsigned long long m_cell_mask(const MTiles &t, const
     return gload(t.wmask + wcell_index(block_of(P0), block_of(P1), block_of(P2))) & L.mask;
 }
 
+// Turns through the submaps of the lanes' masks cm, in ascending order in every
+// lane.  Usually the wave takes the tile's submaps one by one (k the same in
+// every lane; a lane takes part in those of its mask): neighbouring rays read
+// the same ones.  LANES: each lane takes those of its own mask, as where the
+// tile's table is incomplete.  Such a tile spans much of the map: its lanes need
+// different submaps, and wait for reads of those submaps' tables at the same
+// time (12 submaps 12 m away, 64x48: 1500 us one by one, 1100 so).  Both in one
+// kernel and the range's two ways cost four 320x240 views from within the map,
+// with no such tile, 2985 -> 3030 us.
+template <int NT, bool LANES, typename F>
+__device__ __forceinline__ void m_each_submap(const MTileLds<NT> &L, unsigned long long tile, unsigned long long cm, F f)
+{
+    if (LANES) {
+        for (; cm; cm &= cm - 1ull)
+            if (!f(__popcll(tile & ((cm & -cm) - 1ull)))) break;
+    } else {
+        const int nsub = __popcll(tile);
+        bool on = true;
+        for (int k = 0; k < nsub; ++k) {
+            const int sm = __builtin_amdgcn_readfirstlane(L.smid[k]);
+            if (on && ((cm >> (uint32_t)sm) & 1ull)) on = f(k);
+        }
+    }
+}
+
 // "allocated" of the combined map: some submap has a device block at
-// floor(P_i X); only the submaps of P's cell mask cm can.  The submaps are
-// taken one by one by the whole wave (k and its data uniform); a lane takes
-// part in those of its mask.
-template <int NT>
-__device__ __forceinline__ bool m_allocated(const MTileLds<NT> &L, int nsub, unsigned long long cm, float P0, float P1,
-                                            float P2, bool local)
+// floor(P_i X); only the submaps of P's cell mask cm can.  `tile`: the tile's
+// submaps.
+template <int NT, bool LANES>
+__device__ __forceinline__ bool m_allocated(const MTileLds<NT> &L, unsigned long long tile, unsigned long long cm,
+                                            float P0, float P1, float P2, bool local)
 {
     bool found = false;
-    for (int k = 0; k < nsub; ++k) {
-        const int sm = __builtin_amdgcn_readfirstlane(L.smid[k]);
-        if (found || !((cm >> (uint32_t)sm) & 1ull)) continue;
+    m_each_submap<NT, LANES>(L, tile, cm, [&](int k) {
         float Q0, Q1, Q2;
         to_sub(L, k, P0, P1, P2, Q0, Q1, Q2);
         found = m_lookup(L, k, block_of(Q0), block_of(Q1), block_of(Q2), local) >= 0;
-    }
+        return !found;
+    });
     return found;
 }
 
@@ -728,7 +790,7 @@ __device__ __forceinline__ bool m_allocated(const MTileLds<NT> &L, int nsub, uns
 // Corners c and c + 4 are one voxel apart along z, next to each other in
 // memory unless the cell crosses its block's upper z face: SDF and weights are
 // read as pairs.
-template <int NT>
+template <int NT, bool LANES>
 __device__ __forceinline__ void m_term(const MTileLds<NT> &L, int k, float P0, float P1, float P2, bool local, int &cnt,
                                        float &first, float &num, float &den)
 {
@@ -767,12 +829,37 @@ __device__ __forceinline__ void m_term(const MTileLds<NT> &L, int k, float P0, f
             if ((n & need) == n) open |= (hi != kn && (hi != 0u || !local)) ? 1u << n : 0u;
         }
     }
-    while (open) {
+    while (!LANES && open) {
         const int n = __ffs((int)open) - 1;
         open &= open - 1u;
         const int q = m_lookup(L, k, Bx + (n & 1), By + ((n >> 1) & 1), Bz + (n >> 2), local);
 #pragma unroll
         for (int m = 0; m < 8; ++m) p[m] = m == n ? q : p[m];
+    }
+    while (LANES && open) {   // two at a time, their map reads in flight together
+        int n[2], q[2];
+        MProbe mp[2];
+        bool ask[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            n[c] = open ? __ffs((int)open) - 1 : -1;
+            open &= open - 1u;
+            const int bx = Bx + (n[c] & 1), by = By + ((n[c] >> 1) & 1), bz = Bz + (n[c] >> 2);
+            q[c] = -1;
+            ask[c] = false;
+            uint32_t kn;
+            if (n[c] >= 0) {
+                if (m_key(L, k, bx, by, bz, kn)) q[c] = m_table_find(L, kn, kn * kHashMul);
+                ask[c] = q[c] < 0 && !local && in_short_range(bx) && in_short_range(by) && in_short_range(bz);
+            }
+            if (ask[c]) mp[c] = m_map_probe(L, k, bx, by, bz);
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            if (ask[c]) q[c] = m_map_resolve(L, k, mp[c], Bx + (n[c] & 1), By + ((n[c] >> 1) & 1), Bz + (n[c] >> 2));
+#pragma unroll
+            for (int m = 0; m < 8; ++m) p[m] = m == n[c] ? q[c] : p[m];
+        }
     }
     // corner blocks, lower then upper z
     const int lo[4] = {p[0], sx ? p[1] : p[0], sy ? p[2] : p[0], sx ? (sy ? p[3] : p[1]) : (sy ? p[2] : p[0])};
@@ -829,17 +916,17 @@ __device__ __forceinline__ void m_term(const MTileLds<NT> &L, int k, float P0, f
 
 // combined field at world voxel-unit P over the submaps of P's cell mask cm
 // (every submap with positive weight at P is one of them), in ascending
-// submap order: the wave takes the submaps one by one, as in m_allocated
-template <int NT>
-__device__ __forceinline__ float m_field(const MTileLds<NT> &L, int nsub, unsigned long long cm, float P0, float P1,
-                                         float P2, bool local)
+// submap order
+template <int NT, bool LANES>
+__device__ __forceinline__ float m_field(const MTileLds<NT> &L, unsigned long long tile, unsigned long long cm, float P0,
+                                         float P1, float P2, bool local)
 {
     int cnt = 0;
     float first = 1.0f, num = 0.0f, den = 0.0f;
-    for (int k = 0; k < nsub; ++k) {
-        const int sm = __builtin_amdgcn_readfirstlane(L.smid[k]);
-        if ((cm >> (uint32_t)sm) & 1ull) m_term(L, k, P0, P1, P2, local, cnt, first, num, den);
-    }
+    m_each_submap<NT, LANES>(L, tile, cm, [&](int k) {
+        m_term<NT, LANES>(L, k, P0, P1, P2, local, cnt, first, num, den);
+        return true;
+    });
     if (cnt == 0) return 1.0f;
     if (cnt == 1) return first;
     return num / den;
@@ -878,7 +965,8 @@ __global__ __launch_bounds__(TW *TH) void k_m_raycast(const MSub *subs, const MF
     float zmin, zmax;
     m_pixel_range<NT, TW, TH>(t, (uint32_t)g, tx0, ty0, px, py, L, zmin, zmax);
     m_table<NT, TW, TH>(subs, t, (uint32_t)g, tx0, ty0, V.cam, voxel, L);
-    const int nsub = __builtin_amdgcn_readfirstlane(__popcll(L.mask));
+    const unsigned long long tile_mask = (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)L.mask) |
+                                         ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(L.mask >> 32)) << 32);
     // reads at points shallower than dcut (the table's depth limit less a
     // voxel for the normal's taps and a millimetre for rounding) can trust a
     // table miss
@@ -907,108 +995,115 @@ __global__ __launch_bounds__(TW *TH) void k_m_raycast(const MSub *subs, const MF
         // field's code stands once (three copies and their lookups were 100 KB,
         // more than the instruction cache), and lanes at a hit read their taps
         // beside lanes that still march
-        for (;;) {
-            const bool marching = state < M_REFINE;
-            if (marching && !(tt < t_end && steps < kMaxRaySteps)) break;
-            if (state == M_COARSE || state == M_FINE) {
-                // Empty-space skip: while no block is found the march keeps
-                // its fixed step; the world cells of the next kSkip positions
-                // are tested together, a clear cell proves the position
-                // unallocated, so the iterations skipped are those the loop
-                // would run.
-                const float stp = state == M_COARSE ? 8.0f : mu_v;
-                constexpr int kSkip = 4;
-                float tk[kSkip];
-                unsigned long long wk[kSkip];
-                float t2 = tt;
+        auto march = [&](auto lanes) {
+            constexpr bool kLanes = decltype(lanes)::value;
+            for (;;) {
+                const bool marching = state < M_REFINE;
+                if (marching && !(tt < t_end && steps < kMaxRaySteps)) break;
+                if (state == M_COARSE || state == M_FINE) {
+                    // Empty-space skip: while no block is found the march keeps
+                    // its fixed step; the world cells of the next kSkip positions
+                    // are tested together, a clear cell proves the position
+                    // unallocated, so the iterations skipped are those the loop
+                    // would run.
+                    const float stp = state == M_COARSE ? 8.0f : mu_v;
+                    constexpr int kSkip = 4;
+                    float tk[kSkip];
+                    unsigned long long wk[kSkip];
+                    float t2 = tt;
 #pragma unroll
-                for (int k = 0; k < kSkip; ++k) {
-                    tk[k] = t2;
-                    wk[k] = m_cell_mask<NT>(t, L, ox + t2 * dx, oy + t2 * dy, oz + t2 * dz);
-                    t2 += stp;
+                    for (int k = 0; k < kSkip; ++k) {
+                        tk[k] = t2;
+                        wk[k] = m_cell_mask<NT>(t, L, ox + t2 * dx, oy + t2 * dy, oz + t2 * dz);
+                        t2 += stp;
+                    }
+                    bool stop = false;
+#pragma unroll
+                    for (int k = 0; k < kSkip; ++k) {
+                        if (stop) continue;
+                        tt = tk[k];
+                        if (!(tt < t_end && steps < kMaxRaySteps) || wk[k]) {
+                            stop = true;
+                            continue;
+                        }
+                        ++steps;   // an iteration on unallocated space
+                    }
+                    if (!stop) tt = t2;
+                    if (!(tt < t_end && steps < kMaxRaySteps)) break;
                 }
-                bool stop = false;
-#pragma unroll
-                for (int k = 0; k < kSkip; ++k) {
-                    if (stop) continue;
-                    tt = tk[k];
-                    if (!(tt < t_end && steps < kMaxRaySteps) || wk[k]) {
-                        stop = true;
+                if (marching) ++steps;
+                float P0 = ox + tt * dx, P1 = oy + tt * dy, P2 = oz + tt * dz;
+                // the taps P +- e_a lie within a voxel of the hit, which dcut covers
+                const bool local = tt * zscale >= kZNear && tt * zscale < dcut;
+                if (state == M_TAP) {
+                    const float e = (tap & 1) ? -1.0f : 1.0f;
+                    P0 = (tap >> 1) == 0 ? P0 + e : P0;
+                    P1 = (tap >> 1) == 1 ? P1 + e : P1;
+                    P2 = (tap >> 1) == 2 ? P2 + e : P2;
+                }
+                // only the submaps of P's world cell can be allocated there
+                const unsigned long long cm = m_cell_mask<NT>(t, L, P0, P1, P2);
+                if (marching) {
+                    const bool alloc = cm && m_allocated<NT, kLanes>(L, tile_mask, cm, P0, P1, P2, local);
+                    if (!alloc) {
+                        tt += state == M_COARSE ? 8.0f : mu_v;
+                        state = state == M_COARSE ? M_COARSE : M_FINE;
                         continue;
                     }
-                    ++steps;   // an iteration on unallocated space
+                    if (state == M_COARSE) {
+                        tt -= 8.0f;
+                        state = M_FINE;
+                        continue;
+                    }
                 }
-                if (!stop) tt = t2;
-                if (!(tt < t_end && steps < kMaxRaySteps)) break;
-            }
-            if (marching) ++steps;
-            float P0 = ox + tt * dx, P1 = oy + tt * dy, P2 = oz + tt * dz;
-            // the taps P +- e_a lie within a voxel of the hit, which dcut covers
-            const bool local = tt * zscale >= kZNear && tt * zscale < dcut;
-            if (state == M_TAP) {
-                const float e = (tap & 1) ? -1.0f : 1.0f;
-                P0 = (tap >> 1) == 0 ? P0 + e : P0;
-                P1 = (tap >> 1) == 1 ? P1 + e : P1;
-                P2 = (tap >> 1) == 2 ? P2 + e : P2;
-            }
-            // only the submaps of P's world cell can be allocated there
-            const unsigned long long cm = m_cell_mask<NT>(t, L, P0, P1, P2);
-            if (marching) {
-                const bool alloc = cm && m_allocated(L, nsub, cm, P0, P1, P2, local);
-                if (!alloc) {
-                    tt += state == M_COARSE ? 8.0f : mu_v;
-                    state = state == M_COARSE ? M_COARSE : M_FINE;
-                    continue;
-                }
-                if (state == M_COARSE) {
-                    tt -= 8.0f;
-                    state = M_FINE;
-                    continue;
-                }
-            }
-            const float F = m_field(L, nsub, cm, P0, P1, P2, local);
-            if (state == M_TAP) {
-                if (tap & 1) {
-                    const float d = (plus - F) * 0.5f;
-                    gx = tap == 1 ? d : gx;
-                    gy = tap == 3 ? d : gy;
-                    gz = tap == 5 ? d : gz;
-                    if (tap == 5) break;
-                } else {
-                    plus = F;
-                }
-                ++tap;
-            } else if (state == M_REFINE) {
-                tt += F * mu_v;
-                state = M_TAP;
-            } else if (state == M_SURFACE) {
-                if (F < 0.0f) {
-                    state = M_REFINE;
+                const float F = m_field<NT, kLanes>(L, tile_mask, cm, P0, P1, P2, local);
+                if (state == M_TAP) {
+                    if (tap & 1) {
+                        const float d = (plus - F) * 0.5f;
+                        gx = tap == 1 ? d : gx;
+                        gy = tap == 3 ? d : gy;
+                        gz = tap == 5 ? d : gz;
+                        if (tap == 5) break;
+                    } else {
+                        plus = F;
+                    }
+                    ++tap;
+                } else if (state == M_REFINE) {
                     tt += F * mu_v;
+                    state = M_TAP;
+                } else if (state == M_SURFACE) {
+                    if (F < 0.0f) {
+                        state = M_REFINE;
+                        tt += F * mu_v;
+                    } else {
+                        const float s = F * mu_v;
+                        tt += (s > 1.0f) ? s : 1.0f;
+                    }
+                } else if (F < 0.0f) {
+                    if (state == M_FINE) {
+                        state = M_WRONG_SIDE;
+                    } else {
+                        const float s = -F * mu_v;
+                        tt += (s > 1.0f) ? s : 1.0f;
+                    }
                 } else {
-                    const float s = F * mu_v;
-                    tt += (s > 1.0f) ? s : 1.0f;
-                }
-            } else if (F < 0.0f) {
-                if (state == M_FINE) {
-                    state = M_WRONG_SIDE;
-                } else {
-                    const float s = -F * mu_v;
-                    tt += (s > 1.0f) ? s : 1.0f;
-                }
-            } else {
-                // FINE or WRONG_SIDE meeting F >= 0 turns to SURFACE without
-                // a step; the SURFACE iteration that follows (if the step
-                // bound allows it) reads the same field at the same t, so
-                // its step is taken here with this F
-                state = M_SURFACE;
-                if (steps < kMaxRaySteps) {
-                    ++steps;
-                    const float s = F * mu_v;
-                    tt += (s > 1.0f) ? s : 1.0f;
+                    // FINE or WRONG_SIDE meeting F >= 0 turns to SURFACE without
+                    // a step; the SURFACE iteration that follows (if the step
+                    // bound allows it) reads the same field at the same t, so
+                    // its step is taken here with this F
+                    state = M_SURFACE;
+                    if (steps < kMaxRaySteps) {
+                        ++steps;
+                        const float s = F * mu_v;
+                        tt += (s > 1.0f) ? s : 1.0f;
+                    }
                 }
             }
-        }
+        };
+        if (__builtin_amdgcn_readfirstlane((int)L.dlim) == 0x7f800000)   // nothing left out of the table
+            march(std::false_type{});
+        else
+            march(std::true_type{});
         if (state == M_TAP) {
             const float P0 = ox + tt * dx, P1 = oy + tt * dy, P2 = oz + tt * dz;
             out_p = make_float4(P0 * voxel, P1 * voxel, P2 * voxel, 1.0f);

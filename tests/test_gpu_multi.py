@@ -277,6 +277,80 @@ def test_views_past_the_block_table_s_window(axis, sign):
     assert g.stats()["flags"] == 0
 
 
+@pytest.mark.parametrize("tile", [(16, 16), (32, 8), (16, 8), (8, 8)])
+def test_far_views_of_a_few_tiles(tile):
+    """A ragged 24x20 view with the scene in the middle, then in the first 8x8
+    pixels only (more records than the tile's table holds, tiles without any),
+    then from further off: boxes of a few pixels and larger ones in one bin.
+    Range image exact, outputs as the oracle's."""
+    mp = MultiPair()
+    for k in range(len(mp.d)):
+        mp.integrate(k)
+    import torch
+    mp.g.set_config(tile_w=tile[0], tile_h=tile[1])
+    for eye, f, cx, cy in (([1.1, -0.9, 0.8], 11.0, 11.5, 9.5), ([1.1, -0.9, 0.8], 4.5, 3.5, 3.5),
+                           ([5.5, -4.5, 4.0], 20.0, 11.5, 9.5)):
+        intr = Intrinsics(f, f, cx, cy, 24, 20)
+        pose = look_at(eye, [0.0, 0.0, 0.2]).astype(np.float32)
+        pts = torch.full((20, 24, 4), -7.0, dtype=torch.float32, device="cuda")
+        nrm = torch.full_like(pts, -7.0)
+        b0 = mp.g.stats()["total_bin_entries"]
+        mp.g.raycast([(intr, pose, pts, nrm)])
+        entries = mp.g.stats()["total_bin_entries"] - b0
+        gz0, gz1 = mp.g.range_image(intr, pose)
+        oz0, oz1 = mp.o.range_image(24, 20, intr.as_array(), pose)
+        v, u = np.nonzero(oz1 > 0)
+        _log(f"{tile} f {f} c {cx} {cy}: {entries} bin entries, pixels with a range to ({u.max()}, {v.max()})")
+        assert np.array_equal(gz0.cpu().numpy(), oz0) and np.array_equal(gz1.cpu().numpy(), oz1)
+        op, on = mp.o.raycast(24, 20, intr.as_array(), pose)
+        nhit, flips = compare_raycast(pts.cpu().numpy(), nrm.cpu().numpy(), op, on, f"{tile} f {f}")
+        _log(f"hits {nhit} flips {flips}")
+        assert nhit > 0
+
+
+def test_a_view_from_afar_is_not_far_slower():
+    """Six fine submaps in a few tiles of a 64x48 view, about 10^5 records a
+    bin: against a view of the same map from where it was integrated (2.5 times
+    its time; 4.6 with every record scattered to its pixels, 14 with every
+    record looked at by every pixel of its wave)."""
+    from synth.configs import VolumeParams
+    import paper_1708_00783_amd as T
+    import time
+    import torch
+    vp = VolumeParams(0.0025, 0.01, 100, 1 << 20, 1 << 17, 1 << 17)
+    Kd = Intrinsics(500.0, 500.0, 319.5, 239.5, 640, 480)
+    subs = np.stack([_rot("xyz"[i % 3], 0.4 * i, [0.2 * i, -0.1 * i, 0.05]) for i in range(6)])
+    g = T.MultiMap(vp, subs, 640, 480, 320, 240, 1 << 24)
+    u, v = np.meshgrid(np.arange(640), np.arange(480))
+    near = [_rot("y", 0.3 * i, [0.0, 0.0, 0.0]) for i in range(6)]
+    for i in range(6):
+        depth = (2.0 + 0.2 * i + 0.3 * np.sin(u / 40.0) * np.cos(v / 50.0)).astype(np.float32)
+        g.integrate(to_device(depth), Kd, near[i], [i])
+    far = near[2].copy()
+    far[2, 3] += 10.0
+
+    def us(intr, pose):
+        pts = torch.empty((intr.height, intr.width, 4), dtype=torch.float32, device="cuda")
+        view = [(intr, pose, pts, torch.empty_like(pts))]
+        best = 1e9
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            for _ in range(4):
+                g.raycast(view)
+            torch.cuda.synchronize()
+            best = min(best, (time.perf_counter() - t) / 4 * 1e6)
+        return best
+
+    a = us(Intrinsics(250.0, 250.0, 159.5, 119.5, 320, 240), near[2])
+    b0 = g.stats()["total_bin_entries"]
+    b = us(Intrinsics(50.0, 50.0, 31.5, 23.5, 64, 48), far)
+    st = g.stats()
+    _log(f"near 320x240 {a:.0f} us, far 64x48 {b:.0f} us, {(st['total_bin_entries'] - b0) // 20} entries a far view, "
+         f"{st['allocated_blocks']} blocks, flags {st['flags']}")
+    assert b < 8 * a
+
+
 def _pool_map(fn, items):
     import multiprocessing as mp
     import os
