@@ -9,10 +9,11 @@
 // the window is unrolled for each radius: its LDS reads and exponentials
 // overlap, the weights come with the arguments, and a tap without depth is
 // selected away instead of branched around.  The kernel, against a loop with
-// expf: 160x120 radius 4 12.9 -> 7.7 us, 333x251 radius 2 7.2 -> 4.8 (the call
+// expf: 160x120 radius 4 13.0 -> 6.7 us, 333x251 radius 2 6.8 -> 4.5 (the call
 // stays at 8, the host's share); from some 300000 pixels on bound by vector
-// instructions: 1280x720 radius 2 17.3 -> 16.6, radius 3 28.8 -> 25.9, radius 5
-// 62.9 -> 58.7; 640x480 radius 7 46.8 -> 39.1.
+// instructions, 19 a tap: 1280x720 radius 2 16.5 -> 14.5, radius 3 27.5 -> 25.0,
+// radius 5 60.9 -> 54.5; 640x480 radius 7 45.1 -> 36.5; 3000x2000 radius 7
+// 586 -> 559 (calls without a gap between them 524 -> 535).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -47,21 +48,21 @@ __device__ __forceinline__ float load_depth(const void *src, size_t i)
 __device__ __forceinline__ float exp_neg(float t)
 {
     constexpr float c = 1.44269502162933350f, cl = 1.92596299112661746e-8f;   // log2 e = c + cl
-    if (t < -1000.0f) t = -1000.0f;   // no infinity below; NaN stays
+    t = __builtin_elementwise_maximum(t, -1000.0f);   // no infinity below; NaN stays
     const float hi = t * c;
     const float lo = fmaf(t, cl, fmaf(t, c, -hi));
     const float n = rintf(hi);
     return __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f((hi - n) + lo), (int)n);
 }
 
-// one tap of the window into the sums; a neighbour without depth leaves them as they are
+// one tap of the window into the sums; a neighbour without depth (0 in the tile)
+// leaves them as they are
 __device__ __forceinline__ void tap(float dq, float dp, float ws, float inv2sr2, float &sw, float &swd)
 {
     const float e = dq - dp;
-    const float w = ws * exp_neg(-(e * e) * inv2sr2);
-    const float sw1 = sw + w, swd1 = swd + w * e;
-    sw = dq > 0.0f ? sw1 : sw;
-    swd = dq > 0.0f ? swd1 : swd;
+    const float w = ws * exp_neg(dq > 0.0f ? -(e * e) * inv2sr2 : -1000.0f);   // (2^-1443: none)
+    sw += w;
+    swd += w * e;
 }
 
 template <int FMT, int R>
@@ -74,7 +75,8 @@ __global__ __launch_bounds__(256) void k_bilateral(const void *src, int W, int H
         const int ty = i / side, tx = i - ty * side;
         const int gx = x0 + tx, gy = y0 + ty;
         // outside the image reads as invalid, which the window skips
-        tile[i] = (gx >= 0 && gx < W && gy >= 0 && gy < H) ? load_depth<FMT>(src, (size_t)gy * W + gx) : 0.0f;
+        const float d = (gx >= 0 && gx < W && gy >= 0 && gy < H) ? load_depth<FMT>(src, (size_t)gy * W + gx) : 0.0f;
+        tile[i] = d > 0.0f ? d : 0.0f;
     }
     __syncthreads();
     const int lx = threadIdx.x & 15, ly = threadIdx.x >> 4;
